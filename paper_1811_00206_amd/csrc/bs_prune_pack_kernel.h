@@ -14,376 +14,432 @@
 // Algorithm 1 compares against a threshold with "<", which would keep every
 // element tied with the threshold; counting keeps exactly k instead.
 //
-// prune_pack_lanes: LPB lanes share a bank and hold it in registers as R pieces of
-// 16 bytes each (8, 4 or 2 bytes when the bank's byte length is not a multiple of
-// 16), so a wavefront works on 64/LPB banks at once.  The keys are bit-sliced in
-// registers, so a pass over one bit costs one AND and one popcount for all 32
-// elements of a lane, plus a DPP sum over the LPB lanes.
+// LPB lanes share a bank, each owning C consecutive elements of it (C <= 64), so a
+// wavefront works on 64/LPB banks at once.  What bounds this kernel is the vector ALU
+// until it gets below the stream of W, so every step is built to touch an element few times:
+//   * the wavefront's banks are one contiguous piece of W; it goes to LDS with
+//     direct-to-LDS loads (no registers) and stays there, so that a kept value is fetched
+//     by its offset at the very end and nothing else carries values around;
+//   * the keys are bit-sliced a byte at a time, from the top: eight masks (one bit per
+//     element of the lane) come out of a byte gather and an 8 x 8 bit transpose, and a
+//     select step costs one AND and one popcount per 32 elements plus the exchange over the
+//     LPB lanes.  As soon as every bank of the wavefront needs all of its remaining
+//     candidates the lower bytes are never looked at: for Gaussian fp32 weights the cut is
+//     settled after 8 exponent and about 12 mantissa bits, so the last byte is skipped;
+//   * lanes own consecutive elements, so a lane's survivors are consecutive in the output:
+//     one prefix over the LPB lanes, then a walk over the set bits that writes offsets
+//     only (k steps for a whole bank in one lane);
+//   * offsets and values leave as whole words: four outputs per lane and step, the values
+//     gathered from LDS through the offsets just written.
+// Measured (MI355X, back to back over three matrices), before and now; before, 16-byte pieces
+// striped over the lanes were transposed whole and every element was written or sent to a
+// trash slot: 6000 x 3000 fp32, 10 of 100 kept: 22.4 -> 16.8 us (4.8 TB/s of W, vals and idx;
+// a large copy runs at 4.7); 4096 x 25088 binary16, 6 of 64: 62.9 -> 46.6 us (5.0 TB/s);
+// 11908 x 7616 binary16, 18 of 64: 63.5 -> 52.7 us.  Vector instructions on the first: 12.9 M
+// -> 5.8 M with two mask words per lane, 7 M with one.
 // Re-pruning a packed matrix to fewer weights per bank (one more round of
-// Algorithm 1's loop) runs the same kernels on the stored values, k per bank.
+// Algorithm 1's loop) runs the same kernel on the stored values, k per bank.
 #pragma once
 #include "bs_internal.h"
 
 namespace bs {
 namespace {
 
-template <typename VT> struct Bits;
-template <> struct Bits<float> { using type = uint32_t; static constexpr int mag_bits = 31; };
-template <> struct Bits<__half> { using type = uint16_t; static constexpr int mag_bits = 15; };
-
 // ---- bit-sliced selection ---------------------------------------------------
-// 32 x 32 bit-matrix transpose in registers (five block-swap stages): afterwards
-// bit c of w[r] is what bit r of w[c] was.
+// 8 x 8 bit transpose inside each of the four byte columns of q[0..7]: afterwards bit
+// 8j+g of q[t] is what bit 8j+t of q[g] was.
 template <int J, uint32_t M>
-__device__ __forceinline__ void swap_blocks(uint32_t (&w)[32]) {
+__device__ __forceinline__ void swap_bits(uint32_t (&q)[8]) {
 #pragma unroll
-    for (int i = 0; i < 32; ++i) {
+    for (int i = 0; i < 8; ++i) {
         if ((i & J) == 0) {
-            const uint32_t a = w[i], b = w[i + J];
-            if constexpr (J == 16) {          // whole bytes move: one byte permute per word
-                w[i] = __builtin_amdgcn_perm(b, a, 0x05040100u);       // a0 a1 b0 b1
-                w[i + J] = __builtin_amdgcn_perm(b, a, 0x07060302u);   // a2 a3 b2 b3
-            } else if constexpr (J == 8) {
-                w[i] = __builtin_amdgcn_perm(b, a, 0x06020400u);       // a0 b0 a2 b2
-                w[i + J] = __builtin_amdgcn_perm(b, a, 0x07030501u);   // a1 b1 a3 b3
-            } else {
-                w[i] = (a & M) | ((b << J) & ~M);
-                w[i + J] = ((a >> J) & M) | (b & ~M);
-            }
+            const uint32_t a = q[i], b = q[i + J];
+            q[i] = (a & M) | ((b << J) & ~M);
+            q[i + J] = ((a >> J) & M) | (b & ~M);
         }
     }
 }
-__device__ __forceinline__ void transpose32(uint32_t (&w)[32]) {
-    swap_blocks<16, 0x0000FFFFu>(w);
-    swap_blocks<8, 0x00FF00FFu>(w);
-    swap_blocks<4, 0x0F0F0F0Fu>(w);
-    swap_blocks<2, 0x33333333u>(w);
-    swap_blocks<1, 0x55555555u>(w);
+__device__ __forceinline__ void transpose8(uint32_t (&q)[8]) {
+    swap_bits<4, 0x0F0F0F0Fu>(q);
+    swap_bits<2, 0x33333333u>(q);
+    swap_bits<1, 0x55555555u>(q);
+    // kept opaque: merged into the select steps the last stage loses its bit-field inserts
+#pragma unroll
+    for (int i = 0; i < 8; ++i) asm("" : "+v"(q[i]));
 }
 
-// mask with the n lowest bits set, for words 0 and 1 of a 64-bit set (n >= 0)
-__device__ __forceinline__ uint32_t low_bits(int n, int word) {
-    const int m = n - 32 * word;
-    return m <= 0 ? 0u : m >= 32 ? 0xFFFFFFFFu : ((1u << m) - 1u);
+// State of a lane's search: candidates (keys that agree with the threshold so far), keys
+// known to be greater, and how many more survivors the candidates must give, minus one.
+template <int NM>
+struct Select {
+    uint32_t cand[NM], gt[NM];
+    int r1;
+};
+
+// One bit of the threshold, s[m] = that bit of the lane's elements 32m .. 32m+31.
+template <int LPB, int NM>
+__device__ __forceinline__ void select_bit(Select<NM>& t, const uint32_t (&s)[NM]) {
+    uint32_t ones[NM];
+    int c = 0;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+        ones[m] = t.cand[m] & s[m];
+        c += __popc(ones[m]);
+    }
+    // (kept opaque: folded into the exchange the popcount would be computed twice)
+    if constexpr (LPB > 1) asm("" : "+v"(c));
+    c = group_sum_i<LPB>(c);
+    // take = all ones if enough keys have the bit set (the threshold has it), else zero
+    const int left = t.r1 - c;
+    uint32_t take = (uint32_t)(left >> 31);
+    asm("" : "+v"(take));   // stays a mask: turned back into compares it costs three more per bit
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+        t.gt[m] |= ones[m] & ~take;
+        t.cand[m] &= ~(s[m] ^ take);
+    }
+    t.r1 = (int)(((uint32_t)t.r1 & take) | ((uint32_t)left & ~take));
 }
 
-// LPB lanes per bank, R pieces of PB bytes per lane (PB = 16, or 8 / 4 / 2 when the
-// byte size of a bank is not a multiple of 16, so that every bank still starts on a
-// piece boundary); piece p = q + LPB*j holds the offsets [p*E, p*E + E),
-// E = PB / sizeof(VT).  Requires B % E == 0.
-//
-// A lane numbers its own elements e = j*E + i (ascending offset) and keeps sets of
-// them as bit masks (one word for up to 32 elements, two for binary16's 64).  The
-// keys are transposed so that slice[b] holds bit b of every element; the k-th
-// largest key is then found from the top bit down with one AND and one popcount
-// per bit for all of the lane's elements at once:
-//   ones = cand & slice[b]; c = group count of ones;
-//   if (#greater + c >= k) the threshold has bit b set and only `ones` stay candidates,
-//   else `ones` are greater than the threshold and leave the candidates.
-// At the end `cand` are the keys equal to the threshold.  If a bank has more of them
-// than open slots, the cut between kept and dropped ties is an offset C, found the
-// same way (8 bits): the lane's elements below an offset are its lowest bits.
-// IT is the stored offset: a byte (B <= 256) or 16 bits (wider banks, up to 64 lanes each).
-template <typename VT, typename IT, int PB, int LPB, int R>
-__global__ __launch_bounds__(256) void prune_pack_lanes(const VT* __restrict__ W,
-                                                        VT* __restrict__ vals,
-                                                        IT* __restrict__ idx,
-                                                        const IT* __restrict__ remap,
-                                                        int64_t n_banks, int B, int k) {
-    using U = typename Bits<VT>::type;
-    constexpr int NB = Bits<VT>::mag_bits;
-    using Raw = typename RawBytes<PB>::type;
-    constexpr int E = PB / sizeof(VT);            // elements per piece
-    constexpr int NE = R * E;                     // elements per lane
+// Byte `BYTE` of fp32 keys (3: the sign bit is skipped).  w[e] = the lane's element e.
+template <int BYTE, int LPB, int NE, int NM>
+__device__ __forceinline__ void select_byte(Select<NM>& t, const uint32_t (&w)[NE]) {
+    uint32_t q[NM][8];
+    constexpr uint32_t kPair = 0x0c0c0000u | ((4u + BYTE) << 8) | BYTE;   // {a.byte, b.byte, 0, 0}
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {   // bytes of elements 32m + {g, 8+g, 16+g, 24+g}
+            const int e = 32 * m + g;
+            const uint32_t u = __builtin_amdgcn_perm(w[e + 8 < NE ? e + 8 : e], w[e], e + 8 < NE ? kPair : 0x0c0c0c00u | BYTE);
+            uint32_t v = 0u;
+            if (e + 16 < NE) v = __builtin_amdgcn_perm(w[e + 24 < NE ? e + 24 : e + 16], w[e + 16],
+                                                       e + 24 < NE ? kPair : 0x0c0c0c00u | BYTE);
+            q[m][g] = e + 16 < NE ? __builtin_amdgcn_perm(v, u, 0x05040100u) : u;
+        }
+        transpose8(q[m]);
+    }
+#pragma unroll
+    for (int b = BYTE == 3 ? 6 : 7; b >= 0; --b) {
+        uint32_t s[NM];
+#pragma unroll
+        for (int m = 0; m < NM; ++m) s[m] = q[m][b];
+        select_bit<LPB, NM>(t, s);
+    }
+}
+
+// Byte `BYTE` of binary16 keys (1: the sign bit is skipped).  w[i] = elements 2i, 2i+1.
+template <int BYTE, int LPB, int NE, int NM, int NW>
+__device__ __forceinline__ void select_byte16(Select<NM>& t, const uint32_t (&w)[NW]) {
+    uint32_t q[NM][8];
+    // {a.even, b.even, a.odd, b.odd}
+    constexpr uint32_t kFour = ((6u + BYTE) << 24) | ((2u + BYTE) << 16) | ((4u + BYTE) << 8) | BYTE;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+#pragma unroll
+        for (int g = 0; g < 8; g += 2) {
+            const int i = 16 * m + g / 2;   // words of elements 32m + g + {0, 8, 16, 24}
+            const uint32_t u = __builtin_amdgcn_perm(i + 4 < NW ? w[i + 4 < NW ? i + 4 : i] : 0u, w[i], kFour);
+            uint32_t v = 0u;
+            if (i + 8 < NW)
+                v = __builtin_amdgcn_perm(i + 12 < NW ? w[i + 12 < NW ? i + 12 : i] : 0u, w[i + 8 < NW ? i + 8 : i], kFour);
+            q[m][g] = __builtin_amdgcn_perm(v, u, 0x05040100u);
+            q[m][g + 1] = __builtin_amdgcn_perm(v, u, 0x07060302u);
+        }
+        transpose8(q[m]);
+    }
+#pragma unroll
+    for (int b = BYTE == 1 ? 6 : 7; b >= 0; --b) {
+        uint32_t s[NM];
+#pragma unroll
+        for (int m = 0; m < NM; ++m) s[m] = q[m][b];
+        select_bit<LPB, NM>(t, s);
+    }
+}
+
+// every bank of the wavefront needs all of its remaining candidates
+template <int LPB, int NM>
+__device__ __forceinline__ bool settled(const Select<NM>& t) {
+    int n = 0;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) n += __popc(t.cand[m]);
+    return __all(group_sum_i<LPB>(n) == t.r1 + 1);
+}
+
+// mask with the n lowest bits set (0 <= n <= 32)
+__device__ __forceinline__ uint32_t low_bits(int n) { return n >= 32 ? 0xFFFFFFFFu : (1u << n) - 1u; }
+
+// How a lane's elements lie in LDS.
+//   kAligned   C elements, C*sizeof(VT) a power of two of 64 bytes or more: lanes would start
+//              on the same LDS banks, so 16-byte piece p of a lane sits at p ^ (its 256-byte
+//              window's number), which spreads 16 lanes over all LDS banks;
+//   kWords     as in memory; elements start on 4-byte boundaries;
+//   kHalves    as in memory; binary16 with an odd bank.
+enum LaneLayout { kAligned, kWords, kHalves };
+
+struct PruneArgs {
+    const void* W;
+    void* vals;
+    void* idx;
+    const void* remap;     // re-pruning: the stored offsets; else null
+    int64_t n_banks;
+    int B, k;
+    int C;                 // elements per lane: LPB * C >= B, C <= NE
+    uint32_t magic_k;      // magic_u32(k)
+    int raw_bytes;         // LDS bytes of the wavefront's banks; its offsets follow
+    int wave_bytes;        // both, a multiple of 256
+};
+
+// Wavefronts per workgroup at most; they share nothing.  1 / 2 / 4 on the 6000 x 3000 matrix:
+// 18.6 / 18.5 / 16.9 us (11250 wavefronts of short life: fewer workgroups to dispatch).
+constexpr int kPruneWaves = 4;
+
+// A group of 64/LPB banks per wavefront, no loop.
+template <typename VT, typename IT, int LPB, int NE, LaneLayout LAYOUT>
+__global__ __launch_bounds__(kWave * kPruneWaves) void prune_pack_kernel(PruneArgs a) {
+    constexpr int S = sizeof(VT);
     constexpr int NM = NE > 32 ? 2 : 1;           // mask words
+    constexpr int NW = NE * S / 4;                // words of a lane's elements
     constexpr int BPW = kWave / LPB;              // banks per wavefront
-    constexpr int LOG_LPB = LPB == 1 ? 0 : LPB == 2 ? 1 : LPB == 4 ? 2 : LPB == 8 ? 3 : LPB == 16 ? 4 : LPB == 32 ? 5 : 6;
-    constexpr int LOG_E = E == 1 ? 0 : E == 2 ? 1 : E == 4 ? 2 : 3;
-    static_assert(LPB <= 64 && NE <= 64, "lane shape");
+    constexpr int PPL = NE * S / 16;              // kAligned: 16-byte pieces per lane
+    static_assert(NE <= 64 && NE % 16 == 0, "lane shape");
+    extern __shared__ __align__(256) unsigned char pp_shared[];
 
     const int lane = threadIdx.x & (kWave - 1);
-    const int q = lane % LPB;
-    // one group of BPW banks per wavefront, no loop (a loop's invariants, hoisted, cost this
-    // kernel a fifth of its instructions and spilled scalar registers); the grid's second
-    // dimension only extends the workgroup count past 2^20
-    const int64_t wg = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-    const int64_t n_groups = (n_banks + BPW - 1) / BPW;
-    const int64_t grp = wg * (blockDim.x / kWave) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    if (grp >= n_groups) return;
-    const int pieces = B / E;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    unsigned char* pp_lds = pp_shared + wave * a.wave_bytes;
+    const int64_t grp = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * (blockDim.x / kWave) + wave;
+    const int64_t first = grp * BPW;
+    if (first >= a.n_banks) return;
+    const int n_ok = a.n_banks - first < BPW ? (int)(a.n_banks - first) : BPW;
+    const int B = a.B, k = a.k;
 
-    // per wavefront: BPW*k value slots and one trash slot per lane, then as many offsets (each
-    // rounded up to whole words)
-    extern __shared__ uint32_t pp_lds[];
-    const int words_v = ((BPW * k + kWave) * (int)sizeof(VT) + 3) / 4,
-              words_i = ((BPW * k + kWave) * (int)sizeof(IT) + 3) / 4;
-    U* lds_v = reinterpret_cast<U*>(pp_lds + (threadIdx.x / kWave) * (words_v + words_i));
-    IT* lds_i = reinterpret_cast<IT*>(reinterpret_cast<uint32_t*>(lds_v) + words_v);
+    // ---- the banks -> LDS --------------------------------------------------
+    // Where 16-byte piece p of the group sits, and (the same map) which piece sits at p.
+    auto place = [](uint32_t p) -> uint32_t {
+        if constexpr (LAYOUT == kAligned) return p ^ ((p >> 4) & (uint32_t)(PPL - 1));
+        else return p;
+    };
+    const unsigned char* src = static_cast<const unsigned char*>(a.W) + first * B * S;
+    const int bytes = n_ok * B * S;
+    const int pieces = bytes >> 4;
+    const int places = LAYOUT == kAligned ? (pieces + 15) & ~15 : pieces;
+    for (int p0 = 0; p0 < places; p0 += kWave) {
+        const int p = (int)place((uint32_t)(p0 + lane));
+        if (p0 + lane < places && p < pieces)
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void*)(src + (size_t)p * 16),
+                (__attribute__((address_space(3))) void*)(pp_lds + p0 * 16), 16, 0, 0);
+    }
+    // the matrix's last group may end inside a 16-byte piece (never kAligned)
+    const int rest = bytes & 15;
+    if (lane * S < rest)
+        *reinterpret_cast<VT*>(pp_lds + (bytes - rest) + lane * S) =
+            *reinterpret_cast<const VT*>(src + (bytes - rest) + lane * S);
+    // direct-to-LDS loads are not tracked by the compiler; only this wavefront reads them
+    pin_order();
+    wait_vm_and_lds<0>();
+    pin_order();
 
-    {
-        const int64_t g = grp * BPW + lane / LPB;     // this lane's bank
-        const bool bank_ok = g < n_banks;
-        const Raw* src = reinterpret_cast<const Raw*>(W + (bank_ok ? g : n_banks - 1) * B);
-
-        Raw raw[R];
-        uint32_t valid[NM];
+    // ---- this lane's elements ----------------------------------------------
+    const int q = lane % LPB, bank = lane / LPB;
+    const int e0 = q * a.C;                                   // first element inside the bank
+    const int n_mine = max(0, min(a.C, B - e0));
+    uint32_t w[NW];
+    if constexpr (LAYOUT == kAligned) {
+        const uint32_t p0 = (uint32_t)lane * PPL, x = (p0 >> 4) & (PPL - 1);
 #pragma unroll
-        for (int m = 0; m < NM; ++m) valid[m] = 0u;
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int p = q + LPB * j;
-            raw[j] = src[p < pieces ? p : pieces - 1];
-            if (bank_ok && p < pieces) valid[(j * E) / 32] |= ((1u << E) - 1u) << ((j * E) % 32);
+        for (int p = 0; p < PPL; ++p) {
+            const uint4 t = *reinterpret_cast<const uint4*>(pp_lds + ((p0 + ((uint32_t)p ^ x)) << 4));
+            w[4 * p] = t.x; w[4 * p + 1] = t.y; w[4 * p + 2] = t.z; w[4 * p + 3] = t.w;
         }
-
-        // one word per element (fp32), or elements e and e + 32 in the halves of word e
-        // (binary16); the sign bits land in slices that are never read
-        uint32_t w[32];
+    } else {
+        // past the lane's own elements this reads neighbours' (or bytes past the group, which
+        // the launcher allocates): masked out below
+        const unsigned char* mine = pp_lds + (bank * B + e0) * S;
+        if constexpr (LAYOUT == kWords) {
 #pragma unroll
-        for (int e = 0; e < 32; ++e) {
-            if constexpr (sizeof(VT) == 4) {
-                w[e] = e < NE ? word_of(raw[e / E], e % E) : 0u;
-            } else {
-                uint32_t lo = 0u, hi = 0u;
-                if (e < NE)
-                    lo = (word_of(raw[e / E], (e % E) >> 1) >> (16 * ((e % E) & 1))) & 0xffffu;
-                if (e + 32 < NE)
-                    hi = (word_of(raw[(e + 32) / E], ((e + 32) % E) >> 1) >>
-                          (16 * (((e + 32) % E) & 1))) & 0xffffu;
-                w[e] = lo | (hi << 16);
-            }
-        }
-        transpose32(w);
-
-        uint32_t cand[NM], gt[NM];
-#pragma unroll
-        for (int m = 0; m < NM; ++m) { cand[m] = valid[m]; gt[m] = 0u; }
-        // binary16 keys are short enough that all banks of a wavefront are often settled
-        // (every remaining candidate needed) a few bits early; for fp32 the bookkeeping
-        // costs what the exit saves
-        constexpr bool kEarlyExit = sizeof(VT) == 2;
-        int n_gt = 0, n_cand = 0;
-        if constexpr (kEarlyExit) {
-#pragma unroll
-            for (int m = 0; m < NM; ++m) n_cand += __popc(cand[m]);
-            n_cand = group_sum_i<LPB>(n_cand);
-        }
-#pragma unroll
-        for (int bit = NB - 1; bit >= 0; --bit) {
-            uint32_t ones[NM];
-            int c = 0;
-#pragma unroll
-            for (int m = 0; m < NM; ++m) {
-                ones[m] = cand[m] & w[16 * m + bit];   // NM == 2 only for binary16 (bits 0..14, 16..30)
-                c += __popc(ones[m]);
-            }
-            c = group_sum_i<LPB>(c);
-            const bool take = n_gt + c >= k;
-#pragma unroll
-            for (int m = 0; m < NM; ++m) {
-                gt[m] = take ? gt[m] : (gt[m] | ones[m]);
-                cand[m] = take ? ones[m] : (cand[m] ^ ones[m]);
-            }
-            n_gt = take ? n_gt : n_gt + c;
-            if constexpr (kEarlyExit) {
-                n_cand = take ? c : n_cand - c;
-                if ((bit & 3) == 0 && bit > 0 && __all(n_gt + n_cand == k || !bank_ok)) break;
-            }
-        }
-
-        // cand = keys equal to the k-th largest; `need` of them survive, lowest offsets first
-        const int need = k - n_gt;
-        int n_eq = 0;
-#pragma unroll
-        for (int m = 0; m < NM; ++m) n_eq += __popc(cand[m]);
-        n_eq = group_sum_i<LPB>(n_eq);
-        const bool cut = n_eq > need;
-        if (__any(cut)) {
-            int C = 0;   // largest offset with at most `need` ties below it
-#pragma unroll 1
-            for (int step = sizeof(IT) == 1 ? 128 : 32768; step > 0; step >>= 1) {
-                const int t = C | step;
-                const int P = t >> LOG_E;
-                const int mine = ((P - q + LPB - 1) >> LOG_LPB) * E +
-                                 ((P & (LPB - 1)) == q ? (t & (E - 1)) : 0);   // my elements below t
-                int f = 0;
-#pragma unroll
-                for (int m = 0; m < NM; ++m) f += __popc(cand[m] & low_bits(mine, m));
-                f = group_sum_i<LPB>(f);
-                if (f <= need) C = t;
-            }
-            const int P = C >> LOG_E;
-            const int mine = ((P - q + LPB - 1) >> LOG_LPB) * E +
-                             ((P & (LPB - 1)) == q ? (C & (E - 1)) : 0);
-#pragma unroll
-            for (int m = 0; m < NM; ++m)
-                if (cut) cand[m] &= low_bits(mine, m);
-        }
-        uint32_t keep[NM];
-#pragma unroll
-        for (int m = 0; m < NM; ++m) keep[m] = gt[m] | cand[m];
-
-        // Output slots in offset order: pieces ascend with j, then with the lane.  The
-        // wavefront's banks are adjacent in vals and idx, so the kept entries are put in
-        // order in the wavefront's own LDS and leave as whole words.
-        // The kept counts of a lane's R pieces are packed FPW to a word, so one prefix and one
-        // sum over the group's lanes serve FPW pieces (a field holds a whole group's count).
-        constexpr int FB = LPB * E < 256 ? 8 : 16, FPW = 32 / FB, NW = (R + FPW - 1) / FPW;
-        uint32_t pms[R], packed[NW];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) packed[w] = 0u;
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            pms[j] = (keep[(j * E) / 32] >> ((j * E) % 32)) & ((1u << E) - 1u);
-            packed[j / FPW] |= (uint32_t)__popc(pms[j]) << ((j % FPW) * FB);
-        }
-        uint32_t before[NW], total[NW];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            before[w] = (uint32_t)group_prefix_i<LPB>((int)packed[w], q);
-            total[w] = (uint32_t)group_sum_i<LPB>((int)packed[w]);
-        }
-        int kept_base = (lane / LPB) * k;
-        const int trash = BPW * k + lane;   // a slot of the lane's own behind the wavefront's output
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            constexpr uint32_t kField = (1u << FB) - 1u;
-            const uint32_t pm = pms[j];
-            const int slot = kept_base + (int)((before[j / FPW] >> ((j % FPW) * FB)) & kField);
-            kept_base += (int)((total[j / FPW] >> ((j % FPW) * FB)) & kField);
-            const int off0 = (q + LPB * j) * E;
-            // Pieces of four elements are written without branches (every element is stored,
-            // a dropped one to the lane's trash slot: 5-8 % faster on the fp32 matrices);
-            // with 8 binary16 elements or single elements per piece most stores would be
-            // wasted and the conditional form is faster (measured both ways).
-            constexpr bool kBranchFree = E == 4;
-            if (remap || !kBranchFree) {   // remap: re-pruning, the survivors carry the stored offsets
-                int at = slot;
-#pragma unroll
-                for (int i = 0; i < E; ++i) {
-                    if (pm & (1u << i)) {
-                        uint32_t v = word_of(raw[j], sizeof(VT) == 4 ? i : i >> 1);
-                        if (sizeof(VT) == 2) v = (i & 1) ? (v >> 16) : (v & 0xffffu);
-                        lds_v[at] = (U)v;
-                        lds_i[at] = remap ? remap[g * B + off0 + i] : (IT)(off0 + i);
-                        ++at;
-                    }
-                }
-            } else {
-                int n_before = 0;
-#pragma unroll
-                for (int i = 0; i < E; ++i) {
-                    const int kept = (int)((pm >> i) & 1u);
-                    const int at = kept ? slot + n_before : trash;
-                    uint32_t v = word_of(raw[j], sizeof(VT) == 4 ? i : i >> 1);
-                    if (sizeof(VT) == 2) v = (i & 1) ? (v >> 16) : (v & 0xffffu);
-                    lds_v[at] = (U)v;
-                    lds_i[at] = (IT)(off0 + i);
-                    n_before += kept;
-                }
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-        const int64_t first = grp * BPW;                          // same for the wavefront
-        U* vout = reinterpret_cast<U*>(vals) + first * k;
-        IT* iout = idx + first * k;
-        const int n_ok = n_banks - first < BPW ? (int)(n_banks - first) : BPW;
-        const int n_out = n_ok * k;
-        // a full group whose values and offsets are whole words (always so with 4 or more
-        // banks per wavefront) leaves as words: every group then starts word-aligned
-        if (n_ok == BPW && (BPW * k * (int)sizeof(VT)) % 4 == 0 && (BPW * k * (int)sizeof(IT)) % 4 == 0) {
-            const int vw = n_out * (int)sizeof(VT) / 4, iw = n_out * (int)sizeof(IT) / 4;
-            for (int t = lane; t < vw; t += kWave)
-                reinterpret_cast<uint32_t*>(vout)[t] = reinterpret_cast<const uint32_t*>(lds_v)[t];
-            for (int t = lane; t < iw; t += kWave)
-                reinterpret_cast<uint32_t*>(iout)[t] = reinterpret_cast<const uint32_t*>(lds_i)[t];
+            for (int i = 0; i < NW; ++i) w[i] = reinterpret_cast<const uint32_t*>(mine)[i];
         } else {
-            for (int t = lane; t < n_out; t += kWave) {
-                vout[t] = lds_v[t];
-                iout[t] = lds_i[t];
+#pragma unroll
+            for (int i = 0; i < NW; ++i)
+                w[i] = (uint32_t)reinterpret_cast<const uint16_t*>(mine)[2 * i] |
+                       ((uint32_t)reinterpret_cast<const uint16_t*>(mine)[2 * i + 1] << 16);
+        }
+    }
+
+    // ---- the k largest keys --------------------------------------------------
+    Select<NM> t;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+        t.cand[m] = low_bits(min(32, max(0, n_mine - 32 * m)));
+        t.gt[m] = 0u;
+    }
+    t.r1 = k - 1;
+    if constexpr (S == 4) {
+        select_byte<3, LPB, NE, NM>(t, w);
+        select_byte<2, LPB, NE, NM>(t, w);
+        if (!settled<LPB, NM>(t)) {
+            select_byte<1, LPB, NE, NM>(t, w);
+            if (!settled<LPB, NM>(t)) select_byte<0, LPB, NE, NM>(t, w);
+        }
+    } else {
+        select_byte16<1, LPB, NE, NM, NW>(t, w);
+        if (!settled<LPB, NM>(t)) select_byte16<0, LPB, NE, NM, NW>(t, w);
+    }
+    // candidates beyond the r1 + 1 still needed are ties with the threshold: the lowest
+    // offsets stay, i.e. the first lanes of the bank and each lane's lowest bits
+    {
+        int own = 0;
+#pragma unroll
+        for (int m = 0; m < NM; ++m) own += __popc(t.cand[m]);
+        const int room = t.r1 + 1 - group_prefix_i<LPB>(own, q);   // ties this lane may keep
+        if (__any(own > room)) {
+            const int want = max(0, min(own, room));
+            int left = want;
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                const int here = __popc(t.cand[m]);
+                if (left < here) {
+                    // smallest n with `left` candidates among the n lowest bits
+                    int n = 0;
+#pragma unroll
+                    for (int step = 16; step > 0; step >>= 1)
+                        if (__popc(t.cand[m] & low_bits(n + step)) <= left) n += step;
+                    t.cand[m] &= low_bits(n);
+                    left = 0;
+                } else {
+                    left -= here;
+                }
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
     }
-}
 
-template <typename VT, typename IT, int PB, int LPB, int R>
-int launch_shape(const VT* w, VT* v, IT* idx, const IT* remap, int64_t n_banks, int bank,
-                 int k, hipStream_t st) {
-    constexpr int E = PB / (int)sizeof(VT);
-    if constexpr (R * E > 64 || (sizeof(VT) == 4 && R * E > 32)) {
-        return BS_ERR_UNSUPPORTED;   // not a shape the planner below produces
-    } else {
-        const int threads = 256;
-        const int64_t groups = (n_banks + (kWave / LPB) - 1) / (kWave / LPB);
-        const int64_t wgs = (groups + threads / kWave - 1) / (threads / kWave);
-        const int64_t gx = wgs < ((int64_t)1 << 20) ? wgs : ((int64_t)1 << 20);
-        const int64_t gy = (wgs + gx - 1) / gx;
-        if (gy > 65535) return BS_ERR_UNSUPPORTED;
-        constexpr int BPW = kWave / LPB;
-        const size_t slots = (size_t)BPW * k + kWave;   // the wavefront's output and a trash slot per lane
-        const size_t lds = (size_t)(threads / kWave) * 4 *
-                           ((slots * sizeof(VT) + 3) / 4 + (slots * sizeof(IT) + 3) / 4);
-        hipLaunchKernelGGL((prune_pack_lanes<VT, IT, PB, LPB, R>), dim3((unsigned)gx, (unsigned)gy), dim3(threads),
-                           lds, st, w, v, idx, remap, n_banks, bank, k);
-        return hip_status(hipGetLastError());
-    }
-}
-
-template <typename VT, typename IT, int PB, int LPB>
-int launch_r(int r, const VT* w, VT* v, IT* idx, const IT* remap, int64_t n_banks,
-             int bank, int k, hipStream_t st) {
-#define BS_PP_CASE(RR) case RR: return launch_shape<VT, IT, PB, LPB, RR>(w, v, idx, remap, n_banks, bank, k, st);
-    if constexpr (PB == 16) {
-        switch (r) {
-            BS_PP_CASE(1) BS_PP_CASE(2) BS_PP_CASE(3) BS_PP_CASE(4)
-            BS_PP_CASE(5) BS_PP_CASE(6) BS_PP_CASE(7) BS_PP_CASE(8)
+    // ---- offsets of the survivors, in order ----------------------------------
+    IT* out_i = reinterpret_cast<IT*>(pp_lds + a.raw_bytes);
+    {
+        int own = 0;
+#pragma unroll
+        for (int m = 0; m < NM; ++m) own += __popc(t.gt[m] | t.cand[m]);
+        IT* dst = out_i + bank * k + group_prefix_i<LPB>(own, q);
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            uint32_t keep = t.gt[m] | t.cand[m];
+            while (keep) {
+                *dst++ = (IT)(e0 + 32 * m + __builtin_ctz(keep));
+                keep &= keep - 1u;
+            }
         }
-    } else {   // narrow pieces: fewer shapes, unused pieces are masked
-        switch (r) { BS_PP_CASE(4) BS_PP_CASE(8) BS_PP_CASE(16) BS_PP_CASE(32) }
     }
-#undef BS_PP_CASE
-    return BS_ERR_UNSUPPORTED;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+
+    // ---- values and offsets out ------------------------------------------------
+    auto value = [&](int slot, uint32_t off) -> VT {
+        const uint32_t e = div_magic((uint32_t)slot, (uint32_t)k, a.magic_k) * (uint32_t)B + off;
+        uint32_t at = e * S;
+        if constexpr (LAYOUT == kAligned) at = (place(at >> 4) << 4) | (at & 15u);
+        return *reinterpret_cast<const VT*>(pp_lds + at);
+    };
+    VT* vout = static_cast<VT*>(a.vals) + first * k;
+    IT* iout = static_cast<IT*>(a.idx) + first * k;
+    const int n_out = n_ok * k;
+    if (a.remap) {   // the survivors carry the offsets the packed matrix already holds
+        const IT* stored = static_cast<const IT*>(a.remap) + first * B;
+        for (int s = lane; s < n_out; s += kWave) {
+            const uint32_t off = out_i[s];
+            vout[s] = value(s, off);
+            iout[s] = stored[div_magic((uint32_t)s, (uint32_t)k, a.magic_k) * (uint32_t)B + off];
+        }
+        return;
+    }
+    // four outputs per lane and step; a group starts on a multiple of four outputs unless
+    // it holds two banks (LPB == 32), and only the matrix's last group may end elsewhere
+    const int quads = LPB <= 16 || k % 2 == 0 ? n_out >> 2 : 0;
+    using Quad = typename RawBytes<4 * S>::type;
+    using IQuad = typename RawBytes<4 * sizeof(IT)>::type;
+    for (int s = lane; s < quads; s += kWave) {
+        const IQuad o = reinterpret_cast<const IQuad*>(out_i)[s];
+        VT v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t off = sizeof(IT) == 1 ? (word_of(o, 0) >> (8 * i)) & 0xffu
+                                                 : (word_of(o, i >> 1) >> (16 * (i & 1))) & 0xffffu;
+            v[i] = value(4 * s + i, off);
+        }
+        Quad vq;
+        __builtin_memcpy(&vq, v, sizeof(vq));
+        reinterpret_cast<Quad*>(vout)[s] = vq;
+        reinterpret_cast<IQuad*>(iout)[s] = o;
+    }
+    for (int s = 4 * quads + lane; s < n_out; s += kWave) {
+        const uint32_t off = out_i[s];
+        vout[s] = value(s, off);
+        iout[s] = (IT)off;
+    }
 }
 
-// Byte offsets: 1..16 lanes per bank (B <= 256).  16-bit offsets: 8..64 lanes per bank, banks
-// whose byte length is a multiple of 16 only (PB == 16).
-template <typename VT, typename IT, int PB>
-int launch_pb(const void* W, int64_t n_banks, int bank, int k, void* vals, IT* idx,
-              const IT* remap, hipStream_t st) {
+template <typename VT, typename IT, int LPB, int NE, LaneLayout LAYOUT>
+int prune_launch_one(PruneArgs a, hipStream_t st) {
+    constexpr int BPW = kWave / LPB, S = sizeof(VT);
+    // the banks, and what the last lane's fixed-size read may reach past them
+    a.raw_bytes = (BPW * a.B * S + (LAYOUT == kAligned ? 0 : (LPB * a.C - a.B + NE) * S) + 15) / 16 * 16;
+    a.wave_bytes = (a.raw_bytes + BPW * a.k * (int)sizeof(IT) + 255) / 256 * 256;
+    int waves = kPruneWaves;
+    while (waves * a.wave_bytes > 48 * 1024) waves >>= 1;   // at most 24.5 KB per wavefront
+    const int64_t groups = (a.n_banks + BPW - 1) / BPW;
+    const int64_t wgs = (groups + waves - 1) / waves;
+    const int64_t gx = wgs < ((int64_t)1 << 20) ? wgs : ((int64_t)1 << 20);
+    const int64_t gy = (wgs + gx - 1) / gx;
+    if (gy > 65535) return BS_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((prune_pack_kernel<VT, IT, LPB, NE, LAYOUT>), dim3((unsigned)gx, (unsigned)gy),
+                       dim3(kWave * waves), (size_t)waves * a.wave_bytes, st, a);
+    return hip_status(hipGetLastError());
+}
+
+template <typename VT, typename IT, int LPB, int NE>
+int prune_launch_layout(const PruneArgs& a, hipStream_t st) {
+    if (a.B == LPB * a.C && a.C == NE && NE * sizeof(VT) >= 64)
+        return prune_launch_one<VT, IT, LPB, NE, kAligned>(a, st);
+    if constexpr (sizeof(VT) == 2 && sizeof(IT) == 1)   // wide banks are whole 16-byte pieces
+        if (a.B % 2 != 0) return prune_launch_one<VT, IT, LPB, NE, kHalves>(a, st);
+    return prune_launch_one<VT, IT, LPB, NE, kWords>(a, st);
+}
+
+// W viewed as n_banks banks of `bank` elements, k kept per bank.  As few lanes per bank as 32
+// elements per lane allow (one mask word): a select step costs a wavefront the same whatever
+// its lanes hold, and up to 64 per lane would need a third fewer instructions, but the LDS a
+// wavefront holds doubles and the wavefronts that are left hide less of the stream
+// (one wavefront per workgroup:
+// 19.5 against 18.4 us on the 6000 x 3000 matrix, 48.0 against 44.5 us on the binary16 one).  Banks over 1024 elements: 32 lanes of up to 64.
+template <typename VT, typename IT>
+int prune_banks(const void* W, int64_t n_banks, int bank, int k, void* vals, IT* idx,
+                const IT* remap, hipStream_t st) {
     constexpr bool kWide = sizeof(IT) == 2;
-    static_assert(!kWide || PB == 16, "wide banks are cut into 16-byte pieces");
-    constexpr int E = PB / (int)sizeof(VT);
-    constexpr int kMaxPerLane = (sizeof(VT) == 4 ? 32 : 64) / E;   // elements fit the lane's masks
-    constexpr int r_max = PB == 16 ? 8 : (kMaxPerLane < 32 ? kMaxPerLane : 32);
-    constexpr int lpb_min = kWide ? 8 : 1, lpb_max = kWide ? 64 : 16;
-    const int pieces = bank / E;
-    int lpb = lpb_min;
-    while (lpb < lpb_max && (pieces + lpb - 1) / lpb > r_max) lpb <<= 1;
-    int r = (pieces + lpb - 1) / lpb;
-    if (r > r_max) return BS_ERR_UNSUPPORTED;
-    if (PB != 16) r = r <= 4 ? 4 : r <= 8 ? 8 : r <= 16 ? 16 : 32;
-    const VT* w = static_cast<const VT*>(W);
-    VT* v = static_cast<VT*>(vals);
-    if constexpr (kWide) {
-        switch (lpb) {
-            case 8: return launch_r<VT, IT, PB, 8>(r, w, v, idx, remap, n_banks, bank, k, st);
-            case 16: return launch_r<VT, IT, PB, 16>(r, w, v, idx, remap, n_banks, bank, k, st);
-            case 32: return launch_r<VT, IT, PB, 32>(r, w, v, idx, remap, n_banks, bank, k, st);
-            case 64: return launch_r<VT, IT, PB, 64>(r, w, v, idx, remap, n_banks, bank, k, st);
-        }
-    } else {
-        switch (lpb) {
-            case 1: return launch_r<VT, IT, PB, 1>(r, w, v, idx, remap, n_banks, bank, k, st);
-            case 2: return launch_r<VT, IT, PB, 2>(r, w, v, idx, remap, n_banks, bank, k, st);
-            case 4: return launch_r<VT, IT, PB, 4>(r, w, v, idx, remap, n_banks, bank, k, st);
-            case 8: return launch_r<VT, IT, PB, 8>(r, w, v, idx, remap, n_banks, bank, k, st);
-            case 16: return launch_r<VT, IT, PB, 16>(r, w, v, idx, remap, n_banks, bank, k, st);
-        }
+    PruneArgs a;
+    a.W = W; a.vals = vals; a.idx = idx; a.remap = remap;
+    a.n_banks = n_banks; a.B = bank; a.k = k;
+    a.magic_k = magic_u32((uint32_t)k);
+    a.raw_bytes = a.wave_bytes = 0;
+    int lpb = 1;
+    while (lpb < 32 && (bank + lpb - 1) / lpb > 32) lpb <<= 1;
+    a.C = (bank + lpb - 1) / lpb;
+    if (sizeof(VT) == 2 && lpb > 1) a.C = (a.C + 1) & ~1;   // binary16: a lane starts on a word
+    if (a.C > 64) return BS_ERR_UNSUPPORTED;
+    switch (lpb) {
+        case 1:
+            if (a.C <= 16) return prune_launch_layout<VT, IT, 1, 16>(a, st);
+            return prune_launch_layout<VT, IT, 1, 32>(a, st);
+        case 2: return prune_launch_layout<VT, IT, 2, 32>(a, st);
+        case 4: return prune_launch_layout<VT, IT, 4, 32>(a, st);
+        case 8: return prune_launch_layout<VT, IT, 8, 32>(a, st);
+        case 16: if constexpr (kWide) return prune_launch_layout<VT, IT, 16, 32>(a, st); break;
+        case 32:
+            if constexpr (kWide) {
+                if (a.C <= 32) return prune_launch_layout<VT, IT, 32, 32>(a, st);
+                return prune_launch_layout<VT, IT, 32, 64>(a, st);
+            }
     }
     return BS_ERR_UNSUPPORTED;
 }
