@@ -14,8 +14,8 @@
 // Algorithm 1 compares against a threshold with "<", which would keep every
 // element tied with the threshold; counting keeps exactly k instead.
 //
-// LPB lanes share a bank, each owning C consecutive elements of it (C <= 64), so a
-// wavefront works on 64/LPB banks at once.  What bounds this kernel is the vector ALU
+// LPB lanes share a bank, each owning C consecutive elements of it (C <= 32, 64 in banks over
+// 1024), so a wavefront works on 64/LPB banks at once.  What bounds this kernel is the vector ALU
 // until it gets below the stream of W, so every step is built to touch an element few times:
 //   * the wavefront's banks are one contiguous piece of W; it goes to LDS with
 //     direct-to-LDS loads (no registers) and stays there, so that a kept value is fetched
@@ -36,7 +36,7 @@
 // trash slot: 6000 x 3000 fp32, 10 of 100 kept: 22.4 -> 16.8 us (4.8 TB/s of W, vals and idx;
 // a large copy runs at 4.7); 4096 x 25088 binary16, 6 of 64: 62.9 -> 46.6 us (5.0 TB/s);
 // 11908 x 7616 binary16, 18 of 64: 63.5 -> 52.7 us.  Vector instructions on the first: 12.9 M
-// -> 5.8 M with two mask words per lane, 7 M with one.
+// -> 7.1 M.
 // Re-pruning a packed matrix to fewer weights per bank (one more round of
 // Algorithm 1's loop) runs the same kernel on the stored values, k per bank.
 #pragma once
