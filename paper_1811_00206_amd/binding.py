@@ -2,13 +2,16 @@
 
 Argument marshalling only: each function checks tensor device / dtype /
 contiguity, passes raw device pointers and torch's current HIP stream to the
-library, and raises :class:`BsError` on a non-zero status.  There is no Python
-or CPU implementation behind these names; if the library is missing the first
-call fails.
+library, and raises :class:`BsError` on a non-zero status.  The usual case is
+marshalled in native code (``csrc/bs_calls.cpp``); whatever that does not take
+returns None from it, with nothing enqueued, and goes through the checks below,
+which say what is wrong.  There is no Python or CPU implementation behind these
+names; if a library is missing the first call fails.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 
 import torch
@@ -33,6 +36,7 @@ class BsError(RuntimeError):
 
 
 _lib = None
+_native = None
 
 
 def library_path() -> str:
@@ -41,7 +45,7 @@ def library_path() -> str:
 
 def load_library():
     """Load ``libbs.so`` (built by ``python -m paper_1811_00206_amd.build``)."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -89,8 +93,16 @@ def load_library():
     for name in ("bs_init", "bs_prune_pack", "bs_spmv", "bs_spmv_ex", "bs_spmm", "bs_spmm_static", "bs_dense_gemv",
                  "bs_dense_gemm", "bs_lstm_step", "bs_lstm_sequence", "bs_reprune"):
         getattr(lib, name).restype = i32
+    _native = importlib.import_module("._native", __package__)   # built with libbs.so
     _lib = lib
     return lib
+
+
+def _calls():
+    """The native marshalling module."""
+    if _native is None:
+        load_library()
+    return _native
 
 
 # ------------------------------------------------------------------ helpers
@@ -129,7 +141,7 @@ def _rows(t: torch.Tensor, what: str) -> int:
 
 
 def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_calls().stream())
 
 
 def _ptr(t) -> ctypes.c_void_p:
@@ -198,6 +210,9 @@ def bs_spmm_plan(dtype: int, M: int, K: int, bank: int, k: int, N: int) -> dict:
 def bs_prune_pack(W: torch.Tensor, bank: int, k: int, out=None):
     """W [M, K] on the GPU (fp32/fp16) -> (vals [M, K/bank, k], idx uint8 same shape);
     `out` = (vals, idx) to write into existing tensors."""
+    done = (_native or _calls()).prune_pack(W, bank, k, out, False)
+    if done is not None:
+        return done
     _dev(W, "W")
     code = _dtype_code(W, "W")
     if W.dim() != 2:
@@ -233,6 +248,10 @@ def bs_spmv(vals, idx, bank: int, x, out=None, lanes_per_row: int = 0, rows_per_
             start_event: int = 0, stop_event: int = 0):
     """y [M] = W_sparse . x, x [K] fp32 on the GPU.  start_event / stop_event are
     optional raw hipEvent_t handles that receive the kernel's own time stamps."""
+    if not (lanes_per_row or rows_per_wg or start_event or stop_event):
+        y = (_native or _calls()).spmv(vals, idx, bank, x, out, False)
+        if y is not None:
+            return y
     code, M, K, k = _packed(vals, idx, bank)
     _dev(x, "x", torch.float32)
     if x.numel() != K:
@@ -293,6 +312,9 @@ def bs_spmm(vals, idx, bank: int, X, out=None, workspace=None):
     leading dimensions).  `workspace` is an optional uint8 tensor of at least
     bs_spmm_workspace_bytes(...) bytes; without it one is taken from torch's allocator
     for this call."""
+    Y = (_native or _calls()).spmm(vals, idx, bank, X, out, workspace, False)
+    if Y is not None:
+        return Y
     code, M, K, k = _packed(vals, idx, bank)
     ldx = _rows(X, "X")
     if X.shape[0] != K:
@@ -377,6 +399,9 @@ def bs_spmm_workspace_bytes_wide(dtype: int, M: int, K: int, bank: int, k: int, 
 
 def bs_prune_pack_wide(W: torch.Tensor, bank: int, k: int, out=None):
     """W [M, K] on the GPU (fp32/fp16) -> (vals [M, K/bank, k], idx uint16 same shape)."""
+    done = (_native or _calls()).prune_pack(W, bank, k, out, True)
+    if done is not None:
+        return done
     _dev(W, "W")
     code = _dtype_code(W, "W")
     if W.dim() != 2:
@@ -410,6 +435,9 @@ def _packed_wide(vals, idx, bank):
 
 def bs_spmv_wide(vals, idx, bank: int, x, out=None):
     """y [M] = W_sparse . x for a packed matrix with uint16 offsets."""
+    y = (_native or _calls()).spmv(vals, idx, bank, x, out, True)
+    if y is not None:
+        return y
     code, M, K, k = _packed_wide(vals, idx, bank)
     _dev(x, "x", torch.float32)
     if x.numel() != K:
@@ -425,6 +453,9 @@ def bs_spmv_wide(vals, idx, bank: int, x, out=None):
 
 def bs_spmm_wide(vals, idx, bank: int, X, out=None, workspace=None):
     """Y [M, N] = W_sparse . X for a packed matrix with uint16 offsets (see bs_spmm)."""
+    Y = (_native or _calls()).spmm(vals, idx, bank, X, out, workspace, True)
+    if Y is not None:
+        return Y
     code, M, K, k = _packed_wide(vals, idx, bank)
     ldx = _rows(X, "X")
     if X.shape[0] != K:
@@ -457,6 +488,9 @@ def _lstm_shape(vals, idx, bank):
 
 def bs_lstm_step(vals, idx, bank: int, x, h, bias, c, c_out=None, h_out=None):
     """One LSTM step on the packed 4H x (I+H) gate matrix: returns (c_out, h_out)."""
+    done = (_native or _calls()).lstm_step(vals, idx, bank, x, h, bias, c, c_out, h_out)
+    if done is not None:
+        return done
     code, H, I, k = _lstm_shape(vals, idx, bank)
     for t, name, n in ((x, "x", I), (h, "h", H), (bias, "bias", 4 * H), (c, "c", H)):
         _dev(t, name, torch.float32)
@@ -474,6 +508,9 @@ def bs_lstm_step(vals, idx, bank: int, x, h, bias, c, c_out=None, h_out=None):
 
 def bs_lstm_sequence(vals, idx, bank: int, X, h0, bias, c, H_all=None):
     """T steps; X is [T, I]; `c` is updated in place.  Returns H_all [T, H]."""
+    done = (_native or _calls()).lstm_sequence(vals, idx, bank, X, h0, bias, c, H_all)
+    if done is not None:
+        return done
     code, H, I, k = _lstm_shape(vals, idx, bank)
     _dev(X, "X", torch.float32)
     if X.dim() != 2 or X.shape[1] != I:
@@ -494,6 +531,9 @@ def bs_lstm_sequence(vals, idx, bank: int, X, h0, bias, c, H_all=None):
 def bs_reprune(vals, idx, bank: int, k2: int, out=None):
     """Packed [M, K/bank, k] -> packed [M, K/bank, k2], k2 <= k: (vals2, idx2);
     `out` = (vals2, idx2) to write into existing tensors."""
+    done = (_native or _calls()).reprune(vals, idx, bank, k2, out)
+    if done is not None:
+        return done
     code, M, K, k = _packed(vals, idx, bank)
     if k2 < 1 or k2 > k:
         raise BsError(2, "bs_reprune")

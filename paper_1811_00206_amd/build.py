@@ -1,9 +1,11 @@
-"""Build ``libbs.so`` and ``libbs_probe.so`` in-tree with hipcc for gfx950.
+"""Build ``libbs.so``, ``_native.so`` and ``libbs_probe.so`` in-tree for gfx950.
 
 ``python -m paper_1811_00206_amd.build`` compiles every ``csrc/*.hip`` into the
-product library ``libbs.so`` and every ``probe/*.hip`` (measurement helpers for
-the benchmark, not part of the method) into ``libbs_probe.so``, both next to
-this file.  Cross-compilation needs no GPU.
+product library ``libbs.so``, ``csrc/bs_calls.cpp`` (host code: the marshalling
+of the Python calls, against torch's headers) into the extension module
+``_native.so``, and every ``probe/*.hip`` (measurement helpers for the
+benchmark, not part of the method) into ``libbs_probe.so``, all next to this
+file.  Cross-compilation needs no GPU.
 """
 from __future__ import annotations
 
@@ -11,6 +13,7 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -19,6 +22,8 @@ PROBE_SRC = os.path.join(HERE, "probe")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libbs.so")
 PROBE_LIB = os.path.join(HERE, "libbs_probe.so")
+NATIVE_SRC = os.path.join(CSRC, "bs_calls.cpp")
+NATIVE_LIB = os.path.join(HERE, "_native.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -51,21 +56,44 @@ def _link(lib: str, objs) -> None:
     os.replace(tmp, lib)
 
 
+def _compile_native() -> str:
+    import torch
+    from torch.utils import cpp_extension
+    obj = os.path.join(OBJDIR, "bs_calls.cpp.o")
+    inc = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], "/opt/rocm/include"]
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+                           "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                           *(f"-isystem{d}" for d in inc), "-c", NATIVE_SRC, "-o", obj])
+    return obj
+
+
+def _link_native(obj: str) -> None:
+    # torch's libraries are loaded when this module is; libbs.so lies beside it
+    import torch
+    tmp = NATIVE_LIB + f".tmp{os.getpid()}"
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-shared", "-o", tmp, obj,
+                           "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu",
+                           "-lc10", "-lc10_hip", "-L" + HERE, "-l:libbs.so", "-Wl,-rpath,$ORIGIN"])
+    os.replace(tmp, NATIVE_LIB)
+
+
 def build_library(verbose: bool = False) -> str:
-    """Compile all sources (always; no staleness shortcut) and link libbs.so and
-    libbs_probe.so."""
+    """Compile all sources (always; no staleness shortcut) and link libbs.so, _native.so
+    and libbs_probe.so."""
     os.makedirs(OBJDIR, exist_ok=True)
     srcs, psrcs = sources(), probe_sources()
     if not srcs:
         raise RuntimeError("no HIP sources found under " + CSRC)
-    jobs = max(1, min(len(srcs) + len(psrcs), 8, os.cpu_count() or 1))
+    jobs = max(1, min(len(srcs) + len(psrcs) + 1, 8, os.cpu_count() or 1))
     with ThreadPoolExecutor(jobs) as ex:
+        native = ex.submit(_compile_native)
         objs = list(ex.map(_compile, srcs + psrcs))
     _link(LIB, objs[:len(srcs)])
+    _link_native(native.result())
     if psrcs:
         _link(PROBE_LIB, objs[len(srcs):])
     if verbose:
-        print("built", LIB, "and", PROBE_LIB)
+        print("built", LIB + ",", NATIVE_LIB, "and", PROBE_LIB)
     return LIB
 
 
