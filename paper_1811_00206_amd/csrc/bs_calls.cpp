@@ -74,14 +74,18 @@ int64_t row_pitch(const at::Tensor& t) {
     return ld < n ? -1 : ld;
 }
 
+// Gives the interpreter lock up for its lifetime; a destructor, since tensors without memory
+// (fake ones, those of a transform) throw when their address is asked for.
+struct WithoutLock {
+    PyThreadState* state = PyEval_SaveThread();
+    ~WithoutLock() { PyEval_RestoreThread(state); }
+};
+
 // the C ABI, without the interpreter lock (a full queue makes a launch wait for the GPU)
 template <typename F>
 bool enqueue(F&& call) {
-    int status;
-    Py_BEGIN_ALLOW_THREADS
-    status = call(current_stream());
-    Py_END_ALLOW_THREADS
-    return status == BS_OK;
+    const WithoutLock unlocked;
+    return call(current_stream()) == BS_OK;
 }
 
 #define BS_TRY try {
