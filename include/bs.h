@@ -182,7 +182,7 @@ size_t bs_spmm_workspace_bytes(int dtype, int64_t M, int64_t K, int bank, int k,
  *       column group          [1] entries per 16-byte chunk
  *   [2] column groups of 4 per tile (nl)   [3] columns per tile   [4] column tiles
  *   [5] banks per K slab       [6] K slabs  [7] lanes per (row, column group)
- *   [8] chunk slots per lane   [9] threads per workgroup   [10] rows per workgroup
+ *   [8] chunk slots per lane   [9] threads that walk rows   [10] rows per workgroup
  *   [11] row groups            [12] row passes of a workgroup
  *   [13] LDS bytes per workgroup            [14] workgroups launched
  *   [15] float index of the position table in LDS

@@ -17,7 +17,8 @@ struct SpmmPlan {
     int sb, n_slabs;   // banks per slab
     int lpr, u;        // lanes per (row, column group), chunk slots per lane
     bool rows;         // one lane per (row, column group): bs_spmm_rows_kernel.h
-    int threads;
+    int threads;       // of a workgroup
+    int row_threads;   // of these, the lanes that walk rows
     int rows_per_wg, row_groups;
     int table_off;
     size_t lds_bytes;
@@ -114,6 +115,15 @@ SpmmPlan plan_for(int quads, int dtype, int64_t M, int64_t K, int bank, int k, i
     const int64_t rows_per_pass = (rpw + passes - 1) / passes;
     int64_t threads = (rows_per_pass * lanes_per_row + kWave - 1) / kWave * kWave;
     if (threads > max_threads) threads = max_threads;
+    p.row_threads = (int)threads;
+    // With few rows per workgroup those wavefronts are too few to bring the tile in: each more
+    // copies a share of it and leaves (up to 8 pieces of 16 bytes per lane).  1024 x 1024 at
+    // N = 37: 22.2 -> 12.0 us, at N = 40: 12.8 -> 11.2 us.  Where half of them walk rows already
+    // and the pieces are of 16 bytes, the others cost more than they bring (6000 x 3000 at
+    // N = 40: 17.0 -> 17.7 us); with pieces of 4 bytes they still help (N = 37: 19.8 -> 18.5 us).
+    int64_t copy_threads = (int64_t)(tile_bytes / (8 * 16) + kWave - 1) / kWave * kWave;
+    if (copy_threads > max_threads) copy_threads = max_threads;
+    if (threads * (N % 4 ? 1 : 2) < copy_threads) threads = copy_threads;
     p.threads = (int)threads;
     p.ws_bytes = p.n_slabs > 1 ? (size_t)p.n_slabs * M * N * 4 : 0;
     const double w_bytes = (double)M * row_len * (vsize + isize);
@@ -139,7 +149,7 @@ SpmmPlan make_plan(int dtype, int64_t M, int64_t K, int bank, int k, int64_t N, 
 
 // Y[r][n] = sum over slabs, in slab order.  magic_n = magic_u32(N): rows from element
 // numbers without a 64-bit division (M*N < 2^32 is checked by the caller).
-// V = floats per lane and step: 4 when N, ldy and Y's address allow 16-byte accesses.
+// V = floats per lane and step: 4 when M, N, ldy and Y's address allow 16-byte accesses.
 // The kernel is one round trip to memory long, so the loads of up to kBatch slabs are
 // issued together and only then added, in slab order (one load after the other made
 // three slabs cost three round trips: 4.5 us for a kernel with nothing to compute).
@@ -151,7 +161,7 @@ __global__ __launch_bounds__(256) void spmm_reduce_kernel(const float* __restric
     constexpr int kBatch = 8;
     using Vec = typename std::conditional<V == 4, float4, float>::type;
     const int64_t total = M * N;
-    const int64_t steps = total / V;                       // V divides N
+    const int64_t steps = total / V;                       // V divides N, or M*N if ldy = N
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < steps;
          j += (int64_t)gridDim.x * blockDim.x) {
         const int64_t i = j * V;
@@ -242,9 +252,9 @@ int spmm_plan_describe(int dtype, int64_t M, int64_t K, int bank, int k, int64_t
     const int64_t total = (int64_t)p.n_tiles * p.n_slabs * p.row_groups;
     if (total > INT32_MAX / 2) return BS_ERR_UNSUPPORTED;
     if (p.ws_bytes && M * N > (int64_t)UINT32_MAX) return BS_ERR_UNSUPPORTED;
-    const int rows_per_pass = p.threads / (p.nl * p.lpr);
+    const int rows_per_pass = p.row_threads / (p.nl * p.lpr);
     const int64_t v[16] = {p.rows ? 1 : 0, p.ch, p.nl, p.nt, p.n_tiles, p.sb, p.n_slabs, p.lpr, p.u,
-                           p.threads, p.rows_per_wg, p.row_groups,
+                           p.row_threads, p.rows_per_wg, p.row_groups,
                            (p.rows_per_wg + rows_per_pass - 1) / rows_per_pass,
                            (int64_t)p.lds_bytes, (total + kXcds - 1) / kXcds * kXcds, p.table_off};
     for (int i = 0; i < n_out && i < 16; ++i) out[i] = v[i];
@@ -283,7 +293,8 @@ int launch_spmm_any(const void* vals, const void* idx, int isize, int dtype, int
     a.magic_rgs = magic_u32((uint32_t)(p.row_groups * p.n_slabs));
     // 16-byte direct-to-LDS copies need 16-byte aligned row pieces and whole groups of 4 columns
     a.dma = (N % 4 == 0 && ldx % 4 == 0) ? 1 : 0;
-    const int rows_per_pass = p.threads / (p.nl * p.lpr);
+    const int rows_per_pass = p.row_threads / (p.nl * p.lpr);
+    a.row_threads = p.row_threads;
     a.n_passes = (p.rows_per_wg + rows_per_pass - 1) / rows_per_pass;
     a.vec_out = (a.ld_out % 4 == 0 && a.slab_stride % 4 == 0 && (uintptr_t)a.out % 16 == 0) ? 1 : 0;
 
@@ -295,8 +306,9 @@ int launch_spmm_any(const void* vals, const void* idx, int isize, int dtype, int
     if (st_code != BS_OK) return st_code;
     if (p.n_slabs > 1) {
         // 16 bytes per lane where rows of Y and of the workspace allow it (the workspace is
-        // 16-byte aligned, its rows are N floats)
-        const bool vec = N % 4 == 0 && ldy % 4 == 0 && (uintptr_t)Y % 16 == 0;
+        // 16-byte aligned, its rows are N floats; with rows of Y as long, both are one piece)
+        const bool vec = (uintptr_t)Y % 16 == 0 &&
+                         (ldy == N ? M * N % 4 == 0 : N % 4 == 0 && ldy % 4 == 0);
         const int64_t steps = M * N / (vec ? 4 : 1);
         int64_t grid = (steps + 255) / 256;
         if (grid > 256 * 16) grid = 256 * 16;

@@ -144,7 +144,7 @@ __global__ __launch_bounds__(1024) void spmm_rows_kernel(SpmmArgs a) {
 
     const int cg = tid & (nl - 1);
     const int ql = tid & 3;                      // lane of the quad: which chunks it loads
-    const int rows_per_pass = nthr >> nl_shift;
+    const int rows_per_pass = a.row_threads >> nl_shift;
     const int r_begin = g * a.rows_per_wg;
     const int r_end = min(a.M, r_begin + a.rows_per_wg);
     const int r_first = r_begin + (tid >> nl_shift);
@@ -192,6 +192,7 @@ __global__ __launch_bounds__(1024) void spmm_rows_kernel(SpmmArgs a) {
     wait_vm_and_lds<2 * UC>();
     __builtin_amdgcn_s_barrier();
     pin_order();
+    if (spmm_copies_only(a)) return;
 
     const char* xcol = reinterpret_cast<const char*>(Xs) + cg * 16;
     float* outp = a.out + (size_t)s * a.slab_stride + n0 + cg * 4;
