@@ -31,7 +31,11 @@
  *   - Outputs are fully overwritten; they need no initialisation.
  *   - Base pointers of W, vals, idx, x, X, y, Y must be 16-byte aligned.
  *   - Arguments are validated on the host before anything is launched; a
- *     non-zero return means nothing was enqueued.
+ *     non-zero return other than BS_ERR_HIP means nothing was enqueued.
+ *     BS_ERR_HIP can also report an error that an earlier HIP call of the thread
+ *     left behind, and the launches made before it was seen (the first kernel of a
+ *     product, earlier steps of a sequence) stay enqueued: outputs, and the cell
+ *     state of bs_lstm_sequence, are then undefined.
  *   - NaN or Inf inside W is undefined behaviour for bs_prune_pack.
  *   - Requires: bank in 1..256, K % bank == 0, 1 <= k <= bank, M >= 1,
  *     M*K < 2^40, K <= 2^24.

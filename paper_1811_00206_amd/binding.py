@@ -4,8 +4,9 @@ Argument marshalling only: each function checks tensor device / dtype /
 contiguity, passes raw device pointers and torch's current HIP stream to the
 library, and raises :class:`BsError` on a non-zero status.  The usual case is
 marshalled in native code (``csrc/bs_calls.cpp``); whatever that does not take
-returns None from it, with nothing enqueued, and goes through the checks below,
-which say what is wrong.  There is no Python or CPU implementation behind these
+returns None from it, with no call made, and goes through the checks below,
+which say what is wrong.  A call of the library is made once, whatever status it
+returns.  There is no Python or CPU implementation behind these
 names; if a library is missing the first call fails.
 """
 from __future__ import annotations
@@ -93,8 +94,9 @@ def load_library():
     for name in ("bs_init", "bs_prune_pack", "bs_spmv", "bs_spmv_ex", "bs_spmm", "bs_spmm_static", "bs_dense_gemv",
                  "bs_dense_gemm", "bs_lstm_step", "bs_lstm_sequence", "bs_reprune"):
         getattr(lib, name).restype = i32
-    _native = importlib.import_module("._native", __package__)   # built with libbs.so
-    _lib = lib
+    native = importlib.import_module("._native", __package__)    # built with libbs.so
+    native.BsError = BsError                                     # what it raises for a status
+    _native, _lib = native, lib
     return lib
 
 

@@ -56,14 +56,19 @@ def _link(lib: str, objs) -> None:
     os.replace(tmp, lib)
 
 
-def _compile_native() -> str:
+def native_compiler():
+    """The host compiler and its flags for code against torch's headers."""
     import torch
     from torch.utils import cpp_extension
-    obj = os.path.join(OBJDIR, "bs_calls.cpp.o")
     inc = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], "/opt/rocm/include"]
-    subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
-                           "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-                           *(f"-isystem{d}" for d in inc), "-c", NATIVE_SRC, "-o", obj])
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+            "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            *(f"-isystem{d}" for d in inc)]
+
+
+def _compile_native() -> str:
+    obj = os.path.join(OBJDIR, "bs_calls.cpp.o")
+    subprocess.check_call([*native_compiler(), "-c", NATIVE_SRC, "-o", obj])
     return obj
 
 

@@ -4,8 +4,10 @@
 // four times what the small products take on the GPU; here about 4, 2.5 of them the launch.)
 //
 // Every function returns None for anything it does not handle: a tensor of the wrong kind, an
-// argument of another type, a status other than BS_OK.  Nothing has been enqueued then, and
-// binding.py goes the long way, which raises the errors.
+// argument of another type.  The C ABI has not been called then, and binding.py goes the long
+// way, which raises the errors.  Once the C ABI has been called its status stands: it is raised
+// as BsError and the call is never tried again (BS_ERR_HIP can come after work was enqueued, and
+// a sequence that fails at a later step has already advanced its cell state).
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
 #include <Python.h>
@@ -81,11 +83,22 @@ struct WithoutLock {
     ~WithoutLock() { PyEval_RestoreThread(state); }
 };
 
-// the C ABI, without the interpreter lock (a full queue makes a launch wait for the GPU)
+// the status of the C ABI, called without the interpreter lock (a full queue makes a launch wait
+// for the GPU)
 template <typename F>
-bool enqueue(F&& call) {
+int enqueue(F&& call) {
     const WithoutLock unlocked;
-    return call(current_stream()) == BS_OK;
+    return call(current_stream());
+}
+
+// raises BsError(status, call), which binding.py has put into this module; nullptr
+PyObject* failed(PyObject* self, int status, const char* call) {
+    PyObject* type = PyObject_GetAttrString(self, "BsError");
+    PyObject* error = type ? PyObject_CallFunction(type, "is", status, call) : nullptr;
+    if (error) PyErr_SetObject(type, error);
+    Py_XDECREF(error);
+    Py_XDECREF(type);
+    return nullptr;
 }
 
 #define BS_TRY try {
@@ -103,7 +116,7 @@ PyObject* result(PyObject* out, at::Tensor& t) {
 }
 
 // (vals, idx, bank, x, out, wide) -> y
-PyObject* spmv(PyObject*, PyObject* const* args, Py_ssize_t n) {
+PyObject* spmv(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     BS_TRY
     Packed p;
     if (n != 6) Py_RETURN_NONE;
@@ -115,20 +128,20 @@ PyObject* spmv(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const at::Tensor* out = &y;
     if (args[4] == Py_None) y = p.floats({p.M});
     else if (!(out = gpu_floats(args[4], p.M))) Py_RETURN_NONE;
-    const bool ok = enqueue([&](void* st) {
+    const int status = enqueue([&](void* st) {
         const float* xp = static_cast<const float*>(x->const_data_ptr());
         float* yp = static_cast<float*>(out->mutable_data_ptr());
         const void *v = p.vals->const_data_ptr(), *i = p.idx->const_data_ptr();
         return wide ? bs_spmv_wide(v, static_cast<const uint16_t*>(i), p.dtype, p.M, p.K, p.bank, p.k, xp, yp, st)
                     : bs_spmv(v, static_cast<const uint8_t*>(i), p.dtype, p.M, p.K, p.bank, p.k, xp, yp, st);
     });
-    if (!ok) Py_RETURN_NONE;
+    if (status != BS_OK) return failed(self, status, wide ? "bs_spmv_wide" : "bs_spmv");
     return result(args[4], y);
     BS_CATCH
 }
 
 // (vals, idx, bank, X, out, workspace, wide) -> Y
-PyObject* spmm(PyObject*, PyObject* const* args, Py_ssize_t n) {
+PyObject* spmm(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     BS_TRY
     Packed p;
     if (n != 7) Py_RETURN_NONE;
@@ -159,7 +172,7 @@ PyObject* spmm(PyObject*, PyObject* const* args, Py_ssize_t n) {
         ws = at::empty({(int64_t)ws_bytes}, p.vals->options().dtype(at::kByte));
         wp = ws.mutable_data_ptr();
     }
-    const bool ok = enqueue([&](void* st) {
+    const int status = enqueue([&](void* st) {
         const float* xp = static_cast<const float*>(X->const_data_ptr());
         float* yp = static_cast<float*>(out->mutable_data_ptr());
         const void *v = p.vals->const_data_ptr(), *i = p.idx->const_data_ptr();
@@ -168,7 +181,7 @@ PyObject* spmm(PyObject*, PyObject* const* args, Py_ssize_t n) {
                     : bs_spmm(v, static_cast<const uint8_t*>(i), p.dtype, p.M, p.K, p.bank, p.k, xp, N, ldx, yp, ldy,
                               wp, ws_bytes, st);
     });
-    if (!ok) Py_RETURN_NONE;
+    if (status != BS_OK) return failed(self, status, wide ? "bs_spmm_wide" : "bs_spmm");
     return result(args[4], y);
     BS_CATCH
 }
@@ -205,7 +218,7 @@ bool packed_out(PyObject* out, const at::Tensor& like, at::ScalarType idx_type, 
 }
 
 // (W, bank, k, out, wide) -> (vals, idx)
-PyObject* prune_pack(PyObject*, PyObject* const* args, Py_ssize_t n) {
+PyObject* prune_pack(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     BS_TRY
     int bank, k;
     if (n != 5 || !int_arg(args[1], bank) || !int_arg(args[2], k)) Py_RETURN_NONE;
@@ -217,19 +230,19 @@ PyObject* prune_pack(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const bool wide = args[4] == Py_True;
     at::Tensor v, i;
     if (!packed_out(args[3], *W, wide ? at::kUInt16 : at::kByte, M, K / bank, k, v, i)) Py_RETURN_NONE;
-    const bool ok = enqueue([&](void* st) {
+    const int status = enqueue([&](void* st) {
         const void* w = W->const_data_ptr();
         void *vp = v.mutable_data_ptr(), *ip = i.mutable_data_ptr();
         return wide ? bs_prune_pack_wide(w, dtype, M, K, bank, k, vp, static_cast<uint16_t*>(ip), st)
                     : bs_prune_pack(w, dtype, M, K, bank, k, vp, static_cast<uint8_t*>(ip), st);
     });
-    if (!ok) Py_RETURN_NONE;
+    if (status != BS_OK) return failed(self, status, wide ? "bs_prune_pack_wide" : "bs_prune_pack");
     return pair(args[3], v, i);
     BS_CATCH
 }
 
 // (vals, idx, bank, k2, out) -> (vals2, idx2)
-PyObject* reprune(PyObject*, PyObject* const* args, Py_ssize_t n) {
+PyObject* reprune(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     BS_TRY
     Packed p;
     int k2;
@@ -237,11 +250,11 @@ PyObject* reprune(PyObject*, PyObject* const* args, Py_ssize_t n) {
         Py_RETURN_NONE;
     at::Tensor v, i;
     if (!packed_out(args[4], *p.vals, at::kByte, p.M, p.vals->size(1), k2, v, i)) Py_RETURN_NONE;
-    const bool ok = enqueue([&](void* st) {
+    const int status = enqueue([&](void* st) {
         return bs_reprune(p.vals->const_data_ptr(), static_cast<const uint8_t*>(p.idx->const_data_ptr()), p.dtype, p.M,
                           p.K, p.bank, p.k, k2, v.mutable_data_ptr(), static_cast<uint8_t*>(i.mutable_data_ptr()), st);
     });
-    if (!ok) Py_RETURN_NONE;
+    if (status != BS_OK) return failed(self, status, "bs_reprune");
     return pair(args[4], v, i);
     BS_CATCH
 }
@@ -258,7 +271,7 @@ struct Gates : Packed {
 };
 
 // (vals, idx, bank, x, h, bias, c, c_out, h_out) -> (c_out, h_out)
-PyObject* lstm_step(PyObject*, PyObject* const* args, Py_ssize_t n) {
+PyObject* lstm_step(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     BS_TRY
     Gates g;
     if (n != 9 || !g.read(args)) Py_RETURN_NONE;
@@ -268,7 +281,7 @@ PyObject* lstm_step(PyObject*, PyObject* const* args, Py_ssize_t n) {
     // outputs the caller brings go the long way
     if (args[7] != Py_None || args[8] != Py_None) Py_RETURN_NONE;
     at::Tensor c_out = g.floats({g.H}), h_out = g.floats({g.H});
-    const bool ok = enqueue([&](void* st) {
+    const int status = enqueue([&](void* st) {
         return bs_lstm_step(g.vals->const_data_ptr(), static_cast<const uint8_t*>(g.idx->const_data_ptr()), g.dtype,
                             g.H, g.I, g.bank, g.k, static_cast<const float*>(x->const_data_ptr()),
                             static_cast<const float*>(h->const_data_ptr()),
@@ -277,13 +290,13 @@ PyObject* lstm_step(PyObject*, PyObject* const* args, Py_ssize_t n) {
                             static_cast<float*>(c_out.mutable_data_ptr()),
                             static_cast<float*>(h_out.mutable_data_ptr()), st);
     });
-    if (!ok) Py_RETURN_NONE;
+    if (status != BS_OK) return failed(self, status, "bs_lstm_step");
     return pair(Py_None, c_out, h_out);
     BS_CATCH
 }
 
 // (vals, idx, bank, X, h0, bias, c, H_all) -> H_all
-PyObject* lstm_sequence(PyObject*, PyObject* const* args, Py_ssize_t n) {
+PyObject* lstm_sequence(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     BS_TRY
     Gates g;
     if (n != 8 || !g.read(args)) Py_RETURN_NONE;
@@ -296,7 +309,7 @@ PyObject* lstm_sequence(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const at::Tensor* out = &all;
     if (args[7] == Py_None) all = g.floats({T, g.H});
     else if (!(out = gpu_tensor(args[7], at::kFloat))) Py_RETURN_NONE;
-    const bool ok = enqueue([&](void* st) {
+    const int status = enqueue([&](void* st) {
         return bs_lstm_sequence(g.vals->const_data_ptr(), static_cast<const uint8_t*>(g.idx->const_data_ptr()), g.dtype,
                                 g.H, g.I, g.bank, g.k, static_cast<const float*>(X->const_data_ptr()), T,
                                 static_cast<const float*>(h0->const_data_ptr()),
@@ -304,7 +317,7 @@ PyObject* lstm_sequence(PyObject*, PyObject* const* args, Py_ssize_t n) {
                                 static_cast<float*>(c->mutable_data_ptr()),
                                 static_cast<float*>(out->mutable_data_ptr()), st);
     });
-    if (!ok) Py_RETURN_NONE;
+    if (status != BS_OK) return failed(self, status, "bs_lstm_sequence");
     return result(args[7], all);
     BS_CATCH
 }

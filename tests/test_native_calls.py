@@ -1,0 +1,145 @@
+"""The native marshalling of the Python calls (csrc/bs_calls.cpp) where the library or torch
+fails.  No GPU: each test runs in a process of its own in which a stand-in for the library's
+calls and for torch's current stream is loaded ahead of the real ones, on tensors that claim to
+be on the GPU and lie in host memory; nothing is launched."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+from paper_1811_00206_amd import build as bs_build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+STAND_IN = r"""
+#include <c10/hip/HIPStream.h>
+#include "bs.h"
+
+namespace c10::hip {
+HIPStream getCurrentHIPStream(DeviceIndex) {
+    return HIPStream(HIPStream::UNCHECKED, Stream(Stream::DEFAULT, Device(kCUDA, 0)));
+}
+hipStream_t HIPStream::stream() const { return nullptr; }
+}  // namespace c10::hip
+
+extern "C" {
+int attempts = 0, status = BS_ERR_HIP;   // of every call but the sequence
+#define CALL { ++attempts; return status; }
+int bs_spmv(const void*, const uint8_t*, int, int64_t, int64_t, int, int, const float*, float*, void*) CALL
+int bs_spmv_wide(const void*, const uint16_t*, int, int64_t, int64_t, int, int, const float*, float*, void*) CALL
+int bs_spmm(const void*, const uint8_t*, int, int64_t, int64_t, int, int, const float*, int64_t, int64_t, float*,
+            int64_t, void*, size_t, void*) CALL
+int bs_spmm_wide(const void*, const uint16_t*, int, int64_t, int64_t, int, int, const float*, int64_t, int64_t, float*,
+                 int64_t, void*, size_t, void*) CALL
+int bs_prune_pack(const void*, int, int64_t, int64_t, int, int, void*, uint8_t*, void*) CALL
+int bs_prune_pack_wide(const void*, int, int64_t, int64_t, int, int, void*, uint16_t*, void*) CALL
+int bs_reprune(const void*, const uint8_t*, int, int64_t, int64_t, int, int, int, void*, uint8_t*, void*) CALL
+// advances the cell state step by step; the first attempt fails at its second step
+int bs_lstm_sequence(const void*, const uint8_t*, int, int64_t, int64_t, int, int, const float*, int64_t T,
+                     const float*, const float*, float* c, float*, void*) {
+    const int attempt = ++attempts;
+    for (int64_t t = 0; t < T; ++t) {
+        if (attempt == 1 && t == 1) return BS_ERR_HIP;
+        c[0] += 1.f;
+    }
+    return BS_OK;
+}
+}
+"""
+
+PREAMBLE = """
+    import ctypes, os, sys
+    stand_in = ctypes.CDLL(os.environ["BS_STAND_IN"], mode=ctypes.RTLD_GLOBAL)
+    import torch
+    from paper_1811_00206_amd import binding as bs
+
+    attempts = ctypes.c_int.in_dll(stand_in, "attempts")
+
+    class Library:
+        '''The ctypes library: host-only queries are the real ones, other calls count as attempts.'''
+        def __init__(self, lib):
+            self.lib = lib
+        def __getattr__(self, name):
+            if name in ("bs_status_str", "bs_spmm_workspace_bytes", "bs_spmm_workspace_bytes_wide"):
+                return getattr(self.lib, name)
+            def call(*args):
+                attempts.value += 1
+                return 0
+            return call
+
+    bs._lib = Library(bs.load_library())
+    kept = []
+
+    def gpu(*size, dtype=torch.float32):
+        '''zeros in host memory that claim to be on the GPU'''
+        host = torch.zeros(size, dtype=dtype)
+        kept.append(host)
+        nbytes, dev = host.numel() * host.element_size(), torch.device("cuda", 0)
+        storage = torch._C._construct_storage_from_data_pointer(host.data_ptr(), dev, nbytes)
+        return torch._C._construct_CUDA_Tensor_From_Storage_And_Metadata(
+            dict(size=tuple(size), stride=host.stride(), dtype=dtype, storage_offset=0), storage)
+"""
+
+
+@pytest.fixture(scope="module")
+def stand_in(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("stand_in")
+    src, lib = str(tmp / "stand_in.cpp"), str(tmp / "stand_in.so")
+    with open(src, "w") as f:
+        f.write(STAND_IN)
+    subprocess.check_call([*bs_build.native_compiler(), "-I" + os.path.join(ROOT, "include"), "-shared", "-o", lib, src])
+    return lib
+
+
+def _run(stand_in, body):
+    code = textwrap.dedent(PREAMBLE) + textwrap.dedent(body)
+    out = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env={**os.environ, "BS_STAND_IN": stand_in},
+                         capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0, out.stdout + out.stderr
+
+
+def test_a_sequence_that_fails_at_a_later_step_is_not_tried_again(stand_in):
+    """By the second step the cell state has advanced in place: a second attempt would start
+    from it and return wrong states without an error."""
+    _run(stand_in, """
+        H, I, T, bank, k = 8, 8, 3, 4, 2
+        v, i = gpu(4 * H, 4, k), gpu(4 * H, 4, k, dtype=torch.uint8)
+        c = gpu(H)
+        try:
+            bs.bs_lstm_sequence(v, i, bank, gpu(T, I), gpu(H), gpu(4 * H), c, H_all=gpu(T, H))
+        except bs.BsError as e:
+            assert e.status == 5 and "bs_lstm_sequence" in str(e), e
+        else:
+            raise AssertionError("no error")
+        assert attempts.value == 1, attempts.value
+        assert ctypes.c_float.from_address(c.data_ptr()).value == 1.0
+    """)
+
+
+def test_a_status_is_raised_after_one_attempt(stand_in):
+    _run(stand_in, """
+        M, bank, nb, k, N = 4, 8, 2, 4, 3
+        for wide in (False, True):
+            off = torch.uint16 if wide else torch.uint8
+            v, i, W = gpu(M, nb, k), gpu(M, nb, k, dtype=off), gpu(M, nb * bank)
+            tail = "_wide" if wide else ""
+            call = lambda name: getattr(bs, name + tail)
+            calls = {"bs_spmv": lambda: call("bs_spmv")(v, i, bank, gpu(nb * bank), out=gpu(M)),
+                     "bs_spmm": lambda: call("bs_spmm")(v, i, bank, gpu(nb * bank, N), out=gpu(M, N)),
+                     "bs_prune_pack": lambda: call("bs_prune_pack")(W, bank, k, out=(v, i))}
+            if not wide:
+                calls["bs_reprune"] = lambda: bs.bs_reprune(v, i, bank, k, out=(gpu(M, nb, k), i))
+            for name, f in calls.items():
+                for status in range(1, 9):
+                    ctypes.c_int.in_dll(stand_in, "status").value = status
+                    attempts.value = 0
+                    try:
+                        f()
+                    except bs.BsError as e:
+                        assert e.status == status and str(e).startswith(name + tail + ":"), (name, e)
+                    else:
+                        raise AssertionError(name + ": no error")
+                    assert attempts.value == 1, (name, status, attempts.value)
+    """)
