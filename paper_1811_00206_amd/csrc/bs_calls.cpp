@@ -12,6 +12,7 @@
 #include <ATen/ops/empty.h>
 #include <Python.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/bs.h"
@@ -101,14 +102,6 @@ PyObject* failed(PyObject* self, int status, const char* call) {
     return nullptr;
 }
 
-#define BS_TRY try {
-#define BS_CATCH                                            \
-    }                                                       \
-    catch (const std::exception& e) {                       \
-        PyErr_SetString(PyExc_RuntimeError, e.what());      \
-        return nullptr;                                     \
-    }
-
 // the caller's `out` object as the result (it is returned, so it gains a reference) or a new one
 PyObject* result(PyObject* out, at::Tensor& t) {
     if (out != Py_None) { Py_INCREF(out); return out; }
@@ -117,7 +110,7 @@ PyObject* result(PyObject* out, at::Tensor& t) {
 
 // (vals, idx, bank, x, out, wide) -> y
 PyObject* spmv(PyObject* self, PyObject* const* args, Py_ssize_t n) {
-    BS_TRY
+    HANDLE_TH_ERRORS
     Packed p;
     if (n != 6) Py_RETURN_NONE;
     const bool wide = args[5] == Py_True;
@@ -137,12 +130,12 @@ PyObject* spmv(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     });
     if (status != BS_OK) return failed(self, status, wide ? "bs_spmv_wide" : "bs_spmv");
     return result(args[4], y);
-    BS_CATCH
+    END_HANDLE_TH_ERRORS
 }
 
 // (vals, idx, bank, X, out, workspace, wide) -> Y
 PyObject* spmm(PyObject* self, PyObject* const* args, Py_ssize_t n) {
-    BS_TRY
+    HANDLE_TH_ERRORS
     Packed p;
     if (n != 7) Py_RETURN_NONE;
     const bool wide = args[6] == Py_True;
@@ -183,7 +176,7 @@ PyObject* spmm(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     });
     if (status != BS_OK) return failed(self, status, wide ? "bs_spmm_wide" : "bs_spmm");
     return result(args[4], y);
-    BS_CATCH
+    END_HANDLE_TH_ERRORS
 }
 
 // two results as a tuple: the caller's, or new ones
@@ -219,7 +212,7 @@ bool packed_out(PyObject* out, const at::Tensor& like, at::ScalarType idx_type, 
 
 // (W, bank, k, out, wide) -> (vals, idx)
 PyObject* prune_pack(PyObject* self, PyObject* const* args, Py_ssize_t n) {
-    BS_TRY
+    HANDLE_TH_ERRORS
     int bank, k;
     if (n != 5 || !int_arg(args[1], bank) || !int_arg(args[2], k)) Py_RETURN_NONE;
     const at::Tensor* W = gpu_tensor(args[0]);
@@ -238,12 +231,12 @@ PyObject* prune_pack(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     });
     if (status != BS_OK) return failed(self, status, wide ? "bs_prune_pack_wide" : "bs_prune_pack");
     return pair(args[3], v, i);
-    BS_CATCH
+    END_HANDLE_TH_ERRORS
 }
 
 // (vals, idx, bank, k2, out) -> (vals2, idx2)
 PyObject* reprune(PyObject* self, PyObject* const* args, Py_ssize_t n) {
-    BS_TRY
+    HANDLE_TH_ERRORS
     Packed p;
     int k2;
     if (n != 5 || !p.read(args[0], args[1], args[2], at::kByte) || !int_arg(args[3], k2) || k2 < 1 || k2 > p.k)
@@ -256,7 +249,7 @@ PyObject* reprune(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     });
     if (status != BS_OK) return failed(self, status, "bs_reprune");
     return pair(args[4], v, i);
-    BS_CATCH
+    END_HANDLE_TH_ERRORS
 }
 
 // the gate matrix of an LSTM call: 4H x (I + H)
@@ -272,7 +265,7 @@ struct Gates : Packed {
 
 // (vals, idx, bank, x, h, bias, c, c_out, h_out) -> (c_out, h_out)
 PyObject* lstm_step(PyObject* self, PyObject* const* args, Py_ssize_t n) {
-    BS_TRY
+    HANDLE_TH_ERRORS
     Gates g;
     if (n != 9 || !g.read(args)) Py_RETURN_NONE;
     const at::Tensor *x = gpu_floats(args[3], g.I), *h = gpu_floats(args[4], g.H);
@@ -292,12 +285,12 @@ PyObject* lstm_step(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     });
     if (status != BS_OK) return failed(self, status, "bs_lstm_step");
     return pair(Py_None, c_out, h_out);
-    BS_CATCH
+    END_HANDLE_TH_ERRORS
 }
 
 // (vals, idx, bank, X, h0, bias, c, H_all) -> H_all
 PyObject* lstm_sequence(PyObject* self, PyObject* const* args, Py_ssize_t n) {
-    BS_TRY
+    HANDLE_TH_ERRORS
     Gates g;
     if (n != 8 || !g.read(args)) Py_RETURN_NONE;
     const at::Tensor* X = gpu_tensor(args[3], at::kFloat);
@@ -319,14 +312,14 @@ PyObject* lstm_sequence(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     });
     if (status != BS_OK) return failed(self, status, "bs_lstm_sequence");
     return result(args[7], all);
-    BS_CATCH
+    END_HANDLE_TH_ERRORS
 }
 
 // () -> torch's current stream as an integer
 PyObject* stream(PyObject*, PyObject*) {
-    BS_TRY
+    HANDLE_TH_ERRORS
     return PyLong_FromVoidPtr(current_stream());
-    BS_CATCH
+    END_HANDLE_TH_ERRORS
 }
 
 #define BS_FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}

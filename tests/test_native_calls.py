@@ -8,13 +8,17 @@ import sys
 import textwrap
 
 import pytest
+import torch
 
 from paper_1811_00206_amd import build as bs_build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 STAND_IN = r"""
+#include <ATen/ops/empty.h>
+#include <Python.h>
 #include <c10/hip/HIPStream.h>
+#include <dlfcn.h>
 #include "bs.h"
 
 namespace c10::hip {
@@ -23,6 +27,23 @@ HIPStream getCurrentHIPStream(DeviceIndex) {
 }
 hipStream_t HIPStream::stream() const { return nullptr; }
 }  // namespace c10::hip
+
+// what every allocation of a tensor goes through; runs out of memory when told to
+extern "C" { int out_of_memory = 0, lock_held = -1; }
+namespace at::_ops {
+Tensor empty_memory_format::call(c10::SymIntArrayRef size, ::std::optional<ScalarType> dtype, ::std::optional<Layout> layout,
+                                 ::std::optional<Device> device, ::std::optional<bool> pin, ::std::optional<MemoryFormat> format) {
+    if (out_of_memory) {
+        lock_held = PyGILState_Check();
+        TORCH_CHECK_WITH(OutOfMemoryError, false, "no memory left");
+    }
+    static const auto real = reinterpret_cast<decltype(&call)>(dlsym(
+        dlopen("libtorch_cpu.so", RTLD_NOLOAD | RTLD_LAZY),
+        "_ZN2at4_ops19empty_memory_format4callEN3c108ArrayRefINS2_6SymIntEEESt8optionalINS2_10ScalarTypeEES6_INS2_6"
+        "LayoutEES6_INS2_6DeviceEES6_IbES6_INS2_12MemoryFormatEE"));
+    return real(size, dtype, layout, device, pin, format);
+}
+}  // namespace at::_ops
 
 extern "C" {
 int attempts = 0, status = BS_ERR_HIP;   // of every call but the sequence
@@ -51,8 +72,8 @@ int bs_lstm_sequence(const void*, const uint8_t*, int, int64_t, int64_t, int, in
 
 PREAMBLE = """
     import ctypes, os, sys
-    stand_in = ctypes.CDLL(os.environ["BS_STAND_IN"], mode=ctypes.RTLD_GLOBAL)
     import torch
+    stand_in = ctypes.CDLL(os.environ["BS_STAND_IN"], mode=ctypes.RTLD_GLOBAL)
     from paper_1811_00206_amd import binding as bs
 
     attempts = ctypes.c_int.in_dll(stand_in, "attempts")
@@ -89,12 +110,27 @@ def stand_in(tmp_path_factory):
     src, lib = str(tmp / "stand_in.cpp"), str(tmp / "stand_in.so")
     with open(src, "w") as f:
         f.write(STAND_IN)
-    subprocess.check_call([*bs_build.native_compiler(), "-I" + os.path.join(ROOT, "include"), "-shared", "-o", lib, src])
+    subprocess.check_call([*bs_build.native_compiler(), "-I" + os.path.join(ROOT, "include"), "-shared", "-o", lib, src,
+                           "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"), "-lc10", "-lc10_hip",
+                           "-ltorch_cpu"])
     return lib
 
 
+# calls whose results the native code allocates: name -> call
+ALLOCATING = """
+    M, bank, nb, k, N = 4, 8, 2, 4, 3
+    v, i, W = gpu(M, nb, k), gpu(M, nb, k, dtype=torch.uint8), gpu(M, nb * bank)
+    x, X = gpu(nb * bank), gpu(nb * bank, N)
+    x4, b, h, c, X4 = gpu(15), gpu(4), gpu(1), gpu(1), gpu(2, 15)
+    allocating = {"spmv": lambda: bs.bs_spmv(v, i, bank, x), "spmm": lambda: bs.bs_spmm(v, i, bank, X),
+                  "prune": lambda: bs.bs_prune_pack(W, bank, k), "reprune": lambda: bs.bs_reprune(v, i, bank, k),
+                  "step": lambda: bs.bs_lstm_step(v, i, bank, x4, h, b, c),
+                  "sequence": lambda: bs.bs_lstm_sequence(v, i, bank, X4, h, b, c)}
+"""
+
+
 def _run(stand_in, body):
-    code = textwrap.dedent(PREAMBLE) + textwrap.dedent(body)
+    code = textwrap.dedent(PREAMBLE + ALLOCATING) + textwrap.dedent(body)
     out = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env={**os.environ, "BS_STAND_IN": stand_in},
                          capture_output=True, text=True, timeout=300)
     assert out.returncode == 0, out.stdout + out.stderr
@@ -142,4 +178,32 @@ def test_a_status_is_raised_after_one_attempt(stand_in):
                     else:
                         raise AssertionError(name + ": no error")
                     assert attempts.value == 1, (name, status, attempts.value)
+    """)
+
+
+def test_exceptions_keep_their_types(stand_in):
+    """Out of memory, as the allocator reports it, is torch.OutOfMemoryError; what a dispatch
+    mode raises is what the caller sees."""
+    _run(stand_in, """
+        from torch.utils._python_dispatch import TorchDispatchMode
+
+        class Refuses(TorchDispatchMode):
+            def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+                raise KeyError("refused")
+
+        fails = ctypes.c_int.in_dll(stand_in, "out_of_memory")
+        for name, f in allocating.items():
+            for want, text in ((KeyError, "refused"), (torch.OutOfMemoryError, "no memory left")):
+                fails.value = want is not KeyError
+                try:
+                    if want is KeyError:
+                        with Refuses():
+                            f()
+                    else:
+                        f()
+                except Exception as e:
+                    assert type(e) is want and text in str(e), (name, type(e), e)
+                else:
+                    raise AssertionError(name + ": no error")
+        assert attempts.value == 0
     """)
