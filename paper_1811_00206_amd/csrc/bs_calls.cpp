@@ -84,8 +84,9 @@ struct WithoutLock {
     ~WithoutLock() { PyEval_RestoreThread(state); }
 };
 
-// the status of the C ABI, called without the interpreter lock (a full queue makes a launch wait
-// for the GPU)
+// the status of `call`, which takes new tensors from torch's allocator and calls the C ABI, all
+// without the interpreter lock: a full queue makes a launch wait for the GPU, and an allocation
+// may go to the driver
 template <typename F>
 int enqueue(F&& call) {
     const WithoutLock unlocked;
@@ -119,9 +120,9 @@ PyObject* spmv(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     if (!x) Py_RETURN_NONE;
     at::Tensor y;
     const at::Tensor* out = &y;
-    if (args[4] == Py_None) y = p.floats({p.M});
-    else if (!(out = gpu_floats(args[4], p.M))) Py_RETURN_NONE;
+    if (args[4] != Py_None && !(out = gpu_floats(args[4], p.M))) Py_RETURN_NONE;
     const int status = enqueue([&](void* st) {
+        if (out == &y) y = p.floats({p.M});
         const float* xp = static_cast<const float*>(x->const_data_ptr());
         float* yp = static_cast<float*>(out->mutable_data_ptr());
         const void *v = p.vals->const_data_ptr(), *i = p.idx->const_data_ptr();
@@ -147,10 +148,12 @@ PyObject* spmm(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     const int64_t N = X->size(1);
     at::Tensor y, ws;
     const at::Tensor* out = &y;
-    if (args[4] == Py_None) y = p.floats({p.M, N});
-    else if (!(out = gpu_tensor(args[4]))) Py_RETURN_NONE;
-    const int64_t ldy = row_pitch(*out);
-    if (ldy < 0 || out->size(0) != p.M || out->size(1) != N) Py_RETURN_NONE;
+    int64_t ldy = std::max<int64_t>(N, 1);
+    if (args[4] != Py_None) {
+        if (!(out = gpu_tensor(args[4]))) Py_RETURN_NONE;
+        ldy = row_pitch(*out);
+        if (ldy < 0 || out->size(0) != p.M || out->size(1) != N) Py_RETURN_NONE;
+    }
     const size_t need = wide ? bs_spmm_workspace_bytes_wide(p.dtype, p.M, p.K, p.bank, p.k, N)
                              : bs_spmm_workspace_bytes(p.dtype, p.M, p.K, p.bank, p.k, N);
     void* wp = nullptr;
@@ -160,12 +163,14 @@ PyObject* spmm(PyObject* self, PyObject* const* args, Py_ssize_t n) {
         if (!w) Py_RETURN_NONE;
         wp = w->mutable_data_ptr();
         ws_bytes = (size_t)w->numel() * w->element_size();
-    } else if (need) {
-        ws_bytes = need < 16 ? 16 : need;
-        ws = at::empty({(int64_t)ws_bytes}, p.vals->options().dtype(at::kByte));
-        wp = ws.mutable_data_ptr();
     }
     const int status = enqueue([&](void* st) {
+        if (out == &y) y = p.floats({p.M, N});
+        if (args[5] == Py_None && need) {
+            ws_bytes = need < 16 ? 16 : need;
+            ws = at::empty({(int64_t)ws_bytes}, p.vals->options().dtype(at::kByte));
+            wp = ws.mutable_data_ptr();
+        }
         const float* xp = static_cast<const float*>(X->const_data_ptr());
         float* yp = static_cast<float*>(out->mutable_data_ptr());
         const void *v = p.vals->const_data_ptr(), *i = p.idx->const_data_ptr();
@@ -191,24 +196,31 @@ PyObject* pair(PyObject* out, at::Tensor& a, at::Tensor& b) {
     return t;
 }
 
-// vals and idx of a result: new tensors [M, nb, k], or `out` if it is a tuple of two such
-bool packed_out(PyObject* out, const at::Tensor& like, at::ScalarType idx_type, int64_t M, int64_t nb, int64_t k,
-                at::Tensor& v, at::Tensor& i) {
-    if (out == Py_None) {
-        v = at::empty({M, nb, k}, like.options());
-        i = at::empty({M, nb, k}, like.options().dtype(idx_type));
+// vals and idx of a result: [M, nb, k] each
+struct PackedOut {
+    const at::Tensor& like;
+    at::ScalarType idx_type;
+    int64_t size[3];
+    at::Tensor v, i;
+    // false unless `out` is None or a tuple of two such tensors
+    bool read(PyObject* out) {
+        if (out == Py_None) return true;
+        if (!PyTuple_CheckExact(out) || PyTuple_GET_SIZE(out) != 2) return false;
+        const at::Tensor* tv = gpu_tensor(PyTuple_GET_ITEM(out, 0), like.scalar_type());
+        const at::Tensor* ti = gpu_tensor(PyTuple_GET_ITEM(out, 1), idx_type);
+        const at::IntArrayRef shape(size, 3);
+        if (!tv || !ti || tv->sizes() != shape || ti->sizes() != shape) return false;
+        v = *tv;
+        i = *ti;
         return true;
     }
-    if (!PyTuple_CheckExact(out) || PyTuple_GET_SIZE(out) != 2) return false;
-    const at::Tensor* tv = gpu_tensor(PyTuple_GET_ITEM(out, 0), like.scalar_type());
-    const at::Tensor* ti = gpu_tensor(PyTuple_GET_ITEM(out, 1), idx_type);
-    const int64_t want[3] = {M, nb, k};
-    const at::IntArrayRef shape(want, 3);
-    if (!tv || !ti || tv->sizes() != shape || ti->sizes() != shape) return false;
-    v = *tv;
-    i = *ti;
-    return true;
-}
+    void allocate() {   // unless the caller brought them
+        if (v.defined()) return;
+        const at::IntArrayRef shape(size, 3);
+        v = at::empty(shape, like.options());
+        i = at::empty(shape, like.options().dtype(idx_type));
+    }
+};
 
 // (W, bank, k, out, wide) -> (vals, idx)
 PyObject* prune_pack(PyObject* self, PyObject* const* args, Py_ssize_t n) {
@@ -221,16 +233,17 @@ PyObject* prune_pack(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     const int64_t M = W->size(0), K = W->size(1);
     if (dtype < 0 || bank < 1 || K % bank || k < 1 || k > bank) Py_RETURN_NONE;
     const bool wide = args[4] == Py_True;
-    at::Tensor v, i;
-    if (!packed_out(args[3], *W, wide ? at::kUInt16 : at::kByte, M, K / bank, k, v, i)) Py_RETURN_NONE;
+    PackedOut o{*W, wide ? at::kUInt16 : at::kByte, {M, K / bank, k}};
+    if (!o.read(args[3])) Py_RETURN_NONE;
     const int status = enqueue([&](void* st) {
+        o.allocate();
         const void* w = W->const_data_ptr();
-        void *vp = v.mutable_data_ptr(), *ip = i.mutable_data_ptr();
+        void *vp = o.v.mutable_data_ptr(), *ip = o.i.mutable_data_ptr();
         return wide ? bs_prune_pack_wide(w, dtype, M, K, bank, k, vp, static_cast<uint16_t*>(ip), st)
                     : bs_prune_pack(w, dtype, M, K, bank, k, vp, static_cast<uint8_t*>(ip), st);
     });
     if (status != BS_OK) return failed(self, status, wide ? "bs_prune_pack_wide" : "bs_prune_pack");
-    return pair(args[3], v, i);
+    return pair(args[3], o.v, o.i);
     END_HANDLE_TH_ERRORS
 }
 
@@ -241,14 +254,15 @@ PyObject* reprune(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     int k2;
     if (n != 5 || !p.read(args[0], args[1], args[2], at::kByte) || !int_arg(args[3], k2) || k2 < 1 || k2 > p.k)
         Py_RETURN_NONE;
-    at::Tensor v, i;
-    if (!packed_out(args[4], *p.vals, at::kByte, p.M, p.vals->size(1), k2, v, i)) Py_RETURN_NONE;
+    PackedOut o{*p.vals, at::kByte, {p.M, p.vals->size(1), k2}};
+    if (!o.read(args[4])) Py_RETURN_NONE;
     const int status = enqueue([&](void* st) {
+        o.allocate();
         return bs_reprune(p.vals->const_data_ptr(), static_cast<const uint8_t*>(p.idx->const_data_ptr()), p.dtype, p.M,
-                          p.K, p.bank, p.k, k2, v.mutable_data_ptr(), static_cast<uint8_t*>(i.mutable_data_ptr()), st);
+                          p.K, p.bank, p.k, k2, o.v.mutable_data_ptr(), static_cast<uint8_t*>(o.i.mutable_data_ptr()), st);
     });
     if (status != BS_OK) return failed(self, status, "bs_reprune");
-    return pair(args[4], v, i);
+    return pair(args[4], o.v, o.i);
     END_HANDLE_TH_ERRORS
 }
 
@@ -273,8 +287,10 @@ PyObject* lstm_step(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     if (!x || !h || !bias || !c) Py_RETURN_NONE;
     // outputs the caller brings go the long way
     if (args[7] != Py_None || args[8] != Py_None) Py_RETURN_NONE;
-    at::Tensor c_out = g.floats({g.H}), h_out = g.floats({g.H});
+    at::Tensor c_out, h_out;
     const int status = enqueue([&](void* st) {
+        c_out = g.floats({g.H});
+        h_out = g.floats({g.H});
         return bs_lstm_step(g.vals->const_data_ptr(), static_cast<const uint8_t*>(g.idx->const_data_ptr()), g.dtype,
                             g.H, g.I, g.bank, g.k, static_cast<const float*>(x->const_data_ptr()),
                             static_cast<const float*>(h->const_data_ptr()),
@@ -300,9 +316,9 @@ PyObject* lstm_sequence(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     if (!h0 || !bias || !c) Py_RETURN_NONE;
     at::Tensor all;
     const at::Tensor* out = &all;
-    if (args[7] == Py_None) all = g.floats({T, g.H});
-    else if (!(out = gpu_tensor(args[7], at::kFloat))) Py_RETURN_NONE;
+    if (args[7] != Py_None && !(out = gpu_tensor(args[7], at::kFloat))) Py_RETURN_NONE;
     const int status = enqueue([&](void* st) {
+        if (out == &all) all = g.floats({T, g.H});
         return bs_lstm_sequence(g.vals->const_data_ptr(), static_cast<const uint8_t*>(g.idx->const_data_ptr()), g.dtype,
                                 g.H, g.I, g.bank, g.k, static_cast<const float*>(X->const_data_ptr()), T,
                                 static_cast<const float*>(h0->const_data_ptr()),

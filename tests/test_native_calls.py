@@ -207,3 +207,17 @@ def test_exceptions_keep_their_types(stand_in):
                     raise AssertionError(name + ": no error")
         assert attempts.value == 0
     """)
+
+
+def test_allocations_give_the_interpreter_lock_up(stand_in):
+    _run(stand_in, """
+        ctypes.c_int.in_dll(stand_in, "out_of_memory").value = 1
+        held = ctypes.c_int.in_dll(stand_in, "lock_held")
+        for name, f in allocating.items():
+            held.value = -1
+            try:
+                f()
+            except torch.OutOfMemoryError:
+                pass
+            assert held.value == 0, (name, held.value)
+    """)
