@@ -127,6 +127,14 @@ def _dev(t: torch.Tensor, what: str, dtype=None) -> torch.Tensor:
     return t
 
 
+def _out(t: torch.Tensor, what: str, n: int) -> torch.Tensor:
+    """A caller's fp32 output with room for the n elements that are written."""
+    _dev(t, what, torch.float32)
+    if t.numel() < n:
+        raise ValueError(f"{what} must have {n} elements")
+    return t
+
+
 def _rows(t: torch.Tensor, what: str) -> int:
     """A 2-D fp32 GPU tensor whose rows are contiguous (a column slice of a wider
     row-major tensor is fine): returns its leading dimension in elements."""
@@ -365,8 +373,7 @@ def bs_dense_gemv(W, x, out=None):
     _dev(x, "x", torch.float32)
     if x.numel() != K:
         raise ValueError(f"x must have {K} elements")
-    y = torch.empty(M, dtype=torch.float32, device=W.device) if out is None else _dev(
-        out, "out", torch.float32)
+    y = torch.empty(M, dtype=torch.float32, device=W.device) if out is None else _out(out, "out", M)
     _check(load_library().bs_dense_gemv(_ptr(W), code, M, K, _ptr(x), _ptr(y), _stream()),
            "bs_dense_gemv")
     return y
@@ -381,8 +388,7 @@ def bs_dense_gemm(W, X, out=None):
     if X.dim() != 2 or X.shape[0] != K:
         raise ValueError(f"X must be [{K}, N]")
     N = X.shape[1]
-    Y = torch.empty((M, N), dtype=torch.float32, device=W.device) if out is None else _dev(
-        out, "out", torch.float32)
+    Y = torch.empty((M, N), dtype=torch.float32, device=W.device) if out is None else _out(out, "out", M * N)
     _check(load_library().bs_dense_gemm(_ptr(W), code, M, K, _ptr(X), N, N, _ptr(Y), N, _stream()),
            "bs_dense_gemm")
     return Y
@@ -498,10 +504,8 @@ def bs_lstm_step(vals, idx, bank: int, x, h, bias, c, c_out=None, h_out=None):
         _dev(t, name, torch.float32)
         if t.numel() != n:
             raise ValueError(f"{name} must have {n} elements")
-    c_out = torch.empty(H, dtype=torch.float32, device=vals.device) if c_out is None else _dev(
-        c_out, "c_out", torch.float32)
-    h_out = torch.empty(H, dtype=torch.float32, device=vals.device) if h_out is None else _dev(
-        h_out, "h_out", torch.float32)
+    c_out = torch.empty(H, dtype=torch.float32, device=vals.device) if c_out is None else _out(c_out, "c_out", H)
+    h_out = torch.empty(H, dtype=torch.float32, device=vals.device) if h_out is None else _out(h_out, "h_out", H)
     _check(load_library().bs_lstm_step(_ptr(vals), _ptr(idx), code, H, I, bank, k, _ptr(x), _ptr(h),
                                        _ptr(bias), _ptr(c), _ptr(c_out), _ptr(h_out), _stream()),
            "bs_lstm_step")
@@ -522,8 +526,8 @@ def bs_lstm_sequence(vals, idx, bank: int, X, h0, bias, c, H_all=None):
         _dev(t, name, torch.float32)
         if t.numel() != n:
             raise ValueError(f"{name} must have {n} elements")
-    H_all = torch.empty((T, H), dtype=torch.float32, device=vals.device) if H_all is None else _dev(
-        H_all, "H_all", torch.float32)
+    H_all = torch.empty((T, H), dtype=torch.float32, device=vals.device) if H_all is None else _out(
+        H_all, "H_all", T * H)
     _check(load_library().bs_lstm_sequence(_ptr(vals), _ptr(idx), code, H, I, bank, k, _ptr(X), T,
                                            _ptr(h0), _ptr(bias), _ptr(c), _ptr(H_all), _stream()),
            "bs_lstm_sequence")

@@ -316,7 +316,7 @@ PyObject* lstm_sequence(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     if (!h0 || !bias || !c) Py_RETURN_NONE;
     at::Tensor all;
     const at::Tensor* out = &all;
-    if (args[7] != Py_None && !(out = gpu_tensor(args[7], at::kFloat))) Py_RETURN_NONE;
+    if (args[7] != Py_None && (!(out = gpu_tensor(args[7], at::kFloat)) || out->numel() < T * g.H)) Py_RETURN_NONE;
     const int status = enqueue([&](void* st) {
         if (out == &all) all = g.floats({T, g.H});
         return bs_lstm_sequence(g.vals->const_data_ptr(), static_cast<const uint8_t*>(g.idx->const_data_ptr()), g.dtype,

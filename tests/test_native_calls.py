@@ -221,3 +221,31 @@ def test_allocations_give_the_interpreter_lock_up(stand_in):
                 pass
             assert held.value == 0, (name, held.value)
     """)
+
+
+def test_outputs_that_are_too_small_are_refused(stand_in):
+    """Refused before any call; a larger output is written at its start, as ever."""
+    _run(stand_in, """
+        H, I, T, bank, k = 8, 8, 3, 4, 2
+        v, i = gpu(4 * H, 4, k), gpu(4 * H, 4, k, dtype=torch.uint8)
+        X, h, b, c = gpu(T, I), gpu(H), gpu(4 * H), gpu(H)
+        W = gpu(H, I)
+        calls = {"H_all": (T * H, lambda t: bs.bs_lstm_sequence(v, i, bank, X, h, b, c, H_all=t)),
+                 "c_out": (H, lambda t: bs.bs_lstm_step(v, i, bank, h, h, b, c, c_out=t, h_out=gpu(H))),
+                 "h_out": (H, lambda t: bs.bs_lstm_step(v, i, bank, h, h, b, c, c_out=c, h_out=t)),
+                 "gemv": (H, lambda t: bs.bs_dense_gemv(W, h, out=t)),
+                 "gemm": (H * 2, lambda t: bs.bs_dense_gemm(W, gpu(I, 2), out=t))}
+        ctypes.c_int.in_dll(stand_in, "status").value = 0
+        for name, (n, f) in calls.items():
+            attempts.value = 1       # the stand-in's sequence fails at its first attempt only
+            try:
+                f(gpu(n - 1))
+            except ValueError as e:
+                assert str(n) in str(e), e
+            else:
+                raise AssertionError(name + ": no error")
+            assert attempts.value == 1, name
+            for room in (n, n + 1):
+                f(gpu(room))
+            assert attempts.value == 3, name
+    """)
