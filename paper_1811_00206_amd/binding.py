@@ -311,6 +311,17 @@ def bs_spmv_ex(vals, idx, bank, x, lanes_per_row, rows_per_wg, out=None, start_e
                    rows_per_wg=rows_per_wg, start_event=start_event, stop_event=stop_event)
 
 
+def _workspace(workspace, need: int, device):
+    """The caller's workspace, or a new one where the product needs one."""
+    if not need:
+        return workspace
+    if workspace is None:
+        return new_spmm_workspace(need, device)
+    if not isinstance(workspace, torch.Tensor) or not workspace.is_cuda:
+        raise TypeError("workspace must be a tensor on the GPU")
+    return workspace
+
+
 def new_spmm_workspace(nbytes: int, device) -> torch.Tensor:
     """A workspace for bs_spmm / bs_spmm_wide (uninitialised device memory)."""
     return torch.empty(max(int(nbytes), 16), dtype=torch.uint8, device=device)
@@ -336,8 +347,7 @@ def bs_spmm(vals, idx, bank: int, X, out=None, workspace=None):
         raise ValueError(f"out must be [{M}, {N}]")
     lib = load_library()
     need = lib.bs_spmm_workspace_bytes(code, M, K, bank, k, N)
-    if need and workspace is None:
-        workspace = new_spmm_workspace(need, vals.device)
+    workspace = _workspace(workspace, need, vals.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib.bs_spmm(_ptr(vals), _ptr(idx), code, M, K, bank, k, _ptr(X), N, ldx, _ptr(Y), ldy,
                        _ptr(workspace), ws_bytes, _stream()), "bs_spmm")
@@ -475,8 +485,7 @@ def bs_spmm_wide(vals, idx, bank: int, X, out=None, workspace=None):
         raise ValueError(f"out must be [{M}, {N}]")
     lib = load_library()
     need = lib.bs_spmm_workspace_bytes_wide(code, M, K, bank, k, N)
-    if need and workspace is None:
-        workspace = new_spmm_workspace(need, vals.device)
+    workspace = _workspace(workspace, need, vals.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib.bs_spmm_wide(_ptr(vals), _ptr(idx), code, M, K, bank, k, _ptr(X), N, ldx, _ptr(Y), ldy,
                             _ptr(workspace), ws_bytes, _stream()), "bs_spmm_wide")

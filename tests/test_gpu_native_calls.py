@@ -27,7 +27,14 @@ def _calls(bank, wide):
     v, i = prune(W, bank, k)
     x, X = torch.randn(K, generator=g, device="cuda"), torch.randn((K, 2 * N), generator=g, device="cuda")
     new = lambda *s: torch.empty(s, device="cuda")
-    need = (bs.bs_spmm_workspace_bytes_wide if wide else bs.bs_spmm_workspace_bytes)(bs.BS_F32, M, K, bank, k, N)
+    size = bs.bs_spmm_workspace_bytes_wide if wide else bs.bs_spmm_workspace_bytes
+    need = size(bs.BS_F32, M, K, bank, k, N)
+    # a product of several slabs, for a workspace that the library refuses before it launches anything
+    nb2 = 20000 // bank
+    v2, i2 = new(M, nb2, k), torch.empty((M, nb2, k), device="cuda", dtype=i.dtype)
+    X2 = new(nb2 * bank, 2 * N)
+    need2 = size(bs.BS_F32, M, nb2 * bank, bank, k, 2 * N)
+    assert need2 > 16
     yield "prune", lambda: prune(W, bank, k)
     yield "prune out", lambda: prune(W, bank, k, out=(torch.empty_like(v), torch.empty_like(i)))
     yield "spmv", lambda: spmv(v, i, bank, x)
@@ -51,7 +58,8 @@ def _calls(bank, wide):
                       ("k", lambda: prune(W, bank, bank + 1)),
                       ("X rows", lambda: spmm(v, i, bank, X[1:])),
                       ("X columns", lambda: spmm(v, i, bank, X.t())),
-                      ("workspace", lambda: spmm(v, i, bank, X, workspace=X.cpu()) if need else spmv(v, i, 0, x))):
+                      ("no bank", lambda: spmv(v, i, 0, x)),
+                      ("workspace", lambda: spmm(v2, i2, bank, X2, workspace=bs.new_spmm_workspace(need2 - 16, "cuda")))):
         yield what, bad
 
 
@@ -67,6 +75,7 @@ def _run(call):
 def test_native_and_python_marshalling_agree(bank, wide, monkeypatch):
     names = [n for n, _ in _calls(bank, wide)]
     native = [_run(c) for _, c in _calls(bank, wide)]
+    assert native[names.index("workspace")][0] is bs.BsError and "workspace" in native[names.index("workspace")][1]
     monkeypatch.setattr(bs, "_native", _LongWay(bs._native))
     for name, a, (_, call) in zip(names, native, _calls(bank, wide)):
         print("native calls", bank, name, flush=True)

@@ -249,3 +249,29 @@ def test_outputs_that_are_too_small_are_refused(stand_in):
                 f(gpu(room))
             assert attempts.value == 3, name
     """)
+
+
+def test_a_workspace_in_host_memory_is_refused(stand_in):
+    """The kernels write to it.  Where a product needs none, none is looked at."""
+    _run(stand_in, """
+        ctypes.c_int.in_dll(stand_in, "status").value = 0
+        M, N = 200, 24
+        for wide, bank, k, nb, spmm, size in ((False, 100, 10, 200, bs.bs_spmm, bs.bs_spmm_workspace_bytes),
+                                              (True, 512, 16, 40, bs.bs_spmm_wide, bs.bs_spmm_workspace_bytes_wide)):
+            for nb_ in (nb, 1):
+                need = size(bs.BS_F32, M, nb_ * bank, bank, k, N)
+                assert (need > 0) == (nb_ > 1)
+                v, X = gpu(M, nb_, k), gpu(nb_ * bank, N)
+                i, Y = gpu(M, nb_, k, dtype=torch.uint16 if wide else torch.uint8), gpu(M, N)
+                for host in (torch.empty(max(need, 16), dtype=torch.uint8), bytearray(max(need, 16))):
+                    attempts.value = 0
+                    if not need and not isinstance(host, torch.Tensor):
+                        continue
+                    try:
+                        spmm(v, i, bank, X, out=Y, workspace=host)
+                    except TypeError as e:
+                        assert need and "workspace" in str(e), e
+                    else:
+                        assert not need
+                    assert attempts.value == (0 if need else 1)
+    """)
