@@ -181,7 +181,7 @@ size_t bs_spmm_workspace_bytes(int dtype, int64_t M, int64_t K, int bank, int k,
 /*
  * The launch bs_spmm would make for this shape, for tests and tuning (host only, no GPU
  * call; the tiling itself is ours, the paper gives none for a batch).  Writes up to n_out
- * of these 16 values to out (HOST):
+ * of these 17 values to out (HOST):
  *   [0] kernel: 0 chunk walk (LPR lanes per row and column group), 1 one lane per row and
  *       column group          [1] entries per 16-byte chunk
  *   [2] column groups of 4 per tile (nl)   [3] columns per tile   [4] column tiles
@@ -190,6 +190,7 @@ size_t bs_spmm_workspace_bytes(int dtype, int64_t M, int64_t K, int bank, int k,
  *   [11] row groups            [12] row passes of a workgroup
  *   [13] LDS bytes per workgroup            [14] workgroups launched
  *   [15] float index of the position table in LDS
+ *   [16] threads per workgroup (for ldx = N): those of [9] and any that only copy X
  * Returns BS_OK, or the status bs_spmm would return for an unsupported shape.
  */
 int bs_spmm_plan(int dtype, int64_t M, int64_t K, int bank, int k, int64_t N,

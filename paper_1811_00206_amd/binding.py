@@ -205,7 +205,7 @@ def bs_spmv_plan(dtype: int, M: int, K: int, bank: int, k: int, lanes_per_row: i
 
 
 SPMM_PLAN_FIELDS = ("rows_kernel", "ch", "nl", "nt", "n_tiles", "sb", "n_slabs", "lpr", "u", "threads",
-                    "rows_per_wg", "row_groups", "n_passes", "lds_bytes", "workgroups", "table_off")
+                    "rows_per_wg", "row_groups", "n_passes", "lds_bytes", "workgroups", "table_off", "wg_threads")
 
 
 def bs_spmm_plan(dtype: int, M: int, K: int, bank: int, k: int, N: int) -> dict:

@@ -1,5 +1,7 @@
 // Host side of bs_spmm: tiling plan, launch, and the kernel that adds slab
 // partial sums (see bs_spmm_kernel.h for the design of the main kernel).
+#include <algorithm>
+
 #include "bs_spmm_rows_kernel.h"
 
 namespace bs {
@@ -17,11 +19,11 @@ struct SpmmPlan {
     int sb, n_slabs;   // banks per slab
     int lpr, u;        // lanes per (row, column group), chunk slots per lane
     bool rows;         // one lane per (row, column group): bs_spmm_rows_kernel.h
-    int threads;       // of a workgroup
-    int row_threads;   // of these, the lanes that walk rows
+    int row_threads;   // lanes of a workgroup that walk rows; launched_threads() adds those that only copy X
+    int max_threads;
     int rows_per_wg, row_groups;
     int table_off;
-    size_t lds_bytes;
+    size_t tile_bytes, lds_bytes;
     size_t ws_bytes;
     double cost;
 };
@@ -69,6 +71,7 @@ SpmmPlan plan_for(int quads, int dtype, int64_t M, int64_t K, int bank, int k, i
     p.sb = (int)sb;
     p.n_slabs = (int)((nb + sb - 1) / sb);
     const size_t tile_bytes = (size_t)sb * per_bank;
+    p.tile_bytes = tile_bytes;
     p.table_off = (int)(tile_bytes / 4);
     p.lds_bytes = tile_bytes + (size_t)sb * k * 4;
 
@@ -116,21 +119,37 @@ SpmmPlan plan_for(int quads, int dtype, int64_t M, int64_t K, int bank, int k, i
     int64_t threads = (rows_per_pass * lanes_per_row + kWave - 1) / kWave * kWave;
     if (threads > max_threads) threads = max_threads;
     p.row_threads = (int)threads;
-    // With few rows per workgroup those wavefronts are too few to bring the tile in: each more
-    // copies a share of it and leaves (up to 8 pieces of 16 bytes per lane).  1024 x 1024 at
-    // N = 37: 22.2 -> 12.0 us, at N = 40: 12.8 -> 11.2 us.  Where half of them walk rows already
-    // and the pieces are of 16 bytes, the others cost more than they bring (6000 x 3000 at
-    // N = 40: 17.0 -> 17.7 us); with pieces of 4 bytes they still help (N = 37: 19.8 -> 18.5 us).
-    int64_t copy_threads = (int64_t)(tile_bytes / (8 * 16) + kWave - 1) / kWave * kWave;
-    if (copy_threads > max_threads) copy_threads = max_threads;
-    if (threads * (N % 4 ? 1 : 2) < copy_threads) threads = copy_threads;
-    p.threads = (int)threads;
+    p.max_threads = max_threads;
     p.ws_bytes = p.n_slabs > 1 ? (size_t)p.n_slabs * M * N * 4 : 0;
     const double w_bytes = (double)M * row_len * (vsize + isize);
     p.cost = (double)p.row_groups * p.n_tiles * p.n_slabs * tile_bytes + p.n_tiles * w_bytes +
              2.0 * p.ws_bytes;
     p.ok = true;
     return p;
+}
+
+// 16-byte direct-to-LDS copies need 16-byte aligned row pieces and whole groups of 4 columns
+bool wide_copies(int64_t N, int64_t ldx) { return N % 4 == 0 && ldx % 4 == 0; }
+
+// Threads of a workgroup.  With few rows per workgroup the wavefronts that walk them are too few
+// to bring the tile in: each more copies a share of it and leaves.
+//   * Pieces of 16 bytes, up to 8 of them per lane: 1024 x 1024 at N = 40: 12.8 -> 11.2 us.  Where
+//     half of that many wavefronts walk rows already, the others cost more than they bring
+//     (6000 x 3000 at N = 40: 17.0 -> 17.7 us).
+//   * Pieces of 4 bytes are four times as many, so up to four times the lanes (300 x 320 at N = 8
+//     with an odd row pitch, 304 workgroups: 5.5 -> 3.6 us), as far as the chip has room for them:
+//     512 per compute unit, or two wavefronts per workgroup (3723 x 600 at N = 37, 1960 workgroups:
+//     6.7 us with 128 lanes each, 8.4 with 256).
+int launched_threads(const SpmmPlan& p, bool wide) {
+    auto whole = [](int64_t lanes) { return (lanes + kWave - 1) / kWave * kWave; };
+    int64_t copy_threads = whole((int64_t)p.tile_bytes / (8 * 16));
+    if (!wide) {
+        const int64_t wgs = (int64_t)p.n_tiles * p.n_slabs * p.row_groups;
+        const int64_t room = std::max<int64_t>((int64_t)kCus * 512 / wgs / kWave * kWave, 2 * kWave);
+        copy_threads = std::max(copy_threads, std::min(whole((int64_t)p.tile_bytes / (8 * 4)), room));
+    }
+    if (copy_threads > p.max_threads) copy_threads = p.max_threads;
+    return (int)(p.row_threads * (wide ? 2 : 1) < copy_threads ? copy_threads : p.row_threads);
 }
 
 SpmmPlan make_plan(int dtype, int64_t M, int64_t K, int bank, int k, int64_t N, int isize = 1) {
@@ -253,11 +272,12 @@ int spmm_plan_describe(int dtype, int64_t M, int64_t K, int bank, int k, int64_t
     if (total > INT32_MAX / 2) return BS_ERR_UNSUPPORTED;
     if (p.ws_bytes && M * N > (int64_t)UINT32_MAX) return BS_ERR_UNSUPPORTED;
     const int rows_per_pass = p.row_threads / (p.nl * p.lpr);
-    const int64_t v[16] = {p.rows ? 1 : 0, p.ch, p.nl, p.nt, p.n_tiles, p.sb, p.n_slabs, p.lpr, p.u,
+    const int64_t v[17] = {p.rows ? 1 : 0, p.ch, p.nl, p.nt, p.n_tiles, p.sb, p.n_slabs, p.lpr, p.u,
                            p.row_threads, p.rows_per_wg, p.row_groups,
                            (p.rows_per_wg + rows_per_pass - 1) / rows_per_pass,
-                           (int64_t)p.lds_bytes, (total + kXcds - 1) / kXcds * kXcds, p.table_off};
-    for (int i = 0; i < n_out && i < 16; ++i) out[i] = v[i];
+                           (int64_t)p.lds_bytes, (total + kXcds - 1) / kXcds * kXcds, p.table_off,
+                           launched_threads(p, wide_copies(N, N))};
+    for (int i = 0; i < n_out && i < 17; ++i) out[i] = v[i];
     return BS_OK;
 }
 
@@ -291,14 +311,13 @@ int launch_spmm_any(const void* vals, const void* idx, int isize, int dtype, int
     a.magic_k = magic_u32((uint32_t)k);
     a.magic_rg = magic_u32((uint32_t)p.row_groups);
     a.magic_rgs = magic_u32((uint32_t)(p.row_groups * p.n_slabs));
-    // 16-byte direct-to-LDS copies need 16-byte aligned row pieces and whole groups of 4 columns
-    a.dma = (N % 4 == 0 && ldx % 4 == 0) ? 1 : 0;
+    a.dma = wide_copies(N, ldx) ? 1 : 0;
     const int rows_per_pass = p.row_threads / (p.nl * p.lpr);
     a.row_threads = p.row_threads;
     a.n_passes = (p.rows_per_wg + rows_per_pass - 1) / rows_per_pass;
     a.vec_out = (a.ld_out % 4 == 0 && a.slab_stride % 4 == 0 && (uintptr_t)a.out % 16 == 0) ? 1 : 0;
 
-    const SpmmLaunch l{p.threads, p.lds_bytes, st};
+    const SpmmLaunch l{launched_threads(p, a.dma != 0), p.lds_bytes, st};
     int st_code = isize == 2 ? spmm_launch_wide(dtype, p.rows, p.ch, p.lpr, p.u, a, l)
                   : p.rows ? spmm_rows_launch(dtype, p.ch, a, l)
                   : dtype == BS_F16 ? spmm_launch_f16(p.ch, p.lpr, p.u, p.q, a, l)

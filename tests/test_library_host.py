@@ -143,7 +143,8 @@ def _plan_invariants(b, dtype, M, K, bank, k, N):
     assert p["table_off"] * 4 == tile, where
     assert p["lds_bytes"] == tile + p["sb"] * k * 4 <= 160 * 1024, where
     # lanes
-    assert p["threads"] % 64 == 0 and 64 <= p["threads"] <= 1024, where
+    assert p["threads"] % 64 == 0 and 64 <= p["threads"] <= p["wg_threads"] <= 1024, where
+    assert p["wg_threads"] % 64 == 0, where
     if p["rows_kernel"]:
         assert p["nl"] >= 4 and p["lpr"] == 1 and p["u"] == 4, where
     else:
