@@ -128,8 +128,14 @@ SpmmPlan plan_for(int quads, int dtype, int64_t M, int64_t K, int bank, int k, i
     return p;
 }
 
-// 16-byte direct-to-LDS copies need 16-byte aligned row pieces and whole groups of 4 columns
-bool wide_copies(int64_t N, int64_t ldx) { return N % 4 == 0 && ldx % 4 == 0; }
+// 16-byte direct-to-LDS copies need 16-byte aligned row pieces and whole groups of 4 columns.
+// One or two columns, and three in adjacent rows, go through registers: 4441 x 736 at N = 2:
+// 5.4 -> 4.7 us, 11772 x 3072 at N = 3: 11.0 -> 7.1 us; with three in a wider pitch each load would
+// touch as many cache lines as it has lanes for few bytes (2182 x 2704, ldx = 4: 6.4 against 9.0 us).
+SpmmCopy copy_kind(int64_t N, int64_t ldx) {
+    if (N % 4 == 0 && ldx % 4 == 0) return kCopyWide;
+    return N <= 2 || (N == 3 && ldx == 3) ? kCopyRegisters : kCopyNarrow;
+}
 
 // Threads of a workgroup.  With few rows per workgroup the wavefronts that walk them are too few
 // to bring the tile in: each more copies a share of it and leaves.
@@ -140,7 +146,8 @@ bool wide_copies(int64_t N, int64_t ldx) { return N % 4 == 0 && ldx % 4 == 0; }
 //     with an odd row pitch, 304 workgroups: 5.5 -> 3.6 us), as far as the chip has room for them:
 //     512 per compute unit, or two wavefronts per workgroup (3723 x 600 at N = 37, 1960 workgroups:
 //     6.7 us with 128 lanes each, 8.4 with 256).
-int launched_threads(const SpmmPlan& p, bool wide) {
+int launched_threads(const SpmmPlan& p, SpmmCopy copy) {
+    const bool wide = copy == kCopyWide;
     auto whole = [](int64_t lanes) { return (lanes + kWave - 1) / kWave * kWave; };
     int64_t copy_threads = whole((int64_t)p.tile_bytes / (8 * 16));
     if (!wide) {
@@ -276,7 +283,7 @@ int spmm_plan_describe(int dtype, int64_t M, int64_t K, int bank, int k, int64_t
                            p.row_threads, p.rows_per_wg, p.row_groups,
                            (p.rows_per_wg + rows_per_pass - 1) / rows_per_pass,
                            (int64_t)p.lds_bytes, (total + kXcds - 1) / kXcds * kXcds, p.table_off,
-                           launched_threads(p, wide_copies(N, N))};
+                           launched_threads(p, copy_kind(N, N))};
     for (int i = 0; i < n_out && i < 17; ++i) out[i] = v[i];
     return BS_OK;
 }
@@ -311,13 +318,13 @@ int launch_spmm_any(const void* vals, const void* idx, int isize, int dtype, int
     a.magic_k = magic_u32((uint32_t)k);
     a.magic_rg = magic_u32((uint32_t)p.row_groups);
     a.magic_rgs = magic_u32((uint32_t)(p.row_groups * p.n_slabs));
-    a.dma = wide_copies(N, ldx) ? 1 : 0;
+    a.copy = copy_kind(N, ldx);
     const int rows_per_pass = p.row_threads / (p.nl * p.lpr);
     a.row_threads = p.row_threads;
     a.n_passes = (p.rows_per_wg + rows_per_pass - 1) / rows_per_pass;
     a.vec_out = (a.ld_out % 4 == 0 && a.slab_stride % 4 == 0 && (uintptr_t)a.out % 16 == 0) ? 1 : 0;
 
-    const SpmmLaunch l{launched_threads(p, a.dma != 0), p.lds_bytes, st};
+    const SpmmLaunch l{launched_threads(p, copy_kind(N, ldx)), p.lds_bytes, st};
     int st_code = isize == 2 ? spmm_launch_wide(dtype, p.rows, p.ch, p.lpr, p.u, a, l)
                   : p.rows ? spmm_rows_launch(dtype, p.ch, a, l)
                   : dtype == BS_F16 ? spmm_launch_f16(p.ch, p.lpr, p.u, p.q, a, l)

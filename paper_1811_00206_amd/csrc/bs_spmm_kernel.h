@@ -39,6 +39,9 @@ namespace bs {
 
 constexpr int kXcds = 8;
 
+// The tile of X: direct-to-LDS loads of 16 bytes or of 4, or through registers.
+enum SpmmCopy { kCopyNarrow, kCopyWide, kCopyRegisters };
+
 struct SpmmArgs {
     const void* vals;
     const void* idx;       // uint8_t, or uint16_t in the kernels for balance ranges over 256
@@ -57,7 +60,7 @@ struct SpmmArgs {
     int table_off;         // float index in LDS of the position table
     uint32_t magic_k;
     uint32_t magic_rg, magic_rgs;   // magic_u32(row_groups), magic_u32(row_groups * n_slabs)
-    int dma;               // tile rows can be copied with 16-byte direct-to-LDS loads
+    int copy;              // how the tile of X is brought in (SpmmCopy)
     int n_passes;          // row passes of a workgroup: ceil(rows_per_wg / rows per pass)
     int row_threads;       // lanes that walk rows; the workgroup's other wavefronts only copy X
     // one lane per (row, column group) (bs_spmm_rows_kernel.h)
@@ -85,7 +88,7 @@ __device__ __forceinline__ void spmm_stage_tile(const SpmmArgs& a, float* Xs, in
                                                 int nthr) {
     const float* Xg = a.X + (size_t)j0 * a.B * a.ldx + n0;
     const int total_f4 = slab_rows * f4_per_row;
-    if (a.dma) {
+    if (a.copy == kCopyWide) {
         // A lane's pieces are nthr float4 apart: the same column group every time and a
         // constant number of rows further on (f4_per_row is a power of two <= 64), so the
         // source address advances by a constant.
@@ -118,6 +121,27 @@ __device__ __forceinline__ void spmm_stage_tile(const SpmmArgs& a, float* Xs, in
                     (const __attribute__((address_space(1))) void*)src,
                     (__attribute__((address_space(3))) void*)(Xs + p * 64), 4, 0, 0);
         }
+    }
+}
+
+// The same for N <= NC columns, through registers: NC loads and one LDS store of 16 bytes per 64
+// rows of X, where the narrow walk above takes four instructions.  Indexes past the end repeat
+// the last row (and the last column).
+template <int NC>
+__device__ __forceinline__ void spmm_stage_few(const SpmmArgs& a, float* Xs, int j0, int slab_rows, int tid, int nthr) {
+    constexpr int kRows = 4;   // the loads of as many rows are in flight before the first store
+    const float* Xg = a.X + (size_t)j0 * a.B * a.ldx;
+    for (int i0 = tid; i0 < slab_rows; i0 += kRows * nthr) {
+        float t[kRows][4] = {};
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            const float* src = Xg + (size_t)min(i0 + u * nthr, slab_rows - 1) * a.ldx;
+#pragma unroll
+            for (int n = 0; n < NC; ++n) t[u][n] = src[min(n, a.N - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < kRows; ++u)
+            reinterpret_cast<float4*>(Xs)[min(i0 + u * nthr, slab_rows - 1)] = make_float4(t[u][0], t[u][1], t[u][2], t[u][3]);
     }
 }
 
@@ -221,8 +245,8 @@ __device__ __forceinline__ void spmm_consume(const char* xcol, const uint32_t* t
     if (live == 1) return spmm_slots<VT, CH, LPR, U, Q, 1>(xcol, tab, pitch, v, o, c0, ragged, cps, acc);
 }
 
-template <typename VT, int CH, int LPR, int U, int Q, typename IT = uint8_t>
-__global__ __launch_bounds__(1024) void spmm_kernel(SpmmArgs a) {
+template <typename VT, int CH, int LPR, int U, int Q, typename IT, bool FEW>
+__device__ __forceinline__ void spmm_body(const SpmmArgs& a) {
     static_assert(Q == 1, "one group of four columns per lane");
     extern __shared__ __align__(16) float Xs[];
     using VRaw = typename RawBytes<CH * sizeof(VT)>::type;
@@ -256,7 +280,10 @@ __global__ __launch_bounds__(1024) void spmm_kernel(SpmmArgs a) {
     const int r_end = min(a.M, r_begin + a.rows_per_wg);
 
     // (1) the tile of X -> LDS
-    spmm_stage_tile(a, Xs, j0, n0, ntw, slab_rows, f4_per_row, f4_shift, tid, nthr);
+    if constexpr (FEW) {
+        if (a.N <= 2) spmm_stage_few<2>(a, Xs, j0, slab_rows, tid, nthr);
+        else spmm_stage_few<3>(a, Xs, j0, slab_rows, tid, nthr);
+    } else spmm_stage_tile(a, Xs, j0, n0, ntw, slab_rows, f4_per_row, f4_shift, tid, nthr);
     pin_order();
 
     // (2) the weight stream in rounds of U*LPR chunks of a row: a row's run takes `rounds`
@@ -347,14 +374,31 @@ __global__ __launch_bounds__(1024) void spmm_kernel(SpmmArgs a) {
 }
 
 template <typename VT, int CH, int LPR, int U, int Q, typename IT = uint8_t>
-int spmm_launch_one(const SpmmArgs& a, const SpmmLaunch& l) {
-    constexpr auto kern = spmm_kernel<VT, CH, LPR, U, Q, IT>;
+__global__ __launch_bounds__(1024) void spmm_kernel(SpmmArgs a) {
+    spmm_body<VT, CH, LPR, U, Q, IT, false>(a);
+}
+
+// copy == kCopyRegisters.  A kernel of its own: with the third way to copy in the same one the
+// other two were 3-10 % slower on products of 6 us.
+template <typename VT, int CH, int LPR, int U, int Q, typename IT = uint8_t>
+__global__ __launch_bounds__(1024) void spmm_few_kernel(SpmmArgs a) {
+    spmm_body<VT, CH, LPR, U, Q, IT, true>(a);
+}
+
+template <auto KERNEL>
+int spmm_launch_kernel(const SpmmArgs& a, const SpmmLaunch& l) {
     if (l.lds > 48 * 1024) {
-        const int st_code = ensure_lds_limit(LdsKernelOf<kern>::reg, l.st);
+        const int st_code = ensure_lds_limit(LdsKernelOf<KERNEL>::reg, l.st);
         if (st_code != BS_OK) return st_code;
     }
-    hipLaunchKernelGGL(kern, dim3(a.wgs_per_xcd * kXcds), dim3(l.threads), l.lds, l.st, a);
+    hipLaunchKernelGGL(KERNEL, dim3(a.wgs_per_xcd * kXcds), dim3(l.threads), l.lds, l.st, a);
     return hip_status(hipGetLastError());
+}
+
+template <typename VT, int CH, int LPR, int U, int Q, typename IT = uint8_t>
+int spmm_launch_one(const SpmmArgs& a, const SpmmLaunch& l) {
+    if (a.copy == kCopyRegisters) return spmm_launch_kernel<spmm_few_kernel<VT, CH, LPR, U, Q, IT>>(a, l);
+    return spmm_launch_kernel<spmm_kernel<VT, CH, LPR, U, Q, IT>>(a, l);
 }
 
 template <typename VT, int CH, int LPR, int U>

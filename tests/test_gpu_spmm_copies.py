@@ -29,3 +29,27 @@ def test_copied_tiles(bank, k, M, N):
         # sum of the terms' magnitudes, and one more rounding per term
         bound = (K // bank * k + 1) * 2.0 ** -24 * (dense.abs() @ x.abs())
         assert ((Y - dense @ x).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("bank,k", [(16, 3), (25, 7), (512, 40)])
+@pytest.mark.parametrize("M,nb", [(1, 1), (9, 5), (300, 17), (2100, 41)])
+@pytest.mark.parametrize("N", [1, 2, 3, 5])
+def test_few_columns(bank, k, M, nb, N):
+    """The kinds of copy and the workgroup sizes meet here: one to three columns in rows that are
+    adjacent or lie further apart, tiles of less than a wavefront's rows and of many times a
+    workgroup's."""
+    K = nb * bank
+    g = torch.Generator(device="cuda").manual_seed(M * 1000 + K + N)
+    prune, spmm = (bs.bs_prune_pack_wide, bs.bs_spmm_wide) if bank > 256 else (bs.bs_prune_pack, bs.bs_spmm)
+    W = torch.randn((M, K), generator=g, device="cuda")
+    v, i = prune(W, bank, k)
+    dense = torch.zeros((M, nb, bank), dtype=torch.float64)
+    dense.scatter_(2, i.cpu().to(torch.int64), v.cpu().double())
+    dense = dense.view(M, K)
+    for pitch in (N, N + 1, 7):
+        print("few columns", bank, k, M, nb, N, pitch, flush=True)
+        X = torch.randn((K, pitch), generator=g, device="cuda")[:, :N]
+        x = X.cpu().double()
+        # as above
+        bound = (nb * k + 1) * 2.0 ** -24 * (dense.abs() @ x.abs())
+        assert ((spmm(v, i, bank, X).cpu().double() - dense @ x).abs() <= bound).all()
