@@ -38,7 +38,9 @@
 // 11908 x 7616 binary16, 18 of 64: 63.5 -> 52.7 us.  Vector instructions on the first: 12.9 M
 // -> 7.1 M.
 // Re-pruning a packed matrix to fewer weights per bank (one more round of
-// Algorithm 1's loop) runs the same kernel on the stored values, k per bank.
+// Algorithm 1's loop) runs the same kernel on the stored values, k per bank: 10 -> 5 of 100 on the
+// 6000 x 3000 matrix 7.9 us (9.6 with one byte fetched per lane and step, 9.5 with the kernel before
+// the bit-sliced bytes), 128 -> 64 of 256 on 16384 x 8192 90 us (134, 144).
 #pragma once
 #include "bs_internal.h"
 
@@ -177,6 +179,15 @@ __device__ __forceinline__ uint32_t low_bits(int n) { return n >= 32 ? 0xFFFFFFF
 //   kHalves    as in memory; binary16 with an odd bank.
 enum LaneLayout { kAligned, kWords, kHalves };
 
+// The offsets that go out with the survivors: their positions in the bank or, re-pruning, the
+// offsets that the packed matrix holds there.  Those are fetched by position where a wavefront
+// keeps at most kFewOutputs (a lane's four together: one round trip); with more it would be several
+// dependent round trips, and all stored offsets come to LDS while the keys are searched
+// (2048 x 8192, 100 -> 90 of 256: 26.3 -> 17.8 us; where few are kept the copy costs up to 15 %:
+// 4096 x 4096, 32 -> 2 of 64: 12.1 against 11.4 us).
+enum Offsets { kPositions, kStored, kStoredInLds };
+constexpr int kFewOutputs = 4 * kWave;
+
 struct PruneArgs {
     const void* W;
     void* vals;
@@ -187,15 +198,32 @@ struct PruneArgs {
     int C;                 // elements per lane: LPB * C >= B, C <= NE
     uint32_t magic_k;      // magic_u32(k)
     int raw_bytes;         // LDS bytes of the wavefront's banks; its offsets follow
-    int wave_bytes;        // both, a multiple of 256
+    int stored_at;         // kStoredInLds: where the stored offsets lie behind those
+    int wave_bytes;        // all of them, a multiple of 256
 };
 
 // Wavefronts per workgroup at most; they share nothing.  1 / 2 / 4 on the 6000 x 3000 matrix:
 // 18.6 / 18.5 / 16.9 us (11250 wavefronts of short life: fewer workgroups to dispatch).
 constexpr int kPruneWaves = 4;
 
+// n bytes from memory to LDS by one wavefront, P (4 or 16) at a time and the last ones singly;
+// direct-to-LDS loads, so the caller waits.
+template <int P>
+__device__ __forceinline__ void copy_bytes(const unsigned char* src, unsigned char* dst, int n, int lane) {
+    const int pieces = n / P;
+    for (int p0 = 0; p0 < pieces; p0 += kWave)
+        if (p0 + lane < pieces) {
+            const auto from = (const __attribute__((address_space(1))) void*)(src + (size_t)(p0 + lane) * P);
+            const auto to = (__attribute__((address_space(3))) void*)(dst + p0 * P);
+            if constexpr (P == 16) __builtin_amdgcn_global_load_lds(from, to, 16, 0, 0);
+            else __builtin_amdgcn_global_load_lds(from, to, 4, 0, 0);
+        }
+    const int done = pieces * P;
+    if (lane < n - done) dst[done + lane] = src[done + lane];
+}
+
 // A group of 64/LPB banks per wavefront, no loop.
-template <typename VT, typename IT, int LPB, int NE, LaneLayout LAYOUT>
+template <typename VT, typename IT, int LPB, int NE, LaneLayout LAYOUT, Offsets OFFSETS>
 __global__ __launch_bounds__(kWave * kPruneWaves) void prune_pack_kernel(PruneArgs a) {
     constexpr int S = sizeof(VT);
     constexpr int NM = NE > 32 ? 2 : 1;           // mask words
@@ -266,6 +294,18 @@ __global__ __launch_bounds__(kWave * kPruneWaves) void prune_pack_kernel(PruneAr
                 w[i] = (uint32_t)reinterpret_cast<const uint16_t*>(mine)[2 * i] |
                        ((uint32_t)reinterpret_cast<const uint16_t*>(mine)[2 * i + 1] << 16);
         }
+    }
+
+    // ---- the stored offsets -> LDS ----------------------------------------------
+    const unsigned char* idx_src = static_cast<const unsigned char*>(a.remap) + first * B;
+    unsigned char* stored = pp_lds + a.stored_at;
+    if constexpr (OFFSETS == kStoredInLds) {
+        static_assert(sizeof(IT) == 1 && BPW >= 8, "byte offsets, groups of 8 banks or more");
+        pin_order();
+        // pieces that every group starts on
+        if (BPW % 16 == 0 || B % 2 == 0) copy_bytes<16>(idx_src, stored, n_ok * B, lane);
+        else copy_bytes<4>(idx_src, stored, n_ok * B, lane);
+        pin_order();
     }
 
     // ---- the k largest keys --------------------------------------------------
@@ -345,29 +385,36 @@ __global__ __launch_bounds__(kWave * kPruneWaves) void prune_pack_kernel(PruneAr
     VT* vout = static_cast<VT*>(a.vals) + first * k;
     IT* iout = static_cast<IT*>(a.idx) + first * k;
     const int n_out = n_ok * k;
-    if (a.remap) {   // the survivors carry the offsets the packed matrix already holds
-        const IT* stored = static_cast<const IT*>(a.remap) + first * B;
-        for (int s = lane; s < n_out; s += kWave) {
-            const uint32_t off = out_i[s];
-            vout[s] = value(s, off);
-            iout[s] = stored[div_magic((uint32_t)s, (uint32_t)k, a.magic_k) * (uint32_t)B + off];
-        }
-        return;
+    // the offset that goes out for the survivor at position `off` of its bank
+    auto offset = [&](int slot, uint32_t off) -> IT {
+        if constexpr (OFFSETS == kPositions) return (IT)off;
+        const uint32_t at = div_magic((uint32_t)slot, (uint32_t)k, a.magic_k) * (uint32_t)B + off;
+        return OFFSETS == kStoredInLds ? stored[at] : idx_src[at];
+    };
+    if constexpr (OFFSETS == kStoredInLds) {   // the copies above are not tracked by the compiler
+        pin_order();
+        wait_vm_and_lds<0>();
+        pin_order();
     }
     // four outputs per lane and step; a group starts on a multiple of four outputs unless
-    // it holds two banks (LPB == 32), and only the matrix's last group may end elsewhere
-    const int quads = LPB <= 16 || k % 2 == 0 ? n_out >> 2 : 0;
+    // it holds two banks (LPB == 32), and only the matrix's last group may end elsewhere.
+    // Offsets that are fetched by position: one per lane where that takes one step.
+    int quads = LPB <= 16 || k % 2 == 0 ? n_out >> 2 : 0;
+    if (OFFSETS == kStored && n_out <= kWave) quads = 0;
     using Quad = typename RawBytes<4 * S>::type;
     using IQuad = typename RawBytes<4 * sizeof(IT)>::type;
     for (int s = lane; s < quads; s += kWave) {
-        const IQuad o = reinterpret_cast<const IQuad*>(out_i)[s];
+        IQuad o = reinterpret_cast<const IQuad*>(out_i)[s];
         VT v[4];
+        IT out[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const uint32_t off = sizeof(IT) == 1 ? (word_of(o, 0) >> (8 * i)) & 0xffu
                                                  : (word_of(o, i >> 1) >> (16 * (i & 1))) & 0xffffu;
             v[i] = value(4 * s + i, off);
+            if constexpr (OFFSETS != kPositions) out[i] = offset(4 * s + i, off);
         }
+        if constexpr (OFFSETS != kPositions) __builtin_memcpy(&o, out, sizeof(o));
         Quad vq;
         __builtin_memcpy(&vq, v, sizeof(vq));
         reinterpret_cast<Quad*>(vout)[s] = vq;
@@ -376,16 +423,17 @@ __global__ __launch_bounds__(kWave * kPruneWaves) void prune_pack_kernel(PruneAr
     for (int s = 4 * quads + lane; s < n_out; s += kWave) {
         const uint32_t off = out_i[s];
         vout[s] = value(s, off);
-        iout[s] = (IT)off;
+        iout[s] = offset(s, off);
     }
 }
 
-template <typename VT, typename IT, int LPB, int NE, LaneLayout LAYOUT>
-int prune_launch_one(PruneArgs a, hipStream_t st) {
+template <typename VT, typename IT, int LPB, int NE, LaneLayout LAYOUT, Offsets OFFSETS>
+int prune_launch_kernel(PruneArgs a, hipStream_t st) {
     constexpr int BPW = kWave / LPB, S = sizeof(VT);
     // the banks, and what the last lane's fixed-size read may reach past them
     a.raw_bytes = (BPW * a.B * S + (LAYOUT == kAligned ? 0 : (LPB * a.C - a.B + NE) * S) + 15) / 16 * 16;
-    a.wave_bytes = (a.raw_bytes + BPW * a.k * (int)sizeof(IT) + 255) / 256 * 256;
+    a.stored_at = (a.raw_bytes + BPW * a.k * (int)sizeof(IT) + 15) / 16 * 16;
+    a.wave_bytes = (a.stored_at + (OFFSETS == kStoredInLds ? BPW * a.B : 0) + 255) / 256 * 256;
     int waves = kPruneWaves;
     while (waves * a.wave_bytes > 48 * 1024) waves >>= 1;   // at most 24.5 KB per wavefront
     const int64_t groups = (a.n_banks + BPW - 1) / BPW;
@@ -393,9 +441,19 @@ int prune_launch_one(PruneArgs a, hipStream_t st) {
     const int64_t gx = wgs < ((int64_t)1 << 20) ? wgs : ((int64_t)1 << 20);
     const int64_t gy = (wgs + gx - 1) / gx;
     if (gy > 65535) return BS_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((prune_pack_kernel<VT, IT, LPB, NE, LAYOUT>), dim3((unsigned)gx, (unsigned)gy),
+    hipLaunchKernelGGL((prune_pack_kernel<VT, IT, LPB, NE, LAYOUT, OFFSETS>), dim3((unsigned)gx, (unsigned)gy),
                        dim3(kWave * waves), (size_t)waves * a.wave_bytes, st, a);
     return hip_status(hipGetLastError());
+}
+
+template <typename VT, typename IT, int LPB, int NE, LaneLayout LAYOUT>
+int prune_launch_one(const PruneArgs& a, hipStream_t st) {
+    if constexpr (sizeof(IT) == 1) {
+        if (a.remap && kWave / LPB * a.k <= kFewOutputs)
+            return prune_launch_kernel<VT, IT, LPB, NE, LAYOUT, kStored>(a, st);
+        if (a.remap) return prune_launch_kernel<VT, IT, LPB, NE, LAYOUT, kStoredInLds>(a, st);
+    }
+    return prune_launch_kernel<VT, IT, LPB, NE, LAYOUT, kPositions>(a, st);
 }
 
 template <typename VT, typename IT, int LPB, int NE>
@@ -421,7 +479,7 @@ int prune_banks(const void* W, int64_t n_banks, int bank, int k, void* vals, IT*
     a.W = W; a.vals = vals; a.idx = idx; a.remap = remap;
     a.n_banks = n_banks; a.B = bank; a.k = k;
     a.magic_k = magic_u32((uint32_t)k);
-    a.raw_bytes = a.wave_bytes = 0;
+    a.raw_bytes = a.stored_at = a.wave_bytes = 0;
     int lpb = 1;
     while (lpb < 32 && (bank + lpb - 1) / lpb > 32) lpb <<= 1;
     a.C = (bank + lpb - 1) / lpb;

@@ -38,3 +38,24 @@ def test_prune_pack_layout_edges(bank, dtype):
                 v_ref, i_ref = bs_ref.prune_pack(W, bank, k, wide=wide)
                 assert i.cpu().numpy().tobytes() == i_ref.tobytes(), (kind, rows, nb, k)
                 assert v.cpu().numpy().tobytes() == v_ref.tobytes(), (kind, rows, nb, k)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("k", [1, 3, 16, 32, 33, 64, 100, 128, 129, 131, 255, 256])
+def test_reprune_edges(k, dtype):
+    """bs_reprune where the way to the stored offsets changes: survivors of a wavefront around one
+    and four per lane, stored offsets in whole 16-byte pieces or not, last groups that end inside
+    a piece."""
+    lanes = next(n for n in (1, 2, 4, 8) if k <= 32 * n)
+    per_wave = 64 // lanes
+    bank = min(256, 2 * k)
+    kept = {1, 2, 64 // per_wave, 64 // per_wave + 1, 256 // per_wave, 256 // per_wave + 1, k - 1, k}
+    for rows, nb in ((1, 1), (3, 3), (67, 2)):
+        v, i = bs_ref.prune_pack(_weights("ties" if rows == 3 else "gauss", rows, nb * bank, dtype, k), bank, k)
+        vd, idd = torch.from_numpy(v).to("cuda:0"), torch.from_numpy(i).to("cuda:0")
+        for k2 in sorted(n for n in kept if 1 <= n <= k):
+            print("reprune edges", k, dtype, rows, nb, k2, flush=True)
+            v2, i2 = bs.bs_reprune(vd, idd, bank, k2)
+            v_ref, i_ref = bs_ref.reprune(v, i, k2)
+            assert i2.cpu().numpy().tobytes() == i_ref.tobytes(), (rows, nb, k2)
+            assert v2.cpu().numpy().tobytes() == v_ref.tobytes(), (rows, nb, k2)
