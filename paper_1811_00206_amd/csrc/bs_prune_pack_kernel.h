@@ -458,8 +458,8 @@ int prune_launch_one(const PruneArgs& a, hipStream_t st) {
 
 template <typename VT, typename IT, int LPB, int NE>
 int prune_launch_layout(const PruneArgs& a, hipStream_t st) {
-    if (a.B == LPB * a.C && a.C == NE && NE * sizeof(VT) >= 64)
-        return prune_launch_one<VT, IT, LPB, NE, kAligned>(a, st);
+    if constexpr (NE * sizeof(VT) >= 64)
+        if (a.B == LPB * a.C && a.C == NE) return prune_launch_one<VT, IT, LPB, NE, kAligned>(a, st);
     if constexpr (sizeof(VT) == 2 && sizeof(IT) == 1)   // wide banks are whole 16-byte pieces
         if (a.B % 2 != 0) return prune_launch_one<VT, IT, LPB, NE, kHalves>(a, st);
     return prune_launch_one<VT, IT, LPB, NE, kWords>(a, st);

@@ -19,6 +19,7 @@ import pytest
 
 from paper_1811_00206_amd import build as bs_build
 
+PRUNE_SOURCES = ["bs_prune_pack.hip", "bs_prune_pack_wide.hip"]
 SOURCES = ["bs_spmv_f32.hip", "bs_spmv_f16.hip", "bs_spmm_f32.hip", "bs_spmm_f16.hip",
            "bs_spmm_rows.hip", "bs_spmv_slab.hip", "bs_spmv_wide.hip", "bs_spmm_wide.hip"]
 
@@ -123,3 +124,43 @@ def test_no_kernel_spills_registers(texts):
         for m in re.finditer(r"\.private_segment_fixed_size:\s+(\d+)", t):
             assert int(m.group(1)) == 0, "a kernel uses scratch memory"
     assert n > 0
+
+
+@pytest.fixture(scope="module")
+def prune_texts():
+    with ThreadPoolExecutor(2) as ex:
+        return list(ex.map(_assembly, PRUNE_SOURCES))
+
+
+def test_prune_kernels_wait_for_their_copies(prune_texts):
+    """A wavefront of the prune kernels copies its banks (re-pruning: the stored offsets too) to LDS
+    with direct-to-LDS loads and is the only one that reads them: nothing may be read from LDS
+    between such loads and a wait for all of them."""
+    n = 0
+    for text in prune_texts:
+        name, pending = None, False
+        for line in text.splitlines():
+            m = re.match(r"^(_ZN2bs\w*prune_pack_kernel\w+):", line)
+            s = line.strip()
+            if m:
+                name, pending, copies = m.group(1), False, 0
+            elif name is None:
+                continue
+            elif s.startswith("s_endpgm") or s.startswith(".Lfunc_end"):
+                if s.startswith(".Lfunc_end"):
+                    assert copies > 0, f"{name}: no direct-to-LDS load"
+                    n += 1
+                    name = None
+            elif s.startswith("global_load_lds"):
+                pending, copies = True, copies + 1
+            elif s.startswith("s_waitcnt") and "vmcnt(0)" in s:
+                pending = False
+            elif s.startswith("ds_read"):
+                assert not pending, f"{name}: LDS is read before the copies have landed"
+    # byte offsets: 5 lane shapes in 3 layouts (binary16, whose smallest cannot be an aligned one)
+    # and 2 (fp32), each for pruning and for re-pruning in two forms; 16-bit offsets: 8 lane shapes in 2 layouts
+    assert n == (5 * 3 - 1 + 5 * 2) * 3 + (8 * 2 - 1) + 8 * 2
+
+
+def test_no_prune_kernel_spills_registers(prune_texts):
+    test_no_kernel_spills_registers(prune_texts)
