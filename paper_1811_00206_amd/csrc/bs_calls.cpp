@@ -77,8 +77,8 @@ int64_t row_pitch(const at::Tensor& t) {
     return ld < n ? -1 : ld;
 }
 
-// Gives the interpreter lock up for its lifetime; a destructor, since tensors without memory
-// (fake ones, those of a transform) throw when their address is asked for.
+// Gives the interpreter lock up for its lifetime; a destructor, since what runs without it may
+// throw: allocations, and tensors of a transform when their address is asked for.
 struct WithoutLock {
     PyThreadState* state = PyEval_SaveThread();
     ~WithoutLock() { PyEval_RestoreThread(state); }

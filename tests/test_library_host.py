@@ -235,19 +235,3 @@ def test_spmv_plan_invariants_on_the_paper_shapes_and_random_ones():
         b.bs_spmv_plan(b.BS_F32, 70, 65536, 256, 16, 64, 4)
     with pytest.raises(b.BsError):
         b.bs_spmv_plan(b.BS_F32, 64, 256, 64, 16, 3, 0)        # lanes per row not a power of two
-
-
-def test_tensors_without_memory_raise():
-    """A call on tensors that have no memory ends in an exception (which has to be raised with
-    the interpreter lock held), as every other bad argument does."""
-    torch = pytest.importorskip("torch")
-    from torch._subclasses.fake_tensor import FakeTensorMode
-    from paper_1811_00206_amd import binding as bs
-    bs.load_library()
-    with FakeTensorMode():
-        v, x = torch.empty((8, 4, 4), device="cuda"), torch.empty(64, device="cuda")
-        i = torch.empty((8, 4, 4), device="cuda", dtype=torch.uint8)
-        for call in (lambda: bs.bs_spmv(v, i, 16, x), lambda: bs.bs_spmm(v, i, 16, x.view(64, 1)),
-                     lambda: bs.bs_prune_pack(x.view(4, 16), 16, 4), lambda: bs.bs_reprune(v, i, 16, 2)):
-            with pytest.raises(RuntimeError):
-                call()

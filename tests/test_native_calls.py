@@ -47,16 +47,16 @@ Tensor empty_memory_format::call(c10::SymIntArrayRef size, ::std::optional<Scala
 
 extern "C" {
 int attempts = 0, status = BS_ERR_HIP;   // of every call but the sequence
-#define CALL { ++attempts; return status; }
-int bs_spmv(const void*, const uint8_t*, int, int64_t, int64_t, int, int, const float*, float*, void*) CALL
-int bs_spmv_wide(const void*, const uint16_t*, int, int64_t, int64_t, int, int, const float*, float*, void*) CALL
-int bs_spmm(const void*, const uint8_t*, int, int64_t, int64_t, int, int, const float*, int64_t, int64_t, float*,
+#define CALL { ++attempts; return first ? status : BS_ERR_NULL; }
+int bs_spmv(const void* first, const uint8_t*, int, int64_t, int64_t, int, int, const float*, float*, void*) CALL
+int bs_spmv_wide(const void* first, const uint16_t*, int, int64_t, int64_t, int, int, const float*, float*, void*) CALL
+int bs_spmm(const void* first, const uint8_t*, int, int64_t, int64_t, int, int, const float*, int64_t, int64_t, float*,
             int64_t, void*, size_t, void*) CALL
-int bs_spmm_wide(const void*, const uint16_t*, int, int64_t, int64_t, int, int, const float*, int64_t, int64_t, float*,
+int bs_spmm_wide(const void* first, const uint16_t*, int, int64_t, int64_t, int, int, const float*, int64_t, int64_t, float*,
                  int64_t, void*, size_t, void*) CALL
-int bs_prune_pack(const void*, int, int64_t, int64_t, int, int, void*, uint8_t*, void*) CALL
-int bs_prune_pack_wide(const void*, int, int64_t, int64_t, int, int, void*, uint16_t*, void*) CALL
-int bs_reprune(const void*, const uint8_t*, int, int64_t, int64_t, int, int, int, void*, uint8_t*, void*) CALL
+int bs_prune_pack(const void* first, int, int64_t, int64_t, int, int, void*, uint8_t*, void*) CALL
+int bs_prune_pack_wide(const void* first, int, int64_t, int64_t, int, int, void*, uint16_t*, void*) CALL
+int bs_reprune(const void* first, const uint8_t*, int, int64_t, int64_t, int, int, int, void*, uint8_t*, void*) CALL
 // advances the cell state step by step; the first attempt fails at its second step
 int bs_lstm_sequence(const void*, const uint8_t*, int, int64_t, int64_t, int, int, const float*, int64_t T,
                      const float*, const float*, float* c, float*, void*) {
@@ -274,4 +274,54 @@ def test_a_workspace_in_host_memory_is_refused(stand_in):
                     else:
                         assert not need
                     assert attempts.value == (0 if need else 1)
+    """)
+
+
+def test_tensors_without_memory_raise(stand_in):
+    """Tensors of a transform have no address to ask for and raise, with the interpreter lock held;
+    fake ones have a null one, which the library refuses."""
+    _run(stand_in, """
+        import warnings
+        from torch._subclasses.fake_tensor import FakeTensorMode
+        warnings.simplefilter("ignore")      # torch's own, about addresses of fake tensors
+        M, bank, nb, k, N = 8, 16, 4, 4, 3
+        K, H, T = nb * bank, M // 4, 3
+        i, iw = gpu(M, nb, k, dtype=torch.uint8), gpu(M, nb, k, dtype=torch.uint16)
+
+        def calls(v, x, X, W, Xs, h, b):
+            y, Y, out = gpu(M), gpu(M, N), (gpu(M, nb, k), i)
+            return {"bs_spmv": lambda: bs.bs_spmv(v, i, bank, x, out=y),
+                    "bs_spmv_wide": lambda: bs.bs_spmv_wide(v, iw, bank, x, out=y),
+                    "bs_spmm": lambda: bs.bs_spmm(v, i, bank, X, out=Y),
+                    "bs_prune_pack": lambda: bs.bs_prune_pack(W, bank, k, out=out),
+                    "bs_reprune": lambda: bs.bs_reprune(v, i, bank, k, out=out),
+                    "bs_lstm_sequence": lambda: bs.bs_lstm_sequence(v, i, bank, Xs, h, b, h, H_all=gpu(T, H))}
+
+        sizes = ((M, nb, k), (K,), (K, N), (M, K), (T, K - H), (H,), (M,))
+        refused = {}
+
+        def of_a_transform(*tensors):
+            for name, f in calls(*tensors).items():
+                try:
+                    f()
+                except RuntimeError as e:
+                    refused[name] = str(e)
+            return tensors[0]
+
+        torch.func.vmap(of_a_transform)(*(gpu(2, *s) for s in sizes))
+        assert len(refused) == 6 and all("data pointer" in e for e in refused.values()), refused
+        assert attempts.value == 0
+
+        with FakeTensorMode():
+            fake = [torch.empty(s, device="cuda") for s in sizes]
+        for name, f in calls(*fake).items():
+            if name == "bs_lstm_sequence":    # the stand-in's takes no notice of its pointers
+                continue
+            attempts.value = 0
+            try:
+                f()
+            except bs.BsError as e:
+                assert e.status == 1 and attempts.value == 1, (name, e, attempts.value)
+            else:
+                raise AssertionError(name + ": no error")
     """)
