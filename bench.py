@@ -391,9 +391,9 @@ def main():
     from paper_1811_00206_amd import probe
     from paper_1811_00206_amd import workloads
 
-    if not os.path.exists(bs.library_path()) or not os.path.exists(probe.library_path()):
-        from paper_1811_00206_amd.build import build_library
-        build_library()
+    from paper_1811_00206_amd import build as bs_build
+    if not bs_build.is_built() or not os.path.exists(probe.library_path()):
+        bs_build.build_library()
     if not torch.cuda.is_available():
         print("bench.py: no GPU visible", file=sys.stderr)
         return 2

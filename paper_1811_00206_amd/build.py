@@ -36,6 +36,11 @@ FLAGS = [
 ]
 
 
+def is_built() -> bool:
+    """Whether what the calls load is there: the library and the native marshalling beside it."""
+    return os.path.exists(LIB) and os.path.exists(NATIVE_LIB)
+
+
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 

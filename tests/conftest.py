@@ -16,7 +16,7 @@ def pytest_configure(config):
 def _native_library():
     """Use the library that is built; build it only if there is none."""
     from paper_1811_00206_amd import binding
-    if not os.path.exists(binding.library_path()):
-        from paper_1811_00206_amd.build import build_library
-        build_library()
+    from paper_1811_00206_amd import build as bs_build
+    if not bs_build.is_built():
+        bs_build.build_library()
     return binding.load_library()

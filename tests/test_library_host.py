@@ -235,3 +235,14 @@ def test_spmv_plan_invariants_on_the_paper_shapes_and_random_ones():
         b.bs_spmv_plan(b.BS_F32, 70, 65536, 256, 16, 64, 4)
     with pytest.raises(b.BsError):
         b.bs_spmv_plan(b.BS_F32, 64, 256, 64, 16, 3, 0)        # lanes per row not a power of two
+
+
+def test_built_means_everything_a_call_loads(tmp_path, monkeypatch):
+    """smoke(), the tests and the benchmark build when either library is missing."""
+    from paper_1811_00206_amd import build
+    there = tmp_path / "lib.so"
+    there.write_bytes(b"")
+    for lib, native, built in ((there, there, True), (there, tmp_path / "no.so", False), (tmp_path / "no.so", there, False)):
+        monkeypatch.setattr(build, "LIB", str(lib))
+        monkeypatch.setattr(build, "NATIVE_LIB", str(native))
+        assert build.is_built() is built
