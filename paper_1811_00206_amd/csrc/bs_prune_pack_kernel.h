@@ -15,8 +15,9 @@
 // element tied with the threshold; counting keeps exactly k instead.
 //
 // LPB lanes share a bank, each owning C consecutive elements of it (C <= 32, 64 in banks over
-// 1024), so a wavefront works on 64/LPB banks at once.  What bounds this kernel is the vector ALU
-// until it gets below the stream of W, so every step is built to touch an element few times:
+// 1024), so a wavefront works on 64/LPB banks at once.  Two things bound this kernel: the stream of
+// W and the vector ALU, which overlap only across the wavefronts that are resident (a wavefront
+// copies, waits, then selects), so every step is built to touch an element few times:
 //   * the wavefront's banks are one contiguous piece of W; it goes to LDS with
 //     direct-to-LDS loads (no registers) and stays there, so that a kept value is fetched
 //     by its offset at the very end and nothing else carries values around;
@@ -33,10 +34,11 @@
 //     gathered from LDS through the offsets just written.
 // Measured (MI355X, back to back over three matrices), before and now; before, 16-byte pieces
 // striped over the lanes were transposed whole and every element was written or sent to a
-// trash slot: 6000 x 3000 fp32, 10 of 100 kept: 22.4 -> 16.8 us (4.8 TB/s of W, vals and idx;
-// a large copy runs at 4.7); 4096 x 25088 binary16, 6 of 64: 62.9 -> 46.6 us (5.0 TB/s);
-// 11908 x 7616 binary16, 18 of 64: 63.5 -> 52.7 us.  Vector instructions on the first: 12.9 M
-// -> 7.1 M.
+// trash slot: 6000 x 3000 fp32, 10 of 100 kept: 22.4 -> 16.8 us (4.8 TB/s of W, vals and idx);
+// 4096 x 25088 binary16, 6 of 64: 62.9 -> 46.6 us (5.0 TB/s); 11908 x 7616 binary16, 18 of 64:
+// 63.5 -> 52.7 us.  Vector instructions on the first: 12.9 M -> 6.6 M, 585 per wavefront, 11
+// wavefronts per SIMD: 10.7 of the 16.8 us; its bytes alone take 13.3 us at the 6.1 TB/s at which
+// a product streams weights here.
 // Re-pruning a packed matrix to fewer weights per bank (one more round of
 // Algorithm 1's loop) runs the same kernel on the stored values, k per bank: 10 -> 5 of 100 on the
 // 6000 x 3000 matrix 7.9 us (9.6 with one byte fetched per lane and step, 9.5 with the kernel before
