@@ -18,7 +18,7 @@ int raise_on_current_device(LdsKernel& k, uint64_t bit) {
 }
 }  // namespace
 
-int ensure_lds_limit(LdsKernel& k, hipStream_t st) {
+int ensure_lds_limit(LdsKernel& k, hipStream_t st, LdsKernel* sibling) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev > 63) return BS_ERR_HIP;
     const uint64_t bit = (uint64_t)1 << dev;
@@ -26,6 +26,10 @@ int ensure_lds_limit(LdsKernel& k, hipStream_t st) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess) return BS_ERR_HIP;
     if (cs != hipStreamCaptureStatusNone) return BS_ERR_NOT_INITIALISED;
+    if (sibling) {
+        const int rc = raise_on_current_device(*sibling, bit);
+        if (rc != BS_OK) return rc;
+    }
     return raise_on_current_device(k, bit);
 }
 

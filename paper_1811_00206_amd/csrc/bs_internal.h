@@ -85,8 +85,9 @@ LdsKernel LdsKernelOf<KERNEL>::reg{reinterpret_cast<const void*>(KERNEL)};
 
 // BS_OK when the kernel's limit is raised on the current device.  The limit is never
 // changed while `st` is being captured: BS_ERR_NOT_INITIALISED then (call bs_init() on
-// this device first, or make the first call outside the capture).
-int ensure_lds_limit(LdsKernel& k, hipStream_t st);
+// this device first, or make the first call outside the capture).  `sibling`: a kernel that the
+// same shape is launched as for another operand; the first launch of either prepares both.
+int ensure_lds_limit(LdsKernel& k, hipStream_t st, LdsKernel* sibling = nullptr);
 // raises every registered kernel's limit on the current device (bs_init)
 int init_current_device();
 

@@ -385,10 +385,10 @@ __global__ __launch_bounds__(1024) void spmm_few_kernel(SpmmArgs a) {
     spmm_body<VT, CH, LPR, U, Q, IT, true>(a);
 }
 
-template <auto KERNEL>
+template <auto KERNEL, auto SIBLING>
 int spmm_launch_kernel(const SpmmArgs& a, const SpmmLaunch& l) {
     if (l.lds > 48 * 1024) {
-        const int st_code = ensure_lds_limit(LdsKernelOf<KERNEL>::reg, l.st);
+        const int st_code = ensure_lds_limit(LdsKernelOf<KERNEL>::reg, l.st, &LdsKernelOf<SIBLING>::reg);
         if (st_code != BS_OK) return st_code;
     }
     hipLaunchKernelGGL(KERNEL, dim3(a.wgs_per_xcd * kXcds), dim3(l.threads), l.lds, l.st, a);
@@ -397,8 +397,9 @@ int spmm_launch_kernel(const SpmmArgs& a, const SpmmLaunch& l) {
 
 template <typename VT, int CH, int LPR, int U, int Q, typename IT = uint8_t>
 int spmm_launch_one(const SpmmArgs& a, const SpmmLaunch& l) {
-    if (a.copy == kCopyRegisters) return spmm_launch_kernel<spmm_few_kernel<VT, CH, LPR, U, Q, IT>>(a, l);
-    return spmm_launch_kernel<spmm_kernel<VT, CH, LPR, U, Q, IT>>(a, l);
+    constexpr auto kern = spmm_kernel<VT, CH, LPR, U, Q, IT>;
+    constexpr auto few = spmm_few_kernel<VT, CH, LPR, U, Q, IT>;
+    return a.copy == kCopyRegisters ? spmm_launch_kernel<few, kern>(a, l) : spmm_launch_kernel<kern, few>(a, l);
 }
 
 template <typename VT, int CH, int LPR, int U>

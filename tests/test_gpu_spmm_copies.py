@@ -53,3 +53,36 @@ def test_few_columns(bank, k, M, nb, N):
         # as above
         bound = (nb * k + 1) * 2.0 ** -24 * (dense.abs() @ x.abs())
         assert ((spmm(v, i, bank, X).cpu().double() - dense @ x).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("first,captured", [(4, 2), (2, 4)])
+def test_a_first_product_prepares_the_capture_of_another_width(first, captured):
+    """One to three columns run in a kernel of their own.  A product outside a capture prepares
+    both kernels of its shape, as it did when there was one.  Run in a fresh process."""
+    import pathlib
+    import subprocess
+    import sys
+    code = f"""
+import torch
+from paper_1811_00206_amd import binding as bs
+W = torch.randn((300, 4096), device="cuda")
+v, i = bs.bs_prune_pack(W, 64, 6)
+X = {{n: torch.randn((4096, n), device="cuda") for n in (2, 4)}}
+p = {{n: bs.bs_spmm_plan(bs.BS_F32, 300, 4096, 64, 6, n) for n in (2, 4)}}
+assert p[2]["lds_bytes"] > 48 * 1024 and all(p[2][f] == p[4][f] for f in ("ch", "lpr", "u", "rows_kernel"))
+bs.bs_spmm(v, i, 64, X[{first}])
+torch.cuda.synchronize()
+Y = torch.empty((300, {captured}), device="cuda")
+g = torch.cuda.CUDAGraph()
+with torch.cuda.graph(g):
+    bs.bs_spmm(v, i, 64, X[{captured}], out=Y)
+Y.zero_()
+g.replay()
+torch.cuda.synchronize()
+assert torch.equal(Y, bs.bs_spmm(v, i, 64, X[{captured}]))
+print("RESULT captured")
+"""
+    print("capture after another width", first, captured, flush=True)
+    out = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100,
+                         cwd=str(pathlib.Path(__file__).resolve().parent.parent))
+    assert out.returncode == 0 and "RESULT captured" in out.stdout, out.stdout + out.stderr[-2000:]
