@@ -115,6 +115,7 @@ __device__ __forceinline__ void select_byte(Select<NM>& t, const uint32_t (&w)[N
 #pragma unroll
         for (int g = 0; g < 8; ++g) {   // bytes of elements 32m + {g, 8+g, 16+g, 24+g}
             const int e = 32 * m + g;
+            if (e >= NE) { q[m][g] = 0u; continue; }
             const uint32_t u = __builtin_amdgcn_perm(w[e + 8 < NE ? e + 8 : e], w[e], e + 8 < NE ? kPair : 0x0c0c0c00u | BYTE);
             uint32_t v = 0u;
             if (e + 16 < NE) v = __builtin_amdgcn_perm(w[e + 24 < NE ? e + 24 : e + 16], w[e + 16],
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(kWave * kPruneWaves) void prune_pack_kernel(PruneAr
     constexpr int NW = NE * S / 4;                // words of a lane's elements
     constexpr int BPW = kWave / LPB;              // banks per wavefront
     constexpr int PPL = NE * S / 16;              // kAligned: 16-byte pieces per lane
-    static_assert(NE <= 64 && NE % 16 == 0, "lane shape");
+    static_assert(NE <= 64 && (NE % 16 == 0 || (NE == 4 && S == 4)), "lane shape");
     extern __shared__ __align__(256) unsigned char pp_shared[];
 
     const int lane = threadIdx.x & (kWave - 1);
@@ -489,6 +490,10 @@ int prune_banks(const void* W, int64_t n_banks, int bank, int k, void* vals, IT*
     if (a.C > 64) return BS_ERR_UNSUPPORTED;
     switch (lpb) {
         case 1:
+            // up to four fp32: half the transpose of each byte is of zeros and goes (3627 x 1024,
+            // 1 of 4, ties, so that all four bytes are looked at: 20.4 -> 16.7 us)
+            if constexpr (sizeof(VT) == 4)
+                if (a.C <= 4) return prune_launch_layout<VT, IT, 1, 4>(a, st);
             if (a.C <= 16) return prune_launch_layout<VT, IT, 1, 16>(a, st);
             return prune_launch_layout<VT, IT, 1, 32>(a, st);
         case 2: return prune_launch_layout<VT, IT, 2, 32>(a, st);

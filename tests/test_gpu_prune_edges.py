@@ -41,7 +41,22 @@ def test_prune_pack_layout_edges(bank, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
-@pytest.mark.parametrize("k", [1, 3, 16, 32, 33, 64, 100, 128, 129, 131, 255, 256])
+@pytest.mark.parametrize("bank", [3, 4, 5])
+def test_prune_pack_smallest_banks(bank, dtype):
+    """Around the four elements up to which fp32 lanes have a kernel of their own; four, the
+    smallest whole piece, with 16-bit offsets too."""
+    test_prune_pack_layout_edges(bank, dtype)
+    if bank == 4 and dtype == "f32":
+        for kind in ("gauss", "ties", "low_bits"):
+            for k in (1, 2, 4):
+                W = _weights(kind, 67, 5 * bank, dtype, k)
+                v, i = bs.bs_prune_pack_wide(torch.from_numpy(W).to("cuda:0"), bank, k)
+                v_ref, i_ref = bs_ref.prune_pack(W, bank, k, wide=True)
+                assert i.cpu().numpy().tobytes() == i_ref.tobytes() and v.cpu().numpy().tobytes() == v_ref.tobytes()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("k", [1, 3, 4, 5, 16, 32, 33, 64, 100, 128, 129, 131, 255, 256])
 def test_reprune_edges(k, dtype):
     """bs_reprune where the way to the stored offsets changes: survivors of a wavefront around one
     and four per lane, stored offsets in whole 16-byte pieces or not, last groups that end inside

@@ -157,9 +157,10 @@ def test_prune_kernels_wait_for_their_copies(prune_texts):
                 pending = False
             elif s.startswith("ds_read"):
                 assert not pending, f"{name}: LDS is read before the copies have landed"
-    # byte offsets: 5 lane shapes in 3 layouts (binary16, whose smallest cannot be an aligned one)
-    # and 2 (fp32), each for pruning and for re-pruning in two forms; 16-bit offsets: 8 lane shapes in 2 layouts
-    assert n == (5 * 3 - 1 + 5 * 2) * 3 + (8 * 2 - 1) + 8 * 2
+    # byte offsets: 5 lane shapes of binary16 in 3 layouts and 6 of fp32 in 2 (the smallest of either
+    # type cannot be an aligned one), each for pruning and for re-pruning in two forms; 16-bit
+    # offsets: 8 and 9 lane shapes in 2 layouts
+    assert n == (5 * 3 - 1 + 6 * 2 - 1) * 3 + (8 * 2 - 1) + (9 * 2 - 1)
 
 
 def test_no_prune_kernel_spills_registers(prune_texts):
