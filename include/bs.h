@@ -181,7 +181,7 @@ size_t bs_spmm_workspace_bytes(int dtype, int64_t M, int64_t K, int bank, int k,
 /*
  * The launch bs_spmm would make for this shape, for tests and tuning (host only, no GPU
  * call; the tiling itself is ours, the paper gives none for a batch).  Writes up to n_out
- * of these 17 values to out (HOST):
+ * of these 30 values to out (HOST):
  *   [0] kernel: 0 chunk walk (LPR lanes per row and column group), 1 one lane per row and
  *       column group          [1] entries per 16-byte chunk
  *   [2] column groups of 4 per tile (nl)   [3] columns per tile   [4] column tiles
@@ -191,6 +191,13 @@ size_t bs_spmm_workspace_bytes(int dtype, int64_t M, int64_t K, int bank, int k,
  *   [13] LDS bytes per workgroup            [14] workgroups launched
  *   [15] float index of the position table in LDS
  *   [16] threads per workgroup (for ldx = N): those of [9] and any that only copy X
+ *   [17] 1 if the product is left to the kernels that walk K in stages (for ldx = N); [0] to
+ *       [16] then still fix the workspace, and apply to a first use inside a capture
+ *   [18] column tiles   [19] K slabs   [20] banks per slab   [21] banks per stage
+ *   [22] stages held in LDS at once (1 or 2)   [23] LDS bytes of one
+ *   [24] rows per workgroup   [25] row groups   [26] groups of wavefronts along K
+ *   [27] wavefronts per such group   [28] wavefronts that copy X   [29] LDS bytes per workgroup
+ *       (18 to 29 are 0 where [17] is and the shape was not looked at)
  * Returns BS_OK, or the status bs_spmm would return for an unsupported shape.
  */
 int bs_spmm_plan(int dtype, int64_t M, int64_t K, int bank, int k, int64_t N,

@@ -205,7 +205,9 @@ def bs_spmv_plan(dtype: int, M: int, K: int, bank: int, k: int, lanes_per_row: i
 
 
 SPMM_PLAN_FIELDS = ("rows_kernel", "ch", "nl", "nt", "n_tiles", "sb", "n_slabs", "lpr", "u", "threads",
-                    "rows_per_wg", "row_groups", "n_passes", "lds_bytes", "workgroups", "table_off", "wg_threads")
+                    "rows_per_wg", "row_groups", "n_passes", "lds_bytes", "workgroups", "table_off", "wg_threads",
+                    "stages", "stage_tiles", "stage_slabs", "stage_slab_banks", "stage_banks", "stage_bufs", "stage_buf_bytes",
+                    "stage_rows_per_wg", "stage_row_groups", "stage_ksplit", "stage_row_waves", "stage_copy_waves", "stage_lds_bytes")
 
 
 def bs_spmm_plan(dtype: int, M: int, K: int, bank: int, k: int, N: int) -> dict:

@@ -1,8 +1,10 @@
 // Host side of bs_spmm: tiling plan, launch, and the kernel that adds slab
 // partial sums (see bs_spmm_kernel.h for the design of the main kernel).
 #include <algorithm>
+#include <cmath>
 
 #include "bs_spmm_rows_kernel.h"
+#include "bs_spmm_stream_kernel.h"
 
 namespace bs {
 namespace {
@@ -173,6 +175,44 @@ SpmmPlan make_plan(int dtype, int64_t M, int64_t K, int bank, int k, int64_t N, 
     return best;
 }
 
+// What the tile kernels are expected to take for a plan of more than 8 columns, in ns, the slab sums included:
+// a fit to 442 random products on MI355X (median error 5 %, 9 % rms).
+double tiles_ns(const SpmmPlan& p, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, SpmmCopy copy) {
+    const int threads = launched_threads(p, copy);
+    const int64_t wgs = (int64_t)p.n_tiles * p.n_slabs * p.row_groups, nb = K / bank;
+    const double per_cu = (double)std::max<int64_t>(1, std::min<int64_t>({(int64_t)(kMaxLdsBytes / p.lds_bytes), 1024 / threads, (wgs + kCus - 1) / kCus}));
+    const double rounds = std::ceil(wgs / (kCus * per_cu)), walkers = p.row_threads / 64.0 * per_cu;
+    const int64_t run = std::min<int64_t>(p.sb, nb) * k;      // entries of a row inside a slab
+    const int rows_per_pass = p.row_threads / (p.nl * p.lpr);
+    double pass;
+    if (p.rows) {
+        pass = run * std::max(14.2, 3.68 * walkers) + 530 * std::ceil(run / (16.0 * p.ch)) + 223;
+        pass *= (p.ch == 2 ? 0.94 : p.ch == 1 ? 0.9 : 1.0) * (vsize == 2 ? 1.07 : 1.0);
+    } else {
+        const int64_t slots = (run / p.ch + p.lpr - 1) / p.lpr;
+        pass = (slots * p.ch * std::max(41.3, 2.84 * walkers) + 629) * (p.ch <= 2 ? 1.4 : 1.0);
+    }
+    const double tile = 104 + (double)p.tile_bytes * per_cu * (copy == kCopyWide ? 1.0 : 1.37) / std::min(15.0 * threads / 64 * per_cu, 54.2);
+    double t = 2930 + rounds * (tile + (p.rows_per_wg + rows_per_pass - 1) / rows_per_pass * pass);
+    const double w_bytes = (double)M * nb * k * (vsize + isize), y_bytes = 4.0 * M * N;
+    t = std::max(t, 2500 + (w_bytes * std::min(p.n_tiles, 2) + 4.0 * K * N + y_bytes) / 3019);
+    if (p.n_slabs > 1) t += 1920 + 2.0 * p.n_slabs * y_bytes / 4800;
+    return t;
+}
+
+// The stage kernels are taken where they are expected to be faster by more than either expectation is off: over 456
+// random products of 9 to 50 000 columns they were chosen for 215, took 0.67 of the tile kernels' time there and at
+// most 1.07 of it.  Products of a few microseconds are not worth the planning.
+constexpr double kStreamMargin = 0.85, kStreamWorthNs = 6000;
+SpmmStreamPlan stream_choice(const SpmmPlan& p, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int64_t ldx) {
+    if (N <= 8 || k < kStreamMinK) return {};
+    const double tiles = tiles_ns(p, vsize, isize, M, K, bank, k, N, copy_kind(N, ldx));
+    if (tiles <= kStreamWorthNs) return {};
+    SpmmStreamPlan sp = spmm_stream_plan(vsize, isize, M, K, bank, k, N, ldx, p.n_slabs);
+    if (sp.ok && sp.ns >= kStreamMargin * tiles) sp.ok = false;
+    return sp;
+}
+
 // Y[r][n] = sum over slabs, in slab order.  magic_n = magic_u32(N): rows from element
 // numbers without a 64-bit division (M*N < 2^32 is checked by the caller).
 // V = floats per lane and step: 4 when M, N, ldy and Y's address allow 16-byte accesses.
@@ -279,12 +319,15 @@ int spmm_plan_describe(int dtype, int64_t M, int64_t K, int bank, int k, int64_t
     if (total > INT32_MAX / 2) return BS_ERR_UNSUPPORTED;
     if (p.ws_bytes && M * N > (int64_t)UINT32_MAX) return BS_ERR_UNSUPPORTED;
     const int rows_per_pass = p.row_threads / (p.nl * p.lpr);
-    const int64_t v[17] = {p.rows ? 1 : 0, p.ch, p.nl, p.nt, p.n_tiles, p.sb, p.n_slabs, p.lpr, p.u,
+    const SpmmStreamPlan sp = stream_choice(p, dtype == BS_F16 ? 2 : 4, 1, M, K, bank, k, N, N);
+    const int64_t v[30] = {p.rows ? 1 : 0, p.ch, p.nl, p.nt, p.n_tiles, p.sb, p.n_slabs, p.lpr, p.u,
                            p.row_threads, p.rows_per_wg, p.row_groups,
                            (p.rows_per_wg + rows_per_pass - 1) / rows_per_pass,
                            (int64_t)p.lds_bytes, (total + kXcds - 1) / kXcds * kXcds, p.table_off,
-                           launched_threads(p, copy_kind(N, N))};
-    for (int i = 0; i < n_out && i < 17; ++i) out[i] = v[i];
+                           launched_threads(p, copy_kind(N, N)),
+                           sp.ok ? 1 : 0, sp.n_tiles, sp.n_slabs, sp.slab_banks, sp.sb, sp.n_bufs, sp.buf_bytes,
+                           sp.rows_per_wg, sp.row_groups, sp.ksplit, sp.row_waves, sp.copy_waves, (int64_t)sp.lds_bytes};
+    for (int i = 0; i < n_out && i < 30; ++i) out[i] = v[i];
     return BS_OK;
 }
 
@@ -324,13 +367,35 @@ int launch_spmm_any(const void* vals, const void* idx, int isize, int dtype, int
     a.n_passes = (p.rows_per_wg + rows_per_pass - 1) / rows_per_pass;
     a.vec_out = (a.ld_out % 4 == 0 && a.slab_stride % 4 == 0 && (uintptr_t)a.out % 16 == 0) ? 1 : 0;
 
-    const SpmmLaunch l{launched_threads(p, copy_kind(N, ldx)), p.lds_bytes, st};
-    int st_code = isize == 2 ? spmm_launch_wide(dtype, p.rows, p.ch, p.lpr, p.u, a, l)
-                  : p.rows ? spmm_rows_launch(dtype, p.ch, a, l)
-                  : dtype == BS_F16 ? spmm_launch_f16(p.ch, p.lpr, p.u, p.q, a, l)
-                                    : spmm_launch_f32(p.ch, p.lpr, p.u, p.q, a, l);
+    auto tiles = [&](bool prepare_only) {
+        const SpmmLaunch l{launched_threads(p, copy_kind(N, ldx)), p.lds_bytes, st, prepare_only};
+        return isize == 2 ? spmm_launch_wide(dtype, p.rows, p.ch, p.lpr, p.u, a, l)
+               : p.rows ? spmm_rows_launch(dtype, p.ch, a, l)
+               : dtype == BS_F16 ? spmm_launch_f16(p.ch, p.lpr, p.u, p.q, a, l)
+                                 : spmm_launch_f32(p.ch, p.lpr, p.u, p.q, a, l);
+    };
+    int n_slabs = p.n_slabs, st_code = BS_ERR_NOT_INITIALISED;
+    const SpmmStreamPlan sp = stream_choice(p, dtype == BS_F16 ? 2 : 4, isize, M, K, bank, k, N, ldx);
+    if (sp.ok) {
+        SpmmArgs t = a;
+        if (sp.n_slabs == 1 && p.n_slabs > 1) {
+            t.out = Y; t.ld_out = ldy; t.slab_stride = 0;
+            t.vec_out = ldy % 4 == 0 && (uintptr_t)Y % 16 == 0;
+        }
+        // First uses inside a capture: where this kernel is not prepared the tile kernels answer as they
+        // would without it, and a first use of this one outside a capture prepares those too.
+        st_code = spmm_stream_launch(sp, t, dtype, isize, st);
+        if (st_code == BS_OK) {
+            n_slabs = sp.n_slabs;
+            const int prepared = tiles(true);
+            if (prepared != BS_OK && prepared != BS_ERR_NOT_INITIALISED) return prepared;
+        } else if (st_code != BS_ERR_NOT_INITIALISED) {
+            return st_code;
+        }
+    }
+    if (st_code == BS_ERR_NOT_INITIALISED) st_code = tiles(false);
     if (st_code != BS_OK) return st_code;
-    if (p.n_slabs > 1) {
+    if (n_slabs > 1) {
         // 16 bytes per lane where rows of Y and of the workspace allow it (the workspace is
         // 16-byte aligned, its rows are N floats; with rows of Y as long, both are one piece)
         const bool vec = (uintptr_t)Y % 16 == 0 &&
@@ -340,7 +405,7 @@ int launch_spmm_any(const void* vals, const void* idx, int isize, int dtype, int
         if (grid > 256 * 16) grid = 256 * 16;
         auto kern = vec ? spmm_reduce_kernel<4> : spmm_reduce_kernel<1>;
         hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), 0, st,
-                           static_cast<const float*>(workspace), Y, M, N, ldy, p.n_slabs,
+                           static_cast<const float*>(workspace), Y, M, N, ldy, n_slabs,
                            magic_u32((uint32_t)N));
         return hip_status(hipGetLastError());
     }

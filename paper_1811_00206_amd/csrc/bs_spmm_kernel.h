@@ -71,6 +71,7 @@ struct SpmmLaunch {
     int threads;
     size_t lds;
     hipStream_t st;
+    bool prepare_only;     // raise the kernel's LDS limit (where this launch needs it) and return
 };
 
 int spmm_launch_f32(int ch, int lpr, int u, int q, const SpmmArgs& a, const SpmmLaunch& l);
@@ -391,6 +392,7 @@ int spmm_launch_kernel(const SpmmArgs& a, const SpmmLaunch& l) {
         const int st_code = ensure_lds_limit(LdsKernelOf<KERNEL>::reg, l.st, &LdsKernelOf<SIBLING>::reg);
         if (st_code != BS_OK) return st_code;
     }
+    if (l.prepare_only) return BS_OK;
     hipLaunchKernelGGL(KERNEL, dim3(a.wgs_per_xcd * kXcds), dim3(l.threads), l.lds, l.st, a);
     return hip_status(hipGetLastError());
 }

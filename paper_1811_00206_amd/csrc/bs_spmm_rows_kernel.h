@@ -264,6 +264,7 @@ int spmm_rows_launch_one(const SpmmArgs& a, const SpmmLaunch& l) {
         const int st_code = ensure_lds_limit(LdsKernelOf<kern>::reg, l.st);
         if (st_code != BS_OK) return st_code;
     }
+    if (l.prepare_only) return BS_OK;
     hipLaunchKernelGGL(kern, dim3(a.wgs_per_xcd * kXcds), dim3(l.threads), l.lds, l.st, a);
     return hip_status(hipGetLastError());
 }

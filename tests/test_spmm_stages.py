@@ -1,0 +1,150 @@
+"""The launches of the SpMM kernels that walk K in stages, checked on the host: every bank of X copied once to where
+it is read, every bank walked once, the same barriers in every wavefront, LDS within a compute unit's; and the
+generated code of every instantiation."""
+import os
+import random
+import re
+import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
+
+import pytest
+
+from paper_1811_00206_amd import binding as bs
+from paper_1811_00206_amd import build as bs_build
+
+P = 4                        # pieces of 4 columns per tile
+BANKS = 16 // P              # banks side by side in LDS
+
+
+def _copied(p, bank, banks, ragged):
+    """LDS byte -> (row of X, piece) of one stage, as the copying wavefronts write it."""
+    groups = -(-banks // BANKS)
+    spare, quads, wrote = groups * BANKS - banks, (bank + 3) // 4, {}
+    for wave in range(p["stage_copy_waves"]):
+        g, rq = divmod(wave, quads)
+        while g < groups:
+            for lane in range(64):
+                b, c, lrow = (lane & 15) // P, lane & (P - 1), lane >> 4
+                last = 0 if b >= BANKS - spare else bank - 1 if ragged and b == BANKS - spare - 1 else bank
+                if rq * 4 + lrow < (last if g == groups - 1 else bank):
+                    at = (g * bank + rq * 4) * 256 + lane * 16
+                    assert at not in wrote and at + 16 <= p["stage_buf_bytes"]
+                    wrote[at] = ((g * BANKS + b) * bank + rq * 4 + lrow, c)
+            g, rq = g + (rq + p["stage_copy_waves"]) // quads, (rq + p["stage_copy_waves"]) % quads
+    return wrote
+
+
+def _check(p, M, nb, bank, k, N, copies):
+    where = str((M, nb, bank, k, N, p))
+    slab, sb, ks, rows = p["stage_slab_banks"], p["stage_banks"], p["stage_ksplit"], p["stage_rows_per_wg"]
+    assert p["stage_tiles"] * 4 * P >= N > (p["stage_tiles"] - 1) * 4 * P, where
+    assert p["stage_slabs"] * slab >= nb > (p["stage_slabs"] - 1) * slab and p["stage_slabs"] <= p["n_slabs"], where
+    assert p["stage_row_groups"] * rows >= M > (p["stage_row_groups"] - 1) * rows and rows <= 4 * P * p["stage_row_waves"], where
+    assert sb % BANKS == 0 and slab % BANKS == 0 and p["stage_buf_bytes"] == sb * bank * 16 * P, where
+    assert p["stage_bufs"] * p["stage_buf_bytes"] <= p["stage_lds_bytes"] <= 160 * 1024, where
+    assert (ks - 1) * p["stage_row_waves"] * 1024 <= p["stage_lds_bytes"], where
+    assert p["stage_copy_waves"] >= 1 and ks * p["stage_row_waves"] + p["stage_copy_waves"] <= 16, where
+    for s in {0, p["stage_slabs"] - 1}:
+        banks = min(slab, nb - s * slab)
+        stages, groups, sg = -(-banks // sb), -(-banks // BANKS), sb // BANKS
+        assert stages == 1 or sg % ks == 0, where
+        barriers = stages + (stages - 1 if p["stage_bufs"] == 1 else 0)     # of a wavefront that copies
+        walked = []
+        for kq in range(ks):
+            g, stage, first, end, met = kq, 0, 0, sg if stages > 1 else groups, 1
+            while g < groups:
+                if g >= end:
+                    stage, met, first, end = stage + 1, met + 1 + (p["stage_bufs"] == 1), end, min(end + sg, groups)
+                assert first <= g < end and (g - first + 1) * bank * 256 <= p["stage_buf_bytes"], where
+                walked.append(g)
+                g += ks
+            assert met + (stages - 1 - stage) * (1 + (p["stage_bufs"] == 1)) == barriers, where
+        assert sorted(walked) == list(range(groups)), where
+        if copies:
+            for stage, ragged in {(0, 0), (stages - 1, 1)}:
+                sbk = min(sb, banks - stage * sb)
+                wrote = _copied(p, bank, sbk, ragged)
+                assert len(wrote) == (sbk * bank - ragged) * P, where
+                for (at, (row, c)) in wrote.items():
+                    j, r = divmod(row, bank)
+                    assert at == ((j // BANKS) * bank + r) * 256 + (j % BANKS) * 16 * P + c * 16, where
+
+
+def test_launches_of_random_shapes():
+    rng = random.Random(811)
+    taken = 0
+    for n in range(3000):
+        bank = rng.choice([4, 5, 8, 16, 25, 32, 50, 64, 100, 128, 255, 256])
+        nb = rng.choice([1, 2, 3, 5, 7, 16, 30, 41, 60, 392])
+        k = min(bank, rng.choice([*range(1, 18), 20, 32, 33, 63, 64, 128]))
+        M = rng.choice([1, 3, 8, 37, 94, 128, 500, 1111, 6000, 16384])
+        N = rng.choice([1, 8, 9, 13, 16, 17, 31, 32, 33, 37, 48, 49, 64, 100, 128, 784, 5000])
+        dtype = rng.choice([bs.BS_F32, bs.BS_F16])
+        try:
+            p = bs.bs_spmm_plan(dtype, M, nb * bank, bank, k, N)
+        except bs.BsError:
+            continue
+        assert p["stages"] in (0, 1)
+        if p["stages"]:
+            assert N > 8 and k >= 4
+            taken += 1
+            _check(p, M, nb, bank, k, N, bank * min(p["stage_banks"], nb) < 2000 and n % 3 == 0)
+    assert taken > 500
+
+
+def test_the_timed_sizes_and_small_ones():
+    for M, K, bank, k, N, dtype in [(6000, 3000, 100, 10, 128, bs.BS_F32), (6000, 3000, 50, 15, 37, bs.BS_F32),
+                                    (512, 4608, 64, 16, 784, bs.BS_F32)]:
+        p = bs.bs_spmm_plan(dtype, M, K, bank, k, N)
+        assert p["stages"] == 1
+        _check(p, M, K // bank, bank, k, N, True)
+    assert bs.bs_spmm_plan(bs.BS_F32, 6000, 3000, 100, 10, 8)["stages"] == 0        # few columns: the chunk walk
+    assert bs.bs_spmm_plan(bs.BS_F32, 256, 256, 64, 16, 32)["stages"] == 0          # a few microseconds
+    assert bs.bs_spmm_plan(bs.BS_F32, 6000, 3000, 100, 3, 128)["stages"] == 0       # fewer than four per bank
+
+
+SOURCES = ["bs_spmm_stream_f32.hip", "bs_spmm_stream_f16.hip", "bs_spmm_stream_wide.hip"]
+
+
+@pytest.fixture(scope="module")
+def texts():
+    def assembly(src):
+        out = tempfile.NamedTemporaryFile(suffix=".s", delete=False).name
+        flags = [f for f in bs_build.FLAGS if f != "-fPIC"]
+        subprocess.check_call([bs_build.HIPCC, *flags, "-S", "--cuda-device-only", "-o", out, os.path.join(bs_build.CSRC, src)],
+                              stderr=subprocess.DEVNULL)
+        text = open(out).read()
+        os.unlink(out)
+        return text
+    with ThreadPoolExecutor(3) as ex:
+        return list(ex.map(assembly, SOURCES))
+
+
+def test_generated_code(texts):
+    """No scratch memory; between a direct-to-LDS copy and the next barrier there is a wait for every load (the
+    compiler does not track these copies itself)."""
+    kernels = 0
+    for text in texts:
+        assert all(int(n) == 0 for n in re.findall(r"\.vgpr_spill_count:\s+(\d+)", text))
+        assert all(int(n) == 0 for n in re.findall(r"\.private_segment_fixed_size:\s+(\d+)", text))
+        # 128 registers: 16 wavefronts on a compute unit
+        assert all(int(n) <= 128 for n in re.findall(r"\.vgpr_count:\s+(\d+)", text))
+        name, pending, copies = None, False, 0
+        for line in text.splitlines():
+            s = line.strip()
+            m = re.match(r"^(_ZN2bs18spmm_stream_kernel\w+):", line)
+            if m:
+                name, pending, copies = m.group(1), False, 0
+            elif name is None:
+                continue
+            elif s.startswith(".Lfunc_end"):
+                assert copies == 2, name         # the first stage's and the later ones'
+                kernels, name = kernels + 1, None
+            elif s.startswith("global_load_lds"):
+                pending, copies = True, copies + 1
+            elif s.startswith("s_waitcnt") and "vmcnt(0)" in s:
+                pending = False
+            elif s.startswith("s_barrier"):
+                assert not pending, name
+    assert kernels == 2 * 14 + 4
