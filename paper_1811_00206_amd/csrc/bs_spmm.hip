@@ -200,16 +200,31 @@ double tiles_ns(const SpmmPlan& p, int vsize, int isize, int64_t M, int64_t K, i
     return t;
 }
 
-// The stage kernels are taken where they are expected to be faster by more than either expectation is off: over 456
-// random products of 9 to 50 000 columns they were chosen for 215, took 0.67 of the tile kernels' time there and at
-// most 1.07 of it.  Products of a few microseconds are not worth the planning.
-constexpr double kStreamMargin = 0.85, kStreamWorthNs = 6000;
+// The stage kernels are taken where they are expected to be faster by more than either expectation is off.  Over 1050
+// random products of 9 to 50 000 columns, both kernels timed (926 with an expectation above kStreamWorthNs; products
+// below it are not worth the planning), they are taken for 539 and need 0.73 of the tile kernels' time there (geometric
+// mean); 5 lose more than 8 %, at most 14 %.  With 0.85 for all and none of the terms below: 505 products, 16 such
+// losses, the worst 1.7.  The terms are what the expectations leave out:
+//   * Banks of more than 32 entries: a lane returns to a cache line of its bank for every 8 entries, and
+//     the lanes of a compute unit hold several times more lines than its L1.  With one tile of columns that is most
+//     of the time (15947 x 6144, 124 entries per bank, N = 12: 40.1 us by tiles, 68.7 in stages).
+//   * More workgroups than compute units: copies of the first stage have nothing to hide behind, unaligned
+//     ones the longest (303 x 350 at N = 5687, 28.1 against 34.6 us).
+//   * An X of hundreds of MB comes from memory in rows of 64 bytes (142 x 12900 at N = 4846: 112.8 against 141.3 us).
+constexpr double kStreamMargin = 0.93, kStreamWorthNs = 6000;
+constexpr double kStreamManyAligned = 1.05, kStreamManyUnaligned = 1.2, kStreamLongBank = 1.1;
+constexpr int kStreamLongK = 32;
+constexpr double kStreamMaxXBytes = 128e6;
 SpmmStreamPlan stream_choice(const SpmmPlan& p, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int64_t ldx) {
     if (N <= 8 || k < kStreamMinK) return {};
+    if ((k > kStreamLongK && N <= 16) || 4.0 * K * N > kStreamMaxXBytes) return {};
     const double tiles = tiles_ns(p, vsize, isize, M, K, bank, k, N, copy_kind(N, ldx));
     if (tiles <= kStreamWorthNs) return {};
     SpmmStreamPlan sp = spmm_stream_plan(vsize, isize, M, K, bank, k, N, ldx, p.n_slabs);
-    if (sp.ok && sp.ns >= kStreamMargin * tiles) sp.ok = false;
+    double ns = sp.ns;
+    if ((int64_t)sp.n_tiles * sp.n_slabs * sp.row_groups > kCus) ns *= ldx % 4 == 0 ? kStreamManyAligned : kStreamManyUnaligned;
+    if (k > kStreamLongK) ns *= kStreamLongBank;
+    if (sp.ok && ns >= kStreamMargin * tiles) sp.ok = false;
     return sp;
 }
 

@@ -40,6 +40,7 @@ SHAPES = [
     (5, 68, 20, 5, 46, "f32"), (5, 67, 20, 20, 58, "f32"), (5, 26, 50, 11, 107, "f32"), (5, 25, 50, 20, 128, "f32"),
     (400, 51, 64, 33, 114, "f16"), (1000, 37, 64, 5, 60, "f32"), (5, 49, 16, 7, 62, "f32"), (5, 30, 100, 9, 94, "f32"),
     (700, 63, 50, 10, 115, "f32"), (1000, 25, 128, 17, 134, "f32"), (1000, 66, 64, 33, 139, "f32"), (200, 23, 256, 33, 132, "f32"),
+    (300, 200, 64, 6, 16, "f16"),     # six slabs of one tile
 ]
 
 

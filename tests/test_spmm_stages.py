@@ -95,13 +95,17 @@ def test_launches_of_random_shapes():
 
 def test_the_timed_sizes_and_small_ones():
     for M, K, bank, k, N, dtype in [(6000, 3000, 100, 10, 128, bs.BS_F32), (6000, 3000, 50, 15, 37, bs.BS_F32),
-                                    (512, 4608, 64, 16, 784, bs.BS_F32)]:
+                                    (512, 4608, 64, 16, 784, bs.BS_F32), (4096, 25088, 64, 6, 16, bs.BS_F16),
+                                    (512, 6400, 64, 16, 5000, bs.BS_F32)]:
         p = bs.bs_spmm_plan(dtype, M, K, bank, k, N)
         assert p["stages"] == 1
         _check(p, M, K // bank, bank, k, N, True)
     assert bs.bs_spmm_plan(bs.BS_F32, 6000, 3000, 100, 10, 8)["stages"] == 0        # few columns: the chunk walk
     assert bs.bs_spmm_plan(bs.BS_F32, 256, 256, 64, 16, 32)["stages"] == 0          # a few microseconds
     assert bs.bs_spmm_plan(bs.BS_F32, 6000, 3000, 100, 3, 128)["stages"] == 0       # fewer than four per bank
+    # one tile of columns and more than 32 entries per bank; an X of more than 128 MB
+    assert bs.bs_spmm_plan(bs.BS_F32, 700, 6144, 128, 33, 16)["stages"] == 0
+    assert bs.bs_spmm_plan(bs.BS_F32, 512, 6400, 64, 16, 5001)["stages"] == 0
 
 
 SOURCES = ["bs_spmm_stream_f32.hip", "bs_spmm_stream_f16.hip", "bs_spmm_stream_wide.hip"]
