@@ -18,10 +18,14 @@
 //   8 columns per lane, banks side by side (no collisions, but DPP at 1.8 ns per value)  21.7
 //   a bank per lane, 16 columns (no value passes between lanes)                           18.5
 //   the first stage copied by all wavefronts, whole words only in the weights' ring       17.4
+// Beside them the weights: a lane reads its own bank, so a load instruction makes about three accesses of
+// 64 bytes per four lanes, 240 per 64 banks of 10, and the address unit is busy 24 of 36 thousand cycles (N = 128).
 // The accumulators of columns 2i and 2i+1 are kept in each other's place: a multiply-add whose
 // addend and X operand are both in even or both in odd registers takes 1.4 ns instead of 1.
 // Tried and not kept: more than 14 walking wavefronts (the copies fall behind), the gathers of
-// a unit's first entries issued before the last multiply-adds of the unit before (spills).
+// a unit's first entries issued before the last multiply-adds of the unit before (spills), 32 columns per lane (half
+// the weights' accesses, but three to six wavefronts then walk: 25.9 us against 19.5), offsets in one load that
+// reaches back into the bank before (18.1 us against 17.9).
 #pragma once
 #include "bs_spmm_kernel.h"
 
