@@ -200,6 +200,14 @@ double tiles_ns(const SpmmPlan& p, int vsize, int isize, int64_t M, int64_t K, i
     return t;
 }
 
+// The rounding error of the tile kernels' sums (chain_rounding): `lpr` lanes walk every lpr-th chunk of a slab's run.
+double tiles_rounding(const SpmmPlan& p, int64_t nb, int k) {
+    const int64_t run = nb * k / p.n_slabs, chunks = std::max<int64_t>(1, run / p.ch), slots = chunks / p.lpr, longer = chunks - slots * p.lpr;
+    auto lanes = [&](int64_t n, int64_t entries) { return n * entries * chain_rounding((double)entries, true); };
+    return (lanes(longer, (slots + 1) * p.ch) + lanes(p.lpr - longer, slots * p.ch)) / (double)(chunks * p.ch) +
+           std::log2((double)std::min<int64_t>(p.lpr, chunks)) + chain_rounding(p.n_slabs, false);
+}
+
 // The stage kernels are taken where they are expected to be faster by more than either expectation is off.  Over 1050
 // random products of 9 to 50 000 columns, both kernels timed (926 with an expectation above kStreamWorthNs; products
 // below it are not worth the planning), they are taken for 539 and need 0.73 of the tile kernels' time there (geometric
@@ -211,6 +219,9 @@ double tiles_ns(const SpmmPlan& p, int vsize, int isize, int64_t M, int64_t K, i
 //   * More workgroups than compute units: copies of the first stage have nothing to hide behind, unaligned
 //     ones the longest (303 x 350 at N = 5687, 28.1 against 34.6 us).
 //   * An X of hundreds of MB comes from memory in rows of 64 bytes (142 x 12900 at N = 4846: 112.8 against 141.3 us).
+// A launch whose sums would round worse than the tile kernels' is not looked at: those walk an odd row length or a small
+// tile with up to 64 lanes per row, so their sums are short (6722 x 144, banks of 16, k = 13, N = 40: 4 entries per lane and
+// an exchange, against 39 in a lane of the stage kernels, 1.5 times the error).  Of 4000 random products, 4 %.
 constexpr double kStreamMargin = 0.93, kStreamWorthNs = 6000;
 constexpr double kStreamManyAligned = 1.05, kStreamManyUnaligned = 1.2, kStreamLongBank = 1.1;
 constexpr int kStreamLongK = 32;
@@ -220,7 +231,7 @@ SpmmStreamPlan stream_choice(const SpmmPlan& p, int vsize, int isize, int64_t M,
     if ((k > kStreamLongK && N <= 16) || 4.0 * K * N > kStreamMaxXBytes) return {};
     const double tiles = tiles_ns(p, vsize, isize, M, K, bank, k, N, copy_kind(N, ldx));
     if (tiles <= kStreamWorthNs) return {};
-    SpmmStreamPlan sp = spmm_stream_plan(vsize, isize, M, K, bank, k, N, ldx, p.n_slabs);
+    SpmmStreamPlan sp = spmm_stream_plan(vsize, isize, M, K, bank, k, N, ldx, p.n_slabs, tiles_rounding(p, K / bank, k));
     double ns = sp.ns;
     if ((int64_t)sp.n_tiles * sp.n_slabs * sp.row_groups > kCus) ns *= ldx % 4 == 0 ? kStreamManyAligned : kStreamManyUnaligned;
     if (k > kStreamLongK) ns *= kStreamLongBank;

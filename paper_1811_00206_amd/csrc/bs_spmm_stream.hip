@@ -43,9 +43,18 @@ double expected_ns(const SpmmStreamPlan& p, int vsize, int isize, int64_t M, int
     return t;
 }
 
+// A lane adds its banks' entries of a stage, then the stages; then come the banks side by side, the wavefronts
+// along K and the slabs.
+double rounding(const SpmmStreamPlan& p, int64_t nb, int k) {
+    const int64_t groups = div_up(std::min<int64_t>(p.slab_banks, nb), stream_banks(kP)), sg = p.sb / stream_banks(kP);
+    return chain_rounding((double)k * div_up(std::min(sg, groups), p.ksplit), true) + chain_rounding((double)div_up(groups, sg), false) +
+           std::log2(stream_banks(kP)) + chain_rounding(p.ksplit, false) + chain_rounding(p.n_slabs, false);
+}
+
 }  // namespace
 
-SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int64_t ldx, int max_slabs) {
+SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int64_t ldx, int max_slabs,
+                                double max_rounding) {
     SpmmStreamPlan best{};
     constexpr int ib = stream_banks(kP), rows = stream_rows(kP);
     if (k < kStreamMinK) return best;
@@ -84,7 +93,7 @@ SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int 
                 p.lds_bytes = std::max<size_t>((size_t)bufs * p.buf_bytes, (size_t)(ks - 1) * row_waves * 1024);
                 if (p.lds_bytes > (size_t)kMaxLdsBytes) continue;
                 p.ns = expected_ns(p, vsize, isize, M, K, bank, k, N, aligned);
-                if (!best.ok || p.ns < best.ns) best = p;
+                if ((!best.ok || p.ns < best.ns) && rounding(p, nb, k) <= max_rounding) best = p;
             }
         }
     }

@@ -78,8 +78,14 @@ struct SpmmStreamPlan {
     size_t lds_bytes;
     double ns;                               // expected time, the slab sums included
 };
-// The best launch for a shape, with at most max_slabs slabs; ok = false where the kernels do not apply.
-SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int64_t ldx, int max_slabs);
+// The rounding error of a sum, as its variance over that of its terms' own rounding when all terms are of one size: an
+// addition rounds its result, so it counts as many times as the result has terms, over the number of terms
+// of the whole sum.  Of `n` terms (or sums of equally many terms each, exact themselves) added one after the other:
+inline double chain_rounding(double n, bool terms) { return (n + 1) / 2 - (terms ? 0 : 1 / n); }
+// The best launch for a shape, with at most max_slabs slabs and sums whose rounding is at most max_rounding; ok =
+// false where there is none or the kernels do not apply.
+SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int64_t ldx, int max_slabs,
+                                double max_rounding);
 // t: the operands as for the tile kernels, out and slab_stride for p's number of slabs
 int spmm_stream_launch(const SpmmStreamPlan& p, const SpmmArgs& t, int dtype, int isize, hipStream_t st);
 int spmm_stream_launch_f32(const SpmmStreamArgs& a, const SpmmLaunch& l);

@@ -1,6 +1,7 @@
 """The launches of the SpMM kernels that walk K in stages, checked on the host: every bank of X copied once to where
 it is read, every bank walked once, the same barriers in every wavefront, LDS within a compute unit's; and the
 generated code of every instantiation."""
+import math
 import os
 import random
 import re
@@ -8,6 +9,7 @@ import subprocess
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
+import numpy as np
 import pytest
 
 from paper_1811_00206_amd import binding as bs
@@ -106,6 +108,68 @@ def test_the_timed_sizes_and_small_ones():
     # one tile of columns and more than 32 entries per bank; an X of more than 128 MB
     assert bs.bs_spmm_plan(bs.BS_F32, 700, 6144, 128, 33, 16)["stages"] == 0
     assert bs.bs_spmm_plan(bs.BS_F32, 512, 6400, 64, 16, 5001)["stages"] == 0
+
+
+def _chain(parts):
+    """The parts (last axis: exact products or sums in fp32) added one after the other, each addition rounded to fp32."""
+    total = np.zeros(parts.shape[:-1], np.float32)
+    for i in range(parts.shape[-1]):
+        total = (total.astype(np.float64) + parts[..., i]).astype(np.float32)
+    return total
+
+
+def _tile_sums(p, t):
+    """The tile kernels' order: [sums, banks, k] products -> fp32 sums."""
+    slabs = []
+    for s in range(p["n_slabs"]):
+        run = t[:, s * p["sb"]:(s + 1) * p["sb"]].reshape(len(t), -1)
+        chunks = run.reshape(len(t), -1, p["ch"])
+        lanes = [_chain(chunks[:, lane::p["lpr"]].reshape(len(t), -1)) for lane in range(p["lpr"])]
+        while len(lanes) > 1:       # the exchange between lanes
+            lanes = [lanes[i] + lanes[i + 1] for i in range(0, len(lanes), 2)]
+        slabs.append(lanes[0])
+    return _chain(np.stack(slabs, -1))
+
+
+def _stage_sums(p, t):
+    """The stage kernels' order."""
+    nb, k, slabs = t.shape[1], t.shape[2], []
+    sg, ks = p["stage_banks"] // BANKS, p["stage_ksplit"]
+    for s in range(p["stage_slabs"]):
+        banks = t[:, s * p["stage_slab_banks"]:(s + 1) * p["stage_slab_banks"]]
+        groups = -(-banks.shape[1] // BANKS)
+        banks = np.pad(banks, [(0, 0), (0, groups * BANKS - banks.shape[1]), (0, 0)]).reshape(len(t), groups, BANKS, k)
+        waves = []
+        for kq in range(ks):
+            stages = []
+            for first in range(0, groups, sg):
+                mine = banks[:, first:first + sg][:, kq::ks] if groups > sg else banks[:, kq::ks]
+                stages.append(_chain(mine.transpose(0, 2, 1, 3).reshape(len(t), BANKS, -1)))
+            lane = _chain(np.stack(stages, -1))
+            waves.append((lane[:, 0] + lane[:, 1]) + (lane[:, 2] + lane[:, 3]))
+        slabs.append(_chain(np.stack(waves, -1)))
+    return _chain(np.stack(slabs, -1))
+
+
+# odd row lengths and small tiles, which the tile kernels walk with up to 64 lanes per row; many banks; the timed sizes
+@pytest.mark.parametrize("M,K,bank,k,N", [
+    (6722, 144, 16, 13, 40), (3700, 350, 50, 25, 17), (146, 384, 128, 43, 1375), (6774, 320, 64, 19, 54),
+    (6109, 300, 100, 38, 53), (14391, 384, 128, 31, 100), (2387, 500, 100, 33, 32), (3432, 400, 100, 45, 43),
+    (2880, 336, 16, 6, 81), (700, 3150, 50, 10, 115), (400, 3264, 64, 33, 114), (6000, 3000, 100, 10, 128),
+    (6000, 3000, 50, 15, 37), (512, 4608, 64, 16, 784)])
+def test_sums_are_no_less_exact_than_the_tile_kernels(M, K, bank, k, N):
+    """Both orders of addition on the same products, against 64 bits."""
+    p = bs.bs_spmm_plan(bs.BS_F32, M, K, bank, k, N)
+    if not p["stages"]:
+        return
+    g = np.random.default_rng(K + k)
+    n = 40000 * 64 // (K // bank * k)
+    w, x = (g.standard_normal((n, K // bank, k)).astype(np.float32) for _ in range(2))
+    t = w.astype(np.float64) * x
+    exact = t.sum(axis=(1, 2))
+    tiles, stages = (np.linalg.norm(sums(p, t) - exact) for sums in (_tile_sums, _stage_sums))
+    # each norm is over n independent errors: known to about 1 / sqrt(2 n) of itself
+    assert stages <= tiles * (1 + 3 / math.sqrt(n)), (p, stages / tiles)
 
 
 SOURCES = ["bs_spmm_stream_f32.hip", "bs_spmm_stream_f16.hip", "bs_spmm_stream_wide.hip"]
