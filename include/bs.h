@@ -191,7 +191,7 @@ size_t bs_spmm_workspace_bytes(int dtype, int64_t M, int64_t K, int bank, int k,
  *   [13] LDS bytes per workgroup            [14] workgroups launched
  *   [15] float index of the position table in LDS
  *   [16] threads per workgroup (for ldx = N): those of [9] and any that only copy X
- *   [17] 1 if the product is left to the kernels that walk K in stages (for ldx = N); [0] to
+ *   [17] 1 if the product is left to the kernels that walk K in stages; [0] to
  *       [16] then still fix the workspace, and apply to a first use inside a capture
  *   [18] column tiles   [19] K slabs   [20] banks per slab   [21] banks per stage
  *   [22] stages held in LDS at once (1 or 2)   [23] LDS bytes of one

@@ -208,7 +208,7 @@ double tiles_rounding(const SpmmPlan& p, int64_t nb, int k) {
            std::log2((double)std::min<int64_t>(p.lpr, chunks)) + chain_rounding(p.n_slabs, false);
 }
 
-// The stage kernels are taken where they are expected to be faster by more than either expectation is off.  Over 1050
+// The stage kernels are taken, for every row pitch of X alike, where they are expected to be faster by more than either expectation is off.  Over 1050
 // random products of 9 to 50 000 columns, both kernels timed (926 with an expectation above kStreamWorthNs; products
 // below it are not worth the planning), they are taken for 539 and need 0.73 of the tile kernels' time there (geometric
 // mean); 5 lose more than 8 %, at most 14 %.  With 0.85 for all and none of the terms below: 505 products, 16 such
@@ -226,14 +226,14 @@ constexpr double kStreamMargin = 0.93, kStreamWorthNs = 6000;
 constexpr double kStreamManyAligned = 1.05, kStreamManyUnaligned = 1.2, kStreamLongBank = 1.1;
 constexpr int kStreamLongK = 32;
 constexpr double kStreamMaxXBytes = 128e6;
-SpmmStreamPlan stream_choice(const SpmmPlan& p, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int64_t ldx) {
+SpmmStreamPlan stream_choice(const SpmmPlan& p, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N) {
     if (N <= 8 || k < kStreamMinK) return {};
     if ((k > kStreamLongK && N <= 16) || 4.0 * K * N > kStreamMaxXBytes) return {};
-    const double tiles = tiles_ns(p, vsize, isize, M, K, bank, k, N, copy_kind(N, ldx));
+    const double tiles = tiles_ns(p, vsize, isize, M, K, bank, k, N, copy_kind(N, N));
     if (tiles <= kStreamWorthNs) return {};
-    SpmmStreamPlan sp = spmm_stream_plan(vsize, isize, M, K, bank, k, N, ldx, p.n_slabs, tiles_rounding(p, K / bank, k));
+    SpmmStreamPlan sp = spmm_stream_plan(vsize, isize, M, K, bank, k, N, p.n_slabs, tiles_rounding(p, K / bank, k));
     double ns = sp.ns;
-    if ((int64_t)sp.n_tiles * sp.n_slabs * sp.row_groups > kCus) ns *= ldx % 4 == 0 ? kStreamManyAligned : kStreamManyUnaligned;
+    if ((int64_t)sp.n_tiles * sp.n_slabs * sp.row_groups > kCus) ns *= N % 4 == 0 ? kStreamManyAligned : kStreamManyUnaligned;
     if (k > kStreamLongK) ns *= kStreamLongBank;
     if (sp.ok && ns >= kStreamMargin * tiles) sp.ok = false;
     return sp;
@@ -345,7 +345,7 @@ int spmm_plan_describe(int dtype, int64_t M, int64_t K, int bank, int k, int64_t
     if (total > INT32_MAX / 2) return BS_ERR_UNSUPPORTED;
     if (p.ws_bytes && M * N > (int64_t)UINT32_MAX) return BS_ERR_UNSUPPORTED;
     const int rows_per_pass = p.row_threads / (p.nl * p.lpr);
-    const SpmmStreamPlan sp = stream_choice(p, dtype == BS_F16 ? 2 : 4, 1, M, K, bank, k, N, N);
+    const SpmmStreamPlan sp = stream_choice(p, dtype == BS_F16 ? 2 : 4, 1, M, K, bank, k, N);
     const int64_t v[30] = {p.rows ? 1 : 0, p.ch, p.nl, p.nt, p.n_tiles, p.sb, p.n_slabs, p.lpr, p.u,
                            p.row_threads, p.rows_per_wg, p.row_groups,
                            (p.rows_per_wg + rows_per_pass - 1) / rows_per_pass,
@@ -401,7 +401,7 @@ int launch_spmm_any(const void* vals, const void* idx, int isize, int dtype, int
                                  : spmm_launch_f32(p.ch, p.lpr, p.u, p.q, a, l);
     };
     int n_slabs = p.n_slabs, st_code = BS_ERR_NOT_INITIALISED;
-    const SpmmStreamPlan sp = stream_choice(p, dtype == BS_F16 ? 2 : 4, isize, M, K, bank, k, N, ldx);
+    const SpmmStreamPlan sp = stream_choice(p, dtype == BS_F16 ? 2 : 4, isize, M, K, bank, k, N);
     if (sp.ok) {
         SpmmArgs t = a;
         if (sp.n_slabs == 1 && p.n_slabs > 1) {

@@ -53,13 +53,12 @@ double rounding(const SpmmStreamPlan& p, int64_t nb, int k) {
 
 }  // namespace
 
-SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int64_t ldx, int max_slabs,
+SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int max_slabs,
                                 double max_rounding) {
     SpmmStreamPlan best{};
     constexpr int ib = stream_banks(kP), rows = stream_rows(kP);
     if (k < kStreamMinK) return best;
-    if ((double)(ib * bank + 4) * ldx * 4 > INT32_MAX) return best;   // the copy's 32-bit offsets inside a group of banks
-    const bool aligned = ldx % 4 == 0;
+    const bool aligned = N % 4 == 0;         // as in the usual X, whose rows are adjacent
     const int64_t nb = K / bank;
     const int64_t group = (int64_t)bank * kStreamPitch;
     const int64_t n_tiles = div_up(N, 4 * kP);
@@ -120,7 +119,8 @@ int spmm_stream_launch(const SpmmStreamPlan& p, const SpmmArgs& t, int dtype, in
     a.magic_slab = magic_u32(p.n_tiles * p.row_groups);
     a.magic_sb = magic_u32(p.sb);
     a.magic_rw = magic_u32(p.row_waves);
-    a.by_registers = t.ldx % 4 != 0;
+    // the direct copies' 32-bit offsets inside a group of banks
+    a.by_registers = t.ldx % 4 != 0 || (double)(stream_banks(kP) * t.B + 4) * (double)t.ldx * 4 > INT32_MAX;
     a.vec_out = t.vec_out;
     const SpmmLaunch l{64 * (p.ksplit * p.row_waves + p.copy_waves), p.lds_bytes, st, false};
     if (isize == 2) return spmm_stream_launch_wide(dtype, a, l);

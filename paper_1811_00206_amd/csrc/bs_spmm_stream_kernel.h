@@ -67,7 +67,8 @@ struct SpmmStreamArgs {
     int total_wgs, wgs_per_xcd;
     uint32_t magic_inner, magic_slab;   // magic_u32 of the faster index's count, of tiles * row groups
     uint32_t magic_sb, magic_rw;
-    int by_registers;      // rows of X start at any multiple of 4 bytes
+    int by_registers;      // X is copied through registers: rows that start at any multiple of 4 bytes, or lie so far
+                           // apart that four banks of them span 2 GB
     int vec_out;
 };
 
@@ -82,9 +83,10 @@ struct SpmmStreamPlan {
 // addition rounds its result, so it counts as many times as the result has terms, over the number of terms
 // of the whole sum.  Of `n` terms (or sums of equally many terms each, exact themselves) added one after the other:
 inline double chain_rounding(double n, bool terms) { return (n + 1) / 2 - (terms ? 0 : 1 / n); }
-// The best launch for a shape, with at most max_slabs slabs and sums whose rounding is at most max_rounding; ok =
+// The best launch for a shape (of any row pitch of X: a product's sums are in the same order whatever the
+// pitch), with at most max_slabs slabs and sums whose rounding is at most max_rounding; ok =
 // false where there is none or the kernels do not apply.
-SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int64_t ldx, int max_slabs,
+SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int max_slabs,
                                 double max_rounding);
 // t: the operands as for the tile kernels, out and slab_stride for p's number of slabs
 int spmm_stream_launch(const SpmmStreamPlan& p, const SpmmArgs& t, int dtype, int isize, hipStream_t st);
@@ -138,7 +140,6 @@ __device__ __forceinline__ void spmm_stream_copy(const SpmmStreamArgs& a, char* 
     // Rows of X are read in pieces of 16 bytes, which may reach up to 12 bytes past a row's last
     // column: into the next row, but not past the last row of X, which is brought in by itself.
     const bool ragged_end = bank0 + banks == a.nb && (ntw & 3);
-    const uint32_t lane_off = (uint32_t)((p * B + lrow) * (int)a.ldx + min(c * 4, (ntw - 1) & ~3)) * 4u;
     const char* X0 = reinterpret_cast<const char*>(a.X + (size_t)bank0 * B * a.ldx + n0);
     const size_t group_step = (size_t)kBanks * B * a.ldx * 4, quad_step = (size_t)4 * a.ldx * 4;
     // rows of this lane's bank in the last group: none if there is no such bank
@@ -146,6 +147,7 @@ __device__ __forceinline__ void spmm_stream_copy(const SpmmStreamArgs& a, char* 
     int g = 0, rq = wave;
     while (rq >= quads) { rq -= quads; ++g; }
     if (!a.by_registers) {
+        const uint32_t lane_off = (uint32_t)((p * B + lrow) * (int)a.ldx + min(c * 4, (ntw - 1) & ~3)) * 4u;
         while (g < groups) {
             const int r = rq * 4 + lrow;
             if (r < (g == groups - 1 ? last_rows : B))
@@ -160,6 +162,7 @@ __device__ __forceinline__ void spmm_stream_copy(const SpmmStreamArgs& a, char* 
         // is there: no branch comes between the loads.
         constexpr int kBatch = 8;
         using Four = WordsAt<4, 4>;
+        const size_t lane_off = ((size_t)(p * B + lrow) * (size_t)a.ldx + (size_t)min(c * 4, (ntw - 1) & ~3)) * 4u;
         while (g < groups) {
             Four t[kBatch];
             int at[kBatch];                      // LDS row of each piece, or -1

@@ -61,6 +61,24 @@ def test_stages_against_float64(M, nb, bank, k, N, dtype):
         assert torch.equal(out[:, :N], Y) and bool((out[:, N:] == 7.0).all())
 
 
+# 522 304 columns: four banks of X span more than 2 GB
+@pytest.mark.parametrize("M,nb,bank,k,N,pitches", [
+    (700, 63, 50, 10, 112, (113, 116, 121)), (700, 63, 50, 10, 115, (116, 117, 120)), (512, 72, 64, 16, 784, (785, 788)),
+    (4000, 4, 256, 64, 100, (101, 104, 522304))])
+def test_a_product_has_the_same_bits_for_every_row_pitch(M, nb, bank, k, N, pitches):
+    assert bs.bs_spmm_plan(bs.BS_F32, M, nb * bank, bank, k, N)["stages"] == 1
+    v, i, dense, g, spmm = _product(M, nb, bank, k, "f32", 7)
+    X = torch.randn((nb * bank, N), generator=g, device="cuda")
+    Y = spmm(v, i, bank, X)
+    _check(Y, dense, X.cpu().double(), nb * k)
+    for pitch in pitches:
+        print("pitch", M, nb, bank, k, N, pitch, flush=True)
+        wide = torch.empty((nb * bank, pitch), device="cuda")[:, :N]
+        wide.copy_(X)
+        out = torch.empty((M, N + 3), device="cuda")[:, :N]
+        assert torch.equal(spmm(v, i, bank, wide, out=out), Y)
+
+
 @pytest.mark.parametrize("bank,k,nb", [(512, 4, 9), (512, 7, 9), (600, 40, 6), (264, 9, 23)])
 @pytest.mark.parametrize("M,N", [(300, 200), (1000, 37)])
 def test_16_bit_offsets(bank, k, nb, M, N):
