@@ -23,7 +23,8 @@
  *   - State: the only thing the library remembers between calls is, per kernel and
  *     device, that the kernel's LDS limit has been raised (an atomic bit mask; calls
  *     are safe from several threads).  That step happens at a kernel's first launch
- *     on a device, or for all kernels at once in bs_init(), and never while the
+ *     on a device (and there for the kernels that products of another N or k with the
+ *     same types may need), or for all kernels at once in bs_init(), and never while the
  *     stream is being captured: a first use inside a capture returns
  *     BS_ERR_NOT_INITIALISED and enqueues nothing.
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).
@@ -172,6 +173,8 @@ int bs_spmv_plan(int dtype, int64_t M, int64_t K, int bank, int k, int lanes_per
  * X   DEVICE in   K x N fp32 row-major, leading dimension ldx >= N
  * Y   DEVICE out  M x N fp32 row-major, leading dimension ldy >= N
  * Y[r][n] = sum_j sum_t vals[r][j][t] * X[j*bank + idx[r][j][t]][n]
+ * The order of the additions depends on dtype, M, K, bank, k and N alone: not on ldx or ldy,
+ * and not on whether the call is captured or what has run before.
  * workspace / workspace_bytes: DEVICE scratch of at least
  * bs_spmm_workspace_bytes(...) bytes (may be NULL when that is 0), 16-byte aligned; it
  * needs no initialisation.  Calls that overlap in time must not share a workspace.
@@ -191,8 +194,8 @@ size_t bs_spmm_workspace_bytes(int dtype, int64_t M, int64_t K, int bank, int k,
  *   [13] LDS bytes per workgroup            [14] workgroups launched
  *   [15] float index of the position table in LDS
  *   [16] threads per workgroup (for ldx = N): those of [9] and any that only copy X
- *   [17] 1 if the product is left to the kernels that walk K in stages; [0] to
- *       [16] then still fix the workspace, and apply to a first use inside a capture
+ *   [17] 1 if the product is left to the kernels that walk K in stages; [0] to [16] then
+ *       still fix the workspace, and [13] whether a first use inside a capture is refused
  *   [18] column tiles   [19] K slabs   [20] banks per slab   [21] banks per stage
  *   [22] stages held in LDS at once (1 or 2)   [23] LDS bytes of one
  *   [24] rows per workgroup   [25] row groups   [26] groups of wavefronts along K

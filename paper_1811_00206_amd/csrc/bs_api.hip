@@ -7,7 +7,7 @@ namespace bs {
 
 LdsKernel* g_lds_kernels = nullptr;
 
-LdsKernel::LdsKernel(const void* f) : fn(f), raised(0), next(g_lds_kernels) { g_lds_kernels = this; }
+LdsKernel::LdsKernel(const void* f, int g) : fn(f), raised(0), next(g_lds_kernels), group(g) { g_lds_kernels = this; }
 
 namespace {
 int raise_on_current_device(LdsKernel& k, uint64_t bit) {
@@ -18,7 +18,7 @@ int raise_on_current_device(LdsKernel& k, uint64_t bit) {
 }
 }  // namespace
 
-int ensure_lds_limit(LdsKernel& k, hipStream_t st, LdsKernel* sibling) {
+int ensure_lds_limit(LdsKernel& k, hipStream_t st, LdsKernel* sibling, int group) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev > 63) return BS_ERR_HIP;
     const uint64_t bit = (uint64_t)1 << dev;
@@ -29,6 +29,13 @@ int ensure_lds_limit(LdsKernel& k, hipStream_t st, LdsKernel* sibling) {
     if (sibling) {
         const int rc = raise_on_current_device(*sibling, bit);
         if (rc != BS_OK) return rc;
+    }
+    if (group) {
+        for (LdsKernel* o = g_lds_kernels; o; o = o->next) {
+            if (o->group != group || (o->raised.load(std::memory_order_acquire) & bit)) continue;
+            const int rc = raise_on_current_device(*o, bit);
+            if (rc != BS_OK) return rc;
+        }
     }
     return raise_on_current_device(k, bit);
 }

@@ -183,7 +183,7 @@ int gemm_stream_launch(const VT* w, int64_t M, int64_t K, const float* X, int64_
     const int64_t grid = (M + rows_per_wg - 1) / rows_per_wg;
     const size_t lds = (size_t)(KS + 4) * NC * sizeof(float);
     constexpr auto kern = dense_gemm_stream<VT, NC, R, P>;
-    if (lds > 48 * 1024) {
+    if (lds > kLdsWithoutLimit) {
         const int st_code = ensure_lds_limit(LdsKernelOf<kern>::reg, st);
         if (st_code != BS_OK) return st_code;
     }

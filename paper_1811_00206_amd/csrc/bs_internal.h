@@ -72,22 +72,28 @@ struct LdsKernel {
     const void* fn;
     std::atomic<uint64_t> raised;
     LdsKernel* next;
-    explicit LdsKernel(const void* f);
+    int group;             // kernels that are raised together with another's first launch (0: none)
+    LdsKernel(const void* f, int g);
 };
 extern LdsKernel* g_lds_kernels;   // bs_api.hip; constant-initialised, filled at load time
 
-template <auto KERNEL>
+template <auto KERNEL, int GROUP = 0>
 struct LdsKernelOf {
     static LdsKernel reg;
 };
-template <auto KERNEL>
-LdsKernel LdsKernelOf<KERNEL>::reg{reinterpret_cast<const void*>(KERNEL)};
+template <auto KERNEL, int GROUP>
+LdsKernel LdsKernelOf<KERNEL, GROUP>::reg{reinterpret_cast<const void*>(KERNEL), GROUP};
+
+// A kernel that needs at most this much of LDS is launched as it is.
+constexpr size_t kLdsWithoutLimit = 48 * 1024;
 
 // BS_OK when the kernel's limit is raised on the current device.  The limit is never
 // changed while `st` is being captured: BS_ERR_NOT_INITIALISED then (call bs_init() on
 // this device first, or make the first call outside the capture).  `sibling`: a kernel that the
 // same shape is launched as for another operand; the first launch of either prepares both.
-int ensure_lds_limit(LdsKernel& k, hipStream_t st, LdsKernel* sibling = nullptr);
+// `group`: kernels that other shapes are launched as in k's place; they are prepared before k is, so that no
+// choice between them and k depends on what has run before.
+int ensure_lds_limit(LdsKernel& k, hipStream_t st, LdsKernel* sibling = nullptr, int group = 0);
 // raises every registered kernel's limit on the current device (bs_init)
 int init_current_device();
 

@@ -231,7 +231,9 @@ SpmmStreamPlan stream_choice(const SpmmPlan& p, int vsize, int isize, int64_t M,
     if ((k > kStreamLongK && N <= 16) || 4.0 * K * N > kStreamMaxXBytes) return {};
     const double tiles = tiles_ns(p, vsize, isize, M, K, bank, k, N, copy_kind(N, N));
     if (tiles <= kStreamWorthNs) return {};
-    SpmmStreamPlan sp = spmm_stream_plan(vsize, isize, M, K, bank, k, N, p.n_slabs, tiles_rounding(p, K / bank, k));
+    // a product whose tile kernel needs no LDS limit raised can be captured as the first of all, so this one may not need it either
+    const int max_lds = p.lds_bytes > kLdsWithoutLimit ? kMaxLdsBytes : (int)kLdsWithoutLimit;
+    SpmmStreamPlan sp = spmm_stream_plan(vsize, isize, M, K, bank, k, N, p.n_slabs, max_lds, tiles_rounding(p, K / bank, k));
     double ns = sp.ns;
     if ((int64_t)sp.n_tiles * sp.n_slabs * sp.row_groups > kCus) ns *= N % 4 == 0 ? kStreamManyAligned : kStreamManyUnaligned;
     if (k > kStreamLongK) ns *= kStreamLongBank;
@@ -400,7 +402,7 @@ int launch_spmm_any(const void* vals, const void* idx, int isize, int dtype, int
                : dtype == BS_F16 ? spmm_launch_f16(p.ch, p.lpr, p.u, p.q, a, l)
                                  : spmm_launch_f32(p.ch, p.lpr, p.u, p.q, a, l);
     };
-    int n_slabs = p.n_slabs, st_code = BS_ERR_NOT_INITIALISED;
+    int n_slabs = p.n_slabs, st_code;
     const SpmmStreamPlan sp = stream_choice(p, dtype == BS_F16 ? 2 : 4, isize, M, K, bank, k, N);
     if (sp.ok) {
         SpmmArgs t = a;
@@ -408,18 +410,14 @@ int launch_spmm_any(const void* vals, const void* idx, int isize, int dtype, int
             t.out = Y; t.ld_out = ldy; t.slab_stride = 0;
             t.vec_out = ldy % 4 == 0 && (uintptr_t)Y % 16 == 0;
         }
-        // First uses inside a capture: where this kernel is not prepared the tile kernels answer as they
-        // would without it, and a first use of this one outside a capture prepares those too.
-        st_code = spmm_stream_launch(sp, t, dtype, isize, st);
-        if (st_code == BS_OK) {
-            n_slabs = sp.n_slabs;
-            const int prepared = tiles(true);
-            if (prepared != BS_OK && prepared != BS_ERR_NOT_INITIALISED) return prepared;
-        } else if (st_code != BS_ERR_NOT_INITIALISED) {
-            return st_code;
-        }
+        // A first use inside a capture is answered as for the tile kernel of this shape, whose preparation includes
+        // every stage kernel of these types: which kernel runs does not depend on what has run before.
+        st_code = tiles(true);
+        if (st_code == BS_OK) st_code = spmm_stream_launch(sp, t, dtype, isize, st);
+        n_slabs = sp.n_slabs;
+    } else {
+        st_code = tiles(false);
     }
-    if (st_code == BS_ERR_NOT_INITIALISED) st_code = tiles(false);
     if (st_code != BS_OK) return st_code;
     if (n_slabs > 1) {
         // 16 bytes per lane where rows of Y and of the workspace allow it (the workspace is

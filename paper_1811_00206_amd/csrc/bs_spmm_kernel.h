@@ -74,6 +74,11 @@ struct SpmmLaunch {
     bool prepare_only;     // raise the kernel's LDS limit (where this launch needs it) and return
 };
 
+// The kernels that walk K in stages (bs_spmm_stream_kernel.h) of one type of values and offsets: shapes that
+// differ in k or N alone go to them or to the kernels here, so the first launch of one here prepares them.
+template <typename VT, typename IT>
+constexpr int kStageGroup = 1 + (sizeof(VT) == 2 ? 1 : 0) + (sizeof(IT) == 2 ? 2 : 0);
+
 int spmm_launch_f32(int ch, int lpr, int u, int q, const SpmmArgs& a, const SpmmLaunch& l);
 int spmm_launch_f16(int ch, int lpr, int u, int q, const SpmmArgs& a, const SpmmLaunch& l);
 // 16-bit offsets (bs_spmm_wide.hip): both kernels, ch the widest chunk or 1
@@ -386,10 +391,10 @@ __global__ __launch_bounds__(1024) void spmm_few_kernel(SpmmArgs a) {
     spmm_body<VT, CH, LPR, U, Q, IT, true>(a);
 }
 
-template <auto KERNEL, auto SIBLING>
+template <auto KERNEL, auto SIBLING, int STAGE_GROUP>
 int spmm_launch_kernel(const SpmmArgs& a, const SpmmLaunch& l) {
-    if (l.lds > 48 * 1024) {
-        const int st_code = ensure_lds_limit(LdsKernelOf<KERNEL>::reg, l.st, &LdsKernelOf<SIBLING>::reg);
+    if (l.lds > kLdsWithoutLimit) {
+        const int st_code = ensure_lds_limit(LdsKernelOf<KERNEL>::reg, l.st, &LdsKernelOf<SIBLING>::reg, STAGE_GROUP);
         if (st_code != BS_OK) return st_code;
     }
     if (l.prepare_only) return BS_OK;
@@ -401,7 +406,8 @@ template <typename VT, int CH, int LPR, int U, int Q, typename IT = uint8_t>
 int spmm_launch_one(const SpmmArgs& a, const SpmmLaunch& l) {
     constexpr auto kern = spmm_kernel<VT, CH, LPR, U, Q, IT>;
     constexpr auto few = spmm_few_kernel<VT, CH, LPR, U, Q, IT>;
-    return a.copy == kCopyRegisters ? spmm_launch_kernel<few, kern>(a, l) : spmm_launch_kernel<kern, few>(a, l);
+    return a.copy == kCopyRegisters ? spmm_launch_kernel<few, kern, kStageGroup<VT, IT>>(a, l)
+                                    : spmm_launch_kernel<kern, few, kStageGroup<VT, IT>>(a, l);
 }
 
 template <typename VT, int CH, int LPR, int U>

@@ -260,8 +260,8 @@ __global__ __launch_bounds__(1024) void spmm_rows_kernel(SpmmArgs a) {
 template <typename VT, int CH, typename IT = uint8_t>
 int spmm_rows_launch_one(const SpmmArgs& a, const SpmmLaunch& l) {
     constexpr auto kern = spmm_rows_kernel<VT, CH, 4, IT>;
-    if (l.lds > 48 * 1024) {
-        const int st_code = ensure_lds_limit(LdsKernelOf<kern>::reg, l.st);
+    if (l.lds > kLdsWithoutLimit) {
+        const int st_code = ensure_lds_limit(LdsKernelOf<kern>::reg, l.st, nullptr, kStageGroup<VT, IT>);
         if (st_code != BS_OK) return st_code;
     }
     if (l.prepare_only) return BS_OK;

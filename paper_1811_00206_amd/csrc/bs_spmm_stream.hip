@@ -54,7 +54,7 @@ double rounding(const SpmmStreamPlan& p, int64_t nb, int k) {
 }  // namespace
 
 SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int max_slabs,
-                                double max_rounding) {
+                                int max_lds, double max_rounding) {
     SpmmStreamPlan best{};
     constexpr int ib = stream_banks(kP), rows = stream_rows(kP);
     if (k < kStreamMinK) return best;
@@ -75,10 +75,10 @@ SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int 
             if ((double)rpwg * nb * k * 4 > UINT32_MAX || (double)n_tiles * slabs * groups > INT32_MAX / 2) continue;
             for (int ks = 1; ks * row_waves <= kMaxWalkers && ks <= slab_groups; ks = ks < 4 ? ks + 1 : ks + ks / 2) {
                 // a stage holds a group of banks for each of the ks; two of them side by side
-                int64_t sg = std::min(slab_groups, (kMaxLdsBytes / 2 / group) / ks * ks);
+                int64_t sg = std::min(slab_groups, (max_lds / 2 / group) / ks * ks);
                 int bufs = sg >= slab_groups ? 1 : 2;
-                if (sg < 1 || (sg < slab_groups && slab_groups * group <= kMaxLdsBytes / 2)) {
-                    sg = std::min(slab_groups, (kMaxLdsBytes / group) / ks * ks);
+                if (sg < 1 || (sg < slab_groups && slab_groups * group <= std::min(max_lds, kMaxLdsBytes / 2))) {
+                    sg = std::min(slab_groups, (max_lds / group) / ks * ks);
                     bufs = 1;
                 }
                 if (sg < 1) continue;
@@ -90,7 +90,7 @@ SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int 
                 p.ksplit = ks; p.row_waves = (int)row_waves;
                 p.copy_waves = std::min(4, kWavesPerCu - ks * (int)row_waves);
                 p.lds_bytes = std::max<size_t>((size_t)bufs * p.buf_bytes, (size_t)(ks - 1) * row_waves * 1024);
-                if (p.lds_bytes > (size_t)kMaxLdsBytes) continue;
+                if (p.lds_bytes > (size_t)max_lds) continue;
                 p.ns = expected_ns(p, vsize, isize, M, K, bank, k, N, aligned);
                 if ((!best.ok || p.ns < best.ns) && rounding(p, nb, k) <= max_rounding) best = p;
             }

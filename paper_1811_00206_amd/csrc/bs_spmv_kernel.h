@@ -354,7 +354,7 @@ __global__ __launch_bounds__(1024) void spmv_kernel(SpmvArgs a) {
 template <typename VT, int CH, int LPR, int U, bool LSTM = false, typename IT = uint8_t>
 int spmv_launch_one(const SpmvArgs& a, const SpmvLaunch& l) {
     constexpr auto kern = spmv_kernel<VT, CH, LPR, U, LSTM, IT>;
-    if (l.lds > 48 * 1024) {
+    if (l.lds > kLdsWithoutLimit) {
         const int st_code = ensure_lds_limit(LdsKernelOf<kern>::reg, l.st);
         if (st_code != BS_OK) return st_code;
     }

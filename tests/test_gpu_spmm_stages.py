@@ -1,5 +1,9 @@
 """bs_spmm by the kernels that walk K in stages (csrc/bs_spmm_stream_kernel.h), at the sizes where they can
 go wrong, against float64 and against the oracle."""
+import pathlib
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -130,3 +134,57 @@ def test_a_capture_replays_what_the_eager_call_gives():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(Y, spmm(v, i, bank, X))
+
+
+# (M, K, bank, k, N): in stages
+STAGED = (400, 3264, 64, 33, 114)           # the tile kernel of this shape needs its LDS limit raised
+SMALL_TILE = (14019, 350, 50, 11, 36)       # ... and of this one not
+
+
+@pytest.mark.parametrize("first,captured,refused", [
+    (None, STAGED, True),                   # nothing has run: as bs.h says of a first use
+    (None, SMALL_TILE, False),              # nothing needs preparing
+    ((400, 656, 16, 3, 100), STAGED, False),    # the tile kernel of the captured shape has run, no stage kernel has
+    ((6000, 3000, 100, 10, 128), STAGED, True),  # another stage kernel has run, and another tile kernel's shape
+])
+def test_which_kernel_a_capture_records_does_not_depend_on_what_has_run(first, captured, refused):
+    """In a fresh process: a capture is refused, or records the kernel that the eager call launches."""
+    code = f"""
+import torch
+from paper_1811_00206_amd import binding as bs
+def product(M, K, bank, k, N):
+    W = torch.randn((M, K), device="cuda")
+    return *bs.bs_prune_pack(W, bank, k), bank, torch.randn((K, N), device="cuda")
+captured, first = {captured}, {first}
+torch.manual_seed(1)
+p = bs.bs_spmm_plan(bs.BS_F32, *captured)
+assert p["stages"] == 1 and (p["lds_bytes"] > 48 * 1024) == (captured == {STAGED})
+if first:
+    q = bs.bs_spmm_plan(bs.BS_F32, *first)
+    assert q["lds_bytes"] > 48 * 1024
+    assert {refused} or (q["stages"] == 0 and all(p[f] == q[f] for f in ("rows_kernel", "ch")))
+    bs.bs_spmm(*product(*first))
+args = product(*captured)
+Y = torch.full((captured[0], captured[4]), 7.0, device="cuda")
+torch.cuda.synchronize()
+g, status = torch.cuda.CUDAGraph(), 0
+with torch.cuda.graph(g):
+    Y.mul_(1.0)
+    try:
+        bs.bs_spmm(*args, out=Y)
+    except bs.BsError as e:
+        status = e.status
+for _ in range(3):
+    g.replay()
+    torch.cuda.synchronize()
+    Z = bs.bs_spmm(*args) if not {refused} else torch.full_like(Y, 7.0)
+    assert torch.equal(Y, Z)
+    if not {refused}:
+        Y.zero_()
+        args[3].normal_()
+print("RESULT", status)
+"""
+    print("captured", first, captured, flush=True)
+    out = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100,
+                         cwd=str(pathlib.Path(__file__).resolve().parent.parent))
+    assert out.returncode == 0 and f"RESULT {7 if refused else 0}\n" in out.stdout, out.stdout + out.stderr[-2000:]
