@@ -200,7 +200,7 @@ size_t bs_spmm_workspace_bytes(int dtype, int64_t M, int64_t K, int bank, int k,
  *   [22] stages held in LDS at once (1 or 2)   [23] LDS bytes of one
  *   [24] rows per workgroup   [25] row groups   [26] groups of wavefronts along K
  *   [27] wavefronts per such group   [28] wavefronts that copy X   [29] LDS bytes per workgroup
- *       (18 to 29 are 0 where [17] is and the shape was not looked at)
+ *       (18 to 29 are 0 where [17] is)
  * Returns BS_OK, or the status bs_spmm would return for an unsupported shape.
  */
 int bs_spmm_plan(int dtype, int64_t M, int64_t K, int bank, int k, int64_t N,

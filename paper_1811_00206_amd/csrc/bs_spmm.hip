@@ -233,11 +233,10 @@ SpmmStreamPlan stream_choice(const SpmmPlan& p, int vsize, int isize, int64_t M,
     if (tiles <= kStreamWorthNs) return {};
     // a product whose tile kernel needs no LDS limit raised can be captured as the first of all, so this one may not need it either
     const int max_lds = p.lds_bytes > kLdsWithoutLimit ? kMaxLdsBytes : (int)kLdsWithoutLimit;
-    SpmmStreamPlan sp = spmm_stream_plan(vsize, isize, M, K, bank, k, N, p.n_slabs, max_lds, tiles_rounding(p, K / bank, k));
-    double ns = sp.ns;
-    if ((int64_t)sp.n_tiles * sp.n_slabs * sp.row_groups > kCus) ns *= N % 4 == 0 ? kStreamManyAligned : kStreamManyUnaligned;
-    if (k > kStreamLongK) ns *= kStreamLongBank;
-    if (sp.ok && ns >= kStreamMargin * tiles) sp.ok = false;
+    const double max_ns = kStreamMargin * tiles / (k > kStreamLongK ? kStreamLongBank : 1.0);
+    const SpmmStreamPlan sp = spmm_stream_plan(vsize, isize, M, K, bank, k, N, p.n_slabs, max_lds, tiles_rounding(p, K / bank, k), max_ns);
+    const bool many = (int64_t)sp.n_tiles * sp.n_slabs * sp.row_groups > kCus;
+    if (sp.ok && many && sp.ns * (N % 4 == 0 ? kStreamManyAligned : kStreamManyUnaligned) >= max_ns) return {};
     return sp;
 }
 

@@ -12,87 +12,122 @@ constexpr int kP = 4;                        // pieces of 4 columns per tile
 constexpr int kCus = 256, kWavesPerCu = 16;  // wavefronts: by the kernels' registers
 constexpr int kMaxWalkers = 14;
 
-int64_t div_up(int64_t a, int64_t b) { return (a + b - 1) / b; }
+template <typename I>
+constexpr I div_up(I a, I b) { return (a + b - 1) / b; }
 
 // entries of a bank that a lane loads at once (the kernel's U)
 int unit_of(int isize, int k) { return isize == 2 ? (k < 8 ? 4 : 8) : k > kStreamMaxK ? 8 : k; }
 
 // Expected time of a launch in ns.  The terms are the kernel's own steps; their factors are a fit to
 // 1332 launches of random shapes and plans on MI355X (median error 6 %, 11 % rms).
-double expected_ns(const SpmmStreamPlan& p, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, bool aligned) {
-    const int walkers = p.ksplit * p.row_waves, waves = walkers + p.copy_waves;
-    const int64_t wgs = (int64_t)p.n_tiles * p.n_slabs * p.row_groups;
-    const int64_t slab_groups = div_up(std::min<int64_t>(p.slab_banks, K / bank), stream_banks(kP)), sg = p.sb / stream_banks(kP);
-    const int64_t stages = div_up(slab_groups, sg);
-    double per_cu = std::max<int64_t>(1, std::min<int64_t>({(int64_t)(kMaxLdsBytes / p.lds_bytes), kWavesPerCu / waves, div_up(wgs, kCus)}));
-    const double rounds = std::ceil(wgs / (kCus * per_cu));
-    // an entry costs a wavefront 66 ns by itself, and 13.7 ns for each that shares the compute unit
-    const double entry = std::max(66.0, 13.7 * walkers * per_cu) * (isize == 2 || k > kStreamMaxK ? 1.24 : 1.0);
-    const double unit = k * entry + 29.0 * std::max(1.0, walkers * per_cu / 4);
-    const double walk = std::ceil((double)std::min(sg, slab_groups) / p.ksplit) * unit;
-    const double tail = std::ceil((double)(slab_groups - (stages - 1) * sg) / p.ksplit) * unit;
-    const double group = (double)bank * kStreamPitch * per_cu * (aligned ? 1.0 : 1.57);
-    const double first = 874 + std::min(sg, slab_groups) * group / std::min(15.7 * waves * per_cu, 82.0);
-    const double copy = 874 + sg * group / std::min(15.7 * p.copy_waves * per_cu, 82.0);
-    double t = first + walk;
-    if (stages > 1) t = first + tail + (stages - 1) * (p.n_bufs == 2 ? std::max(walk, copy) : walk + copy);
-    t = 1670 + rounds * (t + 1800);
-    const double w_bytes = (double)M * (K / bank) * k * (vsize + isize), y_bytes = 4.0 * M * N;
-    t = std::max(t, 3000 + (w_bytes * std::min(p.n_tiles, 2) + 4.0 * K * N + y_bytes) / 3835);
-    if (p.n_slabs > 1) t += 2700 + 2.0 * p.n_slabs * y_bytes / 3750;
-    return t;
-}
+constexpr double kEntryAlone = 66.0, kEntryShared = 13.7;   // of an entry: a wavefront by itself, each that shares the compute unit
+constexpr double kLaunchNs = 1670, kRoundNs = 1800, kFirstCopyNs = 874, kUnitNs = 29;
+constexpr double kWaveCopyRate = 15.7, kCopyRate = 82.0;      // bytes per ns that a wavefront, a compute unit copies
+struct Expectation {
+    double slow, memory, slab;   // factor of an entry; what passing all operands once takes; the slab sums, per slab
+    double group;                // bytes of a group of banks, weighted by the way it is copied
+    int k;
+
+    Expectation(int vsize, int isize, int64_t M, int64_t K, int bank, int k_, int64_t N, int64_t n_tiles) : k(k_) {
+        const double w_bytes = (double)M * (K / bank) * k * (vsize + isize), y_bytes = 4.0 * M * N;
+        slow = isize == 2 || k > kStreamMaxK ? 1.24 : 1.0;
+        memory = 3000 + (w_bytes * std::min<int64_t>(n_tiles, 2) + 4.0 * K * N + y_bytes) / 3835;
+        slab = 2.0 * y_bytes / 3750;
+        group = (double)bank * kStreamPitch * (N % 4 == 0 ? 1.0 : 1.57);   // as in the usual X, whose rows are adjacent
+    }
+    double slabs(int n) const { return n > 1 ? 2700 + n * slab : 0.0; }
+    // No launch of so many slabs takes less, ...
+    double at_least(int n_slabs) const { return memory + slabs(n_slabs); }
+    // ... nor one of so many wavefronts side by side (as many entries and copies in all, whatever ks), ...
+    double at_least(int n_slabs, int slab_groups, int row_waves, double rounds, double per_cu) const {
+        const double walk = slab_groups * k * slow * row_waves * std::max(kEntryAlone / kMaxWalkers, kEntryShared * per_cu);
+        return total(n_slabs, rounds, std::max(walk, slab_groups * group * per_cu * (1.0 / kCopyRate)));
+    }
+    // ... nor with ks groups of those.
+    double at_least(int n_slabs, int slab_groups, int row_waves, double rounds, double per_cu, int ks) const {
+        const double unit = k * slow * std::max(kEntryAlone, kEntryShared * ks * row_waves * per_cu) + kUnitNs;
+        return total(n_slabs, rounds, ks * group * (1.0 / kCopyRate) + div_up(slab_groups, ks) * unit);
+    }
+    double total(int n_slabs, double rounds, double ns) const { return kLaunchNs + rounds * (kRoundNs + kFirstCopyNs + ns) + slabs(n_slabs); }
+    double operator()(const SpmmStreamPlan& p, int slab_groups, int wgs) const {
+        const int walkers = p.ksplit * p.row_waves, waves = walkers + p.copy_waves, sg = p.sb / stream_banks(kP), stages = div_up(slab_groups, sg);
+        const int per_cu = std::max(1, std::min({kMaxLdsBytes / (int)p.lds_bytes, kWavesPerCu / waves, div_up(wgs, kCus)}));
+        const double entry = std::max(kEntryAlone, kEntryShared * walkers * per_cu) * slow;
+        const double unit = k * entry + kUnitNs * std::max(1.0, walkers * per_cu / 4.0);
+        const double walk = div_up(std::min(sg, slab_groups), p.ksplit) * unit;
+        const double first = kFirstCopyNs + std::min(sg, slab_groups) * group * per_cu / std::min(kWaveCopyRate * waves * per_cu, kCopyRate);
+        double t = first + walk;
+        if (stages > 1) {
+            const double tail = div_up(slab_groups - (stages - 1) * sg, p.ksplit) * unit;
+            const double copy = kFirstCopyNs + sg * group * per_cu / std::min(kWaveCopyRate * p.copy_waves * per_cu, kCopyRate);
+            t = first + tail + (stages - 1) * (p.n_bufs == 2 ? std::max(walk, copy) : walk + copy);
+        }
+        return std::max(kLaunchNs + div_up(wgs, kCus * per_cu) * (t + kRoundNs), memory) + slabs(p.n_slabs);
+    }
+};
 
 // A lane adds its banks' entries of a stage, then the stages; then come the banks side by side, the wavefronts
 // along K and the slabs.
-double rounding(const SpmmStreamPlan& p, int64_t nb, int k) {
-    const int64_t groups = div_up(std::min<int64_t>(p.slab_banks, nb), stream_banks(kP)), sg = p.sb / stream_banks(kP);
-    return chain_rounding((double)k * div_up(std::min(sg, groups), p.ksplit), true) + chain_rounding((double)div_up(groups, sg), false) +
+double rounding(const SpmmStreamPlan& p, int slab_groups, int k) {
+    const int sg = p.sb / stream_banks(kP);
+    return chain_rounding((double)k * div_up(std::min(sg, slab_groups), p.ksplit), true) + chain_rounding(div_up(slab_groups, sg), false) +
            std::log2(stream_banks(kP)) + chain_rounding(p.ksplit, false) + chain_rounding(p.n_slabs, false);
 }
 
 }  // namespace
 
-SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int max_slabs,
-                                int max_lds, double max_rounding) {
+// This runs in every call, so most launches are passed over by what they take at least.  The planning of fc6 (4096 x 25088,
+// banks of 64) at N = 16 takes 0.9 us of host time instead of 2.9, of 3000 random products 0.37 instead of 0.65 in
+// the mean and 1.1 instead of 3.3 at the 99th percentile, the tile kernels' 0.17 included; the plans are the same.
+SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int max_slabs, int max_lds,
+                                double max_rounding, double max_ns) {
     SpmmStreamPlan best{};
     constexpr int ib = stream_banks(kP), rows = stream_rows(kP);
-    if (k < kStreamMinK) return best;
-    const bool aligned = N % 4 == 0;         // as in the usual X, whose rows are adjacent
-    const int64_t nb = K / bank;
-    const int64_t group = (int64_t)bank * kStreamPitch;
-    const int64_t n_tiles = div_up(N, 4 * kP);
+    const int64_t tiles = div_up(N, (int64_t)4 * kP);
+    if (k < kStreamMinK || tiles > INT32_MAX / 2) return best;
+    const int nb = (int)(K / bank), n_tiles = (int)tiles, group = bank * kStreamPitch;
+    const int fit = max_lds / group, fit_half = max_lds / 2 / group, fit_one = std::min(max_lds, kMaxLdsBytes / 2) / group;
+    if (fit < 1) return best;
+    const Expectation expected(vsize, isize, M, K, bank, k, N, tiles);
+    best.ns = max_ns;
     for (int s = 1; s <= max_slabs; s = s < 4 ? s + 1 : s + s / 2) {
-        const int64_t slab = div_up(div_up(nb, s), ib) * ib, slabs = div_up(nb, slab), slab_groups = slab / ib;
-        int64_t seen_waves = 0;
+        const int slab_groups = div_up(div_up(nb, s), ib), slabs = div_up(nb, slab_groups * ib);
+        if (expected.at_least(slabs) >= best.ns) break;          // more slabs take longer still
+        int seen_waves = 0, seen_rows = 0;
         for (int c = 1; c <= 4; ++c) {           // workgroups per compute unit to aim at
-            int64_t groups = std::max<int64_t>(1, (int64_t)kCus * c / (n_tiles * slabs));
-            const int64_t row_waves = std::min<int64_t>(div_up(div_up(M, groups), rows), 12);
-            const int64_t rpwg = std::min(div_up(M, groups), row_waves * rows);
-            if (row_waves * 4096 + rpwg == seen_waves) continue;
-            seen_waves = row_waves * 4096 + rpwg;
-            groups = div_up(M, rpwg);
+            const int target = (int)std::max<int64_t>(1, (int64_t)kCus * c / ((int64_t)n_tiles * slabs)), m = (int)div_up(M, (int64_t)target);
+            const int row_waves = std::min(div_up(m, rows), 12), rpwg = std::min(m, row_waves * rows);
+            if (row_waves == seen_waves && rpwg == seen_rows) continue;
+            seen_waves = row_waves;
+            seen_rows = rpwg;
+            const int groups = (int)div_up(M, (int64_t)rpwg);
             if ((double)rpwg * nb * k * 4 > UINT32_MAX || (double)n_tiles * slabs * groups > INT32_MAX / 2) continue;
+            const int wgs = n_tiles * slabs * groups;
+            // several stages fill more than half of LDS, whatever ks: one workgroup per compute unit at a time
+            const bool alone = slab_groups > fit_half && max_lds == kMaxLdsBytes;
+            const double rounds = alone ? div_up(wgs, kCus) : 1, per_cu = alone ? 1 : std::max(1.0, wgs * (1.0 / kCus));
+            if (expected.at_least(slabs, slab_groups, row_waves, rounds, per_cu) >= best.ns) continue;
             for (int ks = 1; ks * row_waves <= kMaxWalkers && ks <= slab_groups; ks = ks < 4 ? ks + 1 : ks + ks / 2) {
+                if (expected.at_least(slabs, slab_groups, row_waves, rounds, per_cu, ks) >= best.ns) continue;
                 // a stage holds a group of banks for each of the ks; two of them side by side
-                int64_t sg = std::min(slab_groups, (max_lds / 2 / group) / ks * ks);
+                int sg = std::min(slab_groups, fit_half / ks * ks);
                 int bufs = sg >= slab_groups ? 1 : 2;
-                if (sg < 1 || (sg < slab_groups && slab_groups * group <= std::min(max_lds, kMaxLdsBytes / 2))) {
-                    sg = std::min(slab_groups, (max_lds / group) / ks * ks);
+                if (sg < 1 || (sg < slab_groups && slab_groups <= fit_one)) {
+                    sg = std::min(slab_groups, fit / ks * ks);
                     bufs = 1;
                 }
                 if (sg < 1) continue;
                 SpmmStreamPlan p{};
                 p.ok = true;
-                p.n_tiles = (int)n_tiles; p.n_slabs = (int)slabs; p.slab_banks = (int)slab;
-                p.sb = (int)(sg * ib); p.n_bufs = bufs; p.buf_bytes = (int)(sg * group);
-                p.rows_per_wg = (int)rpwg; p.row_groups = (int)groups;
-                p.ksplit = ks; p.row_waves = (int)row_waves;
-                p.copy_waves = std::min(4, kWavesPerCu - ks * (int)row_waves);
+                p.n_tiles = n_tiles; p.n_slabs = slabs; p.slab_banks = slab_groups * ib;
+                p.sb = sg * ib; p.n_bufs = bufs; p.buf_bytes = sg * group;
+                p.rows_per_wg = rpwg; p.row_groups = groups;
+                p.ksplit = ks; p.row_waves = row_waves;
+                p.copy_waves = std::min(4, kWavesPerCu - ks * row_waves);
                 p.lds_bytes = std::max<size_t>((size_t)bufs * p.buf_bytes, (size_t)(ks - 1) * row_waves * 1024);
                 if (p.lds_bytes > (size_t)max_lds) continue;
-                p.ns = expected_ns(p, vsize, isize, M, K, bank, k, N, aligned);
-                if ((!best.ok || p.ns < best.ns) && rounding(p, nb, k) <= max_rounding) best = p;
+                p.ns = expected(p, slab_groups, wgs);
+                if (p.ns < best.ns && rounding(p, slab_groups, k) <= max_rounding) best = p;
             }
         }
     }

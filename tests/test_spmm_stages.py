@@ -1,12 +1,14 @@
 """The launches of the SpMM kernels that walk K in stages, checked on the host: every bank of X copied once to where
 it is read, every bank walked once, the same barriers in every wavefront, LDS within a compute unit's; and the
 generated code of every instantiation."""
+import ctypes
 import math
 import os
 import random
 import re
 import subprocess
 import tempfile
+import time
 from concurrent.futures import ThreadPoolExecutor
 
 import numpy as np
@@ -108,6 +110,26 @@ def test_the_timed_sizes_and_small_ones():
     # one tile of columns and more than 32 entries per bank; an X of more than 128 MB
     assert bs.bs_spmm_plan(bs.BS_F32, 700, 6144, 128, 33, 16)["stages"] == 0
     assert bs.bs_spmm_plan(bs.BS_F32, 512, 6400, 64, 16, 5001)["stages"] == 0
+
+
+@pytest.mark.parametrize("dtype,M,K,bank,k,N", [
+    (bs.BS_F16, 4096, 25088, 64, 6, 16), (bs.BS_F32, 879, 12400, 100, 8, 20), (bs.BS_F16, 108, 19125, 25, 10, 251)])
+def test_planning_many_slabs_costs_little(dtype, M, K, bank, k, N):
+    """Every call plans its launch.  In units of the tile kernels' planning alone (0.17 us on the development host):
+    16 to 32 if every launch is priced in full, 6 to 10 as it is."""
+    plan, out = bs.load_library().bs_spmm_plan, (ctypes.c_int64 * 30)()
+
+    def seconds(*shape):
+        best = math.inf
+        for _ in range(40):
+            t = time.perf_counter()
+            for _ in range(250):
+                plan(*shape, out, 30)
+            best = min(best, time.perf_counter() - t)
+        return best
+    call = seconds(dtype, M, K, bank, bank + 1, N)      # refused at once: what the call itself costs
+    tiles = seconds(dtype, M, K, bank, k, 8) - call
+    assert seconds(dtype, M, K, bank, k, N) - call < 14 * tiles
 
 
 def _chain(parts):
