@@ -242,7 +242,8 @@ int bs_spmm_static(const void* vals, const uint8_t* idx, int dtype, int64_t M, i
  *                       (bank % 4 == 0 for fp32, bank % 8 == 0 for binary16):
  *                       BS_ERR_UNSUPPORTED otherwise.
  *   bs_spmv_wide        K <= 40960 (x must fit LDS): BS_ERR_UNSUPPORTED beyond.
- *   bs_spmm_wide        workspace of bs_spmm_workspace_bytes_wide(...) bytes, as for bs_spmm.
+ *   bs_spmm_wide        workspace of bs_spmm_workspace_bytes_wide(...) bytes, as for bs_spmm;
+ *                       bs_spmm_plan_wide reports its launch as bs_spmm_plan does.
  */
 #define BS_WIDE_BANK_MAX 2048
 size_t bs_idx_bytes_wide(int64_t M, int64_t K, int bank, int k);
@@ -251,6 +252,8 @@ int bs_prune_pack_wide(const void* W, int dtype, int64_t M, int64_t K, int bank,
 int bs_spmv_wide(const void* vals, const uint16_t* idx, int dtype, int64_t M, int64_t K,
                  int bank, int k, const float* x, float* y, void* stream);
 size_t bs_spmm_workspace_bytes_wide(int dtype, int64_t M, int64_t K, int bank, int k, int64_t N);
+int bs_spmm_plan_wide(int dtype, int64_t M, int64_t K, int bank, int k, int64_t N,
+                      int64_t* out, int n_out);
 int bs_spmm_wide(const void* vals, const uint16_t* idx, int dtype, int64_t M, int64_t K,
                  int bank, int k, const float* X, int64_t N, int64_t ldx,
                  float* Y, int64_t ldy, void* workspace, size_t workspace_bytes, void* stream);

@@ -26,7 +26,7 @@ EXPORTS = (
     "bs_init", "bs_nnz", "bs_vals_bytes", "bs_idx_bytes", "bs_status_str", "bs_prune_pack", "bs_spmv",
     "bs_spmv_ex", "bs_spmv_plan", "bs_spmm_workspace_bytes", "bs_spmm_plan", "bs_spmm", "bs_spmm_static", "bs_spmm_static_limit", "bs_dense_gemv", "bs_dense_gemm",
     "bs_lstm_step", "bs_lstm_sequence", "bs_reprune",
-    "bs_idx_bytes_wide", "bs_prune_pack_wide", "bs_spmv_wide", "bs_spmm_workspace_bytes_wide", "bs_spmm_wide",
+    "bs_idx_bytes_wide", "bs_prune_pack_wide", "bs_spmv_wide", "bs_spmm_workspace_bytes_wide", "bs_spmm_plan_wide", "bs_spmm_wide",
 )
 
 
@@ -71,7 +71,9 @@ def load_library():
     lib.bs_spmm_workspace_bytes.argtypes = [i32, i64, i64, i32, i32, i64]
     lib.bs_spmm_workspace_bytes.restype = sz
     lib.bs_spmm_plan.argtypes = [i32, i64, i64, i32, i32, i64, ctypes.POINTER(ctypes.c_int64), i32]
-    lib.bs_spmm_plan.restype = i32
+    lib.bs_spmm_plan_wide.argtypes = lib.bs_spmm_plan.argtypes
+    for name in ("bs_spmm_plan", "bs_spmm_plan_wide"):
+        getattr(lib, name).restype = i32
     lib.bs_spmm.argtypes = [vp, vp, i32, i64, i64, i32, i32, vp, i64, i64, vp, i64, vp, sz, vp]
     lib.bs_spmm_static.argtypes = [vp, vp, i32, i64, i64, i32, i32, vp, i64, i64, vp, i64, vp]
     lib.bs_spmm_static_limit.argtypes = []
@@ -212,8 +214,17 @@ SPMM_PLAN_FIELDS = ("rows_kernel", "ch", "nl", "nt", "n_tiles", "sb", "n_slabs",
 
 def bs_spmm_plan(dtype: int, M: int, K: int, bank: int, k: int, N: int) -> dict:
     """The launch bs_spmm would make (host only).  Raises on an unsupported shape."""
+    return _spmm_plan("bs_spmm_plan", dtype, M, K, bank, k, N)
+
+
+def bs_spmm_plan_wide(dtype: int, M: int, K: int, bank: int, k: int, N: int) -> dict:
+    """The launch bs_spmm_wide would make (host only).  Raises on an unsupported shape."""
+    return _spmm_plan("bs_spmm_plan_wide", dtype, M, K, bank, k, N)
+
+
+def _spmm_plan(call: str, *shape) -> dict:
     out = (ctypes.c_int64 * len(SPMM_PLAN_FIELDS))()
-    _check(load_library().bs_spmm_plan(dtype, M, K, bank, k, N, out, len(SPMM_PLAN_FIELDS)), "bs_spmm_plan")
+    _check(getattr(load_library(), call)(*shape, out, len(SPMM_PLAN_FIELDS)), call)
     return dict(zip(SPMM_PLAN_FIELDS, (int(v) for v in out)))
 
 

@@ -337,16 +337,16 @@ size_t spmm_workspace_bytes(int dtype, int64_t M, int64_t K, int bank, int k, in
     return p.ok ? p.ws_bytes : 0;
 }
 
-int spmm_plan_describe(int dtype, int64_t M, int64_t K, int bank, int k, int64_t N, int64_t* out,
+int spmm_plan_describe(int dtype, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int64_t* out,
                        int n_out) {
     if (M > INT32_MAX / 4 || N > INT32_MAX / 4) return BS_ERR_UNSUPPORTED;
-    const SpmmPlan p = make_plan(dtype, M, K, bank, k, N);
+    const SpmmPlan p = make_plan(dtype, M, K, bank, k, N, isize);
     if (!p.ok || p.lds_bytes > (size_t)kMaxLdsBytes) return BS_ERR_UNSUPPORTED;
     const int64_t total = (int64_t)p.n_tiles * p.n_slabs * p.row_groups;
     if (total > INT32_MAX / 2) return BS_ERR_UNSUPPORTED;
     if (p.ws_bytes && M * N > (int64_t)UINT32_MAX) return BS_ERR_UNSUPPORTED;
     const int rows_per_pass = p.row_threads / (p.nl * p.lpr);
-    const SpmmStreamPlan sp = stream_choice(p, dtype == BS_F16 ? 2 : 4, 1, M, K, bank, k, N);
+    const SpmmStreamPlan sp = stream_choice(p, dtype == BS_F16 ? 2 : 4, isize, M, K, bank, k, N);
     const int64_t v[30] = {p.rows ? 1 : 0, p.ch, p.nl, p.nt, p.n_tiles, p.sb, p.n_slabs, p.lpr, p.u,
                            p.row_threads, p.rows_per_wg, p.row_groups,
                            (p.rows_per_wg + rows_per_pass - 1) / rows_per_pass,

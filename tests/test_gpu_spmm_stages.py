@@ -83,9 +83,39 @@ def test_a_product_has_the_same_bits_for_every_row_pitch(M, nb, bank, k, N, pitc
         assert torch.equal(spmm(v, i, bank, wide, out=out), Y)
 
 
+# both kernels of either type (k below 8, and from there on) with one stage, several in one half of LDS and several in two;
+# 640: a group of four banks fills LDS
+WIDE_SHAPES = [
+    (5, 3, 264, 17, 64, "f32"), (5, 5, 264, 17, 15, "f16"), (5, 7, 264, 5, 15, "f32"), (5, 7, 264, 7, 15, "f16"),
+    (5, 14, 400, 9, 1497, "f32"), (5, 14, 400, 8, 1497, "f16"), (5, 14, 400, 7, 1497, "f32"), (5, 14, 400, 6, 1497, "f16"),
+    (5, 31, 264, 33, 1000, "f32"), (5, 18, 264, 9, 1497, "f16"), (5, 31, 300, 5, 1000, "f32"), (5, 37, 264, 6, 1000, "f16"),
+    (5, 23, 512, 17, 15, "f16"), (100, 7, 640, 4, 1000, "f32"), (100, 7, 640, 4, 1000, "f16"), (351, 7, 512, 108, 1497, "f16"),
+]
+
+
+def test_the_16_bit_shapes_reach_every_kernel():
+    seen = set()
+    for M, nb, bank, k, N, dtype in WIDE_SHAPES:
+        p = bs.bs_spmm_plan_wide(bs.BS_F16 if dtype == "f16" else bs.BS_F32, M, nb * bank, bank, k, N)
+        assert p["stages"] == 1, (M, nb, bank, k, N, dtype)
+        seen.add((dtype, k < 8, min(p["stage_slab_banks"], nb) > p["stage_banks"], p["stage_bufs"]))
+    assert seen == {(d, few, s, b) for d in ("f32", "f16") for few in (True, False) for s, b in ((0, 1), (1, 1), (1, 2))}
+
+
+@pytest.mark.parametrize("M,nb,bank,k,N,dtype", WIDE_SHAPES)
+def test_16_bit_offsets_in_stages(M, nb, bank, k, N, dtype):
+    v, i, dense, g, spmm = _product(M, nb, bank, k, dtype, bank + k)
+    for pitch in (N, N + 4 - N % 4):
+        print("16-bit offsets in stages", M, nb, bank, k, N, dtype, pitch, flush=True)
+        X = torch.randn((nb * bank, pitch), generator=g, device="cuda")[:, :N]
+        _check(spmm(v, i, bank, X), dense, X.cpu().double(), nb * k)
+
+
 @pytest.mark.parametrize("bank,k,nb", [(512, 4, 9), (512, 7, 9), (600, 40, 6), (264, 9, 23)])
 @pytest.mark.parametrize("M,N", [(300, 200), (1000, 37)])
 def test_16_bit_offsets(bank, k, nb, M, N):
+    """Products of the same kind that stay on the tile kernels."""
+    assert bs.bs_spmm_plan_wide(bs.BS_F32, M, nb * bank, bank, k, N)["stages"] == 0
     print("16-bit offsets", bank, k, nb, M, N, flush=True)
     for dtype in ("f32", "f16"):
         v, i, dense, g, spmm = _product(M, nb, bank, k, dtype, bank + k)

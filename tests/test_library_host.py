@@ -82,6 +82,11 @@ def test_bad_arguments_are_refused_before_launch():
     assert lib.bs_spmm_plan(0, 4, 10, 4, 2, 4, out, 16) == 2             # K % bank
     assert lib.bs_spmm_plan(0, 4, 8, 4, 2, 0, out, 16) == 2              # N < 1
     assert lib.bs_spmm_plan(5, 4, 8, 4, 2, 4, out, 16) == 3              # dtype
+    assert lib.bs_spmm_plan(0, 4, 1024, 512, 2, 4, out, 16) == 3         # bank > 256
+    assert lib.bs_spmm_plan_wide(0, 4, 1024, 512, 2, 4, None, 16) == 1
+    assert lib.bs_spmm_plan_wide(0, 4, 1024, 500, 2, 4, out, 16) == 2
+    assert lib.bs_spmm_plan_wide(0, 4, 8192, 4096, 2, 4, out, 16) == 3   # bank > BS_WIDE_BANK_MAX
+    assert lib.bs_spmm_plan_wide(0, 4, 1024, 512, 2, 4, out, 16) == 0
     # LSTM step and pruning round: shape rules of their own
     assert lib.bs_lstm_step(p, p, 0, 6, 8, 2, 1, p, p, p, p, p, p, null) == 3       # H % 4
     assert lib.bs_lstm_step(p, p, 0, 8, 8, 2, 1, p, p, p, p, p, p, null) == 3       # h_out == h_in

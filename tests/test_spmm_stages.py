@@ -97,6 +97,27 @@ def test_launches_of_random_shapes():
     assert taken > 500
 
 
+def test_launches_of_random_shapes_with_16_bit_offsets():
+    rng = random.Random(1811)
+    taken = 0
+    for n in range(3000):
+        dtype = rng.choice([bs.BS_F32, bs.BS_F16])
+        bank = rng.choice([264, 320, 400, 512, 600, 640, 648, 1024])
+        nb = rng.choice([1, 2, 3, 5, 7, 9, 14, 18, 31, 37])
+        k = rng.choice([*range(1, 18), 20, 33, 64, 128])
+        M = rng.choice([1, 5, 37, 94, 351, 1111, 6000, 16384])
+        N = rng.choice([8, 9, 15, 33, 64, 100, 784, 1000, 1497])
+        try:
+            p = bs.bs_spmm_plan_wide(dtype, M, nb * bank, bank, k, N)
+        except bs.BsError:
+            continue
+        if p["stages"]:
+            assert N > 8 and k >= 4 and bank <= 640     # four banks of 640 fill LDS
+            taken += 1
+            _check(p, M, nb, bank, k, N, n % 12 == 0)
+    assert taken > 150
+
+
 def test_the_timed_sizes_and_small_ones():
     for M, K, bank, k, N, dtype in [(6000, 3000, 100, 10, 128, bs.BS_F32), (6000, 3000, 50, 15, 37, bs.BS_F32),
                                     (512, 4608, 64, 16, 784, bs.BS_F32), (4096, 25088, 64, 6, 16, bs.BS_F16),
