@@ -8,7 +8,6 @@
 namespace bs {
 namespace {
 
-constexpr int kP = 4;                        // pieces of 4 columns per tile
 constexpr int kCus = 256, kWavesPerCu = 16;  // wavefronts: by the kernels' registers
 constexpr int kMaxWalkers = 14;
 
@@ -50,7 +49,7 @@ struct Expectation {
     }
     double total(int n_slabs, double rounds, double ns) const { return kLaunchNs + rounds * (kRoundNs + kFirstCopyNs + ns) + slabs(n_slabs); }
     double operator()(const SpmmStreamPlan& p, int slab_groups, int wgs) const {
-        const int walkers = p.ksplit * p.row_waves, waves = walkers + p.copy_waves, sg = p.sb / stream_banks(kP), stages = div_up(slab_groups, sg);
+        const int walkers = p.ksplit * p.row_waves, waves = walkers + p.copy_waves, sg = p.sb / kStreamBanks, stages = div_up(slab_groups, sg);
         const int per_cu = std::max(1, std::min({kMaxLdsBytes / (int)p.lds_bytes, kWavesPerCu / waves, div_up(wgs, kCus)}));
         const double entry = std::max(kEntryAlone, kEntryShared * walkers * per_cu) * slow;
         const double unit = k * entry + kUnitNs * std::max(1.0, walkers * per_cu / 4.0);
@@ -69,9 +68,9 @@ struct Expectation {
 // A lane adds its banks' entries of a stage, then the stages; then come the banks side by side, the wavefronts
 // along K and the slabs.
 double rounding(const SpmmStreamPlan& p, int slab_groups, int k) {
-    const int sg = p.sb / stream_banks(kP);
+    const int sg = p.sb / kStreamBanks;
     return chain_rounding((double)k * div_up(std::min(sg, slab_groups), p.ksplit), true) + chain_rounding(div_up(slab_groups, sg), false) +
-           std::log2(stream_banks(kP)) + chain_rounding(p.ksplit, false) + chain_rounding(p.n_slabs, false);
+           std::log2(kStreamBanks) + chain_rounding(p.ksplit, false) + chain_rounding(p.n_slabs, false);
 }
 
 }  // namespace
@@ -82,8 +81,8 @@ double rounding(const SpmmStreamPlan& p, int slab_groups, int k) {
 SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int max_slabs, int max_lds,
                                 double max_rounding, double max_ns) {
     SpmmStreamPlan best{};
-    constexpr int ib = stream_banks(kP), rows = stream_rows(kP);
-    const int64_t tiles = div_up(N, (int64_t)4 * kP);
+    constexpr int ib = kStreamBanks, rows = kStreamRows;
+    const int64_t tiles = div_up(N, (int64_t)kStreamColumns);
     if (k < kStreamMinK || tiles > INT32_MAX / 2) return best;
     const int nb = (int)(K / bank), n_tiles = (int)tiles, group = bank * kStreamPitch;
     const int fit = max_lds / group, fit_half = max_lds / 2 / group, fit_one = std::min(max_lds, kMaxLdsBytes / 2) / group;
@@ -155,7 +154,7 @@ int spmm_stream_launch(const SpmmStreamPlan& p, const SpmmArgs& t, int dtype, in
     a.magic_sb = magic_u32(p.sb);
     a.magic_rw = magic_u32(p.row_waves);
     // the direct copies' 32-bit offsets inside a group of banks
-    a.by_registers = t.ldx % 4 != 0 || (double)(stream_banks(kP) * t.B + 4) * (double)t.ldx * 4 > INT32_MAX;
+    a.by_registers = t.ldx % 4 != 0 || (double)(kStreamBanks * t.B + 4) * (double)t.ldx * 4 > INT32_MAX;
     a.vec_out = t.vec_out;
     const SpmmLaunch l{64 * (p.ksplit * p.row_waves + p.copy_waves), p.lds_bytes, st, false};
     if (isize == 2) return spmm_stream_launch_wide(dtype, a, l);

@@ -31,13 +31,14 @@
 
 namespace bs {
 
-// SpmmStream layout.  A tile is 4*P columns of X.  In LDS the same row of 16/P banks lies side by side in 256 bytes, the
-// width of the 64 LDS banks.  A lane owns one bank of a row of W and reads the P pieces of 16 bytes
-// of an entry's row of X; of 16 neighbouring lanes, 16/P work on different banks and P on different
+// SpmmStream layout.  A tile is 16 columns of X: four pieces of 16 bytes.  In LDS the same row of four banks lies side by
+// side in 256 bytes, the width of the 64 LDS banks.  A lane owns one bank of a row of W and reads the four pieces
+// of an entry's row of X; of 16 neighbouring lanes, four work on different banks and four on different
 // rows of W, which start at different pieces: every read touches each LDS bank once, whatever
 // the offsets.
-constexpr int stream_banks(int p) { return 16 / p; }     // banks side by side = lanes per row of W
-constexpr int stream_rows(int p) { return 4 * p; }       // rows of W per wavefront
+constexpr int kStreamPieces = 4, kStreamColumns = 4 * kStreamPieces;
+constexpr int kStreamBanks = 16 / kStreamPieces;         // banks side by side = lanes per row of W
+constexpr int kStreamRows = kWave / kStreamBanks;        // rows of W per wavefront
 constexpr int kStreamPitch = 256;
 constexpr int kStreamMinK = 4;    // the fewest entries per bank (a word of byte offsets)
 constexpr int kStreamMaxK = 16;   // up to here the kernel knows k at compile time
@@ -54,7 +55,7 @@ struct SpmmStreamArgs {
     int64_t slab_stride;   // M*N for the workspace, 0 for Y
     int M, K, B, k, N;
     int nb;
-    int n_tiles;           // tiles of 4*P columns
+    int n_tiles;           // tiles of 16 columns
     int slab_banks, n_slabs;   // banks of K per workgroup
     int sb;                // banks per stage
     int n_bufs;            // halves of LDS: 2, or 1 where only one stage's tile fits
@@ -127,12 +128,11 @@ struct EntryWords {
 // LDS operations of this wavefront are finished (its direct-to-LDS loads are not among them)
 __device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xc07f); }
 
-// One stage's banks of X (`banks` from bank `bank0`; columns n0 .. n0+4*P) to LDS, by the `waves`
+// One stage's banks of X (`banks` from bank `bank0`; columns n0 .. n0+16) to LDS, by the `waves`
 // copying wavefronts: four LDS rows at a time.
-template <int P>
 __device__ __forceinline__ void spmm_stream_copy(const SpmmStreamArgs& a, char* dst, int bank0, int banks, int n0, int ntw,
                                                  int wave, int waves, int lane) {
-    constexpr int kBanks = stream_banks(P);
+    constexpr int P = kStreamPieces, kBanks = kStreamBanks;
     const int B = a.B;
     const int p = (lane & 15) / P, c = lane & (P - 1), lrow = lane >> 4;
     const int groups = (banks + kBanks - 1) / kBanks, spare = groups * kBanks - banks;
@@ -223,16 +223,15 @@ __device__ __forceinline__ float stream_value(const EntryWords<VT, U>& v, int i)
 
 // Entries E0 .. U-1 of the unit, the gathers of D entries ahead of the multiply-adds (left to itself
 // the compiler waits for each gather by itself).
-template <int P>
-__device__ __forceinline__ void spmm_stream_gather(uint32_t at, SpmmAcc (&x)[P]) {
+__device__ __forceinline__ void spmm_stream_gather(uint32_t at, SpmmAcc (&x)[kStreamPieces]) {
 #pragma unroll
-    for (int j = 0; j < P; ++j) x[j] = *reinterpret_cast<LdsFour*>(at ^ (16u * j));
+    for (int j = 0; j < kStreamPieces; ++j) x[j] = *reinterpret_cast<LdsFour*>(at ^ (16u * j));
 }
-template <typename VT, typename IT, int U, int P, int D, int E0>
-__device__ __forceinline__ void spmm_stream_walk(uint32_t base, const EntryWords<VT, U>& v, const StreamOffsets<IT, U>& o, SpmmAcc (&acc)[P]) {
-    SpmmAcc x[D][P];
+template <typename VT, typename IT, int U, int D, int E0>
+__device__ __forceinline__ void spmm_stream_walk(uint32_t base, const EntryWords<VT, U>& v, const StreamOffsets<IT, U>& o, SpmmAcc (&acc)[kStreamPieces]) {
+    SpmmAcc x[D][kStreamPieces];
 #pragma unroll
-    for (int e = E0; e < E0 + D && e < U; ++e) spmm_stream_gather<P>(o.address(e, base), x[(e - E0) % D]);
+    for (int e = E0; e < E0 + D && e < U; ++e) spmm_stream_gather(o.address(e, base), x[(e - E0) % D]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int e = E0; e < U; ++e) {
@@ -240,33 +239,33 @@ __device__ __forceinline__ void spmm_stream_walk(uint32_t base, const EntryWords
         uint32_t at = 0;
         if (e + D < U) at = o.address(e + D, base);   // its result cannot be used at once
 #pragma unroll
-        for (int j = 0; j < P; ++j)
+        for (int j = 0; j < kStreamPieces; ++j)
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[j][i ^ 1] = fmaf(w, x[(e - E0) % D][j][i], acc[j][i ^ 1]);
         __builtin_amdgcn_sched_barrier(0);
         if (e + D < U) {
-            spmm_stream_gather<P>(at, x[(e - E0) % D]);
+            spmm_stream_gather(at, x[(e - E0) % D]);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
 }
 // ... of which the last n (1 .. U) count: known only at run time, the same for every lane
-template <typename VT, typename IT, int U, int P, int D, int LO, int HI>
-__device__ __forceinline__ void spmm_stream_walk_n(uint32_t base, const EntryWords<VT, U>& v, const StreamOffsets<IT, U>& o, int n, SpmmAcc (&acc)[P]) {
+template <typename VT, typename IT, int U, int D, int LO, int HI>
+__device__ __forceinline__ void spmm_stream_walk_n(uint32_t base, const EntryWords<VT, U>& v, const StreamOffsets<IT, U>& o, int n, SpmmAcc (&acc)[kStreamPieces]) {
     if constexpr (LO == HI) {
-        spmm_stream_walk<VT, IT, U, P, D, U - LO>(base, v, o, acc);
+        spmm_stream_walk<VT, IT, U, D, U - LO>(base, v, o, acc);
     } else {
         constexpr int kMid = (LO + HI + 1) / 2;
-        if (n >= kMid) spmm_stream_walk_n<VT, IT, U, P, D, kMid, HI>(base, v, o, n, acc);
-        else spmm_stream_walk_n<VT, IT, U, P, D, LO, kMid - 1>(base, v, o, n, acc);
+        if (n >= kMid) spmm_stream_walk_n<VT, IT, U, D, kMid, HI>(base, v, o, n, acc);
+        else spmm_stream_walk_n<VT, IT, U, D, LO, kMid - 1>(base, v, o, n, acc);
     }
 }
 
 // KC = k, or -U for any k >= U, walked in units of U entries.
-template <typename VT, typename IT, int KC, int P>
+template <typename VT, typename IT, int KC>
 __global__ __launch_bounds__(1024) void spmm_stream_kernel(SpmmStreamArgs a) {
     extern __shared__ __align__(16) char Xs[];
-    constexpr int U = stream_unit(KC), kBanks = stream_banks(P), kRows = stream_rows(P);
+    constexpr int U = stream_unit(KC), P = kStreamPieces, kBanks = kStreamBanks;
     constexpr int kRing = U > 4 ? 2 : 4;         // units in flight per lane
     constexpr int kAhead = U * sizeof(VT) > 48 || KC < 0 ? 2 : 3;   // gathered entries in flight
     using VR = EntryWords<VT, U>;
@@ -283,7 +282,7 @@ __global__ __launch_bounds__(1024) void spmm_stream_kernel(SpmmStreamArgs a) {
     const int z = a.tiles_fast ? wi : wo, g = a.tiles_fast ? wo : wi;
 
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int n0 = z * 4 * P, ntw = min(4 * P, a.N - n0);
+    const int n0 = z * kStreamColumns, ntw = min(kStreamColumns, a.N - n0);
     const int bank0 = s * a.slab_banks, banks = min(a.slab_banks, a.nb - bank0);
     const int stages = (int)div_magic((uint32_t)(banks + a.sb - 1), (uint32_t)a.sb, a.magic_sb);
     const int row_waves = a.row_waves;
@@ -293,7 +292,7 @@ __global__ __launch_bounds__(1024) void spmm_stream_kernel(SpmmStreamArgs a) {
     const int wr = wave - kq * row_waves;
     const int p = lane & (kBanks - 1), turn = (lane & 15) / kBanks;   // bank of a group; which piece comes first
     const int r0 = g * a.rows_per_wg, r_end = min(a.M, r0 + a.rows_per_wg);
-    const int row = r0 + wr * kRows + (lane >> 4) * P + turn;
+    const int row = r0 + wr * kStreamRows + (lane >> 4) * P + turn;
     const int k = KC > 0 ? KC : a.k;
     const int groups = (banks + kBanks - 1) / kBanks, spare = groups * kBanks - banks;
     const char* vbase = static_cast<const char*>(a.vals) + ((size_t)r0 * a.nb + bank0) * k * sizeof(VT);
@@ -319,7 +318,7 @@ __global__ __launch_bounds__(1024) void spmm_stream_kernel(SpmmStreamArgs a) {
         for (int u = 0; u < kRing; ++u) issue(vr[u], ir[u]);
     }
     pin_order();
-    spmm_stream_copy<P>(a, Xs, bank0, min(a.sb, banks), n0, ntw, wave, (int)(blockDim.x >> 6), lane);
+    spmm_stream_copy(a, Xs, bank0, min(a.sb, banks), n0, ntw, wave, (int)(blockDim.x >> 6), lane);
     pin_order();
     wait_vm_and_lds<0>();
     __builtin_amdgcn_s_barrier();
@@ -328,7 +327,7 @@ __global__ __launch_bounds__(1024) void spmm_stream_kernel(SpmmStreamArgs a) {
         for (int st = 1; st < stages; ++st) {
             if (a.n_bufs == 1) __builtin_amdgcn_s_barrier();
             const int b0 = st * a.sb;
-            spmm_stream_copy<P>(a, Xs + (a.n_bufs == 2 && (st & 1) ? a.buf_bytes : 0), bank0 + b0, min(a.sb, banks - b0), n0, ntw,
+            spmm_stream_copy(a, Xs + (a.n_bufs == 2 && (st & 1) ? a.buf_bytes : 0), bank0 + b0, min(a.sb, banks - b0), n0, ntw,
                                 wave - walkers, (int)(blockDim.x >> 6) - walkers, lane);
             pin_order();
             wait_vm_and_lds<0>();
@@ -367,8 +366,8 @@ __global__ __launch_bounds__(1024) void spmm_stream_kernel(SpmmStreamArgs a) {
                 const StreamOffsets<IT, U> o(ir[u]);
                 const uint32_t base = lds0 + (buf + (uint32_t)(gi - stage_g0) * group_bytes);
                 if (gi < groups - 1 || p < kBanks - spare) {
-                    if (KC > 0 || r + 1 < a.rounds) spmm_stream_walk<VT, IT, U, P, kAhead, 0>(base, vr[u], o, acc);
-                    else if constexpr (KC <= 0) spmm_stream_walk_n<VT, IT, U, P, kAhead, 1, U>(base, vr[u], o, a.last, acc);
+                    if (KC > 0 || r + 1 < a.rounds) spmm_stream_walk<VT, IT, U, kAhead, 0>(base, vr[u], o, acc);
+                    else if constexpr (KC <= 0) spmm_stream_walk_n<VT, IT, U, kAhead, 1, U>(base, vr[u], o, a.last, acc);
                 }
             }
             pin_order();
@@ -381,21 +380,17 @@ __global__ __launch_bounds__(1024) void spmm_stream_kernel(SpmmStreamArgs a) {
     for (int j = 0; j < P; ++j) tot[j] += acc[j];
     while (st + 1 < stages) next_stage();
 
-    // the banks of a row, then one piece (or P / banks of them) per lane
-    constexpr int kOwn = P > kBanks ? P / kBanks : 1;
+    // the sums of a row's four lanes, then one piece per lane
+    static_assert(P == kBanks, "as many pieces as lanes of a row");
 #pragma unroll
     for (int j = 0; j < P; ++j)
 #pragma unroll
         for (int i = 0; i < 4; ++i) tot[j][i] = group_sum<kBanks>(tot[j][i]);
-    SpmmAcc mine[kOwn];
+    SpmmAcc t = tot[0];
 #pragma unroll
-    for (int m = 0; m < kOwn; ++m) {
-        SpmmAcc t = tot[m];
-#pragma unroll
-        for (int j = 1; j < P; ++j)
-            if (j == p * kOwn + m) t = tot[j];
-        mine[m] = SpmmAcc{t[1], t[0], t[3], t[2]};
-    }
+    for (int j = 1; j < P; ++j)
+        if (j == p) t = tot[j];
+    SpmmAcc mine = {t[1], t[0], t[3], t[2]};
     if (a.ksplit > 1) {
         SpmmAcc* part = reinterpret_cast<SpmmAcc*>(Xs);
         const int at = wr * kWave + lane, per = row_waves * kWave;
@@ -403,39 +398,30 @@ __global__ __launch_bounds__(1024) void spmm_stream_kernel(SpmmStreamArgs a) {
         wait_lds();
         __builtin_amdgcn_s_barrier();
         pin_order();
-        if (kq > 0) {
-#pragma unroll
-            for (int m = 0; m < kOwn; ++m) part[((kq - 1) * kOwn + m) * per + at] = mine[m];
-        }
+        if (kq > 0) part[(kq - 1) * per + at] = mine;
         pin_order();
         wait_lds();
         __builtin_amdgcn_s_barrier();
         pin_order();
         if (kq > 0) return;
-        for (int o = 0; o + 1 < a.ksplit; ++o) {
-#pragma unroll
-            for (int m = 0; m < kOwn; ++m) mine[m] += part[(o * kOwn + m) * per + at];
-        }
+        for (int o = 0; o + 1 < a.ksplit; ++o) mine += part[o * per + at];
     }
-    if (row < r_end && p * kOwn < P) {
+    if (row < r_end) {
         float* dst = a.out + (size_t)s * a.slab_stride + (size_t)row * a.ld_out + n0;
+        const int c = (p ^ turn) * 4;
+        if (a.vec_out && c + 4 <= ntw) {
+            *reinterpret_cast<SpmmAcc*>(dst + c) = mine;
+        } else {
 #pragma unroll
-        for (int m = 0; m < kOwn; ++m) {
-            const int c = ((p * kOwn + m) ^ turn) * 4;
-            if (a.vec_out && c + 4 <= ntw) {
-                *reinterpret_cast<SpmmAcc*>(dst + c) = mine[m];
-            } else {
-#pragma unroll
-                for (int n = 0; n < 4; ++n)
-                    if (c + n < ntw) dst[c + n] = mine[m][n];
-            }
+            for (int n = 0; n < 4; ++n)
+                if (c + n < ntw) dst[c + n] = mine[n];
         }
     }
 }
 
-template <typename VT, typename IT, int KC, int P>
+template <typename VT, typename IT, int KC>
 int spmm_stream_launch_one(const SpmmStreamArgs& a, const SpmmLaunch& l) {
-    constexpr auto kern = spmm_stream_kernel<VT, IT, KC, P>;
+    constexpr auto kern = spmm_stream_kernel<VT, IT, KC>;
     if (l.lds > kLdsWithoutLimit) {
         const int st_code = ensure_lds_limit(LdsKernelOf<kern, kStageGroup<VT, IT>>::reg, l.st);
         if (st_code != BS_OK) return st_code;
@@ -447,9 +433,9 @@ int spmm_stream_launch_one(const SpmmStreamArgs& a, const SpmmLaunch& l) {
 template <typename VT, typename IT, int KC = kStreamMaxK>
 int spmm_stream_launch_k(const SpmmStreamArgs& a, const SpmmLaunch& l) {
     if constexpr (KC == kStreamMaxK) {
-        if (a.k > KC) return spmm_stream_launch_one<VT, IT, -8, 4>(a, l);
+        if (a.k > KC) return spmm_stream_launch_one<VT, IT, -8>(a, l);
     }
-    if (a.k == KC) return spmm_stream_launch_one<VT, IT, KC, 4>(a, l);
+    if (a.k == KC) return spmm_stream_launch_one<VT, IT, KC>(a, l);
     if constexpr (KC > kStreamMinK) return spmm_stream_launch_k<VT, IT, KC - 1>(a, l);
     return BS_ERR_UNSUPPORTED;
 }

@@ -5,7 +5,7 @@ namespace bs {
 namespace {
 template <typename VT>
 int launch_wide(const SpmmStreamArgs& a, const SpmmLaunch& l) {
-    return a.k < 8 ? spmm_stream_launch_one<VT, uint16_t, -4, 4>(a, l) : spmm_stream_launch_one<VT, uint16_t, -8, 4>(a, l);
+    return a.k < 8 ? spmm_stream_launch_one<VT, uint16_t, -4>(a, l) : spmm_stream_launch_one<VT, uint16_t, -8>(a, l);
 }
 }  // namespace
 int spmm_stream_launch_wide(int dtype, const SpmmStreamArgs& a, const SpmmLaunch& l) {
