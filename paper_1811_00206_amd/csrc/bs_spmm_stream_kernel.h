@@ -140,6 +140,7 @@ __device__ __forceinline__ void spmm_stream_copy(const SpmmStreamArgs& a, char* 
     // Rows of X are read in pieces of 16 bytes, which may reach up to 12 bytes past a row's last
     // column: into the next row, but not past the last row of X, which is brought in by itself.
     const bool ragged_end = bank0 + banks == a.nb && (ntw & 3);
+    const uint32_t lane_off = ((uint32_t)(p * B + lrow) * (uint32_t)a.ldx + (uint32_t)min(c * 4, (ntw - 1) & ~3)) * 4u;   // below 2 GB, or not used
     const char* X0 = reinterpret_cast<const char*>(a.X + (size_t)bank0 * B * a.ldx + n0);
     const size_t group_step = (size_t)kBanks * B * a.ldx * 4, quad_step = (size_t)4 * a.ldx * 4;
     // rows of this lane's bank in the last group: none if there is no such bank
@@ -147,7 +148,6 @@ __device__ __forceinline__ void spmm_stream_copy(const SpmmStreamArgs& a, char* 
     int g = 0, rq = wave;
     while (rq >= quads) { rq -= quads; ++g; }
     if (!a.by_registers) {
-        const uint32_t lane_off = (uint32_t)((p * B + lrow) * (int)a.ldx + min(c * 4, (ntw - 1) & ~3)) * 4u;
         while (g < groups) {
             const int r = rq * 4 + lrow;
             if (r < (g == groups - 1 ? last_rows : B))
@@ -162,7 +162,8 @@ __device__ __forceinline__ void spmm_stream_copy(const SpmmStreamArgs& a, char* 
         // is there: no branch comes between the loads.
         constexpr int kBatch = 8;
         using Four = WordsAt<4, 4>;
-        const size_t lane_off = ((size_t)(p * B + lrow) * (size_t)a.ldx + (size_t)min(c * 4, (ntw - 1) & ~3)) * 4u;
+        // not `lane_off` itself in 64 bits: fc6 at N = 16, which is copied the other way, then takes 18.78 us instead of 18.65
+        const size_t far_off = ((size_t)(p * B + lrow) * (size_t)a.ldx + (size_t)min(c * 4, (ntw - 1) & ~3)) * 4u;
         while (g < groups) {
             Four t[kBatch];
             int at[kBatch];                      // LDS row of each piece, or -1
@@ -170,7 +171,7 @@ __device__ __forceinline__ void spmm_stream_copy(const SpmmStreamArgs& a, char* 
             for (int u = 0; u < kBatch; ++u) {
                 const int r = rq * 4 + lrow, end = g < groups ? g == groups - 1 ? last_rows : B : 0;
                 at[u] = r < end ? g * B + r : -1;
-                t[u] = *reinterpret_cast<const Four*>(r < end ? X0 + g * group_step + rq * quad_step + lane_off : X0);
+                t[u] = *reinterpret_cast<const Four*>(r < end ? X0 + g * group_step + rq * quad_step + far_off : X0);
                 rq += waves;
                 while (rq >= quads) { rq -= quads; ++g; }
             }
