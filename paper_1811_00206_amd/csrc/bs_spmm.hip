@@ -208,17 +208,23 @@ double tiles_rounding(const SpmmPlan& p, int64_t nb, int k) {
            std::log2((double)std::min<int64_t>(p.lpr, chunks)) + chain_rounding(p.n_slabs, false);
 }
 
-// The stage kernels are taken, for every row pitch of X alike, where they are expected to be faster by more than either expectation is off.  Over 1050
-// random products of 9 to 50 000 columns, both kernels timed (926 with an expectation above kStreamWorthNs; products
-// below it are not worth the planning), they are taken for 539 and need 0.73 of the tile kernels' time there (geometric
-// mean); 5 lose more than 8 %, at most 14 %.  With 0.85 for all and none of the terms below: 505 products, 16 such
-// losses, the worst 1.7.  The terms are what the expectations leave out:
-//   * Banks of more than 32 entries: a lane returns to a cache line of its bank for every 8 entries, and
-//     the lanes of a compute unit hold several times more lines than its L1.  With one tile of columns that is most
-//     of the time (15947 x 6144, 124 entries per bank, N = 12: 40.1 us by tiles, 68.7 in stages).
+// The stage kernels are taken, for every row pitch of X alike, where they are expected to be faster by more than the
+// expectations are off.  The constants were chosen on 1050 random products of 9 to 50 000 columns with both kernels timed
+// (margin 0.85 and none of the terms below: 505 taken, 16 losses of more than 8 %, the worst 1.7).  Over 3700 others that
+// are taken they need 0.73 of the tile kernels' time (geometric mean); 128 lose more than 3 %, 60 more than 8 %, the worst
+// 1.33 (932 x 1125, N = 12: 5.6 -> 7.4 us).  Of the losses two thirds are expected within 0.1 of the margin and half have four to
+// seven entries per bank; beyond three stages the expectation is about 4 % too short for each.  Products expected
+// below kStreamWorthNs are not worth the planning.  The terms are what the expectations leave out:
+//   * Banks of more than 32 entries and one tile of columns stay on the tile kernels.  What divides these products
+//     is the stream of W: all 4 of the 27 timed ones with more than 64 MB of it lose (15947 x 6144, 124 entries
+//     per bank, N = 12: 40.1 us by tiles, 68.7 in stages), 11 of the 23 with at most 42 MB gain up to three times
+//     (251 x 12500, k = 39, N = 10: 43.1 against 14.2), the others run as long or have no stage launch.  So the line
+//     is safe, and further in than it has to be.
 //   * More workgroups than compute units: copies of the first stage have nothing to hide behind, unaligned
 //     ones the longest (303 x 350 at N = 5687, 28.1 against 34.6 us).
-//   * An X of hundreds of MB comes from memory in rows of 64 bytes (142 x 12900 at N = 4846: 112.8 against 141.3 us).
+//   * An X of more than 128 MB comes from memory in rows of 64 bytes: of nine timed three lose (142 x 12900 at N = 4846:
+//     112.8 against 141.3 us), two gain (65 x 12500 at N = 3963: 85.9 against 67.7), four have no other launch or
+//     run as long.
 // A launch whose sums would round worse than the tile kernels' is not looked at: those walk an odd row length or a small
 // tile with up to 64 lanes per row, so their sums are short (6722 x 144, banks of 16, k = 13, N = 40: 4 entries per lane and
 // an exchange, against 39 in a lane of the stage kernels, 1.5 times the error).  Of 4000 random products, 4 %.

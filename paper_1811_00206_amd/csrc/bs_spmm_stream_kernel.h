@@ -11,7 +11,7 @@
 // in an LDS bank: see SpmmStream layout below.  What bounds it, counted per entry and 16 columns
 // of a wavefront: 4 reads of 1 KB (LDS: 1.9 ns each for the compute unit when nothing collides,
 // measured), 16 multiply-adds (1.05 ns of a SIMD each), 1 dot product for the address (1.8 ns) and
-// 3 exclusive ors (1 ns): LDS 7.6 ns against 5.9 ns of vector instructions per compute unit;
+// 3 exclusive ors (1 ns each): LDS 7.6 ns against 5.4 ns of vector instructions per compute unit;
 // measured 11 ns with 12 wavefronts.  On the way here, 6000 x 3000 at 90 % and N = 128 (main kernel):
 //   one lane per row and 4 columns, quads sharing the weights by DPP (the tile kernels)  23.6 us
 //   the same walk in stages, addresses by one dot product                               21.3
