@@ -136,21 +136,16 @@ def test_the_timed_sizes_and_small_ones():
 @pytest.mark.parametrize("dtype,M,K,bank,k,N", [
     (bs.BS_F16, 4096, 25088, 64, 6, 16), (bs.BS_F32, 879, 12400, 100, 8, 20), (bs.BS_F16, 108, 19125, 25, 10, 251)])
 def test_planning_many_slabs_costs_little(dtype, M, K, bank, k, N):
-    """Every call plans its launch.  In units of the tile kernels' planning alone (0.17 us on the development host):
-    16 to 32 if every launch is priced in full, 6 to 10 as it is."""
-    plan, out = bs.load_library().bs_spmm_plan, (ctypes.c_int64 * 30)()
-
-    def seconds(*shape):
-        best = math.inf
-        for _ in range(40):
+    """Every call plans its launch.  A host query of this product against one of 8 columns, which only the tile kernels'
+    planning is needed for: 3.1 to 4.3 times as long if every launch is priced in full, 1.5 to 2.0 as it is."""
+    plan, out, best = bs.load_library().bs_spmm_plan, (ctypes.c_int64 * 30)(), {N: math.inf, 8: math.inf}
+    for _ in range(300):             # in turn and in pieces of some 100 us: what else the host does meets both alike
+        for n in best:
             t = time.perf_counter()
-            for _ in range(250):
-                plan(*shape, out, 30)
-            best = min(best, time.perf_counter() - t)
-        return best
-    call = seconds(dtype, M, K, bank, bank + 1, N)      # refused at once: what the call itself costs
-    tiles = seconds(dtype, M, K, bank, k, 8) - call
-    assert seconds(dtype, M, K, bank, k, N) - call < 14 * tiles
+            for _ in range(60):
+                plan(dtype, M, K, bank, k, n, out, 30)
+            best[n] = min(best[n], time.perf_counter() - t)
+    assert best[N] < 2.7 * best[8]
 
 
 def _chain(parts):
