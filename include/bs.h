@@ -283,17 +283,39 @@ int bs_lstm_step(const void* vals, const uint8_t* idx, int dtype, int64_t H, int
                  const float* c_in, float* c_out, float* h_out, void* stream);
 
 /*
- * T steps in a row, enqueued back to back on `stream` (one kernel per step; the
- * packed matrix stays in the last-level cache between them):
+ * T steps in a row on `stream`:
  * X      DEVICE in      T x I fp32, row t is the input of step t
  * h0     DEVICE in      H fp32, the hidden state before step 0
  * c      DEVICE in/out  H fp32: the cell state before step 0, after step T-1 on return
  * H_all  DEVICE out     T x H fp32, row t is the hidden state after step t
  *                       (must not overlap h0)
+ * Same bits as T calls of bs_lstm_step.  From four steps on, and where the matrix fits the
+ * registers of 128 workgroups, one kernel makes all steps, its workgroups exchanging hidden
+ * states through H_all (filled with an impossible word first), and a second one finishes what
+ * the first had to leave because its workgroups were not on the GPU at the same time; else
+ * one kernel per step.  Each is an ordinary launch.
  */
 int bs_lstm_sequence(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I,
                      int bank, int k, const float* X, int64_t T, const float* h0,
                      const float* bias, float* c, float* H_all, void* stream);
+
+/*
+ * The same with the launch spelled out, for sweeps and tests: lanes per workgroup and
+ * most workgroups of the kernel that makes all steps (0: the library's choice; a shape
+ * that does not go is launched step by step), and how long a workgroup waits for the
+ * others' hidden states before it leaves the rest to the finishing kernel, in ticks of the GPU's
+ * 100 MHz clock (negative: the library's 20 ms; 0: not at all).  The results are the same.
+ */
+int bs_lstm_sequence_ex(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I,
+                        int bank, int k, const float* X, int64_t T, const float* h0,
+                        const float* bias, float* c, float* H_all, int threads, int workgroups,
+                        int64_t wait_ticks, void* stream);
+
+/* HOST ONLY: that kernel's launch.  out: 1 if there is one, entries per chunk, lanes per row,
+ * chunks of a row per lane, rows per lane, units per workgroup, chunks that read x alone,
+ * lanes per workgroup, workgroups, LDS bytes, LDS bytes of the finishing kernel. */
+int bs_lstm_sequence_plan(int dtype, int64_t H, int64_t I, int bank, int k, int threads, int workgroups,
+                          int64_t* out, int n_out);
 
 /* ---- dense baseline the sparse path is compared with (Sec. 4: the paper's
  *      dense column; here a hand-written kernel on the same GPU) ----------- */

@@ -92,6 +92,17 @@ int check_packed_wide(const void* vals, const uint16_t* idx, int dtype, int64_t 
     return BS_OK;
 }
 
+int check_lstm(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I, int bank, int k, const float* x,
+               const float* h_in, const float* bias, const float* c_in, const float* c_out, const float* h_out) {
+    if (!x || !h_in || !bias || !c_in || !c_out || !h_out) return BS_ERR_NULL;
+    if (H < 1 || I < 1 || H > (INT64_MAX >> 3) || I > (INT64_MAX >> 3)) return BS_ERR_SHAPE;
+    const int st = check_packed(vals, idx, dtype, 4 * H, I + H, bank, k);
+    if (st) return st;
+    if (!aligned16(x) || !aligned16(h_in) || !aligned16(bias) || !aligned16(c_in) || !aligned16(c_out) || !aligned16(h_out))
+        return BS_ERR_ALIGN;
+    return h_out == h_in ? BS_ERR_UNSUPPORTED : BS_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -221,32 +232,42 @@ int bs_spmv(const void* vals, const uint8_t* idx, int dtype, int64_t M, int64_t 
 int bs_lstm_step(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I, int bank,
                  int k, const float* x, const float* h_in, const float* bias, const float* c_in,
                  float* c_out, float* h_out, void* stream) {
-    if (!x || !h_in || !bias || !c_in || !c_out || !h_out) return BS_ERR_NULL;
-    if (H < 1 || I < 1 || H > (INT64_MAX >> 3) || I > (INT64_MAX >> 3)) return BS_ERR_SHAPE;
-    int st = check_packed(vals, idx, dtype, 4 * H, I + H, bank, k);
+    const int st = check_lstm(vals, idx, dtype, H, I, bank, k, x, h_in, bias, c_in, c_out, h_out);
     if (st) return st;
-    if (!aligned16(x) || !aligned16(h_in) || !aligned16(bias) || !aligned16(c_in) ||
-        !aligned16(c_out) || !aligned16(h_out))
-        return BS_ERR_ALIGN;
-    if (h_out == h_in) return BS_ERR_UNSUPPORTED;
     return bs::launch_lstm_step(vals, idx, dtype, H, I, bank, k, x, h_in, bias, c_in, c_out, h_out,
                                 static_cast<hipStream_t>(stream));
+}
+
+int bs_lstm_sequence_ex(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I,
+                        int bank, int k, const float* X, int64_t T, const float* h0,
+                        const float* bias, float* c, float* H_all, int threads, int workgroups,
+                        int64_t wait_ticks, void* stream) {
+    if (!X || !h0 || !bias || !c || !H_all) return BS_ERR_NULL;
+    if (T < 1) return BS_ERR_SHAPE;
+    if (H_all == h0) return BS_ERR_UNSUPPORTED;
+    // rows of X and H_all start on 16-byte boundaries because I and H are multiples of 4
+    const int st = check_lstm(vals, idx, dtype, H, I, bank, k, X, h0, bias, c, c, H_all);
+    if (st) return st;
+    if (H % 4 || I % 4 || threads < 0 || workgroups < 0) return BS_ERR_UNSUPPORTED;
+    return bs::launch_lstm_sequence(vals, idx, dtype, H, I, bank, k, X, T, h0, bias, c, H_all, threads,
+                                    workgroups, wait_ticks, static_cast<hipStream_t>(stream));
+}
+
+int bs_lstm_sequence_plan(int dtype, int64_t H, int64_t I, int bank, int k, int threads, int workgroups,
+                          int64_t* out, int n_out) {
+    if (!out) return BS_ERR_NULL;
+    if (H < 1 || I < 1 || H > (INT64_MAX >> 3) || I > (INT64_MAX >> 3) || n_out < 0) return BS_ERR_SHAPE;
+    if (!shape_ok(4 * H, I + H, bank, k)) return BS_ERR_SHAPE;
+    if (!dtype_ok(dtype) || !size_ok(4 * H, I + H, bank) || H % 4 || I % 4 || threads < 0 || workgroups < 0)
+        return BS_ERR_UNSUPPORTED;
+    bs::lstm_seq_plan_describe(dtype, H, I, bank, k, threads, workgroups, out, n_out);
+    return BS_OK;
 }
 
 int bs_lstm_sequence(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I,
                      int bank, int k, const float* X, int64_t T, const float* h0,
                      const float* bias, float* c, float* H_all, void* stream) {
-    if (!X || !h0 || !bias || !c || !H_all) return BS_ERR_NULL;
-    if (T < 1) return BS_ERR_SHAPE;
-    if (H_all == h0) return BS_ERR_UNSUPPORTED;
-    // rows of X and H_all start on 16-byte boundaries because I and H are multiples of 4
-    for (int64_t t = 0; t < T; ++t) {
-        const float* h_in = t == 0 ? h0 : H_all + (t - 1) * H;
-        int st = bs_lstm_step(vals, idx, dtype, H, I, bank, k, X + t * I, h_in, bias, c, c,
-                              H_all + t * H, stream);
-        if (st) return st;   // step 0 validates everything the later steps use
-    }
-    return BS_OK;
+    return bs_lstm_sequence_ex(vals, idx, dtype, H, I, bank, k, X, T, h0, bias, c, H_all, 0, 0, -1, stream);
 }
 
 size_t bs_spmm_workspace_bytes(int dtype, int64_t M, int64_t K, int bank, int k, int64_t N) {

@@ -44,6 +44,14 @@ int launch_spmv_slabbed(const void* vals, const uint8_t* idx, int dtype, int64_t
 int launch_lstm_step(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I, int bank,
                      int k, const float* x, const float* h_in, const float* bias,
                      const float* c_in, float* c_out, float* h_out, hipStream_t st);
+// the launch of that step: entries per chunk and lanes per row; false where there is none
+bool lstm_step_lanes(int dtype, int64_t H, int64_t I, int bank, int k, int* ch, int* lpr);
+// T steps (bs_lstm_seq.hip).  threads, workgroups: 0, or the shape of the kernel that makes all steps; wait_ticks: how long
+// one of its workgroups waits for another's hidden state (negative: as long as in bs_lstm_sequence)
+int launch_lstm_sequence(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I, int bank, int k,
+                         const float* X, int64_t T, const float* h0, const float* bias, float* c, float* H_all,
+                         int threads, int workgroups, int64_t wait_ticks, hipStream_t st);
+void lstm_seq_plan_describe(int dtype, int64_t H, int64_t I, int bank, int k, int threads, int workgroups, int64_t* out, int n_out);
 size_t spmm_workspace_bytes(int dtype, int64_t M, int64_t K, int bank, int k, int64_t N);
 int spmm_plan_describe(int dtype, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int64_t* out,
                        int n_out);
@@ -126,6 +134,20 @@ __device__ __forceinline__ float dpp_move(float v) {
     int i = __builtin_bit_cast(int, v);
     int r = __builtin_amdgcn_update_dpp(0, i, CTRL, 0xf, 0xf, true);
     return __builtin_bit_cast(float, r);
+}
+
+// v + the v of the lane whose number differs by 16 (32), without a round trip through LDS: rows of 16 lanes (halves)
+// trade places between two copies of v.  (The wait states are those of a VALU result that a lane exchange reads;
+// the builtin of this compiler returns the same register twice for equal operands.)
+__device__ __forceinline__ float add_across_16(float v) {
+    float a = v, b = v;
+    asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    return a + b;
+}
+__device__ __forceinline__ float add_across_32(float v) {
+    float a = v, b = v;
+    asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    return a + b;
 }
 
 template <int W>

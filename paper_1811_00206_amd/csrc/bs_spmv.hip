@@ -183,6 +183,14 @@ int spmv_plan_describe(int dtype, int64_t M, int64_t K, int bank, int k, int lan
     return BS_OK;
 }
 
+bool lstm_step_lanes(int dtype, int64_t H, int64_t I, int bank, int k, int* ch, int* lpr) {
+    SpmvPlan p;
+    if (plan_spmv(dtype, 4 * H, I + H, bank, k, 0, 0, true, 1, p) != BS_OK) return false;
+    *ch = p.ch;
+    *lpr = p.lpr;
+    return true;
+}
+
 int launch_lstm_step(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I, int bank,
                      int k, const float* x, const float* h_in, const float* bias,
                      const float* c_in, float* c_out, float* h_out, hipStream_t st) {

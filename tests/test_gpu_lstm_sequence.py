@@ -1,0 +1,100 @@
+"""bs_lstm_sequence by the kernel that makes all steps (csrc/bs_lstm_seq_kernel.h): the bits of bs_lstm_step called T times,
+whatever the launch, and whatever its workgroups had to leave to the finishing kernel."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import bs_ref
+from paper_1811_00206_amd import binding as bs
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _inputs(H, I, bank, k, dtype, T, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    W = torch.randn((4 * H, H + I), generator=g, device="cuda") * 0.2
+    v, i = bs.bs_prune_pack(W.half() if dtype == "f16" else W, bank, k)
+    u = lambda *s: torch.empty(s, device="cuda").uniform_(-1, 1, generator=g)
+    return v, i, u(T, I), u(H), u(4 * H), u(H)
+
+
+def _steps(v, i, bank, X, h, bias, c):
+    rows = []
+    for x in X:
+        c, h = bs.bs_lstm_step(v, i, bank, x, h, bias, c)
+        rows.append(h)
+    return torch.stack(rows), c
+
+
+def _sequence(v, i, bank, X, h0, bias, c, *launch):
+    return bs.bs_lstm_sequence_ex(v, i, bank, X, h0, bias, c, torch.full((X.shape[0], h0.numel()), 7.0, device=DEV), *launch)
+
+
+# chunks of 1, 2, 4 and 8 entries; 8 to 64 lanes per row; 1 to 4 chunks and rows per lane; a last workgroup of few units
+SHAPES = [
+    # H, I, bank, k, dtype, lanes, workgroups
+    (64, 64, 16, 4, "f32", 256, 4), (68, 60, 16, 3, "f32", 256, 4), (100, 92, 16, 5, "f16", 512, 8), (4, 12, 8, 8, "f32", 0, 0),
+    (36, 64, 25, 7, "f16", 0, 0), (132, 124, 32, 5, "f32", 512, 16), (260, 252, 64, 20, "f16", 768, 33), (12, 988, 100, 10, "f32", 0, 0),
+    (996, 28, 64, 1, "f32", 768, 128), (516, 512, 257 - 1, 51, "f32", 512, 128), (1020, 4, 128, 40, "f16", 768, 128),
+    (640, 1500, 107, 9, "f16", 0, 0), (1536, 1536, 64, 4, "f16", 0, 0), (1500, 1500, 100, 10, "f32", 0, 0),
+    (200, 824, 64, 33, "f32", 512, 128), (48, 1000, 131, 44, "f32", 256, 16), (300, 300, 50, 13, "f32", 512, 128),
+]
+
+
+@pytest.mark.parametrize("H,I,bank,k,dtype,threads,workgroups", SHAPES)
+def test_sequence_is_the_step_repeated(H, I, bank, k, dtype, threads, workgroups):
+    while (H + I) % bank:
+        I += 4
+    code = bs.BS_F16 if dtype == "f16" else bs.BS_F32
+    plan = bs.bs_lstm_sequence_plan(code, H, I, bank, k, threads, workgroups)
+    print("sequence", H, I, bank, k, dtype, plan, flush=True)
+    assert plan["one_kernel"] == 1
+    v, i, X, h0, bias, c0 = _inputs(H, I, bank, k, dtype, 9, H + k)
+    for T in (1, 4, 9):
+        want, c_want = _steps(v, i, bank, X[:T], h0, bias, c0)
+        for wait in (-1, 0):       # 0: what is not there at the first look is left to the finishing kernel
+            c = c0.clone()
+            got = _sequence(v, i, bank, X[:T], h0, bias, c, threads or plan["threads"], workgroups, wait)
+            assert torch.equal(got, want) and torch.equal(c, c_want), (T, wait)
+    c = c0.clone()
+    H_ref, c_ref = bs_ref.lstm_sequence(v.cpu().numpy(), i.cpu().numpy(), bank, X.cpu().numpy(), h0.cpu().numpy(), bias.cpu().numpy(),
+                                        c0.cpu().numpy())
+    got = bs.bs_lstm_sequence(v, i, bank, X, h0, bias, c)
+    assert bs_ref.rel_l2(got.cpu().numpy(), H_ref) <= 1e-5 and bs_ref.rel_l2(c.cpu().numpy(), c_ref) <= 1e-5
+
+
+def test_sequences_side_by_side():
+    """Eight streams, more than may be on the GPU at a time, each with states of its own."""
+    H, I, bank, k, T = 512, 512, 64, 8, 12
+    sets = [_inputs(H, I, bank, k, "f32", T, s) for s in range(8)]
+    want = [_steps(v, i, bank, X, h0, bias, c0) for v, i, X, h0, bias, c0 in sets]
+    streams = [torch.cuda.Stream() for _ in sets]
+    cells = [s[5].clone() for s in sets]
+    torch.cuda.synchronize()
+    got = []
+    for st, (v, i, X, h0, bias, _), c in zip(streams, sets, cells):
+        with torch.cuda.stream(st):
+            got.append(bs.bs_lstm_sequence(v, i, bank, X, h0, bias, c))
+    torch.cuda.synchronize()
+    for g, c, (w, cw) in zip(got, cells, want):
+        assert torch.equal(g, w) and torch.equal(c, cw)
+
+
+def test_states_that_share_memory_and_states_that_are_no_numbers():
+    H, I, bank, k, T = 256, 256, 64, 8, 6
+    v, i, X, h0, bias, c0 = _inputs(H, I, bank, k, "f32", T, 3)
+    # the first state is the last row of the result of the call before
+    want, c_want = _steps(v, i, bank, X, h0, bias, c0)
+    H_all, c = torch.empty(T, H, device=DEV), c0.clone()
+    H_all[T - 1].copy_(h0)
+    bs.bs_lstm_sequence(v, i, bank, X, H_all[T - 1], bias, c, H_all=H_all)
+    assert torch.equal(H_all, want) and torch.equal(c, c_want)
+    # every bit of a NaN set, the mark of an absent state
+    X[1, 5] = torch.tensor(-1, dtype=torch.int32, device=DEV).view(torch.float32)
+    X[3, 7] = float("inf")
+    want, c_want = _steps(v, i, bank, X, h0, bias, c0)
+    c = c0.clone()
+    got = _sequence(v, i, bank, X, h0, bias, c, 512, 16)
+    same = lambda a, b: np.array_equal(a.cpu().numpy(), b.cpu().numpy(), equal_nan=True)
+    assert torch.isnan(want).any() and same(got, want) and same(c, c_want)

@@ -165,3 +165,14 @@ def test_prune_kernels_wait_for_their_copies(prune_texts):
 
 def test_no_prune_kernel_spills_registers(prune_texts):
     test_no_kernel_spills_registers(prune_texts)
+
+
+def test_lstm_sequence_kernels_keep_their_weights_in_registers():
+    """The kernels that make all steps of a sequence, and the finishing ones, use no scratch memory: what they hold for the whole
+    sequence stays in the registers that let two workgroups share a compute unit."""
+    with ThreadPoolExecutor(2) as ex:
+        texts = list(ex.map(_assembly, ["bs_lstm_seq_f32.hip", "bs_lstm_seq_f16.hip"]))
+    assert all(t.count("lstm_seq_kernel") for t in texts)
+    for t in texts:
+        for m in re.finditer(r"\.(?:vgpr_spill_count|private_segment_fixed_size):\s+(\d+)", t):
+            assert int(m.group(1)) == 0

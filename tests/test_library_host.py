@@ -3,6 +3,7 @@ symbol the header declares, sizes are right, and bad arguments are refused
 before anything is launched."""
 import ctypes
 import os
+import random
 import re
 
 import pytest
@@ -251,3 +252,43 @@ def test_built_means_everything_a_call_loads(tmp_path, monkeypatch):
         monkeypatch.setattr(build, "LIB", str(lib))
         monkeypatch.setattr(build, "NATIVE_LIB", str(native))
         assert build.is_built() is built
+
+
+def test_lstm_sequence_plan():
+    """What the kernel that makes all steps assumes about its launch, over random models."""
+    from paper_1811_00206_amd import binding as b
+    rng = random.Random(11)
+    taken = 0
+    for _ in range(4000):
+        bank = rng.choice((16, 25, 32, 50, 64, 100, 128, 256))
+        k = rng.randint(1, bank)
+        H = 4 * rng.randint(1, 500)
+        nb = -(-(H + rng.randint(4, 2000)) // bank)
+        while (nb * bank) % 4:
+            nb += 1
+        I, dtype = nb * bank - H, rng.choice((b.BS_F32, b.BS_F16))
+        threads, workgroups = rng.choice(((0, 0), (256, 16), (512, 128), (768, 128), (768, 40)))
+        p = b.bs_lstm_sequence_plan(dtype, H, I, bank, k, threads, workgroups)
+        if not p["one_kernel"]:
+            continue
+        taken += 1
+        chunks = nb * k // p["ch"]
+        assert chunks * p["ch"] == nb * k and p["ch"] * (2 if dtype == b.BS_F16 else 4) <= 16
+        # every chunk of a row in a slot of one lane, every row in one lane group of one workgroup, whole units
+        assert p["lpr"] * (p["slots"] - 1) < chunks <= p["lpr"] * p["slots"] and p["slots"] <= 4 and p["rows"] <= 4
+        groups = p["threads"] // p["lpr"]
+        assert p["threads"] % 64 == 0 and groups * p["lpr"] == p["threads"] and groups % 4 == 0
+        assert 4 * p["units"] == groups * p["rows"]
+        assert (p["workgroups"] - 1) * p["units"] < H <= p["workgroups"] * p["units"]
+        assert p["workgroups"] <= (workgroups or 128)
+        # registers: two workgroups per compute unit
+        entries = p["slots"] * p["rows"] * p["ch"]
+        assert entries <= 36 and p["slots"] * p["rows"] <= 12 and p["threads"] <= (768 if entries <= 24 else 512)
+        # an operand's address in 16 bits, the zero behind [x ; h] too; one lane copies four floats of x
+        assert 4 * (H + I) < 1 << 16 and I <= 4 * p["threads"]
+        assert p["lds_bytes"] >= 4 * (2 * (H + I + 4) + 4 * p["units"] + 1) and p["lds_bytes"] <= 48 * 1024
+        assert p["finish_lds_bytes"] >= 4 * (H + I + 4 + 4 * H) + H and p["finish_lds_bytes"] <= 48 * 1024
+        # slots counted as reading x alone do so in their last lane's last entry
+        last = p["x_slots"] * p["lpr"] * p["ch"] - 1
+        assert last < 0 or (last // k + 1) * bank <= I
+    assert taken > 500
