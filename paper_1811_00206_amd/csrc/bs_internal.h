@@ -16,6 +16,7 @@ namespace bs {
 
 constexpr int kWave = 64;
 constexpr int kMaxLdsBytes = 160 * 1024;   // LDS of one gfx950 compute unit
+constexpr double kLastLevelBytes = 256.0 * (1 << 20);   // the cache that all XCDs share
 
 // Launchers (host).  Arguments are already validated by the C-ABI layer.
 int launch_prune_pack(const void* W, int dtype, int64_t M, int64_t K, int bank, int k,

@@ -152,7 +152,8 @@ int launch_common(const void* vals, const void* idx, int isize, int dtype, int64
         a.c_out = lstm->c_out; a.h_out = lstm->h_out; a.H = lstm->H; a.I = lstm->I;
     }
 
-    const SpmvLaunch l{lstm != nullptr, p.threads, (int)p.grid, p.lds, ev_start, ev_stop, st};
+    const bool streamed = (double)M * p.row_len * ((dtype == BS_F16 ? 2 : 4) + isize) > kLastLevelBytes;
+    const SpmvLaunch l{lstm != nullptr, streamed, p.threads, (int)p.grid, p.lds, ev_start, ev_stop, st};
     if (isize == 2) return spmv_launch_wide(dtype, p.ch, p.lpr, p.u, a, l);
     if (dtype == BS_F16) return spmv_launch_f16(p.ch, p.lpr, p.u, a, l);
     return spmv_launch_f32(p.ch, p.lpr, p.u, a, l);

@@ -24,6 +24,8 @@
 // the flat stream instead, because per-bank lanes would read HBM with a
 // k*sizeof stride.
 #pragma once
+#include <type_traits>
+
 #include "bs_internal.h"
 
 namespace bs {
@@ -61,6 +63,7 @@ struct SpmvArgs {
 
 struct SpmvLaunch {
     bool lstm;                      // fused LSTM cell update instead of storing y
+    bool streamed;                  // the packed matrix is larger than the last-level cache
     int threads;
     int grid;
     size_t lds;
@@ -75,6 +78,20 @@ int spmv_launch_f16(int ch, int lpr, int u, const SpmvArgs& a, const SpmvLaunch&
 int spmv_launch_wide(int dtype, int ch, int lpr, int u, const SpmvArgs& a, const SpmvLaunch& l);
 
 #ifdef __HIPCC__
+
+// A chunk of the packed matrix; STREAMED: one that no cache keeps (non-temporal).
+template <bool STREAMED, typename RAW>
+__device__ __forceinline__ RAW load_chunk(const RAW* p) {
+    if constexpr (!STREAMED) {
+        return *p;
+    } else if constexpr (sizeof(RAW) >= 8) {
+        typedef uint32_t Words __attribute__((ext_vector_type(sizeof(RAW) / 4)));
+        return __builtin_bit_cast(RAW, __builtin_nontemporal_load(reinterpret_cast<const Words*>(p)));
+    } else {
+        using Word = typename std::conditional<sizeof(RAW) == 4, uint32_t, typename std::conditional<sizeof(RAW) == 2, uint16_t, uint8_t>::type>::type;
+        return __builtin_bit_cast(RAW, __builtin_nontemporal_load(reinterpret_cast<const Word*>(p)));
+    }
+}
 
 // Sum over the U chunk slots a lane holds in registers.  Slot u is chunk
 // c0 + u*LPR of the row; slots past the end of the row hold a re-read of the
@@ -204,8 +221,9 @@ __device__ __forceinline__ float tanh_fast(float v) {
 // ends with the cell update (the model of Sec. 4.3; bias as in eq. (1)) instead of
 // storing y: a workgroup owns rows_per_wg/4 units, its row i is gate i%4 of unit i/4.
 // IT: the stored offset type (uint8_t, or uint16_t for balance ranges over 256).
-template <typename VT, int CH, int LPR, int U, bool LSTM = false, typename IT = uint8_t>
-__global__ __launch_bounds__(1024) void spmv_kernel(SpmvArgs a) {
+// STREAMED: see load_chunk.
+template <typename VT, int CH, int LPR, int U, bool LSTM, typename IT, bool STREAMED>
+__device__ __forceinline__ void spmv_rows(const SpmvArgs& a) {
     extern __shared__ __align__(16) float xs[];
     using VRaw = typename RawBytes<CH * sizeof(VT)>::type;
     using IRaw = typename IdxChunk<IT, CH>::type;
@@ -284,8 +302,8 @@ __global__ __launch_bounds__(1024) void spmv_kernel(SpmvArgs a) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int c = min(lane_in_row + u * LPR, cpr - 1);
-        v[u] = vrow[c];
-        o[u] = irow[c];
+        v[u] = load_chunk<STREAMED>(vrow + c);
+        o[u] = load_chunk<STREAMED>(irow + c);
     }
     pin_order();
 
@@ -309,8 +327,8 @@ __global__ __launch_bounds__(1024) void spmv_kernel(SpmvArgs a) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int c = min(c0 + u * LPR, cpr - 1);
-            v[u] = vrow[c];
-            o[u] = irow[c];
+            v[u] = load_chunk<STREAMED>(vrow + c);
+            o[u] = load_chunk<STREAMED>(irow + c);
         }
         acc += consume_any<VT, CH, LPR, U>(a, xs, v, o, c0, c0 - lane_in_row, cpr);
     }
@@ -352,8 +370,26 @@ __global__ __launch_bounds__(1024) void spmv_kernel(SpmvArgs a) {
 }
 
 template <typename VT, int CH, int LPR, int U, bool LSTM = false, typename IT = uint8_t>
+__global__ __launch_bounds__(1024) void spmv_kernel(SpmvArgs a) { spmv_rows<VT, CH, LPR, U, LSTM, IT, false>(a); }
+
+// For a packed matrix that the last-level cache (256 MB) cannot hold: left in it, it only drives other data, and its own
+// beginning, out before the next product.  16384 x 8192 at 50 % (336 MB): 55.3 -> 51.0 us, 6.1 -> 6.6 TB/s.  Smaller ones come
+// from a cache when they are used again: with such loads 84 MB take 15.7 us instead of 13.8, 29 MB 8.8 instead of 7.1.  Kernels of
+// their own: a branch around the loads costs the others up to 6 %.  For rows of 64 lanes, as matrices of that size have.
+template <typename VT, int CH, int U, typename IT>
+__global__ __launch_bounds__(1024) void spmv_streamed_kernel(SpmvArgs a) { spmv_rows<VT, CH, 64, U, false, IT, true>(a); }
+
+template <typename VT, int CH, int LPR, int U, bool LSTM, typename IT, bool STREAMED>
+constexpr auto spmv_kernel_of() {
+    if constexpr (STREAMED) return spmv_streamed_kernel<VT, CH, U, IT>;
+    else return spmv_kernel<VT, CH, LPR, U, LSTM, IT>;
+}
+
+template <typename VT, int CH, int LPR, int U, bool LSTM = false, typename IT = uint8_t, bool STREAMED = false>
 int spmv_launch_one(const SpmvArgs& a, const SpmvLaunch& l) {
-    constexpr auto kern = spmv_kernel<VT, CH, LPR, U, LSTM, IT>;
+    if constexpr (LPR == 64 && !LSTM && !STREAMED)
+        if (l.streamed) return spmv_launch_one<VT, CH, LPR, U, LSTM, IT, true>(a, l);
+    constexpr auto kern = spmv_kernel_of<VT, CH, LPR, U, LSTM, IT, STREAMED>();
     if (l.lds > kLdsWithoutLimit) {
         const int st_code = ensure_lds_limit(LdsKernelOf<kern>::reg, l.st);
         if (st_code != BS_OK) return st_code;

@@ -1,0 +1,42 @@
+"""bs_spmv on packed matrices that are larger than the last-level cache (spmv_streamed_kernel, csrc/bs_spmv_kernel.h): every
+chunk width and number of chunk slots, against float64 on rows from everywhere."""
+import pytest
+import torch
+
+from paper_1811_00206_amd import binding as bs
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+BYTES = 256 << 20
+
+# chunks of 4, 2 and 1 (fp32), 8, 4, 2 and 1 (binary16) entries; one round of 5 to 8 slots, several rounds; 16-bit offsets
+SHAPES = [
+    # banks, bank, k, dtype
+    (33, 64, 40, "f32"), (31, 100, 50, "f32"), (77, 50, 19, "f32"), (64, 256, 128, "f32"), (97, 128, 64, "f16"), (83, 100, 50, "f16"),
+    (99, 100, 52, "f16"), (97, 64, 33, "f16"), (40, 50, 30, "f32"), (40, 64, 40, "f32"), (16, 1024, 200, "f32"), (15, 512, 201, "f32"), (32, 512, 100, "f16"),
+]
+
+
+@pytest.mark.parametrize("nb,bank,k,dtype", SHAPES)
+def test_matrices_larger_than_the_last_level_cache(nb, bank, k, dtype):
+    wide = bank > 256
+    vt, it = (torch.float16, torch.float32)[dtype == "f32"], (torch.uint8, torch.uint16)[wide]
+    entry = (2 if dtype == "f16" else 4) + (2 if wide else 1)
+    M = BYTES // (nb * k * entry) + 3
+    assert M * nb * k * entry > BYTES
+    print("streamed", M, nb, bank, k, dtype, flush=True)
+    if not wide:
+        assert bs.bs_spmv_plan(bs.BS_F16 if dtype == "f16" else bs.BS_F32, M, nb * bank, bank, k)["lpr"] == 64
+    g = torch.Generator(device="cuda").manual_seed(nb + k)
+    vals = torch.empty((M, nb, k), dtype=vt, device=DEV)
+    vals.view(-1)[:] = torch.randn(M * nb * k, generator=g, device=DEV, dtype=vt)
+    idx = torch.randint(0, bank, (M, nb, k), generator=g, device=DEV, dtype=torch.int32).to(torch.int16).view(it) if wide else torch.randint(
+        0, bank, (M, nb, k), generator=g, device=DEV, dtype=torch.uint8)
+    x = torch.randn(nb * bank, generator=g, device=DEV)
+    y = (bs.bs_spmv_wide if wide else bs.bs_spmv)(vals, idx, bank, x)
+    rows = torch.tensor([0, 1, 2, 3, M // 3, M // 2, M - 5, M - 4, M - 3, M - 2, M - 1], device=DEV)
+    at = (idx.view(torch.int16) if wide else idx)[rows].long() + bank * torch.arange(nb, device=DEV)[None, :, None]
+    terms = vals[rows].double() * x.double()[at]
+    # n terms in fp32, in any order: off by at most n * 2^-24 of the sum of the terms' magnitudes
+    bound = (nb * k + 1) * 2.0 ** -24 * terms.abs().sum((1, 2))
+    assert ((y[rows].double() - terms.sum((1, 2))).abs() <= bound).all()
