@@ -391,7 +391,10 @@ int spmv_launch_one(const SpmvArgs& a, const SpmvLaunch& l) {
         if (l.streamed) return spmv_launch_one<VT, CH, LPR, U, LSTM, IT, true>(a, l);
     constexpr auto kern = spmv_kernel_of<VT, CH, LPR, U, LSTM, IT, STREAMED>();
     if (l.lds > kLdsWithoutLimit) {
-        const int st_code = ensure_lds_limit(LdsKernelOf<kern>::reg, l.st);
+        // a first use inside a capture is answered alike for matrices of either size
+        LdsKernel* sibling = nullptr;
+        if constexpr (LPR == 64 && !LSTM) sibling = &LdsKernelOf<spmv_kernel_of<VT, CH, LPR, U, LSTM, IT, !STREAMED>()>::reg;
+        const int st_code = ensure_lds_limit(LdsKernelOf<kern>::reg, l.st, sibling);
         if (st_code != BS_OK) return st_code;
     }
     if (l.ev_start || l.ev_stop)
