@@ -203,6 +203,7 @@ struct PruneArgs {
     int raw_bytes;         // LDS bytes of the wavefront's banks; its offsets follow
     int stored_at;         // kStoredInLds: where the stored offsets lie behind those
     int wave_bytes;        // all of them, a multiple of 256
+    int streamed;          // W is larger than the last-level cache
 };
 
 // Wavefronts per workgroup at most; they share nothing.  1 / 2 / 4 on the 6000 x 3000 matrix:
@@ -223,6 +224,18 @@ __device__ __forceinline__ void copy_bytes(const unsigned char* src, unsigned ch
         }
     const int done = pieces * P;
     if (lane < n - done) dst[done + lane] = src[done + lane];
+}
+
+// The wavefront's banks to LDS: piece place(p) to place p.  POLICY: 0, or 2 for non-temporal loads.
+template <int POLICY, typename F>
+__device__ __forceinline__ void copy_places(const unsigned char* src, unsigned char* dst, int places, int pieces, int lane, F place) {
+    for (int p0 = 0; p0 < places; p0 += kWave) {
+        const int p = (int)place((uint32_t)(p0 + lane));
+        if (p0 + lane < places && p < pieces)
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void*)(src + (size_t)p * 16),
+                (__attribute__((address_space(3))) void*)(dst + p0 * 16), 16, 0, POLICY);
+    }
 }
 
 // A group of 64/LPB banks per wavefront, no loop.
@@ -255,13 +268,10 @@ __global__ __launch_bounds__(kWave * kPruneWaves) void prune_pack_kernel(PruneAr
     const int bytes = n_ok * B * S;
     const int pieces = bytes >> 4;
     const int places = LAYOUT == kAligned ? (pieces + 15) & ~15 : pieces;
-    for (int p0 = 0; p0 < places; p0 += kWave) {
-        const int p = (int)place((uint32_t)(p0 + lane));
-        if (p0 + lane < places && p < pieces)
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void*)(src + (size_t)p * 16),
-                (__attribute__((address_space(3))) void*)(pp_lds + p0 * 16), 16, 0, 0);
-    }
+    // A matrix that the last-level cache (256 MB) cannot hold is read past it: 336 MB 72.3 -> 63.4 us (4.9 -> 5.6 TB/s), 537 MB
+    // 117 -> 109; 206 MB used again 45.0 -> 52.4, so the line is the cache's size.
+    if (a.streamed) copy_places<2>(src, pp_lds, places, pieces, lane, place);
+    else copy_places<0>(src, pp_lds, places, pieces, lane, place);
     // the matrix's last group may end inside a 16-byte piece (never kAligned)
     const int rest = bytes & 15;
     if (lane * S < rest)
@@ -483,6 +493,7 @@ int prune_banks(const void* W, int64_t n_banks, int bank, int k, void* vals, IT*
     a.n_banks = n_banks; a.B = bank; a.k = k;
     a.magic_k = magic_u32((uint32_t)k);
     a.raw_bytes = a.stored_at = a.wave_bytes = 0;
+    a.streamed = (double)n_banks * bank * sizeof(VT) > kLastLevelBytes;
     int lpb = 1;
     while (lpb < 32 && (bank + lpb - 1) / lpb > 32) lpb <<= 1;
     a.C = (bank + lpb - 1) / lpb;

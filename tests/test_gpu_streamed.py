@@ -40,3 +40,21 @@ def test_matrices_larger_than_the_last_level_cache(nb, bank, k, dtype):
     # n terms in fp32, in any order: off by at most n * 2^-24 of the sum of the terms' magnitudes
     bound = (nb * k + 1) * 2.0 ** -24 * terms.abs().sum((1, 2))
     assert ((y[rows].double() - terms.sum((1, 2))).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("nb,bank,k,dtype", [(33, 64, 5, "f32"), (41, 100, 9, "f32"), (16, 256, 30, "f32"), (77, 51, 6, "f16"), (64, 128, 8, "f16"),
+                                             (16, 512, 16, "f32"), (9, 1024, 8, "f16")])
+def test_pruning_of_matrices_larger_than_the_last_level_cache(nb, bank, k, dtype):
+    """prune_pack_kernel's non-temporal copies: rows from everywhere against the same rows pruned by themselves."""
+    size = 2 if dtype == "f16" else 4
+    M = BYTES // (nb * bank * size) + 5
+    assert M * nb * bank * size > BYTES
+    print("streamed prune", M, nb, bank, k, dtype, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(nb + k)
+    W = torch.randn((M, nb * bank), generator=g, device=DEV, dtype=torch.float16 if dtype == "f16" else torch.float32)
+    prune = bs.bs_prune_pack_wide if bank > 256 else bs.bs_prune_pack
+    vals, idx = prune(W, bank, k)
+    view = lambda t: t.view(torch.int16) if t.dtype == torch.uint16 else t
+    for first in (0, M // 3, M - 64):
+        v, i = prune(W[first:first + 64].clone(), bank, k)
+        assert torch.equal(vals[first:first + 64], v) and torch.equal(view(idx)[first:first + 64], view(i))
