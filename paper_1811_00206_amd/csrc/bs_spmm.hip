@@ -175,28 +175,40 @@ SpmmPlan make_plan(int dtype, int64_t M, int64_t K, int bank, int k, int64_t N, 
     return best;
 }
 
-// What the tile kernels are expected to take for a plan of more than 8 columns, in ns, the slab sums included:
-// a fit to 442 random products on MI355X (median error 5 %, 9 % rms).
+// What the tile kernels are expected to take for a plan of more than 8 columns, in ns, the slab sums included.  Fits to
+// random products on MI355X: with 8-bit offsets 2656 of them, whose operands change from call to call (median error 4.4 %,
+// 8.7 % rms), with 16-bit offsets 442, most of them of 8-bit ones (5 %, 9 % rms).
+struct TileFactors {
+    double rows_alone, rows_shared, rows_simd, load, row;    // lane per row: of an entry as in bs_spmm_stream.hip; of 16 chunks; of a pass
+    double rows_ch2, rows_ch1, rows_half;
+    double alone, shared, simd, pass, few;                   // several lanes per row; `few`: chunks of at most 2 entries
+    double tile, unaligned, wave_copy, cu_copy, launch, memory, memory_rate, slabs, slab_rate;
+};
+constexpr TileFactors kBytes{16.05, 3.42, 13.3, 439, 0, 0.94, 0.96, 1.05, 46.8, 6.22, 14.36, 686, 1.24,
+                             0, 1.61, 550, 65.2, 3460, 3739, 2972, 2324, 4069};
+constexpr TileFactors kTwoBytes{14.2, 3.68, 0, 530, 223, 0.94, 0.9, 1.07, 41.3, 2.84, 0, 629, 1.4,
+                                104, 1.37, 15, 54.2, 2930, 2500, 3019, 1920, 4800};
 double tiles_ns(const SpmmPlan& p, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, SpmmCopy copy) {
+    const TileFactors& f = isize == 2 ? kTwoBytes : kBytes;
     const int threads = launched_threads(p, copy);
     const int64_t wgs = (int64_t)p.n_tiles * p.n_slabs * p.row_groups, nb = K / bank;
     const double per_cu = (double)std::max<int64_t>(1, std::min<int64_t>({(int64_t)(kMaxLdsBytes / p.lds_bytes), 1024 / threads, (wgs + kCus - 1) / kCus}));
-    const double rounds = std::ceil(wgs / (kCus * per_cu)), walkers = p.row_threads / 64.0 * per_cu;
+    const double rounds = std::ceil(wgs / (kCus * per_cu)), walkers = p.row_threads / 64.0 * per_cu, simd = std::ceil(walkers * 0.25);
     const int64_t run = std::min<int64_t>(p.sb, nb) * k;      // entries of a row inside a slab
     const int rows_per_pass = p.row_threads / (p.nl * p.lpr);
     double pass;
     if (p.rows) {
-        pass = run * std::max(14.2, 3.68 * walkers) + 530 * std::ceil(run / (16.0 * p.ch)) + 223;
-        pass *= (p.ch == 2 ? 0.94 : p.ch == 1 ? 0.9 : 1.0) * (vsize == 2 ? 1.07 : 1.0);
+        pass = run * std::max({f.rows_alone, f.rows_shared * walkers, f.rows_simd * simd}) + f.load * std::ceil(run / (16.0 * p.ch)) + f.row;
+        pass *= (p.ch == 2 ? f.rows_ch2 : p.ch == 1 ? f.rows_ch1 : 1.0) * (vsize == 2 ? f.rows_half : 1.0);
     } else {
         const int64_t slots = (run / p.ch + p.lpr - 1) / p.lpr;
-        pass = (slots * p.ch * std::max(41.3, 2.84 * walkers) + 629) * (p.ch <= 2 ? 1.4 : 1.0);
+        pass = (slots * p.ch * std::max({f.alone, f.shared * walkers, f.simd * simd}) + f.pass) * (p.ch <= 2 ? f.few : 1.0);
     }
-    const double tile = 104 + (double)p.tile_bytes * per_cu * (copy == kCopyWide ? 1.0 : 1.37) / std::min(15.0 * threads / 64 * per_cu, 54.2);
-    double t = 2930 + rounds * (tile + (p.rows_per_wg + rows_per_pass - 1) / rows_per_pass * pass);
+    const double tile = f.tile + (double)p.tile_bytes * per_cu * (copy == kCopyWide ? 1.0 : f.unaligned) / std::min(f.wave_copy * threads / 64 * per_cu, f.cu_copy);
+    double t = f.launch + rounds * (tile + (p.rows_per_wg + rows_per_pass - 1) / rows_per_pass * pass);
     const double w_bytes = (double)M * nb * k * (vsize + isize), y_bytes = 4.0 * M * N;
-    t = std::max(t, 2500 + (w_bytes * std::min(p.n_tiles, 2) + 4.0 * K * N + y_bytes) / 3019);
-    if (p.n_slabs > 1) t += 1920 + 2.0 * p.n_slabs * y_bytes / 4800;
+    t = std::max(t, f.memory + (w_bytes * std::min(p.n_tiles, 2) + 4.0 * K * N + y_bytes) / f.memory_rate);
+    if (p.n_slabs > 1) t += f.slabs + 2.0 * p.n_slabs * y_bytes / f.slab_rate;
     return t;
 }
 
@@ -208,12 +220,12 @@ double tiles_rounding(const SpmmPlan& p, int64_t nb, int k) {
            std::log2((double)std::min<int64_t>(p.lpr, chunks)) + chain_rounding(p.n_slabs, false);
 }
 
-// The stage kernels are taken, for every row pitch of X alike, where they are expected to be faster by more than the
-// expectations are off.  The constants were chosen on 1050 random products of 9 to 50 000 columns with both kernels timed
-// (margin 0.85 and none of the terms below: 505 taken, 16 losses of more than 8 %, the worst 1.7).  Over 3700 others that
-// are taken they need 0.73 of the tile kernels' time (geometric mean); 128 lose more than 3 %, 60 more than 8 %, the worst
-// 1.33 (932 x 1125, N = 12: 5.6 -> 7.4 us).  Of the losses two thirds are expected within 0.1 of the margin and half have four to
-// seven entries per bank; beyond three stages the expectation is about 4 % too short for each.  Products expected
+// The stage kernels are taken, for every row pitch of X alike, where they are expected to be faster.  With 8-bit offsets the
+// two expectations are fits to launches of the same products, so the line is where they meet: over 3000 random products that
+// some line between 0.94 and 1.04 plans anew, 1.0 gave 0.948 of the time that the expectations of kTwoBytes and a line at 0.93
+// did (geometric mean), 0.94 0.957 and 1.04 0.947.  Of 6000 other products 789 are planned anew; 395 of them, timed: 0.941 of
+// the time, 226 gain more than 3 %, 64 lose that, 28 lose more than 8 % (11289 x 3900, N = 17: 30.4 -> 38.8 us).
+// The 16-bit ones keep the line of the fit that they have, 0.93.  Products expected
 // below kStreamWorthNs are not worth the planning.  The terms are what the expectations leave out:
 //   * Banks of more than 32 entries and one tile of columns stay on the tile kernels.  What divides these products
 //     is the stream of W: all 4 of the 27 timed ones with more than 64 MB of it lose (15947 x 6144, 124 entries
@@ -228,7 +240,7 @@ double tiles_rounding(const SpmmPlan& p, int64_t nb, int k) {
 // A launch whose sums would round worse than the tile kernels' is not looked at: those walk an odd row length or a small
 // tile with up to 64 lanes per row, so their sums are short (6722 x 144, banks of 16, k = 13, N = 40: 4 entries per lane and
 // an exchange, against 39 in a lane of the stage kernels, 1.5 times the error).  Of 4000 random products, 4 %.
-constexpr double kStreamMargin = 0.93, kStreamWorthNs = 6000;
+constexpr double kStreamMargin = 1.0, kStreamMarginTwoBytes = 0.93, kStreamWorthNs = 6000;
 constexpr double kStreamManyAligned = 1.05, kStreamManyUnaligned = 1.2, kStreamLongBank = 1.1;
 constexpr int kStreamLongK = 32;
 constexpr double kStreamMaxXBytes = 128e6;
@@ -239,7 +251,7 @@ SpmmStreamPlan stream_choice(const SpmmPlan& p, int vsize, int isize, int64_t M,
     if (tiles <= kStreamWorthNs) return {};
     // a product whose tile kernel needs no LDS limit raised can be captured as the first of all, so this one may not need it either
     const int max_lds = p.lds_bytes > kLdsWithoutLimit ? kMaxLdsBytes : (int)kLdsWithoutLimit;
-    const double max_ns = kStreamMargin * tiles / (k > kStreamLongK ? kStreamLongBank : 1.0);
+    const double max_ns = (isize == 2 ? kStreamMarginTwoBytes : kStreamMargin) * tiles / (k > kStreamLongK ? kStreamLongBank : 1.0);
     const SpmmStreamPlan sp = spmm_stream_plan(vsize, isize, M, K, bank, k, N, p.n_slabs, max_lds, tiles_rounding(p, K / bank, k), max_ns);
     const bool many = (int64_t)sp.n_tiles * sp.n_slabs * sp.row_groups > kCus;
     if (sp.ok && many && sp.ns * (N % 4 == 0 ? kStreamManyAligned : kStreamManyUnaligned) >= max_ns) return {};

@@ -17,51 +17,71 @@ constexpr I div_up(I a, I b) { return (a + b - 1) / b; }
 // entries of a bank that a lane loads at once (the kernel's U)
 int unit_of(int isize, int k) { return isize == 2 ? (k < 8 ? 4 : 8) : k > kStreamMaxK ? 8 : k; }
 
-// Expected time of a launch in ns.  The terms are the kernel's own steps; their factors are a fit to
-// 1332 launches of random shapes and plans on MI355X (median error 6 %, 11 % rms).
-constexpr double kEntryAlone = 66.0, kEntryShared = 13.7;   // of an entry: a wavefront by itself, each that shares the compute unit
-constexpr double kLaunchNs = 1670, kRoundNs = 1800, kFirstCopyNs = 874, kUnitNs = 29;
-constexpr double kWaveCopyRate = 15.7, kCopyRate = 82.0;      // bytes per ns that a wavefront, a compute unit copies
+// Expected time of a launch in ns.  The terms are the kernel's own steps; their factors are fits to timed launches on
+// MI355X.  With 8-bit offsets: 19233 of 11000 random products whose operands change from call to call (median error 5 %, 8 %
+// rms; without the term of a SIMD 10 %).  Wavefront w of a workgroup runs on SIMD w % 4 and a stage waits for the busiest of
+// the four, so 5 walking wavefronts take as long as 8.  With 16-bit offsets: 1332 of random shapes and plans, most of them
+// with 8-bit offsets (6 %, 11 % rms); these products keep the launches that they were timed with.
+struct Factors {
+    double alone, shared, simd;      // of an entry: a wavefront by itself, each that shares the compute unit, a SIMD
+    double slow;                     // factor of an entry above k = kStreamMaxK and with 16-bit offsets
+    double launch, round, first_copy, unit;
+    double wave_copy, cu_copy;       // bytes per ns that a wavefront, a compute unit copies
+    double by_registers;             // of the bytes that no direct copy moves
+    double not_overlapped;           // of the shorter of a stage's walk and the next one's copy
+    double slabs, slab_rate;         // of the sum over slabs: ns, bytes per ns
+    double memory, memory_rate;      // passing all operands once
+    double beside;                   // of the shorter of that and of the workgroups' own time
+};
+constexpr Factors kBytes{50.7, 10.9, 35.4, 1.36, 1810, 2190, 662, 31, 15.7, 59.9, 1.55, 0.43, 2600, 4550, 0, 3506, 0.08};
+constexpr Factors kTwoBytes{66.0, 13.7, 0, 1.24, 1670, 1800, 874, 29, 15.7, 82.0, 1.57, 0, 2700, 3750, 3000, 3835, 0};
+
 struct Expectation {
+    const Factors& f;
     double slow, memory, slab;   // factor of an entry; what passing all operands once takes; the slab sums, per slab
+    double least;                // what every launch takes: its fixed times and the walk of all entries, spread over the chip
     double group;                // bytes of a group of banks, weighted by the way it is copied
     int k;
 
-    Expectation(int vsize, int isize, int64_t M, int64_t K, int bank, int k_, int64_t N, int64_t n_tiles) : k(k_) {
+    Expectation(int vsize, int isize, int64_t M, int64_t K, int bank, int k_, int64_t N, int64_t n_tiles)
+        : f(isize == 2 ? kTwoBytes : kBytes), k(k_) {
         const double w_bytes = (double)M * (K / bank) * k * (vsize + isize), y_bytes = 4.0 * M * N;
-        slow = isize == 2 || k > kStreamMaxK ? 1.24 : 1.0;
-        memory = 3000 + (w_bytes * std::min<int64_t>(n_tiles, 2) + 4.0 * K * N + y_bytes) / 3835;
-        slab = 2.0 * y_bytes / 3750;
-        group = (double)bank * kStreamPitch * (N % 4 == 0 ? 1.0 : 1.57);   // as in the usual X, whose rows are adjacent
+        slow = isize == 2 || k > kStreamMaxK ? f.slow : 1.0;
+        memory = f.memory + (w_bytes * std::min<int64_t>(n_tiles, 2) + 4.0 * K * N + y_bytes) / f.memory_rate;
+        slab = 2.0 * y_bytes / f.slab_rate;
+        const double entries = (double)div_up(M, (int64_t)kStreamRows) * n_tiles * div_up(K / bank, (int64_t)kStreamBanks) * k;
+        least = std::max(memory, f.launch + f.round + f.first_copy + entries * slow * std::max(f.shared, f.simd * 0.25) / kCus);
+        group = (double)bank * kStreamPitch * (N % 4 == 0 ? 1.0 : f.by_registers);   // as in the usual X, whose rows are adjacent
     }
-    double slabs(int n) const { return n > 1 ? 2700 + n * slab : 0.0; }
+    double slabs(int n) const { return n > 1 ? f.slabs + n * slab : 0.0; }
     // No launch of so many slabs takes less, ...
-    double at_least(int n_slabs) const { return memory + slabs(n_slabs); }
+    double at_least(int n_slabs) const { return least + slabs(n_slabs); }
     // ... nor one of so many wavefronts side by side (as many entries and copies in all, whatever ks), ...
     double at_least(int n_slabs, int slab_groups, int row_waves, double rounds, double per_cu) const {
-        const double walk = slab_groups * k * slow * row_waves * std::max(kEntryAlone / kMaxWalkers, kEntryShared * per_cu);
-        return total(n_slabs, rounds, std::max(walk, slab_groups * group * per_cu * (1.0 / kCopyRate)));
+        const double walk = slab_groups * k * slow * row_waves * std::max({f.alone / kMaxWalkers, f.shared * per_cu, f.simd * per_cu * 0.25});
+        return total(n_slabs, rounds, std::max(walk, slab_groups * group * per_cu * (1.0 / f.cu_copy)));
     }
-    // ... nor with ks groups of those.
-    double at_least(int n_slabs, int slab_groups, int row_waves, double rounds, double per_cu, int ks) const {
-        const double unit = k * slow * std::max(kEntryAlone, kEntryShared * ks * row_waves * per_cu) + kUnitNs;
-        return total(n_slabs, rounds, ks * group * (1.0 / kCopyRate) + div_up(slab_groups, ks) * unit);
+    // ... nor with ks groups of those and so many groups of banks in the first stage.
+    double at_least(int n_slabs, int slab_groups, int row_waves, double rounds, double per_cu, int ks, int first) const {
+        const double unit = k * slow * std::max({f.alone, f.shared * ks * row_waves * per_cu, f.simd * (int)(ks * row_waves * per_cu * 0.25 + 0.9999)}) + f.unit;
+        return total(n_slabs, rounds, first * group * per_cu * (1.0 / f.cu_copy) + div_up(slab_groups, ks) * unit);
     }
-    double total(int n_slabs, double rounds, double ns) const { return kLaunchNs + rounds * (kRoundNs + kFirstCopyNs + ns) + slabs(n_slabs); }
+    double total(int n_slabs, double rounds, double ns) const { return f.launch + rounds * (f.round + f.first_copy + ns) + slabs(n_slabs); }
     double operator()(const SpmmStreamPlan& p, int slab_groups, int wgs) const {
         const int walkers = p.ksplit * p.row_waves, waves = walkers + p.copy_waves, sg = p.sb / kStreamBanks, stages = div_up(slab_groups, sg);
         const int per_cu = std::max(1, std::min({kMaxLdsBytes / (int)p.lds_bytes, kWavesPerCu / waves, div_up(wgs, kCus)}));
-        const double entry = std::max(kEntryAlone, kEntryShared * walkers * per_cu) * slow;
-        const double unit = k * entry + kUnitNs * std::max(1.0, walkers * per_cu / 4.0);
+        const double entry = std::max({f.alone, f.shared * walkers * per_cu, f.simd * div_up(walkers * per_cu, 4)}) * slow;
+        const double unit = k * entry + f.unit * std::max(1.0, walkers * per_cu / 4.0);
         const double walk = div_up(std::min(sg, slab_groups), p.ksplit) * unit;
-        const double first = kFirstCopyNs + std::min(sg, slab_groups) * group * per_cu / std::min(kWaveCopyRate * waves * per_cu, kCopyRate);
+        const double first = f.first_copy + std::min(sg, slab_groups) * group * per_cu / std::min(f.wave_copy * waves * per_cu, f.cu_copy);
         double t = first + walk;
         if (stages > 1) {
             const double tail = div_up(slab_groups - (stages - 1) * sg, p.ksplit) * unit;
-            const double copy = kFirstCopyNs + sg * group * per_cu / std::min(kWaveCopyRate * p.copy_waves * per_cu, kCopyRate);
-            t = first + tail + (stages - 1) * (p.n_bufs == 2 ? std::max(walk, copy) : walk + copy);
+            const double copy = f.first_copy + sg * group * per_cu / std::min(f.wave_copy * p.copy_waves * per_cu, f.cu_copy);
+            t = first + tail + (stages - 1) * (p.n_bufs == 2 ? std::max(walk, copy) + f.not_overlapped * std::min(walk, copy) : walk + copy);
         }
-        return std::max(kLaunchNs + div_up(wgs, kCus * per_cu) * (t + kRoundNs), memory) + slabs(p.n_slabs);
+        t = f.launch + div_up(wgs, kCus * per_cu) * (t + f.round);
+        return std::max(t, memory) + f.beside * std::min(t, memory) + slabs(p.n_slabs);
     }
 };
 
@@ -76,8 +96,9 @@ double rounding(const SpmmStreamPlan& p, int slab_groups, int k) {
 }  // namespace
 
 // This runs in every call, so most launches are passed over by what they take at least.  The planning of fc6 (4096 x 25088,
-// banks of 64) at N = 16 takes 0.9 us of host time instead of 2.9, of 3000 random products 0.37 instead of 0.65 in
-// the mean and 1.1 instead of 3.3 at the 99th percentile, the tile kernels' 0.17 included; the plans are the same.
+// banks of 64) at N = 16 takes 1.2 us of host time, of 3000 random products 0.41 in the mean and 1.6 at the 99th percentile,
+// the tile kernels' 0.17 included.  The numbers of slabs are tried in steps of a third; in steps of a half (0.35 us and 1.3)
+// fc6 has 9 slabs and 10 walkers (18.6 us) where 11 slabs and 12 walkers take 18.2.
 SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int max_slabs, int max_lds,
                                 double max_rounding, double max_ns) {
     SpmmStreamPlan best{};
@@ -89,9 +110,14 @@ SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int 
     if (fit < 1) return best;
     const Expectation expected(vsize, isize, M, K, bank, k, N, tiles);
     best.ns = max_ns;
-    for (int s = 1; s <= max_slabs; s = s < 4 ? s + 1 : s + s / 2) {
+    // First the slabs that give every compute unit a workgroup of 12 wavefronts, most often the best or near it.
+    const int likely = (int)std::clamp<int64_t>(kCus / std::max<int64_t>(1, n_tiles * div_up(M, (int64_t)12 * rows)), 1, max_slabs);
+    for (int s = likely, next = likely == 1 ? 2 : 1; s <= max_slabs; s = next, next = s < 4 ? s + 1 : s + (s + 1) / 3) {
         const int slab_groups = div_up(div_up(nb, s), ib), slabs = div_up(nb, slab_groups * ib);
-        if (expected.at_least(slabs) >= best.ns) break;          // more slabs take longer still
+        if (expected.at_least(slabs) >= best.ns) {
+            if (next > s) break;          // more slabs take longer still
+            continue;
+        }
         int seen_waves = 0, seen_rows = 0;
         for (int c = 1; c <= 4; ++c) {           // workgroups per compute unit to aim at
             const int target = (int)std::max<int64_t>(1, (int64_t)kCus * c / ((int64_t)n_tiles * slabs)), m = (int)div_up(M, (int64_t)target);
@@ -107,7 +133,7 @@ SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int 
             const double rounds = alone ? div_up(wgs, kCus) : 1, per_cu = alone ? 1 : std::max(1.0, wgs * (1.0 / kCus));
             if (expected.at_least(slabs, slab_groups, row_waves, rounds, per_cu) >= best.ns) continue;
             for (int ks = 1; ks * row_waves <= kMaxWalkers && ks <= slab_groups; ks = ks < 4 ? ks + 1 : ks + ks / 2) {
-                if (expected.at_least(slabs, slab_groups, row_waves, rounds, per_cu, ks) >= best.ns) continue;
+                if (expected.at_least(slabs, slab_groups, row_waves, rounds, per_cu, ks, slab_groups <= fit_one ? slab_groups : ks) >= best.ns) continue;
                 // a stage holds a group of banks for each of the ks; two of them side by side
                 int sg = std::min(slab_groups, fit_half / ks * ks);
                 int bufs = sg >= slab_groups ? 1 : 2;

@@ -65,6 +65,17 @@ def test_stages_against_float64(M, nb, bank, k, N, dtype):
         assert torch.equal(out[:, :N], Y) and bool((out[:, N:] == 7.0).all())
 
 
+# numbers of slabs that steps of a half would pass over
+@pytest.mark.parametrize("M,nb,bank,k,N,dtype,slabs", [
+    (16, 240, 20, 7, 31, "f16", 5), (17, 225, 32, 4, 46, "f32", 8), (16, 373, 25, 8, 58, "f32", 10), (16, 508, 25, 7, 32, "f16", 13)])
+def test_slabs_in_finer_steps(M, nb, bank, k, N, dtype, slabs):
+    p = bs.bs_spmm_plan(bs.BS_F16 if dtype == "f16" else bs.BS_F32, M, nb * bank, bank, k, N)
+    assert (p["stages"], p["stage_slabs"]) == (1, slabs)
+    v, i, dense, g, spmm = _product(M, nb, bank, k, dtype, M + nb + k)
+    X = torch.randn((nb * bank, N), generator=g, device="cuda")
+    _check(spmm(v, i, bank, X), dense, X.cpu().double(), nb * k)
+
+
 # 522 304 columns: four banks of X span more than 2 GB
 @pytest.mark.parametrize("M,nb,bank,k,N,pitches", [
     (700, 63, 50, 10, 112, (113, 116, 121)), (700, 63, 50, 10, 115, (116, 117, 120)), (512, 72, 64, 16, 784, (785, 788)),
