@@ -626,8 +626,8 @@ def main():
         except Exception as exc:
             extras["baselines_error"] = str(exc)[:200]
 
-        # more of the machine's floor: a large streaming read, LDS gather rates, and the
-        # grid-wide barrier a persistent multi-step kernel would need once per step
+        # more of the machine's floor: a large streaming read, LDS gather rates, and a grid-wide
+        # barrier (what a step of several in one kernel would cost, did the data not carry its flag)
         try:
             floor = {}
             big = 288 << 20
@@ -696,8 +696,8 @@ def main():
             extras["machine_floor_error"] = str(exc)[:200]
 
         # fused LSTM time steps (Sec. 4.3's language model: H = I = 1500 is this very gate
-        # matrix): T dependent steps replayed from one graph, weights cache resident as in
-        # a real recurrence; per step = the sparse product + bias, gates and cell update
+        # matrix): T dependent steps of one call replayed from a graph, weights kept on the chip
+        # as in a real recurrence; per step = the sparse product + bias, gates and cell update
         if not spmm and wl.M % 4 == 0 and wl.K > wl.M // 4:
             try:
                 Hn, T = wl.M // 4, 64
