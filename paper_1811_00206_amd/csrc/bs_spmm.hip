@@ -221,10 +221,11 @@ double tiles_rounding(const SpmmPlan& p, int64_t nb, int k) {
 }
 
 // The stage kernels are taken, for every row pitch of X alike, where they are expected to be faster.  With 8-bit offsets the
-// two expectations are fits to launches of the same products, so the line is where they meet: over 3000 random products that
-// some line between 0.94 and 1.04 plans anew, 1.0 gave 0.948 of the time that the expectations of kTwoBytes and a line at 0.93
-// did (geometric mean), 0.94 0.957 and 1.04 0.947.  Of 6000 other products 789 are planned anew; 395 of them, timed: 0.941 of
-// the time, 226 gain more than 3 %, 64 lose that, 28 lose more than 8 % (11289 x 3900, N = 17: 30.4 -> 38.8 us).
+// two expectations are fits to launches of the same products, so the line is near where they meet, and a little beyond, as the
+// stage kernels round less: over 3000 random products that some line between 0.94 and 1.04 plans anew, 1.04 gave 0.947 of the
+// time that the expectations of kTwoBytes and a line at 0.93 did (geometric mean), 1.0 0.948 and 0.94 0.957; 1586 gain more
+// than 3 %, 514 lose that, 212 lose more than 8 % (11289 x 3900, N = 17: 30.4 -> 38.8 us).  With more workgroups than compute
+// units, below, the line is where they meet: of 250 products that 1.04 plans unlike 1.0, 29 lost more than 15 % without that.
 // The 16-bit ones keep the line of the fit that they have, 0.93.  Products expected
 // below kStreamWorthNs are not worth the planning.  The terms are what the expectations leave out:
 //   * Banks of more than 32 entries and one tile of columns stay on the tile kernels.  What divides these products
@@ -240,7 +241,7 @@ double tiles_rounding(const SpmmPlan& p, int64_t nb, int k) {
 // A launch whose sums would round worse than the tile kernels' is not looked at: those walk an odd row length or a small
 // tile with up to 64 lanes per row, so their sums are short (6722 x 144, banks of 16, k = 13, N = 40: 4 entries per lane and
 // an exchange, against 39 in a lane of the stage kernels, 1.5 times the error).  Of 4000 random products, 4 %.
-constexpr double kStreamMargin = 1.0, kStreamMarginTwoBytes = 0.93, kStreamWorthNs = 6000;
+constexpr double kStreamMargin = 1.04, kStreamMarginTwoBytes = 0.93, kStreamWorthNs = 6000;
 constexpr double kStreamManyAligned = 1.05, kStreamManyUnaligned = 1.2, kStreamLongBank = 1.1;
 constexpr int kStreamLongK = 32;
 constexpr double kStreamMaxXBytes = 128e6;
@@ -254,7 +255,8 @@ SpmmStreamPlan stream_choice(const SpmmPlan& p, int vsize, int isize, int64_t M,
     const double max_ns = (isize == 2 ? kStreamMarginTwoBytes : kStreamMargin) * tiles / (k > kStreamLongK ? kStreamLongBank : 1.0);
     const SpmmStreamPlan sp = spmm_stream_plan(vsize, isize, M, K, bank, k, N, p.n_slabs, max_lds, tiles_rounding(p, K / bank, k), max_ns);
     const bool many = (int64_t)sp.n_tiles * sp.n_slabs * sp.row_groups > kCus;
-    if (sp.ok && many && sp.ns * (N % 4 == 0 ? kStreamManyAligned : kStreamManyUnaligned) >= max_ns) return {};
+    const double many_ns = isize == 2 ? max_ns : max_ns / kStreamMargin;     // these at the line where the expectations meet
+    if (sp.ok && many && sp.ns * (N % 4 == 0 ? kStreamManyAligned : kStreamManyUnaligned) >= many_ns) return {};
     return sp;
 }
 
