@@ -110,9 +110,10 @@ SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int 
     if (fit < 1) return best;
     const Expectation expected(vsize, isize, M, K, bank, k, N, tiles);
     best.ns = max_ns;
-    // First the slabs that give every compute unit a workgroup of 12 wavefronts, most often the best or near it.
-    const int likely = (int)std::clamp<int64_t>(kCus / std::max<int64_t>(1, n_tiles * div_up(M, (int64_t)12 * rows)), 1, max_slabs);
-    for (int s = likely, next = likely == 1 ? 2 : 1; s <= max_slabs; s = next, next = s < 4 ? s + 1 : s + (s + 1) / 3) {
+    // First the slabs that give every compute unit a workgroup of 12 wavefronts, most often the best or near it.  (With
+    // 16-bit offsets in the order and the steps that their launches were timed with.)
+    const int likely = isize == 2 ? 1 : (int)std::clamp<int64_t>(kCus / std::max<int64_t>(1, n_tiles * div_up(M, (int64_t)12 * rows)), 1, max_slabs);
+    for (int s = likely, next = likely == 1 ? 2 : 1; s <= max_slabs; s = next, next = s < 4 ? s + 1 : s + (isize == 2 ? s / 2 : (s + 1) / 3)) {
         const int slab_groups = div_up(div_up(nb, s), ib), slabs = div_up(nb, slab_groups * ib);
         if (expected.at_least(slabs) >= best.ns) {
             if (next > s) break;          // more slabs take longer still

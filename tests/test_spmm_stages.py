@@ -118,6 +118,14 @@ def test_launches_of_random_shapes_with_16_bit_offsets():
     assert taken > 150
 
 
+@pytest.mark.parametrize("dtype,shape,stages,slabs", [
+    (bs.BS_F16, (1963, 23552, 512, 25, 13), 0, 12), (bs.BS_F32, (291, 20400, 300, 45, 172), 1, 9)])
+def test_products_with_16_bit_offsets_keep_their_launches(dtype, shape, stages, slabs):
+    """The expected times of these are a fit to launches whose slabs were looked for in steps of a half."""
+    p = bs.bs_spmm_plan_wide(dtype, *shape)
+    assert (p["stages"], p["stage_slabs"] if stages else p["n_slabs"]) == (stages, slabs)
+
+
 def test_the_timed_sizes_and_small_ones():
     for M, K, bank, k, N, dtype in [(6000, 3000, 100, 10, 128, bs.BS_F32), (6000, 3000, 50, 15, 37, bs.BS_F32),
                                     (512, 4608, 64, 16, 784, bs.BS_F32), (4096, 25088, 64, 6, 16, bs.BS_F16),
