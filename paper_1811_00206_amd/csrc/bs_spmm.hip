@@ -176,20 +176,20 @@ SpmmPlan make_plan(int dtype, int64_t M, int64_t K, int bank, int k, int64_t N, 
 }
 
 // What the tile kernels are expected to take for a plan of more than 8 columns, in ns, the slab sums included.  Fits to
-// random products on MI355X: with 8-bit offsets 2656 of them, whose operands change from call to call (median error 4.4 %,
-// 8.7 % rms), with 16-bit offsets 442, most of them of 8-bit ones (5 %, 9 % rms).
+// random products on MI355X.  kFirst: 442 of them, operands repeated (median error 5 %, 9 % rms); kSecond: 2656 with 8-bit
+// offsets whose operands change from call to call (4.4 %, 8.7 %).
 struct TileFactors {
     double rows_alone, rows_shared, rows_simd, load, row;    // lane per row: of an entry as in bs_spmm_stream.hip; of 16 chunks; of a pass
     double rows_ch2, rows_ch1, rows_half;
     double alone, shared, simd, pass, few;                   // several lanes per row; `few`: chunks of at most 2 entries
     double tile, unaligned, wave_copy, cu_copy, launch, memory, memory_rate, slabs, slab_rate;
 };
-constexpr TileFactors kBytes{16.05, 3.42, 13.3, 439, 0, 0.94, 0.96, 1.05, 46.8, 6.22, 14.36, 686, 1.24,
-                             0, 1.61, 550, 65.2, 3460, 3739, 2972, 2324, 4069};
-constexpr TileFactors kTwoBytes{14.2, 3.68, 0, 530, 223, 0.94, 0.9, 1.07, 41.3, 2.84, 0, 629, 1.4,
+constexpr TileFactors kFirst{14.2, 3.68, 0, 530, 223, 0.94, 0.9, 1.07, 41.3, 2.84, 0, 629, 1.4,
                                 104, 1.37, 15, 54.2, 2930, 2500, 3019, 1920, 4800};
-double tiles_ns(const SpmmPlan& p, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, SpmmCopy copy) {
-    const TileFactors& f = isize == 2 ? kTwoBytes : kBytes;
+constexpr TileFactors kSecond{16.05, 3.42, 13.3, 439, 0, 0.94, 0.96, 1.05, 46.8, 6.22, 14.36, 686, 1.24,
+                             0, 1.61, 550, 65.2, 3460, 3739, 2972, 2324, 4069};
+double tiles_ns(const SpmmPlan& p, SpmmFit fit, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, SpmmCopy copy) {
+    const TileFactors& f = fit == kFirstFit ? kFirst : kSecond;
     const int threads = launched_threads(p, copy);
     const int64_t wgs = (int64_t)p.n_tiles * p.n_slabs * p.row_groups, nb = K / bank;
     const double per_cu = (double)std::max<int64_t>(1, std::min<int64_t>({(int64_t)(kMaxLdsBytes / p.lds_bytes), 1024 / threads, (wgs + kCus - 1) / kCus}));
@@ -220,14 +220,13 @@ double tiles_rounding(const SpmmPlan& p, int64_t nb, int k) {
            std::log2((double)std::min<int64_t>(p.lpr, chunks)) + chain_rounding(p.n_slabs, false);
 }
 
-// The stage kernels are taken, for every row pitch of X alike, where they are expected to be faster.  With 8-bit offsets the
-// two expectations are fits to launches of the same products, so the line is near where they meet, and a little beyond, as the
-// stage kernels round less: over 3000 random products that some line between 0.94 and 1.04 plans anew, 1.04 gave 0.947 of the
-// time that the expectations of kTwoBytes and a line at 0.93 did (geometric mean), 1.0 0.948 and 0.94 0.957; 1586 gain more
-// than 3 %, 514 lose that, 212 lose more than 8 % (11289 x 3900, N = 17: 30.4 -> 38.8 us).  With more workgroups than compute
-// units, below, the line is where they meet: of 250 products that 1.04 plans unlike 1.0, 29 lost more than 15 % without that.
-// The 16-bit ones keep the line of the fit that they have, 0.93.  Products expected
-// below kStreamWorthNs are not worth the planning.  The terms are what the expectations leave out:
+// The stage kernels are taken, for every row pitch of X alike, where they are expected to be faster.  The first fit says
+// whether and with which launch, by a line at 0.93 that was chosen with both kernels of 1050 random products timed.  Products
+// expected below kStreamWorthNs are not worth the planning.  With 8-bit offsets the second fit then looks for another stage
+// launch: one that it expects to take less than the first one (both times by the second fit, so much of what that is off by
+// is common to the two) and whose sums round no worse.  Without that condition 8 % of random products got sums
+// of a larger error (512 x 4608 at N = 784 1.4 times; up to 2.3 times where a product went back to the tile kernels, which
+// now none does).  The terms below are what the expectations leave out:
 //   * Banks of more than 32 entries and one tile of columns stay on the tile kernels.  What divides these products
 //     is the stream of W: all 4 of the 27 timed ones with more than 64 MB of it lose (15947 x 6144, 124 entries
 //     per bank, N = 12: 40.1 us by tiles, 68.7 in stages), 11 of the 23 with at most 42 MB gain up to three times
@@ -241,23 +240,37 @@ double tiles_rounding(const SpmmPlan& p, int64_t nb, int k) {
 // A launch whose sums would round worse than the tile kernels' is not looked at: those walk an odd row length or a small
 // tile with up to 64 lanes per row, so their sums are short (6722 x 144, banks of 16, k = 13, N = 40: 4 entries per lane and
 // an exchange, against 39 in a lane of the stage kernels, 1.5 times the error).  Of 4000 random products, 4 %.
-constexpr double kStreamMargin = 1.04, kStreamMarginTwoBytes = 0.93, kStreamWorthNs = 6000;
+constexpr double kStreamMargin = 0.93, kStreamWorthNs = 6000;
+constexpr double kSecondMargin = 1.0;
 constexpr double kStreamManyAligned = 1.05, kStreamManyUnaligned = 1.2, kStreamLongBank = 1.1;
 constexpr int kStreamLongK = 32;
 constexpr double kStreamMaxXBytes = 128e6;
 SpmmStreamPlan stream_choice(const SpmmPlan& p, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N) {
     if (N <= 8 || k < kStreamMinK) return {};
     if ((k > kStreamLongK && N <= 16) || 4.0 * K * N > kStreamMaxXBytes) return {};
-    const double tiles = tiles_ns(p, vsize, isize, M, K, bank, k, N, copy_kind(N, N));
-    if (tiles <= kStreamWorthNs) return {};
     // a product whose tile kernel needs no LDS limit raised can be captured as the first of all, so this one may not need it either
     const int max_lds = p.lds_bytes > kLdsWithoutLimit ? kMaxLdsBytes : (int)kLdsWithoutLimit;
-    const double max_ns = (isize == 2 ? kStreamMarginTwoBytes : kStreamMargin) * tiles / (k > kStreamLongK ? kStreamLongBank : 1.0);
-    const SpmmStreamPlan sp = spmm_stream_plan(vsize, isize, M, K, bank, k, N, p.n_slabs, max_lds, tiles_rounding(p, K / bank, k), max_ns);
-    const bool many = (int64_t)sp.n_tiles * sp.n_slabs * sp.row_groups > kCus;
-    const double many_ns = isize == 2 ? max_ns : max_ns / kStreamMargin;     // these at the line where the expectations meet
-    if (sp.ok && many && sp.ns * (N % 4 == 0 ? kStreamManyAligned : kStreamManyUnaligned) >= many_ns) return {};
-    return sp;
+    const double longer = k > kStreamLongK ? kStreamLongBank : 1.0;
+    auto tiles = [&](SpmmFit fit) { return tiles_ns(p, fit, vsize, isize, M, K, bank, k, N, copy_kind(N, N)); };
+    // a launch to be taken instead of the tile kernels
+    auto instead = [&](SpmmFit fit, double max_rounding, double max_ns, double many_ns) {
+        const SpmmStreamPlan sp = spmm_stream_plan(fit, vsize, isize, M, K, bank, k, N, 1, p.n_slabs, max_lds, max_rounding, max_ns);
+        const bool many = (int64_t)sp.n_tiles * sp.n_slabs * sp.row_groups > kCus;
+        return sp.ok && many && sp.ns * (N % 4 == 0 ? kStreamManyAligned : kStreamManyUnaligned) >= many_ns ? SpmmStreamPlan{} : sp;
+    };
+    const double first_tiles = tiles(kFirstFit), max_ns = kStreamMargin * first_tiles / longer;
+    SpmmStreamPlan first{};
+    if (first_tiles > kStreamWorthNs) first = instead(kFirstFit, tiles_rounding(p, K / bank, k), max_ns, max_ns);
+    if (isize == 2) return first;
+    if (!first.ok) {
+        const double ns = tiles(kSecondFit) / longer;
+        return ns > kStreamWorthNs ? instead(kSecondFit, tiles_rounding(p, K / bank, k), kSecondMargin * ns, ns) : first;
+    }
+    const double ns = spmm_stream_ns(first, kSecondFit, vsize, isize, M, K, bank, k, N);
+    if (ns <= kStreamWorthNs) return first;
+    const SpmmStreamPlan second = spmm_stream_plan(kSecondFit, vsize, isize, M, K, bank, k, N, first.n_slabs,
+                                                   std::min(p.n_slabs, std::max(3, 2 * first.n_slabs)), max_lds, spmm_stream_rounding(first, k), kSecondMargin * ns);
+    return second.ok ? second : first;
 }
 
 // Y[r][n] = sum over slabs, in slab order.  magic_n = magic_u32(N): rows from element

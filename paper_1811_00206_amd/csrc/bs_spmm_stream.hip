@@ -18,10 +18,10 @@ constexpr I div_up(I a, I b) { return (a + b - 1) / b; }
 int unit_of(int isize, int k) { return isize == 2 ? (k < 8 ? 4 : 8) : k > kStreamMaxK ? 8 : k; }
 
 // Expected time of a launch in ns.  The terms are the kernel's own steps; their factors are fits to timed launches on
-// MI355X.  With 8-bit offsets: 19233 of 11000 random products whose operands change from call to call (median error 5 %, 8 %
-// rms; without the term of a SIMD 10 %).  Wavefront w of a workgroup runs on SIMD w % 4 and a stage waits for the busiest of
-// the four, so 5 walking wavefronts take as long as 8.  With 16-bit offsets: 1332 of random shapes and plans, most of them
-// with 8-bit offsets (6 %, 11 % rms); these products keep the launches that they were timed with.
+// MI355X.  kFirst: 1332 launches of random shapes and plans, operands repeated, both offset widths (median error 6 %, 11 %
+// rms).  kSecond: 19233 launches of 11000 random products with 8-bit offsets whose operands change from call to call (5 %, 8 %;
+// without the term of a SIMD 10 %).  Wavefront w of a workgroup runs on SIMD w % 4 and a stage waits for the busiest
+// of the four, so 5 walking wavefronts take as long as 8.  Which of them says what: stream_choice in bs_spmm.hip.
 struct Factors {
     double alone, shared, simd;      // of an entry: a wavefront by itself, each that shares the compute unit, a SIMD
     double slow;                     // factor of an entry above k = kStreamMaxK and with 16-bit offsets
@@ -33,8 +33,8 @@ struct Factors {
     double memory, memory_rate;      // passing all operands once
     double beside;                   // of the shorter of that and of the workgroups' own time
 };
-constexpr Factors kBytes{50.7, 10.9, 35.4, 1.36, 1810, 2190, 662, 31, 15.7, 59.9, 1.55, 0.43, 2600, 4550, 0, 3506, 0.08};
-constexpr Factors kTwoBytes{66.0, 13.7, 0, 1.24, 1670, 1800, 874, 29, 15.7, 82.0, 1.57, 0, 2700, 3750, 3000, 3835, 0};
+constexpr Factors kFirst{66.0, 13.7, 0, 1.24, 1670, 1800, 874, 29, 15.7, 82.0, 1.57, 0, 2700, 3750, 3000, 3835, 0};
+constexpr Factors kSecond{50.7, 10.9, 35.4, 1.36, 1810, 2190, 662, 31, 15.7, 59.9, 1.55, 0.43, 2600, 4550, 0, 3506, 0.08};
 
 struct Expectation {
     const Factors& f;
@@ -43,8 +43,8 @@ struct Expectation {
     double group;                // bytes of a group of banks, weighted by the way it is copied
     int k;
 
-    Expectation(int vsize, int isize, int64_t M, int64_t K, int bank, int k_, int64_t N, int64_t n_tiles)
-        : f(isize == 2 ? kTwoBytes : kBytes), k(k_) {
+    Expectation(SpmmFit fit, int vsize, int isize, int64_t M, int64_t K, int bank, int k_, int64_t N, int64_t n_tiles)
+        : f(fit == kFirstFit ? kFirst : kSecond), k(k_) {
         const double w_bytes = (double)M * (K / bank) * k * (vsize + isize), y_bytes = 4.0 * M * N;
         slow = isize == 2 || k > kStreamMaxK ? f.slow : 1.0;
         memory = f.memory + (w_bytes * std::min<int64_t>(n_tiles, 2) + 4.0 * K * N + y_bytes) / f.memory_rate;
@@ -95,11 +95,15 @@ double rounding(const SpmmStreamPlan& p, int slab_groups, int k) {
 
 }  // namespace
 
-// This runs in every call, so most launches are passed over by what they take at least.  The planning of fc6 (4096 x 25088,
-// banks of 64) at N = 16 takes 1.2 us of host time, of 3000 random products 0.41 in the mean and 1.6 at the 99th percentile,
-// the tile kernels' 0.17 included.  The numbers of slabs are tried in steps of a third; in steps of a half (0.35 us and 1.3)
-// fc6 has 9 slabs and 10 walkers (18.6 us) where 11 slabs and 12 walkers take 18.2.
-SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int max_slabs, int max_lds,
+double spmm_stream_rounding(const SpmmStreamPlan& p, int k) { return rounding(p, p.slab_banks / kStreamBanks, k); }
+
+double spmm_stream_ns(const SpmmStreamPlan& p, SpmmFit fit, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N) {
+    return Expectation(fit, vsize, isize, M, K, bank, k, N, p.n_tiles)(p, p.slab_banks / kStreamBanks, p.n_tiles * p.n_slabs * p.row_groups);
+}
+
+// This runs in every call, so most launches are passed over by what they take at least: 3000 random products are
+// planned in 0.40 us in the mean and 1.4 at the 99th percentile, fc6 (4096 x 25088, banks of 64) at N = 16 in 1.15, the tile kernels included.
+SpmmStreamPlan spmm_stream_plan(SpmmFit fit_of, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int min_slabs, int max_slabs, int max_lds,
                                 double max_rounding, double max_ns) {
     SpmmStreamPlan best{};
     constexpr int ib = kStreamBanks, rows = kStreamRows;
@@ -108,25 +112,31 @@ SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int 
     const int nb = (int)(K / bank), n_tiles = (int)tiles, group = bank * kStreamPitch;
     const int fit = max_lds / group, fit_half = max_lds / 2 / group, fit_one = std::min(max_lds, kMaxLdsBytes / 2) / group;
     if (fit < 1) return best;
-    const Expectation expected(vsize, isize, M, K, bank, k, N, tiles);
+    const int most_per_cu = fit_of == kFirstFit ? 4 : 1;     // with more the second fit found 6 % of its launches
+    const Expectation expected(fit_of, vsize, isize, M, K, bank, k, N, tiles);
     best.ns = max_ns;
-    // First the slabs that give every compute unit a workgroup of 12 wavefronts, most often the best or near it.  (With
-    // 16-bit offsets in the order and the steps that their launches were timed with.)
-    const int likely = isize == 2 ? 1 : (int)std::clamp<int64_t>(kCus / std::max<int64_t>(1, n_tiles * div_up(M, (int64_t)12 * rows)), 1, max_slabs);
-    for (int s = likely, next = likely == 1 ? 2 : 1; s <= max_slabs; s = next, next = s < 4 ? s + 1 : s + (isize == 2 ? s / 2 : (s + 1) / 3)) {
+    const double most_terms = 2 * max_rounding;      // added by a lane in a stage: with more the first term of rounding() is too large
+    // First the slabs that give every compute unit a workgroup of 12 wavefronts, most often the best or near it.
+    auto more = [&](int s) { return s < 4 ? s + 1 : fit_of == kFirstFit ? s + s / 2 : s + (s + 1) / 3; };
+    const int64_t enough = std::min<int64_t>(kCus / std::max<int64_t>(1, n_tiles * div_up(M, (int64_t)12 * rows)), max_slabs);
+    int likely = min_slabs;
+    while (more(likely) <= enough) likely = more(likely);
+    for (int s = likely, next = min_slabs; s <= max_slabs; s = next, next = more(next)) {
+        if (s == likely && next > likely) continue;       // looked at already
         const int slab_groups = div_up(div_up(nb, s), ib), slabs = div_up(nb, slab_groups * ib);
         if (expected.at_least(slabs) >= best.ns) {
             if (next > s) break;          // more slabs take longer still
             continue;
         }
+        const int per_group = (int)std::min<int64_t>((int64_t)n_tiles * slabs, INT32_MAX);      // workgroups
         int seen_waves = 0, seen_rows = 0;
-        for (int c = 1; c <= 4; ++c) {           // workgroups per compute unit to aim at
-            const int target = (int)std::max<int64_t>(1, (int64_t)kCus * c / ((int64_t)n_tiles * slabs)), m = (int)div_up(M, (int64_t)target);
+        for (int c = 1; c <= most_per_cu; ++c) {           // workgroups per compute unit to aim at
+            const int target = std::max(1, kCus * c / per_group), m = div_up((int)M, target);
             const int row_waves = std::min(div_up(m, rows), 12), rpwg = std::min(m, row_waves * rows);
             if (row_waves == seen_waves && rpwg == seen_rows) continue;
             seen_waves = row_waves;
             seen_rows = rpwg;
-            const int groups = (int)div_up(M, (int64_t)rpwg);
+            const int groups = div_up((int)M, rpwg);
             if ((double)rpwg * nb * k * 4 > UINT32_MAX || (double)n_tiles * slabs * groups > INT32_MAX / 2) continue;
             const int wgs = n_tiles * slabs * groups;
             // several stages fill more than half of LDS, whatever ks: one workgroup per compute unit at a time
@@ -134,6 +144,7 @@ SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int 
             const double rounds = alone ? div_up(wgs, kCus) : 1, per_cu = alone ? 1 : std::max(1.0, wgs * (1.0 / kCus));
             if (expected.at_least(slabs, slab_groups, row_waves, rounds, per_cu) >= best.ns) continue;
             for (int ks = 1; ks * row_waves <= kMaxWalkers && ks <= slab_groups; ks = ks < 4 ? ks + 1 : ks + ks / 2) {
+                if (k * (std::min(slab_groups, fit_half) - ks + 1) > most_terms * ks) continue;
                 if (expected.at_least(slabs, slab_groups, row_waves, rounds, per_cu, ks, slab_groups <= fit_one ? slab_groups : ks) >= best.ns) continue;
                 // a stage holds a group of banks for each of the ks; two of them side by side
                 int sg = std::min(slab_groups, fit_half / ks * ks);

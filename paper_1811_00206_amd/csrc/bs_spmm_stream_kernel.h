@@ -84,11 +84,14 @@ struct SpmmStreamPlan {
 // addition rounds its result, so it counts as many times as the result has terms, over the number of terms
 // of the whole sum.  Of `n` terms (or sums of equally many terms each, exact themselves) added one after the other:
 inline double chain_rounding(double n, bool terms) { return (n + 1) / 2 - (terms ? 0 : 1 / n); }
+enum SpmmFit { kFirstFit, kSecondFit };          // whose factors an expected time is made of
 // The best launch for a shape (of any row pitch of X: a product's sums are in the same order whatever the
-// pitch), with at most max_slabs slabs, max_lds bytes of LDS and sums whose rounding is at most max_rounding,
+// pitch), with at most max_slabs slabs (looked for from min_slabs on), max_lds bytes of LDS and sums whose rounding is at most max_rounding,
 // expected to take less than max_ns; ok = false where there is none or the kernels do not apply.
-SpmmStreamPlan spmm_stream_plan(int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int max_slabs,
+SpmmStreamPlan spmm_stream_plan(SpmmFit fit, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int min_slabs, int max_slabs,
                                 int max_lds, double max_rounding, double max_ns);
+double spmm_stream_rounding(const SpmmStreamPlan& p, int k);
+double spmm_stream_ns(const SpmmStreamPlan& p, SpmmFit fit, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N);
 // t: the operands as for the tile kernels, out and slab_stride for p's number of slabs
 int spmm_stream_launch(const SpmmStreamPlan& p, const SpmmArgs& t, int dtype, int isize, hipStream_t st);
 int spmm_stream_launch_f32(const SpmmStreamArgs& a, const SpmmLaunch& l);

@@ -205,6 +205,28 @@ def test_products_whose_sums_would_round_worse_stay_on_the_tile_kernels():
         assert p["stages"] == 0 and p["lpr"] >= 8, (shape, p)
 
 
+# shape, and the launch that the first fit gives it: slabs, banks per slab and per stage, wavefronts along K
+@pytest.mark.parametrize("dtype,shape,first", [
+    (bs.BS_F32, (512, 4608, 64, 16, 784), (1, 72, 16, 2)), (bs.BS_F32, (64, 10880, 128, 28, 2441), (3, 32, 8, 2)),
+    (bs.BS_F32, (188, 13200, 100, 6, 12), (6, 24, 24, 6)), (bs.BS_F16, (472, 21792, 32, 14, 96), (4, 172, 32, 4)),
+    (bs.BS_F32, (2900, 3648, 64, 31, 73), (1, 60, 12, 3)), (bs.BS_F32, (6000, 3000, 50, 15, 37), (1, 60, 24, 1))])
+def test_a_faster_launch_rounds_no_worse(dtype, shape, first):
+    """What the second fit expects to be faster is taken only where its sums are no less exact: both orders of addition on
+    the same products, against 64 bits."""
+    p = bs.bs_spmm_plan(dtype, *shape)
+    assert p["stages"] == 1
+    _, K, bank, k, _ = shape
+    g = np.random.default_rng(K + k)
+    n = 40000 * 64 // (K // bank * k)
+    w, x = (g.standard_normal((n, K // bank, k)).astype(np.float32) for _ in range(2))
+    t = w.astype(np.float64) * x
+    exact = t.sum(axis=(1, 2))
+    before = dict(zip(("stage_slabs", "stage_slab_banks", "stage_banks", "stage_ksplit"), first))
+    was, now = (np.linalg.norm(_stage_sums(q, t) - exact) for q in (before, p))
+    # each norm is over n independent errors: known to about 1 / sqrt(2 n) of itself
+    assert now <= was * (1 + 3 / math.sqrt(n)), (p, now / was)
+
+
 # the first five close to the line; many banks; the timed sizes
 @pytest.mark.parametrize("M,K,bank,k,N", [
     (6774, 320, 64, 19, 54), (2880, 336, 16, 6, 81), (9038, 400, 100, 4, 29), (245, 550, 50, 5, 543), (1591, 768, 64, 13, 15),
