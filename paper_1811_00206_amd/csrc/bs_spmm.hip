@@ -224,9 +224,16 @@ double tiles_rounding(const SpmmPlan& p, int64_t nb, int k) {
 // whether and with which launch, by a line at 0.93 that was chosen with both kernels of 1050 random products timed.  Products
 // expected below kStreamWorthNs are not worth the planning.  With 8-bit offsets the second fit then looks for another stage
 // launch: one that it expects to take less than the first one (both times by the second fit, so much of what that is off by
-// is common to the two) and whose sums round no worse.  Without that condition 8 % of random products got sums
+// is common to the two) and whose sums round no worse.  Without that condition 5 % of random products got sums
 // of a larger error (512 x 4608 at N = 784 1.4 times; up to 2.3 times where a product went back to the tile kernels, which
-// now none does).  The terms below are what the expectations leave out:
+// now none does).  How much less, from 3700 random products with both launches timed:
+//   * With more slabs than the first launch 0.97, with as many 0.95: of those expected at 0.98 to 1 every fifth loses more than 8 %.
+//   * Instead of tiles of 16 and 32 columns 1, above kStreamMaxK 0.96.  There the stream of W again divides the products: of
+//     74 with more than 10 MB of it 34 gain and 28 lose more than 8 % (3833 x 5120, 95 entries per bank, N = 30: 27.4 -> 42.7 us).
+//   * Tiles of 4 and 8 columns stay: of 414 products 243 would gain, but 66 lose more than 8 % (520 x 400, N = 5799: 21.0 -> 30.2).
+// Of 4500 other products that the second fit alone would plan anew, 1480 are: 0.914 of the time (geometric mean), 1125 gain more
+// than 3 %, 123 lose that, 45 more than 8 %.  By itself it plans all of them anew and 395 lose more than 8 %.
+// The terms below are what the expectations leave out:
 //   * Banks of more than 32 entries and one tile of columns stay on the tile kernels.  What divides these products
 //     is the stream of W: all 4 of the 27 timed ones with more than 64 MB of it lose (15947 x 6144, 124 entries
 //     per bank, N = 12: 40.1 us by tiles, 68.7 in stages), 11 of the 23 with at most 42 MB gain up to three times
@@ -241,7 +248,7 @@ double tiles_rounding(const SpmmPlan& p, int64_t nb, int k) {
 // tile with up to 64 lanes per row, so their sums are short (6722 x 144, banks of 16, k = 13, N = 40: 4 entries per lane and
 // an exchange, against 39 in a lane of the stage kernels, 1.5 times the error).  Of 4000 random products, 4 %.
 constexpr double kStreamMargin = 0.93, kStreamWorthNs = 6000;
-constexpr double kSecondMargin = 1.0;
+constexpr double kSecondMoreSlabs = 0.97, kSecondSameSlabs = 0.95, kSecondFromTiles = 1.0, kSecondFromTilesLong = 0.96, kSecondMaxWBytes = 10e6;
 constexpr double kStreamManyAligned = 1.05, kStreamManyUnaligned = 1.2, kStreamLongBank = 1.1;
 constexpr int kStreamLongK = 32;
 constexpr double kStreamMaxXBytes = 128e6;
@@ -263,13 +270,16 @@ SpmmStreamPlan stream_choice(const SpmmPlan& p, int vsize, int isize, int64_t M,
     if (first_tiles > kStreamWorthNs) first = instead(kFirstFit, tiles_rounding(p, K / bank, k), max_ns, max_ns);
     if (isize == 2) return first;
     if (!first.ok) {
+        const bool long_banks = k > kStreamMaxK;
+        if (!p.rows || (long_banks && (double)M * (K / bank) * k * (vsize + 1) > kSecondMaxWBytes)) return first;
         const double ns = tiles(kSecondFit) / longer;
-        return ns > kStreamWorthNs ? instead(kSecondFit, tiles_rounding(p, K / bank, k), kSecondMargin * ns, ns) : first;
+        return ns > kStreamWorthNs ? instead(kSecondFit, tiles_rounding(p, K / bank, k), (long_banks ? kSecondFromTilesLong : kSecondFromTiles) * ns, ns) : first;
     }
     const double ns = spmm_stream_ns(first, kSecondFit, vsize, isize, M, K, bank, k, N);
     if (ns <= kStreamWorthNs) return first;
-    const SpmmStreamPlan second = spmm_stream_plan(kSecondFit, vsize, isize, M, K, bank, k, N, first.n_slabs,
-                                                   std::min(p.n_slabs, std::max(3, 2 * first.n_slabs)), max_lds, spmm_stream_rounding(first, k), kSecondMargin * ns);
+    const SpmmStreamPlan second = spmm_stream_plan(kSecondFit, vsize, isize, M, K, bank, k, N, first.n_slabs, std::min(p.n_slabs, std::max(3, 2 * first.n_slabs)),
+                                                   max_lds, spmm_stream_rounding(first, (int)(K / bank), k), kSecondMoreSlabs * ns);
+    if (second.n_slabs == first.n_slabs && second.ns >= kSecondSameSlabs * ns) return first;
     return second.ok ? second : first;
 }
 

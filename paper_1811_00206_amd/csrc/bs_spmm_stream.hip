@@ -95,7 +95,25 @@ double rounding(const SpmmStreamPlan& p, int slab_groups, int k) {
 
 }  // namespace
 
-double spmm_stream_rounding(const SpmmStreamPlan& p, int k) { return rounding(p, p.slab_banks / kStreamBanks, k); }
+// As rounding(), with the stages, slabs and lanes that are not full counted as what they are.
+double spmm_stream_rounding(const SpmmStreamPlan& p, int nb, int k) {
+    const int sg = p.sb / kStreamBanks, ks = p.ksplit;
+    auto sums = [&](double n) { return (n - 1) * (n + 2) / 2; };               // 2 + 3 + ... + n
+    auto stage = [&](int groups) {                                             // of its terms, in ks wavefronts
+        const int n = groups / ks, longer = groups % ks;
+        auto chain = [&](double terms) { return terms * (terms + 1) / 2; };
+        return kStreamBanks * (longer * chain((double)(n + 1) * k) + (ks - longer) * chain((double)n * k));
+    };
+    auto slab = [&](int groups) {                                              // its stages, and those added
+        const int full = std::max(groups - 1, 0) / sg;
+        return full * stage(std::min(sg, groups)) + stage(groups - full * sg) + (full > 0 ? (double)kStreamBanks * k * (sg * sums(full) + groups) : 0.0);
+    };
+    const int rest = nb - (p.n_slabs - 1) * p.slab_banks, last = div_up(rest, kStreamBanks);
+    const double spare = last - rest * (1.0 / kStreamBanks);                    // share of the lanes that the last group leaves out
+    double all = (p.n_slabs - 1) * slab(p.slab_banks / kStreamBanks) + (1 - spare) * slab(last) + spare * slab(last - 1);
+    if (p.n_slabs > 1) all += k * (p.slab_banks * sums(p.n_slabs - 1) + nb);
+    return all / ((double)nb * k) + std::log2(kStreamBanks) + chain_rounding(ks, false);
+}
 
 double spmm_stream_ns(const SpmmStreamPlan& p, SpmmFit fit, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N) {
     return Expectation(fit, vsize, isize, M, K, bank, k, N, p.n_tiles)(p, p.slab_banks / kStreamBanks, p.n_tiles * p.n_slabs * p.row_groups);
@@ -164,7 +182,7 @@ SpmmStreamPlan spmm_stream_plan(SpmmFit fit_of, int vsize, int isize, int64_t M,
                 p.lds_bytes = std::max<size_t>((size_t)bufs * p.buf_bytes, (size_t)(ks - 1) * row_waves * 1024);
                 if (p.lds_bytes > (size_t)max_lds) continue;
                 p.ns = expected(p, slab_groups, wgs);
-                if (p.ns < best.ns && rounding(p, slab_groups, k) <= max_rounding) best = p;
+                if (p.ns < best.ns && (fit_of == kFirstFit ? rounding(p, slab_groups, k) : spmm_stream_rounding(p, nb, k)) <= max_rounding) best = p;
             }
         }
     }

@@ -90,7 +90,7 @@ enum SpmmFit { kFirstFit, kSecondFit };          // whose factors an expected ti
 // expected to take less than max_ns; ok = false where there is none or the kernels do not apply.
 SpmmStreamPlan spmm_stream_plan(SpmmFit fit, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int min_slabs, int max_slabs,
                                 int max_lds, double max_rounding, double max_ns);
-double spmm_stream_rounding(const SpmmStreamPlan& p, int k);
+double spmm_stream_rounding(const SpmmStreamPlan& p, int nb, int k);
 double spmm_stream_ns(const SpmmStreamPlan& p, SpmmFit fit, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N);
 // t: the operands as for the tile kernels, out and slab_stride for p's number of slabs
 int spmm_stream_launch(const SpmmStreamPlan& p, const SpmmArgs& t, int dtype, int isize, hipStream_t st);

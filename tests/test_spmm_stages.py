@@ -205,6 +205,15 @@ def test_products_whose_sums_would_round_worse_stay_on_the_tile_kernels():
         assert p["stages"] == 0 and p["lpr"] >= 8, (shape, p)
 
 
+@pytest.mark.parametrize("dtype,shape", [
+    (bs.BS_F32, (3833, 5120, 256, 95, 30)), (bs.BS_F32, (2565, 14208, 128, 42, 21)), (bs.BS_F16, (520, 400, 100, 5, 5799)),
+    (bs.BS_F32, (861, 1800, 50, 4, 17))])
+def test_products_that_are_slower_in_stages_stay_on_the_tile_kernels(dtype, shape):
+    """Long banks with a large stream of W, and tiles of few columns: 27.4, 43.4, 21.0 and 6.5 us by tiles, 42.7, 62.8, 30.2 and 8.5
+    in stages."""
+    assert bs.bs_spmm_plan(dtype, *shape)["stages"] == 0
+
+
 # shape, and the launch that the first fit gives it: slabs, banks per slab and per stage, wavefronts along K
 @pytest.mark.parametrize("dtype,shape,first", [
     (bs.BS_F32, (512, 4608, 64, 16, 784), (1, 72, 16, 2)), (bs.BS_F32, (64, 10880, 128, 28, 2441), (3, 32, 8, 2)),
