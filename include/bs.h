@@ -276,7 +276,8 @@ int bs_spmm_wide(const void* vals, const uint16_t* idx, int dtype, int64_t M, in
  * Requires I % 4 == 0 and H % 4 == 0 (BS_ERR_UNSUPPORTED otherwise) and the
  * shape rules above with M = 4H, K = I + H.  fp32 arithmetic throughout; logistic
  * and tanh are built from the hardware's exp2 and reciprocal (about 1 ulp each:
- * absolute error of an activation around 1e-7).
+ * absolute error of an activation around 1e-7).  A state that is no number is the
+ * word 0x7fc00000.
  */
 int bs_lstm_step(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I,
                  int bank, int k, const float* x, const float* h_in, const float* bias,

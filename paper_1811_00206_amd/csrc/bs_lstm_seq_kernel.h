@@ -29,7 +29,7 @@
 
 namespace bs {
 
-constexpr uint32_t kAbsent = 0xffffffffu, kGivenUp = 0xfffffffeu;   // above every other word; no hidden state: NaNs are stored as 0x7fc00000
+constexpr uint32_t kAbsent = 0xffffffffu, kGivenUp = 0xfffffffeu;   // above every other word; no hidden state: lstm_state()
 
 struct LstmSeqArgs {
     const void* vals;
@@ -70,13 +70,12 @@ constexpr int kLstmFinishThreads = 1024;
 
 __device__ __forceinline__ bool lstm_there(uint32_t w) { return w < kGivenUp; }
 
-// The cell update of one unit from its four rows' sums; h as it is stored.
+// The cell update of one unit from its four rows' sums; c and h as they are stored.
 __device__ __forceinline__ float lstm_cell(const float4 sum, const float4 bias, float& c) {
     const float gi = logistic_fast(sum.x + bias.x), gf = logistic_fast(sum.y + bias.y);
     const float gg = tanh_fast(sum.z + bias.z), go = logistic_fast(sum.w + bias.w);
-    c = fmaf(gf, c, gi * gg);
-    const float h = go * tanh_fast(c);
-    return h != h ? __builtin_bit_cast(float, 0x7fc00000u) : h;
+    c = lstm_state(fmaf(gf, c, gi * gg));
+    return lstm_state(go * tanh_fast(c));
 }
 
 // An LDS operation of this wavefront is finished for all the others behind this; global loads and stores stay in flight.

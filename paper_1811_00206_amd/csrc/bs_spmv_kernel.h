@@ -214,6 +214,8 @@ __device__ __forceinline__ float logistic_fast(float v) {
 __device__ __forceinline__ float tanh_fast(float v) {
     return 1.f - 2.f * __builtin_amdgcn_rcpf(1.f + exp_fast(2.f * v));
 }
+// A state as it is stored: every NaN as the same word, whatever the operands' were and their order in an instruction.
+__device__ __forceinline__ float lstm_state(float v) { return v != v ? __builtin_bit_cast(float, 0x7fc00000u) : v; }
 
 // VT: storage type of vals; CH: entries per chunk (CH*sizeof(VT) <= 16, CH divides
 // row_len); LPR: lanes per row; U: chunks a lane keeps in flight per round.
@@ -347,8 +349,8 @@ __device__ __forceinline__ void spmv_rows(const SpmvArgs& a) {
             const float gg = __shfl(act, first + 2 * LPR, kWave), go = __shfl(act, first + 3 * LPR, kWave);
             if (lane_in_row == 0 && (row_in_wg & 3) == 0 && live) {
                 const float c = fmaf(gf, cell_in, gi * gg);
-                a.c_out[row] = c;                                  // row = unit for gate i rows
-                a.h_out[row] = go * tanh_fast(c);
+                a.c_out[row] = lstm_state(c);                      // row = unit for gate i rows
+                a.h_out[row] = lstm_state(go * tanh_fast(c));
             }
             return;
         }
@@ -361,8 +363,8 @@ __device__ __forceinline__ void spmv_rows(const SpmvArgs& a) {
             const float gi = pre[4 * tid + 0], gf = pre[4 * tid + 1];
             const float gg = pre[4 * tid + 2], go = pre[4 * tid + 3];
             const float c = fmaf(gf, cell_in, gi * gg);
-            a.c_out[unit] = c;
-            a.h_out[unit] = go * tanh_fast(c);
+            a.c_out[unit] = lstm_state(c);
+            a.h_out[unit] = lstm_state(go * tanh_fast(c));
         }
     } else {
         if (live && lane_in_row == 0) a.y[row] = acc;

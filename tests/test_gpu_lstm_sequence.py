@@ -1,6 +1,5 @@
 """bs_lstm_sequence by the kernel that makes all steps (csrc/bs_lstm_seq_kernel.h): the bits of bs_lstm_step called T times,
 whatever the launch, and whatever its workgroups had to leave to the finishing kernel."""
-import numpy as np
 import pytest
 import torch
 
@@ -96,5 +95,22 @@ def test_states_that_share_memory_and_states_that_are_no_numbers():
     want, c_want = _steps(v, i, bank, X, h0, bias, c0)
     c = c0.clone()
     got = _sequence(v, i, bank, X, h0, bias, c, 512, 16)
-    same = lambda a, b: np.array_equal(a.cpu().numpy(), b.cpu().numpy(), equal_nan=True)
-    assert torch.isnan(want).any() and same(got, want) and same(c, c_want)
+    bits = lambda t: t.view(torch.int32)
+    assert torch.isnan(want).any() and torch.equal(bits(got), bits(want)) and torch.equal(bits(c), bits(c_want))
+    assert bool((bits(want)[torch.isnan(want)] == 0x7fc00000).all()) and bool((bits(c)[torch.isnan(c)] == 0x7fc00000).all())
+
+
+@pytest.mark.parametrize("H,I,bank,k,dtype", [(64, 64, 16, 4, "f32"), (256, 256, 64, 8, "f32"), (300, 300, 50, 13, "f16"), (1500, 1500, 100, 10, "f32")])
+def test_states_that_are_no_numbers_have_the_same_bits(H, I, bank, k, dtype):
+    """The first states, inputs and cells with NaNs of several bits: T steps, one kernel, and what the finishing kernel makes."""
+    v, i, X, h0, bias, c0 = _inputs(H, I, bank, k, dtype, 4, 5)
+    word = lambda w: torch.tensor(w, dtype=torch.int32, device=DEV).view(torch.float32)
+    h0[0], h0[H - 1], c0[1], c0[2], X[2, 3] = word(-1), word(-2), word(0x7f800001), word(-0x400000 + 77), word(0x7fffffff)
+    want, c_want = _steps(v, i, bank, X, h0, bias, c0)
+    bits = lambda t: t.view(torch.int32)
+    plan = bs.bs_lstm_sequence_plan(bs.BS_F16 if dtype == "f16" else bs.BS_F32, H, I, bank, k)
+    assert plan["one_kernel"] == 1 and torch.isnan(want).any()
+    for wait in (-1, 0):
+        c = c0.clone()
+        got = _sequence(v, i, bank, X, h0, bias, c, plan["threads"], 0, wait)
+        assert torch.equal(bits(got), bits(want)) and torch.equal(bits(c), bits(c_want))
