@@ -303,9 +303,10 @@ int bs_lstm_sequence(const void* vals, const uint8_t* idx, int dtype, int64_t H,
 /*
  * The same with the launch spelled out, for sweeps and tests: lanes per workgroup and
  * most workgroups of the kernel that makes all steps (0: the library's choice; a shape
- * that does not go is launched step by step), and how long a workgroup waits for the
+ * that does not go is launched step by step), and how long a workgroup waits in a step for the
  * others' hidden states before it leaves the rest to the finishing kernel, in ticks of the GPU's
- * 100 MHz clock (negative: the library's 20 ms; 0: not at all).  The results are the same.
+ * 100 MHz clock (negative: the library's 20 ms; 0: not at all).  It counts 14 ticks for each time it looks, so
+ * time in which its queue is switched out does not count.  The results are the same.
  */
 int bs_lstm_sequence_ex(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I,
                         int bank, int k, const float* X, int64_t T, const float* h0,

@@ -48,7 +48,7 @@ int launch_lstm_step(const void* vals, const uint8_t* idx, int dtype, int64_t H,
 // the launch of that step: entries per chunk and lanes per row; false where there is none
 bool lstm_step_lanes(int dtype, int64_t H, int64_t I, int bank, int k, int* ch, int* lpr);
 // T steps (bs_lstm_seq.hip).  threads, workgroups: 0, or the shape of the kernel that makes all steps; wait_ticks: how long
-// one of its workgroups waits for another's hidden state (negative: as long as in bs_lstm_sequence)
+// one of its workgroups waits in a step for the others' hidden states (negative: as long as in bs_lstm_sequence)
 int launch_lstm_sequence(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I, int bank, int k,
                          const float* X, int64_t T, const float* h0, const float* bias, float* c, float* H_all,
                          int threads, int workgroups, int64_t wait_ticks, hipStream_t st);

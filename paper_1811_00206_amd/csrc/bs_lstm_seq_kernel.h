@@ -18,8 +18,8 @@
 //
 // No workgroup relies on the others being there.  The launch is small enough for four such kernels at a time, as many as
 // a process has hardware queues: at most half as many workgroups as compute units, two of which share one's registers and LDS.
-// Where they do not get there all the same (another process, a stream that is bound to a few compute units) a wait ends
-// after wait_ticks: the workgroup marks its units of that step kGivenUp, on which the others stop too, leaves their cell state
+// Where they do not get there all the same (another process, a stream that is bound to a few compute units) a step's wait ends
+// after wait_looks (looks and not time, which passes while a queue is switched out too): the workgroup marks its units of that step kGivenUp, on which the others stop too, leaves their cell state
 // as it was, and the kernel ends.  lstm_finish_kernel, one workgroup that waits for nobody, comes behind it: it does
 // nothing where the last row is whole, and otherwise repeats the sequence for the units that are missing there.
 #pragma once
@@ -47,7 +47,7 @@ struct LstmSeqArgs {
     int lpr, lpr_shift;    // lanes per row, and its logarithm
     int x_slots;           // of a row's chunks in a lane, the first ones that read x alone, in every lane
     int vec;               // floats of one copy of [x ; h], with a zero behind it
-    int wait_ticks;        // of the 100 MHz clock
+    int wait_looks;        // of a lane in a step, before it gives up
 };
 
 struct LstmSeqPlan {
@@ -215,21 +215,19 @@ __global__ __launch_bounds__(lstm_seq_threads(U * R * CH), lstm_seq_threads(U * 
         {
             uint64_t* const to = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(lds) + base + (uint32_t)a.I * 4u);
             const uint64_t* from = reinterpret_cast<const uint64_t*>(t == 0 ? a.h0 : a.H_all + (t - 1) * a.H);
-            for (int i = tid; i < (a.H >> 1); i += (int)blockDim.x) {
+            int looks = a.wait_looks;            // left to this lane in this step
+            for (int i = tid; i < (a.H >> 1) && looks >= 0; i += (int)blockDim.x) {
                 uint64_t w;
                 if (t == 0) {
                     w = from[i];
                 } else {
-                    w = __hip_atomic_load(from + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (!lstm_there(max((uint32_t)w, (uint32_t)(w >> 32)))) {
-                        const int64_t start = wall_clock64();
-                        for (;;) {
-                            if ((uint32_t)w == kGivenUp || (uint32_t)(w >> 32) == kGivenUp || wall_clock64() - start >= a.wait_ticks) {
-                                *stop = 1;
-                                break;
-                            }
-                            w = __hip_atomic_load(from + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            if (lstm_there(max((uint32_t)w, (uint32_t)(w >> 32)))) break;
+                    for (;;) {
+                        w = __hip_atomic_load(from + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if (lstm_there(max((uint32_t)w, (uint32_t)(w >> 32)))) break;
+                        if ((uint32_t)w == kGivenUp || (uint32_t)(w >> 32) == kGivenUp) looks = 0;
+                        if (--looks < 0) {
+                            *stop = 1;
+                            break;
                         }
                     }
                 }
