@@ -313,6 +313,16 @@ int bs_lstm_sequence_ex(const void* vals, const uint8_t* idx, int dtype, int64_t
                         const float* bias, float* c, float* H_all, int threads, int workgroups,
                         int64_t wait_ticks, void* stream);
 
+/*
+ * The second kernel of such a sequence by itself, for tests: hidden units whose word in the last row of H_all is neither
+ * 0xffffffff nor 0xfffffffe are finished; all steps of the others are made, from their cell state before step 0
+ * in c, with the finished units' rows of H_all as they are.  BS_ERR_UNSUPPORTED where bs_lstm_sequence launches step by step
+ * whatever T is.
+ */
+int bs_lstm_sequence_finish(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I,
+                            int bank, int k, const float* X, int64_t T, const float* h0,
+                            const float* bias, float* c, float* H_all, void* stream);
+
 /* HOST ONLY: that kernel's launch.  out: 1 if there is one, entries per chunk, lanes per row,
  * chunks of a row per lane, rows per lane, units per workgroup, chunks that read x alone,
  * lanes per workgroup, workgroups, LDS bytes, LDS bytes of the finishing kernel. */

@@ -25,7 +25,7 @@ BS_F32, BS_F16 = 0, 1
 EXPORTS = (
     "bs_init", "bs_nnz", "bs_vals_bytes", "bs_idx_bytes", "bs_status_str", "bs_prune_pack", "bs_spmv",
     "bs_spmv_ex", "bs_spmv_plan", "bs_spmm_workspace_bytes", "bs_spmm_plan", "bs_spmm", "bs_spmm_static", "bs_spmm_static_limit", "bs_dense_gemv", "bs_dense_gemm",
-    "bs_lstm_step", "bs_lstm_sequence", "bs_lstm_sequence_ex", "bs_lstm_sequence_plan", "bs_reprune",
+    "bs_lstm_step", "bs_lstm_sequence", "bs_lstm_sequence_ex", "bs_lstm_sequence_finish", "bs_lstm_sequence_plan", "bs_reprune",
     "bs_idx_bytes_wide", "bs_prune_pack_wide", "bs_spmv_wide", "bs_spmm_workspace_bytes_wide", "bs_spmm_plan_wide", "bs_spmm_wide",
 )
 
@@ -83,6 +83,7 @@ def load_library():
     lib.bs_reprune.argtypes = [vp, vp, i32, i64, i64, i32, i32, i32, vp, vp, vp]
     lib.bs_lstm_step.argtypes = [vp, vp, i32, i64, i64, i32, i32, vp, vp, vp, vp, vp, vp, vp]
     lib.bs_lstm_sequence.argtypes = [vp, vp, i32, i64, i64, i32, i32, vp, i64, vp, vp, vp, vp, vp]
+    lib.bs_lstm_sequence_finish.argtypes = lib.bs_lstm_sequence.argtypes
     lib.bs_lstm_sequence_ex.argtypes = lib.bs_lstm_sequence.argtypes[:-1] + [i32, i32, i64, vp]
     lib.bs_lstm_sequence_plan.argtypes = [i32, i64, i64, i32, i32, i32, i32, ctypes.POINTER(ctypes.c_int64), i32]
     lib.bs_idx_bytes_wide.argtypes = [i64, i64, i32, i32]
@@ -96,7 +97,7 @@ def load_library():
         getattr(lib, name).restype = i32
     lib.bs_init.argtypes = []
     for name in ("bs_init", "bs_prune_pack", "bs_spmv", "bs_spmv_ex", "bs_spmm", "bs_spmm_static", "bs_dense_gemv",
-                 "bs_dense_gemm", "bs_lstm_step", "bs_lstm_sequence", "bs_lstm_sequence_ex", "bs_lstm_sequence_plan", "bs_reprune"):
+                 "bs_dense_gemm", "bs_lstm_step", "bs_lstm_sequence", "bs_lstm_sequence_ex", "bs_lstm_sequence_finish", "bs_lstm_sequence_plan", "bs_reprune"):
         getattr(lib, name).restype = i32
     native = importlib.import_module("._native", __package__)    # built with libbs.so
     native.BsError = BsError                                     # what it raises for a status
@@ -558,17 +559,27 @@ def bs_lstm_sequence(vals, idx, bank: int, X, h0, bias, c, H_all=None):
     return H_all
 
 
-def bs_lstm_sequence_ex(vals, idx, bank: int, X, h0, bias, c, H_all, threads: int = 0, workgroups: int = 0, wait_ticks: int = -1):
-    """bs_lstm_sequence with its launch spelled out (sweeps and tests)."""
+def _sequence_args(vals, idx, bank, X, h0, bias, c, H_all):
     code, H, I, k = _lstm_shape(vals, idx, bank)
     for t, name, n in ((X, "X", X.shape[0] * I), (h0, "h0", H), (bias, "bias", 4 * H), (c, "c", H)):
         _dev(t, name, torch.float32)
         if t.numel() != n:
             raise ValueError(f"{name} must have {n} elements")
     _out(H_all, "H_all", X.shape[0] * H)
-    _check(load_library().bs_lstm_sequence_ex(_ptr(vals), _ptr(idx), code, H, I, bank, k, _ptr(X), X.shape[0], _ptr(h0), _ptr(bias),
-                                              _ptr(c), _ptr(H_all), threads, workgroups, wait_ticks, _stream()),
-           "bs_lstm_sequence_ex")
+    return (_ptr(vals), _ptr(idx), code, H, I, bank, k, _ptr(X), X.shape[0], _ptr(h0), _ptr(bias), _ptr(c), _ptr(H_all))
+
+
+def bs_lstm_sequence_ex(vals, idx, bank: int, X, h0, bias, c, H_all, threads: int = 0, workgroups: int = 0, wait_ticks: int = -1):
+    """bs_lstm_sequence with its launch spelled out (sweeps and tests)."""
+    _check(load_library().bs_lstm_sequence_ex(*_sequence_args(vals, idx, bank, X, h0, bias, c, H_all), threads, workgroups, wait_ticks,
+                                              _stream()), "bs_lstm_sequence_ex")
+    return H_all
+
+
+def bs_lstm_sequence_finish(vals, idx, bank: int, X, h0, bias, c, H_all):
+    """The second kernel of a sequence by itself (tests): makes the hidden units whose last row of H_all is missing."""
+    _check(load_library().bs_lstm_sequence_finish(*_sequence_args(vals, idx, bank, X, h0, bias, c, H_all), _stream()),
+           "bs_lstm_sequence_finish")
     return H_all
 
 

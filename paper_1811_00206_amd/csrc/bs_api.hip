@@ -253,6 +253,16 @@ int bs_lstm_sequence_ex(const void* vals, const uint8_t* idx, int dtype, int64_t
                                     workgroups, wait_ticks, static_cast<hipStream_t>(stream));
 }
 
+int bs_lstm_sequence_finish(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I,
+                            int bank, int k, const float* X, int64_t T, const float* h0,
+                            const float* bias, float* c, float* H_all, void* stream) {
+    if (!X || !h0 || !bias || !c || !H_all) return BS_ERR_NULL;
+    if (T < 1) return BS_ERR_SHAPE;
+    const int st = check_lstm(vals, idx, dtype, H, I, bank, k, X, h0, bias, c, c, H_all);
+    if (st) return st;
+    return bs::launch_lstm_finish(vals, idx, dtype, H, I, bank, k, X, T, h0, bias, c, H_all, static_cast<hipStream_t>(stream));
+}
+
 int bs_lstm_sequence_plan(int dtype, int64_t H, int64_t I, int bank, int k, int threads, int workgroups,
                           int64_t* out, int n_out) {
     if (!out) return BS_ERR_NULL;

@@ -52,6 +52,9 @@ bool lstm_step_lanes(int dtype, int64_t H, int64_t I, int bank, int k, int* ch, 
 int launch_lstm_sequence(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I, int bank, int k,
                          const float* X, int64_t T, const float* h0, const float* bias, float* c, float* H_all,
                          int threads, int workgroups, int64_t wait_ticks, hipStream_t st);
+// what that leaves to its second kernel, and nothing else
+int launch_lstm_finish(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I, int bank, int k, const float* X,
+                       int64_t T, const float* h0, const float* bias, float* c, float* H_all, hipStream_t st);
 void lstm_seq_plan_describe(int dtype, int64_t H, int64_t I, int bank, int k, int threads, int workgroups, int64_t* out, int n_out);
 size_t spmm_workspace_bytes(int dtype, int64_t M, int64_t K, int bank, int k, int64_t N);
 int spmm_plan_describe(int dtype, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int64_t* out,

@@ -74,6 +74,32 @@ void lstm_seq_plan_describe(int dtype, int64_t H, int64_t I, int bank, int k, in
     for (int i = 0; i < n_out && i < 11; ++i) out[i] = v[i];
 }
 
+static int launch_plan(const LstmSeqPlan& p, const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I, int bank, int k,
+                       const float* X, int64_t T, const float* h0, const float* bias, float* c, float* H_all, int64_t wait_ticks,
+                       hipStream_t st) {
+    LstmSeqArgs a{};
+    a.vals = vals; a.idx = idx; a.X = X; a.h0 = h0; a.bias = bias; a.c = c; a.H_all = H_all;
+    a.T = T; a.H = (int)H; a.I = (int)I; a.B = bank; a.k = k;
+    a.row_len = (int)((H + I) / bank * k);
+    a.chunks_per_row = a.row_len / p.ch;
+    a.magic_k = magic_u32((uint32_t)k);
+    a.units = p.units;
+    a.lpr = p.lpr;
+    while ((1 << a.lpr_shift) < p.lpr) ++a.lpr_shift;
+    a.x_slots = p.x_slots;
+    a.vec = (int)(H + I) + 4;
+    a.wait_looks = (int)std::min<int64_t>((wait_ticks < 0 ? kWaitTicks : wait_ticks) / kLookTicks, INT32_MAX);
+    return dtype == BS_F16 ? lstm_seq_launch_f16(p, a, st) : lstm_seq_launch_f32(p, a, st);
+}
+
+int launch_lstm_finish(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I, int bank, int k, const float* X,
+                       int64_t T, const float* h0, const float* bias, float* c, float* H_all, hipStream_t st) {
+    LstmSeqPlan p = lstm_seq_plan(dtype, H, I, bank, k, 0, 0);
+    if (!p.ok) return BS_ERR_UNSUPPORTED;
+    p.finish_only = true;
+    return launch_plan(p, vals, idx, dtype, H, I, bank, k, X, T, h0, bias, c, H_all, -1, st);
+}
+
 int launch_lstm_sequence(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I, int bank, int k,
                          const float* X, int64_t T, const float* h0, const float* bias, float* c, float* H_all,
                          int threads, int workgroups, int64_t wait_ticks, hipStream_t st) {
@@ -89,19 +115,7 @@ int launch_lstm_sequence(const void* vals, const uint8_t* idx, int dtype, int64_
         }
         return BS_OK;
     }
-    LstmSeqArgs a{};
-    a.vals = vals; a.idx = idx; a.X = X; a.h0 = h0; a.bias = bias; a.c = c; a.H_all = H_all;
-    a.T = T; a.H = (int)H; a.I = (int)I; a.B = bank; a.k = k;
-    a.row_len = (int)((H + I) / bank * k);
-    a.chunks_per_row = a.row_len / p.ch;
-    a.magic_k = magic_u32((uint32_t)k);
-    a.units = p.units;
-    a.lpr = p.lpr;
-    while ((1 << a.lpr_shift) < p.lpr) ++a.lpr_shift;
-    a.x_slots = p.x_slots;
-    a.vec = (int)(H + I) + 4;
-    a.wait_looks = (int)std::min<int64_t>((wait_ticks < 0 ? kWaitTicks : wait_ticks) / kLookTicks, INT32_MAX);
-    return dtype == BS_F16 ? lstm_seq_launch_f16(p, a, st) : lstm_seq_launch_f32(p, a, st);
+    return launch_plan(p, vals, idx, dtype, H, I, bank, k, X, T, h0, bias, c, H_all, wait_ticks, st);
 }
 
 }  // namespace bs

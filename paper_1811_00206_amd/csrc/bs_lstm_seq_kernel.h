@@ -55,6 +55,7 @@ struct LstmSeqPlan {
     int ch, lpr, slots, rows;   // chunks of a row per lane, rows per lane
     int units, x_slots, threads, grid;
     size_t lds, finish_lds;
+    bool finish_only;
 };
 
 int lstm_seq_launch_f32(const LstmSeqPlan& p, const LstmSeqArgs& a, hipStream_t st);
@@ -324,9 +325,11 @@ static __global__ __launch_bounds__(256) void lstm_absent_kernel(uint4* H_all, i
 template <typename VT, int CH, int U, int R>
 int lstm_seq_launch_one(const LstmSeqPlan& p, const LstmSeqArgs& a, hipStream_t st) {
     const int64_t pieces = a.T * a.H / 4;
-    hipLaunchKernelGGL(lstm_absent_kernel, dim3((unsigned)std::min<int64_t>((pieces + 255) / 256, 1024)), dim3(256), 0, st,
-                       reinterpret_cast<uint4*>(a.H_all), pieces);
-    hipLaunchKernelGGL((lstm_seq_kernel<VT, CH, U, R>), dim3(p.grid), dim3(p.threads), p.lds, st, a);
+    if (!p.finish_only) {
+        hipLaunchKernelGGL(lstm_absent_kernel, dim3((unsigned)std::min<int64_t>((pieces + 255) / 256, 1024)), dim3(256), 0, st,
+                           reinterpret_cast<uint4*>(a.H_all), pieces);
+        hipLaunchKernelGGL((lstm_seq_kernel<VT, CH, U, R>), dim3(p.grid), dim3(p.threads), p.lds, st, a);
+    }
     hipLaunchKernelGGL((lstm_finish_kernel<VT>), dim3(1), dim3(kLstmFinishThreads), p.finish_lds, st, a, CH);
     return hip_status(hipGetLastError());
 }

@@ -50,7 +50,7 @@ def test_sequence_is_the_step_repeated(H, I, bank, k, dtype, threads, workgroups
     print("sequence", H, I, bank, k, dtype, plan, flush=True)
     assert plan["one_kernel"] == 1
     v, i, X, h0, bias, c0 = _inputs(H, I, bank, k, dtype, 9, H + k)
-    for T in (1, 4, 9):
+    for T in (1, 2, 4, 9):      # 2 with a wait of 0: units that have made the last step beside others that gave it up
         want, c_want = _steps(v, i, bank, X[:T], h0, bias, c0)
         for wait in (-1, 0):       # 0: what is not there at the first look is left to the finishing kernel
             c = c0.clone()
@@ -61,6 +61,32 @@ def test_sequence_is_the_step_repeated(H, I, bank, k, dtype, threads, workgroups
                                         c0.cpu().numpy())
     got = bs.bs_lstm_sequence(v, i, bank, X, h0, bias, c)
     assert bs_ref.rel_l2(got.cpu().numpy(), H_ref) <= 1e-5 and bs_ref.rel_l2(c.cpu().numpy(), c_ref) <= 1e-5
+
+
+@pytest.mark.parametrize("H,I,bank,k,dtype", [(4, 12, 8, 8, "f32"), (64, 64, 16, 4, "f32"), (100, 92, 16, 5, "f16"), (36, 64, 25, 7, "f16"),
+                                              (260, 252, 64, 20, "f16"), (996, 28, 64, 1, "f32"), (1500, 1500, 100, 10, "f32")])
+@pytest.mark.parametrize("T", [1, 2, 5])
+@pytest.mark.parametrize("missing", ["none", "one", "last", "half", "all"])
+def test_the_finishing_kernel_makes_what_is_missing(H, I, bank, k, dtype, T, missing):
+    """By itself, on states as the kernel of all steps leaves them: finished units have every row and their last cell state, the
+    others any rows up to a step, then a mark, and their first cell state."""
+    v, i, X, h0, bias, c0 = _inputs(H, I, bank, k, dtype, T, H + T)
+    want, c_want = _steps(v, i, bank, X, h0, bias, c0)
+    gone = {"none": torch.zeros(H), "all": torch.ones(H), "half": torch.rand(H, generator=torch.Generator().manual_seed(H)).round(),
+            "one": torch.eye(H)[H // 2], "last": torch.eye(H)[H - 1]}[missing].bool().to(DEV)
+    H_all, c = want.clone(), torch.where(gone, c0, c_want)
+    rows, units = H_all.view(torch.int32), torch.arange(H, device=DEV)
+    stopped = units % T                          # the step that such a unit gave up, marked from there on: -2, then absent
+    for t in range(T):
+        rows[t] = torch.where(gone & (t > stopped), -1, torch.where(gone & (t == stopped), -2, rows[t]))
+        if t < T - 1:
+            rows[t] = torch.where(gone & (units % 3 == 0), 12345, rows[t])      # whatever an earlier row holds, it is made anew
+    bs.bs_lstm_sequence_finish(v, i, bank, X, h0, bias, c, H_all)
+    assert torch.equal(H_all, want) and torch.equal(c, c_want)
+    if missing == "half":                        # and nothing more than that: finished units are not looked at
+        H_all[T - 1] = torch.where(gone, H_all[T - 1], 3.0)
+        bs.bs_lstm_sequence_finish(v, i, bank, X, h0, bias, c, H_all)
+        assert torch.equal(c, c_want) and bool((H_all[T - 1][~gone] == 3.0).all())
 
 
 def test_sequences_side_by_side():
