@@ -21,7 +21,8 @@
 // Where they do not get there all the same (another process, a stream that is bound to a few compute units) a step's wait ends
 // after wait_looks (looks and not time, which passes while a queue is switched out too): the workgroup marks its units of that step kGivenUp, on which the others stop too, leaves their cell state
 // as it was, and the kernel ends.  lstm_finish_kernel, one workgroup that waits for nobody, comes behind it: it does
-// nothing where the last row is whole, and otherwise repeats the sequence for the units that are missing there.
+// nothing where the last row is whole, and otherwise repeats the sequence for the units that are missing there.  That costs
+// far more than launched steps would have: 20 ms and, for 1500 units, 156 us a step.
 #pragma once
 #include <algorithm>
 
@@ -271,11 +272,16 @@ __global__ __launch_bounds__(lstm_seq_threads(U * R * CH), lstm_seq_threads(U * 
     if (tid < units) a.c[unit0 + tid] = cell;
 }
 
-// What lstm_seq_kernel left out, if anything: one workgroup, any number of chunks per row.  Units whose last row is there are
-// finished, their cell state included; the others have theirs as it was before step 0.
-template <typename VT>
-__global__ __launch_bounds__(kLstmFinishThreads) void lstm_finish_kernel(LstmSeqArgs a, int ch) {
+// What lstm_seq_kernel left out, if anything: one workgroup.  Units whose last row is there are finished, their cell state
+// included; the others have theirs as it was before step 0.  A step passes all weights through one compute unit, so the
+// chunks of several rows are in flight together, and the banks of a lane's operands are counted once: a step of
+// 1500 / 1024 / 512 / 128 units takes 156 / 90 / 24 / 3.0 us (entry by entry 748 / 385 / 84 / 8.2; in lstm_seq_kernel 1.2 to 2.0).
+template <typename VT, int CH, int U>
+__global__ __launch_bounds__(kLstmFinishThreads) void lstm_finish_kernel(LstmSeqArgs a) {
     extern __shared__ __align__(16) float lds[];
+    using VRaw = typename RawBytes<CH * sizeof(VT)>::type;
+    using IRaw = typename IdxChunk<uint8_t, CH>::type;
+    constexpr int R = 8 / U;
     const int tid = threadIdx.x, lane_in_row = tid & (a.lpr - 1), group = tid >> a.lpr_shift, groups = (int)blockDim.x >> a.lpr_shift;
     const uint32_t* const last = reinterpret_cast<const uint32_t*>(a.H_all) + (a.T - 1) * a.H;
     int missing = 0;
@@ -285,26 +291,48 @@ __global__ __launch_bounds__(kLstmFinishThreads) void lstm_finish_kernel(LstmSeq
     float* const sums = lds + a.vec;
     uint8_t* const todo = reinterpret_cast<uint8_t*>(sums + 4 * a.H);
     for (int u = tid; u < a.H; u += kLstmFinishThreads) todo[u] = !lstm_there(last[u]);
+    uint32_t bank[U][CH];                        // of an entry: its bank's first place in [x ; h]
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < CH; ++j)
+            bank[u][j] = div_magic((uint32_t)(min(lane_in_row + u * a.lpr, a.chunks_per_row - 1) * CH + j), (uint32_t)a.k, a.magic_k) * (uint32_t)a.B;
     for (int64_t t = 0; t < a.T; ++t) {
         const float* const h_in = t == 0 ? a.h0 : a.H_all + (t - 1) * a.H;
         for (int i = tid; i < a.I; i += kLstmFinishThreads) lds[i] = a.X[t * a.I + i];
         for (int i = tid; i < a.H; i += kLstmFinishThreads) lds[a.I + i] = h_in[i];
         __syncthreads();
-        for (int i = group; i < 4 * a.H; i += groups) {
-            if (!todo[i >> 2]) continue;         // the same for the lanes of a row
-            const size_t row = ((size_t)(i & 3) * a.H + (i >> 2)) * a.row_len;
-            float acc[1] = {0.f};
-            for (int c = lane_in_row; c < a.chunks_per_row; c += a.lpr) {
-                float p = 0.f;
-                for (int e = c * ch; e < (c + 1) * ch; ++e) {
-                    const uint32_t bank = div_magic((uint32_t)e, (uint32_t)a.k, a.magic_k);
-                    const VT w = static_cast<const VT*>(a.vals)[row + e];
-                    p = fmaf((float)w, lds[bank * a.B + a.idx[row + e]], p);
+        // row i is gate i % 4 of unit i / 4: the lanes of a row are of one mind, those of a wavefront need not be
+        for (int i0 = group; i0 < 4 * a.H; i0 += R * groups) {
+            VRaw v[R][U];
+            IRaw o[R][U];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int i = min(i0 + r * groups, 4 * a.H - 1);
+                if (!todo[i >> 2]) continue;
+                const uint32_t row = (uint32_t)((i & 3) * a.H + (i >> 2)) * (uint32_t)a.row_len;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t e = row + (uint32_t)min(lane_in_row + u * a.lpr, a.chunks_per_row - 1) * CH;
+                    v[r][u] = *reinterpret_cast<const VRaw*>(static_cast<const char*>(a.vals) + e * (uint32_t)sizeof(VT));
+                    o[r][u] = *reinterpret_cast<const IRaw*>(a.idx + e);
                 }
-                acc[0] += p;
             }
-            lstm_row_sums(acc, a.lpr);
-            if (lane_in_row == 0) sums[i] = acc[0];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int i = i0 + r * groups;
+                if (i >= 4 * a.H || !todo[i >> 2]) continue;
+                float sum[1] = {0.f};
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float p = 0.f;
+#pragma unroll
+                    for (int j = 0; j < CH; ++j) p = fmaf(value_at<VT>(v[r][u], j), lds[bank[u][j] + offset_at(o[r][u], j)], p);
+                    if (lane_in_row + u * a.lpr < a.chunks_per_row) sum[0] = u == 0 ? p : sum[0] + p;
+                }
+                lstm_row_sums(sum, a.lpr);
+                if (lane_in_row == 0) sums[i] = sum[0];
+            }
         }
         __syncthreads();
         for (int u = tid; u < a.H; u += kLstmFinishThreads) {
@@ -330,7 +358,7 @@ int lstm_seq_launch_one(const LstmSeqPlan& p, const LstmSeqArgs& a, hipStream_t 
                            reinterpret_cast<uint4*>(a.H_all), pieces);
         hipLaunchKernelGGL((lstm_seq_kernel<VT, CH, U, R>), dim3(p.grid), dim3(p.threads), p.lds, st, a);
     }
-    hipLaunchKernelGGL((lstm_finish_kernel<VT>), dim3(1), dim3(kLstmFinishThreads), p.finish_lds, st, a, CH);
+    hipLaunchKernelGGL((lstm_finish_kernel<VT, CH, U>), dim3(1), dim3(kLstmFinishThreads), p.finish_lds, st, a);
     return hip_status(hipGetLastError());
 }
 
