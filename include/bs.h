@@ -290,12 +290,12 @@ int bs_lstm_step(const void* vals, const uint8_t* idx, int dtype, int64_t H, int
  * c      DEVICE in/out  H fp32: the cell state before step 0, after step T-1 on return
  * H_all  DEVICE out     T x H fp32, row t is the hidden state after step t
  *                       (must not overlap h0)
- * Same bits as T calls of bs_lstm_step.  From four steps on, and where the matrix fits the
- * registers of 128 workgroups, one kernel makes all steps, its workgroups exchanging hidden
- * states through H_all (filled with an impossible word first), and a second one finishes what
- * the first had to leave because its workgroups were not on the GPU at the same time (after
- * 20 ms, and in one workgroup: 156 us a step of 1500 units); else one kernel per step.  Each is
- * an ordinary launch.
+ * Same bits as T calls of bs_lstm_step.  From four steps on, where the matrix fits the
+ * registers of 128 workgroups and the stream may use every compute unit, one kernel makes
+ * all steps, its workgroups exchanging hidden states through H_all (filled with an impossible
+ * word first), and a second one finishes what the first had to leave because its workgroups
+ * were not on the GPU at the same time (after 20 ms, and in one workgroup: 156 us a step of
+ * 1500 units); else one kernel per step.  Each is an ordinary launch.
  */
 int bs_lstm_sequence(const void* vals, const uint8_t* idx, int dtype, int64_t H, int64_t I,
                      int bank, int k, const float* X, int64_t T, const float* h0,

@@ -1,4 +1,6 @@
 // Host side of bs_lstm_sequence: one kernel for all steps (bs_lstm_seq_kernel.h), or a launch per step.
+#include <hip/hip_ext.h>
+
 #include <algorithm>
 
 #include "bs_lstm_seq_kernel.h"
@@ -32,6 +34,20 @@ int compute_units() {
     if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
     known[dev].store(n, std::memory_order_relaxed);
     return n;
+}
+
+// Whether the stream's kernels may run on all of them (a query of 0.2 us, as good inside a capture).
+bool on_all_units(hipStream_t st, int units) {
+    uint32_t mask[32] = {};
+    const uint32_t words = ((uint32_t)units + 31) / 32;
+    if (words > 32) return false;
+    if (hipExtStreamGetCUMask(st, words, mask) != hipSuccess) {
+        (void)hipGetLastError();                 // a stream that it knows nothing about
+        return true;
+    }
+    for (int i = 0; i < units; ++i)
+        if (!(mask[i / 32] >> (i % 32) & 1)) return false;
+    return true;
 }
 
 }  // namespace
@@ -107,7 +123,8 @@ int launch_lstm_sequence(const void* vals, const uint8_t* idx, int dtype, int64_
     // H_all is filled ahead of the first step, c is written behind the last
     const bool apart = !overlap(H_all, T * H, X, T * I) && !overlap(H_all, T * H, h0, H) && !overlap(H_all, T * H, bias, 4 * H) &&
                        !overlap(H_all, T * H, c, H) && !overlap(c, H, X, T * I) && !overlap(c, H, bias, 4 * H);
-    if (!p.ok || !apart || p.grid * 2 > compute_units()) {
+    const int units = compute_units();
+    if (!p.ok || !apart || p.grid * 2 > units || !on_all_units(st, units)) {
         for (int64_t t = 0; t < T; ++t) {
             const float* h_in = t == 0 ? h0 : H_all + (t - 1) * H;
             const int rc = launch_lstm_step(vals, idx, dtype, H, I, bank, k, X + t * I, h_in, bias, c, c, H_all + t * H, st);

@@ -18,11 +18,12 @@
 //
 // No workgroup relies on the others being there.  The launch is small enough for four such kernels at a time, as many as
 // a process has hardware queues: at most half as many workgroups as compute units, two of which share one's registers and LDS.
-// Where they do not get there all the same (another process, a stream that is bound to a few compute units) a step's wait ends
-// after wait_looks (looks and not time, which passes while a queue is switched out too): the workgroup marks its units of that step kGivenUp, on which the others stop too, leaves their cell state
-// as it was, and the kernel ends.  lstm_finish_kernel, one workgroup that waits for nobody, comes behind it: it does
-// nothing where the last row is whole, and otherwise repeats the sequence for the units that are missing there.  That costs
-// far more than launched steps would have: 20 ms and, for 1500 units, 156 us a step.
+// A stream that is bound to some of the compute units gets launched steps.  Where the workgroups do not get there all the same
+// (another process, a captured launch on such a stream) a step's wait ends after wait_looks (looks and not time, which passes
+// while a queue is switched out too): the workgroup marks its units of that step kGivenUp, on which the others stop too, leaves
+// their cell state as it was, and the kernel ends.  lstm_finish_kernel, one workgroup that waits for nobody, comes behind it:
+// it does nothing where the last row is whole, and otherwise repeats the sequence for the units that are missing there.
+// That costs far more than launched steps would have: 20 ms and, for 1500 units, 156 us a step.
 #pragma once
 #include <algorithm>
 

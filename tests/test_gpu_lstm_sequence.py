@@ -1,5 +1,8 @@
 """bs_lstm_sequence by the kernel that makes all steps (csrc/bs_lstm_seq_kernel.h): the bits of bs_lstm_step called T times,
 whatever the launch, and whatever its workgroups had to leave to the finishing kernel."""
+import ctypes
+import time
+
 import pytest
 import torch
 
@@ -87,6 +90,30 @@ def test_the_finishing_kernel_makes_what_is_missing(H, I, bank, k, dtype, T, mis
         H_all[T - 1] = torch.where(gone, H_all[T - 1], 3.0)
         bs.bs_lstm_sequence_finish(v, i, bank, X, h0, bias, c, H_all)
         assert torch.equal(c, c_want) and bool((H_all[T - 1][~gone] == 3.0).all())
+
+
+def test_a_stream_that_is_bound_to_some_compute_units():
+    """16 of 256: the workgroups of the kernel of all steps would not meet, and a call take 20 ms and more.  Step by step it takes
+    less than one."""
+    H, I, bank, k, T = 1024, 1024, 64, 8, 12
+    v, i, X, h0, bias, c0 = _inputs(H, I, bank, k, "f32", T, 8)
+    want, c_want = _steps(v, i, bank, X, h0, bias, c0)
+    hip = bs.load_library()      # finds the runtime that it is linked against
+    st, mask = ctypes.c_void_p(), (ctypes.c_uint32 * 8)(0xffff)
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(st), 8, mask) == 0
+    H_all, times = torch.empty(T, H, device=DEV), []
+    torch.cuda.synchronize()
+    for _ in range(3):
+        c = c0.clone()
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        with torch.cuda.stream(torch.cuda.ExternalStream(st.value)):
+            bs.bs_lstm_sequence(v, i, bank, X, h0, bias, c, H_all=H_all)
+        torch.cuda.synchronize()
+        times.append(time.perf_counter() - t)
+        assert torch.equal(H_all, want) and torch.equal(c, c_want)
+    assert hip.hipStreamDestroy(st) == 0
+    assert min(times) < 10e-3, times
 
 
 def test_sequences_side_by_side():
