@@ -37,12 +37,12 @@ def _assembly(src):
 
 def _kernels(text):
     """name -> list of instruction lines (plus the "; bs_pin" markers that
-    pin_order() leaves), for every spmv_kernel / spmm_kernel / spmm_rows_kernel
-    instantiation."""
+    pin_order() leaves), for every spmv_kernel / spmv_streamed_kernel / spmm_kernel /
+    spmm_rows_kernel instantiation."""
     out = {}
     cur = None
     for line in text.splitlines():
-        m = re.match(r"^(_ZN2bs(?:11sp(?:mv|mm)_kernel|16spmm_rows_kernel)\w+):", line)
+        m = re.match(r"^(_ZN2bs(?:11sp(?:mv|mm)_kernel|20spmv_streamed_kernel|16spmm_rows_kernel)\w+):", line)
         if m:
             cur = m.group(1)
             out[cur] = []
@@ -83,6 +83,8 @@ def test_every_instantiation_is_present(kernels):
     # ... and for 16-bit offsets: 2 chunk widths per type, 4 group widths, 3 depths for SpMV;
     # 2 chunk widths, 5 group widths, 2 depths for SpMM
     assert sum("spmv_kernel" in n for n in kernels) == (3 + 4) * 7 * 7 + (3 + 4) * 4 * 2 + 2 * 2 * 4 * 3
+    # matrices larger than the last-level cache: rows of 64 lanes, every chunk width and depth of SpMV
+    assert sum("spmv_streamed_kernel" in n for n in kernels) == (3 + 4) * 7 + 2 * 2 * 3
     assert sum("spmm_kernel" in n for n in kernels) == (3 + 4) * 5 * 2 + 2 * 2 * 5 * 2
     # one lane per (row, column group): chunk widths only
     assert sum("spmm_rows_kernel" in n for n in kernels) == 3 + 4 + 2 * 2
