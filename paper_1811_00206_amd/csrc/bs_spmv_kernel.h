@@ -377,7 +377,9 @@ __global__ __launch_bounds__(1024) void spmv_kernel(SpmvArgs a) { spmv_rows<VT, 
 // For a packed matrix that the last-level cache (256 MB) cannot hold: left in it, it only drives other data, and its own
 // beginning, out before the next product.  16384 x 8192 at 50 % (336 MB): 55.3 -> 51.0 us, 6.1 -> 6.6 TB/s.  Smaller ones come
 // from a cache when they are used again: with such loads 84 MB take 15.7 us instead of 13.8, 29 MB 8.8 instead of 7.1.  Kernels of
-// their own: a branch around the loads costs the others up to 6 %.  For rows of 64 lanes, as matrices of that size have.
+// their own: a branch around the loads costs the others up to 6 %.  For rows of 64 lanes only, which matrices of that size
+// and up to 16384 rows have.  Taller ones with shorter rows (100000 x 4096, binary16, 16 of 64 kept: 32 lanes, 307 MB), an x larger
+// than LDS (spmv_slab_kernel) and products with several columns keep the ordinary loads: not tried there.
 template <typename VT, int CH, int U, typename IT>
 __global__ __launch_bounds__(1024) void spmv_streamed_kernel(SpmvArgs a) { spmv_rows<VT, CH, 64, U, false, IT, true>(a); }
 

@@ -1,5 +1,5 @@
 """bs_spmv on packed matrices that are larger than the last-level cache (spmv_streamed_kernel, csrc/bs_spmv_kernel.h): every
-chunk width and number of chunk slots, against float64 on rows from everywhere."""
+chunk width and number of chunk slots, and those of them that keep the ordinary loads, against float64 on rows from everywhere."""
 import pytest
 import torch
 
@@ -17,8 +17,21 @@ SHAPES = [
 ]
 
 
+# short rows (8 to 32 lanes) and an x that does not fit LDS, which have no kernels with such loads
+OTHERS = [(64, 64, 16, "f16"), (32, 128, 16, "f32"), (16, 64, 16, "f16"), (4, 64, 8, "f32"), (161, 256, 13, "f32"), (20, 512, 16, "f32")]
+
+
 @pytest.mark.parametrize("nb,bank,k,dtype", SHAPES)
 def test_matrices_larger_than_the_last_level_cache(nb, bank, k, dtype):
+    _check(nb, bank, k, dtype, True)
+
+
+@pytest.mark.parametrize("nb,bank,k,dtype", OTHERS)
+def test_large_matrices_without_kernels_of_their_own(nb, bank, k, dtype):
+    _check(nb, bank, k, dtype, False)
+
+
+def _check(nb, bank, k, dtype, streamed):
     wide = bank > 256
     vt, it = (torch.float16, torch.float32)[dtype == "f32"], (torch.uint8, torch.uint16)[wide]
     entry = (2 if dtype == "f16" else 4) + (2 if wide else 1)
@@ -26,7 +39,8 @@ def test_matrices_larger_than_the_last_level_cache(nb, bank, k, dtype):
     assert M * nb * k * entry > BYTES
     print("streamed", M, nb, bank, k, dtype, flush=True)
     if not wide:
-        assert bs.bs_spmv_plan(bs.BS_F16 if dtype == "f16" else bs.BS_F32, M, nb * bank, bank, k)["lpr"] == 64
+        p = bs.bs_spmv_plan(bs.BS_F16 if dtype == "f16" else bs.BS_F32, M, nb * bank, bank, k)
+        assert streamed == (p["lpr"] == 64 and not p["slab_kernel"])
     g = torch.Generator(device="cuda").manual_seed(nb + k)
     vals = torch.empty((M, nb, k), dtype=vt, device=DEV)
     vals.view(-1)[:] = torch.randn(M * nb * k, generator=g, device=DEV, dtype=vt)
