@@ -9,8 +9,8 @@
 // t-1 of H_all, each lane its two words, until none is absent.  No barrier, counter or fence: a step costs one store's
 // and one load's latency (measured without the products, 1500 units: 1.4 us with 63 workgroups, 1.5 with 125, 1.75 with
 // 250; through one atomic counter, 10 with 256).  The chunks of a row that need only x are done before the wait.
-// 32 steps of 1500 / 1024 / 512 / 128 units (I = H; I = 128): 115 -> 72, 105 -> 62, 99 -> 65, 97 -> 53 us, 6 of them the
-// first loads and the kernels ahead and behind.  What is left of a step is those latencies; polling with
+// 32 steps of 1500 / 1024 / 512 / 128 units (I = H), launched and here: 113 -> 68, 101 -> 60, 92 -> 64, 91 -> 45 us, 6 of them
+// the first loads and the kernels ahead and behind.  What is left of a step is those latencies; polling with
 // two loads in flight instead of one takes 3 % longer.
 //
 // Sums are those of spmv_kernel<..., LSTM = true>, bit for bit: same lanes per row, chunks and order.  So which of
@@ -66,6 +66,9 @@ int lstm_seq_launch_f16(const LstmSeqPlan& p, const LstmSeqArgs& a, hipStream_t 
 // Entries that a lane can hold (a value and half an address each), by the workgroup's size: two workgroups of 768 or 512
 // lanes share a compute unit's registers, 80 or 128 of them per lane.
 constexpr int lstm_seq_threads(int entries) { return entries <= 24 ? 768 : 512; }
+// 36: as far as was measured (6000 x 3000 at 90 %, 512 lanes: 78 us for 32 steps).  The fp32 kernels then use 95 of their 128
+// registers, the binary16 ones 77, so more would fit; 1500 units at 80 % and every eighth random model of up to 1536 units
+// go step by step.
 constexpr int kLstmSeqEntries = 36, kLstmSeqSlots = 12, kLstmSeqMost = 4;    // the most; of chunks, and of one row
 constexpr int kLstmFinishThreads = 1024;
 
