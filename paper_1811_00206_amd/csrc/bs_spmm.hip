@@ -231,8 +231,8 @@ double tiles_rounding(const SpmmPlan& p, int64_t nb, int k) {
 //   * Instead of tiles of 16 and 32 columns 1, above kStreamMaxK 0.96.  There the stream of W again divides the products: of
 //     74 with more than 10 MB of it 34 gain and 28 lose more than 8 % (3833 x 5120, 95 entries per bank, N = 30: 27.4 -> 42.7 us).
 //   * Tiles of 4 and 8 columns stay: of 414 products 243 would gain, but 66 lose more than 8 % (520 x 400, N = 5799: 21.0 -> 30.2).
-// Of 4500 other products that the second fit alone would plan anew, 1480 are: 0.914 of the time (geometric mean), 1125 gain more
-// than 3 %, 123 lose that, 45 more than 8 %.  By itself it plans all of them anew and 395 lose more than 8 %.
+// Of 4500 other products that the second fit alone would plan anew, 1765 are: 0.915 of the time (geometric mean), 1305 gain more
+// than 3 %, 192 lose that, 77 more than 8 %.  By itself it plans all of them anew and 388 lose more than 8 %.
 // The terms below are what the expectations leave out:
 //   * Banks of more than 32 entries and one tile of columns stay on the tile kernels.  What divides these products
 //     is the stream of W: all 4 of the 27 timed ones with more than 64 MB of it lose (15947 x 6144, 124 entries

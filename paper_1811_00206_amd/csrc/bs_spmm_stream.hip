@@ -10,6 +10,7 @@ namespace {
 
 constexpr int kCus = 256, kWavesPerCu = 16;  // wavefronts: by the kernels' registers
 constexpr int kMaxWalkers = 14;
+constexpr double kStagesWorth = 1.02;         // of the best launch's time: more than that shorter stages hardly take off
 
 template <typename I>
 constexpr I div_up(I a, I b) { return (a + b - 1) / b; }
@@ -120,7 +121,7 @@ double spmm_stream_ns(const SpmmStreamPlan& p, SpmmFit fit, int vsize, int isize
 }
 
 // This runs in every call, so most launches are passed over by what they take at least: 3000 random products are
-// planned in 0.40 us in the mean and 1.4 at the 99th percentile, fc6 (4096 x 25088, banks of 64) at N = 16 in 1.15, the tile kernels included.
+// planned in 0.42 us in the mean and 1.6 at the 99th percentile, fc6 (4096 x 25088, banks of 64) at N = 16 in 1.2, the tile kernels included.
 SpmmStreamPlan spmm_stream_plan(SpmmFit fit_of, int vsize, int isize, int64_t M, int64_t K, int bank, int k, int64_t N, int min_slabs, int max_slabs, int max_lds,
                                 double max_rounding, double max_ns) {
     SpmmStreamPlan best{};
@@ -162,7 +163,7 @@ SpmmStreamPlan spmm_stream_plan(SpmmFit fit_of, int vsize, int isize, int64_t M,
             const double rounds = alone ? div_up(wgs, kCus) : 1, per_cu = alone ? 1 : std::max(1.0, wgs * (1.0 / kCus));
             if (expected.at_least(slabs, slab_groups, row_waves, rounds, per_cu) >= best.ns) continue;
             for (int ks = 1; ks * row_waves <= kMaxWalkers && ks <= slab_groups; ks = ks < 4 ? ks + 1 : ks + ks / 2) {
-                if (k * (std::min(slab_groups, fit_half) - ks + 1) > most_terms * ks) continue;
+                if (fit_of == kFirstFit && k * (std::min(slab_groups, fit_half) - ks + 1) > most_terms * ks) continue;
                 if (expected.at_least(slabs, slab_groups, row_waves, rounds, per_cu, ks, slab_groups <= fit_one ? slab_groups : ks) >= best.ns) continue;
                 // a stage holds a group of banks for each of the ks; two of them side by side
                 int sg = std::min(slab_groups, fit_half / ks * ks);
@@ -182,7 +183,23 @@ SpmmStreamPlan spmm_stream_plan(SpmmFit fit_of, int vsize, int isize, int64_t M,
                 p.lds_bytes = std::max<size_t>((size_t)bufs * p.buf_bytes, (size_t)(ks - 1) * row_waves * 1024);
                 if (p.lds_bytes > (size_t)max_lds) continue;
                 p.ns = expected(p, slab_groups, wgs);
-                if (p.ns < best.ns && (fit_of == kFirstFit ? rounding(p, slab_groups, k) : spmm_stream_rounding(p, nb, k)) <= max_rounding) best = p;
+                if (fit_of == kFirstFit) {
+                    if (p.ns < best.ns && rounding(p, slab_groups, k) <= max_rounding) best = p;
+                    continue;
+                }
+                // The second fit looks at shorter stages too, whose sums round less: the first copy is shorter, the later ones are
+                // more (512 x 4608 at N = 196, stages of 8 banks instead of 16: 14.7 us as well, 14.8 against 22.2 in rounding).
+                for (int n = div_up(sg, ks); p.ns >= best.ns || spmm_stream_rounding(p, nb, k) > max_rounding;) {
+                    const double longer = p.ns;
+                    n = (n + 1) / 2;
+                    p.sb = n * ks * ib; p.n_bufs = 2; p.buf_bytes = n * ks * group;
+                    p.lds_bytes = std::max<size_t>((size_t)2 * p.buf_bytes, (size_t)(ks - 1) * row_waves * 1024);
+                    p.ok = p.sb < sg * ib && longer < kStagesWorth * best.ns && p.lds_bytes <= (size_t)max_lds;
+                    if (!p.ok) break;
+                    sg = n * ks;
+                    p.ns = expected(p, slab_groups, wgs);
+                }
+                if (p.ok) best = p;
             }
         }
     }

@@ -216,7 +216,7 @@ def test_products_that_are_slower_in_stages_stay_on_the_tile_kernels(dtype, shap
 
 # shape, and the launch that the first fit gives it: slabs, banks per slab and per stage, wavefronts along K
 @pytest.mark.parametrize("dtype,shape,first", [
-    (bs.BS_F32, (512, 4608, 64, 16, 784), (1, 72, 16, 2)), (bs.BS_F32, (64, 10880, 128, 28, 2441), (3, 32, 8, 2)),
+    (bs.BS_F32, (512, 4608, 64, 16, 784), (1, 72, 16, 2)), (bs.BS_F32, (512, 4608, 64, 16, 196), (1, 72, 12, 3)), (bs.BS_F32, (64, 10880, 128, 28, 2441), (3, 32, 8, 2)),
     (bs.BS_F32, (188, 13200, 100, 6, 12), (6, 24, 24, 6)), (bs.BS_F16, (472, 21792, 32, 14, 96), (4, 172, 32, 4)),
     (bs.BS_F32, (2900, 3648, 64, 31, 73), (1, 60, 12, 3)), (bs.BS_F32, (6000, 3000, 50, 15, 37), (1, 60, 24, 1))])
 def test_a_faster_launch_rounds_no_worse(dtype, shape, first):
