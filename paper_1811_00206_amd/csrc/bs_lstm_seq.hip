@@ -41,8 +41,9 @@ bool on_all_units(hipStream_t st, int units) {
     uint32_t mask[32] = {};
     const uint32_t words = ((uint32_t)units + 31) / 32;
     if (words > 32) return false;
+    if (st == hipStreamLegacy || st == hipStreamPerThread) return true;       // names of streams that have no mask of their own
     if (hipExtStreamGetCUMask(st, words, mask) != hipSuccess) {
-        (void)hipGetLastError();                 // a stream that it knows nothing about
+        (void)hipGetLastError();                 // the launch says what is wrong with the stream
         return true;
     }
     for (int i = 0; i < units; ++i)
